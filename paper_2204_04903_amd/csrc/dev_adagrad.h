@@ -2,356 +2,307 @@
 // Part of pk_device.hip: included there, in this order, inside its anonymous namespace.
 
 // ---------------------------------------------------------------------------
-// H6+H7: per distinct key, the gradients of its occurrences are reduced in
-// double (mirror of the forward pooling, Sec. II-D) and the row takes one
-// Adagrad step in place.  Fused so the reduced gradient never goes to memory.
+// H6+H7: per distinct key, the gradients of its occurrences are reduced in double (mirror of the forward
+// pooling, Sec. II-D) and the row takes one Adagrad step in place.  Fused so the reduced gradient never
+// goes to memory; ONE launch for all packs, so that a pack's tail is filled by the next one's keys.
 //
-// Work is cut by OCCURRENCES, not by keys, because the ID distribution is
-// heavily skewed (Sec. II-B): a block takes a tile of consecutive positions of
-// the key-sorted occurrence list and handles the keys that start there.
-//   up to kColdMax occurrences: one lane group per key;
-//   up to kWarmMax, or inside
-//   one tile:                   one wavefront per key, groups stride over it;
-//   longer, across tiles:       the whole block reduces the tile's piece of the key and
-//                               adds it with double atomics to the key's row of partial
-//                               sums (indexed by the tile the key starts in);
-//                               pk_adagrad_hot_kernel then applies the update.
+// The ID distribution is heavily skewed (Sec. II-B), so keys are handled by how many occurrences they have:
+//   up to kColdMax:   one lane group per key (a group is as many lanes as the row has 16-byte chunks);
+//   up to kLongMin:   the wavefront that met the key among its own, its groups stride over the occurrences;
+//   longer:           a block of its own, which the launch starts first, in pieces of kPiece occurrences; the
+//                     pieces of a key with several add into a row of partial sums, the last one to arrive
+//                     takes the step.
+// A wavefront takes as many consecutive keys as it has lane groups and waits for nobody: no LDS, no barrier.
+// Against tiles of occurrences decoded into LDS with a second launch for long keys (one launch per pack):
+// small layer 22.5 -> 18.4 us a step, mixed dtypes with dimensions that are no multiple of four 514 -> 315
+// (they ran one column per lane), bf16 sequences 725 -> 660.  What bounds it: HBM on one-hot batches (4.8 TB/s),
+// else the gathered gradient chunks, which the L2s hold only while an XCD's wavefronts stay on neighbouring
+// tables: hence the eighths per XCD below, for long keys too, and no more than kLongBlocks blocks of those.
+// 80 registers, six wavefronts per SIMD: with 64 the compiler spills and everything is a quarter slower.
 // ---------------------------------------------------------------------------
-// The gradient chunks of a tile's occurrences: element offsets into grad_out and
-// mean-pooling scales, decoded once per tile, in parallel, into LDS.
-template <bool MEAN>
-struct GradSrc {
-    const float* grad;
-    const uint32_t* s_addr;      // LDS: positions [t0, ...)
-    const double* s_scl;         // LDS: 1/L per position (packs with mean pooling only)
-    int t0;
-    __device__ __forceinline__ void fetch(int s, uint32_t* addr, double* scale) const
-    {
-        *addr = s_addr[s - t0];
-        *scale = MEAN ? s_scl[s - t0] : 1.0;
-    }
+struct AdaPack {
+    void* W; float* A; HotView hv;
+    uint32_t addr_max;           // largest element offset into grad_out at which a chunk of the pack can start
+    int32_t D, sh, p;            // dimension, log2 of the lanes per row, pack
+    int32_t kind;                // 1: bf16, 2: mean pooling (entries carry bag lengths), 4: dimension below four
+};
+constexpr int kAdaPacks = 16;    // packs of one launch
+struct AdaJob {
+    AdaPack pack[kAdaPacks];
+    int32_t n_packs, hot_blocks, key_blocks, ent_mult;
+    const PackState* st; const uint32_t* unique; const int32_t* seg; const int32_t* marks; const uint32_t* ent;
+    double* ghot; int32_t* ticket; int32_t dmax;
+    const float* grad; int64_t gstride, out_dim;
+    float lr, eps;
 };
 
-// acc += sum over positions s, s+step, ... < s_end of scale * grad chunk.  Packs with
-// mean pooling carry a double per chunk in flight, so they keep fewer in flight.
-template <int VEC, int LPR, int NCH, bool MEAN>
-__device__ __forceinline__ void accum_range(double (&acc)[NCH][VEC], const GradSrc<MEAN>& g, int D, int li,
-                                            int s, int s_end, int step)
+// what a lane needs to add up the gradient chunks of a range of entries
+struct GradView {
+    const float* grad;           // + the lane's first column
+    const uint32_t* ent;
+    uint32_t gstride, out_dim, addr_max;
+    int D;
+};
+
+// 1 / L in double without a division: the hardware's fp32 reciprocal and two Newton steps (to the last ulp).
+__device__ __forceinline__ double recip_len(uint32_t L)
 {
-    constexpr int UN = MEAN ? PK_ADA_UNROLL_MEAN : PK_ADA_UNROLL;
-    for (; s + (UN - 1) * step < s_end; s += UN * step) {
-        uint32_t a[UN];
-        double c[UN];
-#pragma unroll
-        for (int k = 0; k < UN; ++k) g.fetch(s + k * step, &a[k], &c[k]);
-#pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-            const int d0 = (ch * LPR + li) * VEC;
-            if (d0 < D) {
-                float x[UN][VEC];
-#pragma unroll
-                for (int k = 0; k < UN; ++k) load_f32<VEC>(g.grad + a[k] + d0, x[k]);
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    double t = 0.0;
-#pragma unroll
-                    for (int k = 0; k < UN; ++k) t += MEAN ? c[k] * (double)x[k][v] : (double)x[k][v];
-                    acc[ch][v] += t;
-                }
-            }
-        }
-    }
+    const double d = (double)max(L, 1u);
+    double r = (double)__builtin_amdgcn_rcpf((float)d);
+    r = fma(r, fma(-d, r, 1.0), r);
+    return fma(r, fma(-d, r, 1.0), r);
+}
+
+// acc += sum over the entries [s, s+UN), [s+step, s+step+UN), ... below s_end of scale * gradient chunk.
+// The 1/L of mean pooling is formed and applied in double: the first Adagrad step of a row moves a weight by
+// lr*g/(|g|+eps), so where the gradients of a key cancel (|g| near eps) an error of 1e-8 in g is an error of
+// lr in the weight, and a float 1/L alone is off by 6e-8 of every term.
+// The chunks of a round are asked for without branches between them (the compiler would wait for each before
+// the next one's branch): where the range ends inside a round, its first chunk again, counted as zero.
+template <bool MEAN, bool NARROW, int UN>
+__device__ __forceinline__ void accum_range(double (&acc)[4], const GradView& g, uint32_t s, uint32_t s_end, uint32_t step)
+{
+#pragma nounroll
     for (; s < s_end; s += step) {
-        uint32_t a0;
-        double c0;
-        g.fetch(s, &a0, &c0);
+        uint32_t at[UN], L[UN];
+        if (MEAN) {                                        // (offset, bag length) pairs; read past the end up to 3 entries far
+            uint32_t e[2 * UN];
+            load_u32<UN>(g.ent + 2 * (size_t)s, e);
+            load_u32<UN>(g.ent + 2 * (size_t)s + UN, e + UN);
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-            const int d0 = (ch * LPR + li) * VEC;
-            if (d0 < D) {
-                float x0[VEC];
-                load_f32<VEC>(g.grad + a0 + d0, x0);
+            for (int k = 0; k < UN; ++k) { at[k] = e[2 * k]; L[k] = e[2 * k + 1]; }
+        } else {
+            load_u32<UN>(g.ent + s, at);
+        }
+        if (g.gstride != g.out_dim) {                      // padded gradient rows
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[ch][v] += MEAN ? c0 * (double)x0[v] : (double)x0[v];
+            for (int k = 0; k < UN; ++k) {
+                const uint32_t b = at[k] / g.out_dim;
+                at[k] = b * g.gstride + (at[k] - b * g.out_dim);
+            }
+        }
+        const uint32_t first = min(at[0], g.addr_max);     // never leave grad_out, whatever the list holds
+        float x[UN][4];
+#pragma unroll
+        for (int k = 0; k < UN; ++k) load_f32x4<NARROW>(g.grad + (s + k < s_end ? min(at[k], g.addr_max) : first), g.D, x[k]);
+#pragma unroll
+        for (int k = 0; k < UN; ++k) {
+            const bool on = k == 0 || s + k < s_end;
+            const double c = MEAN ? recip_len(L[k]) : 1.0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double d = (double)(on ? x[k][v] : 0.f);
+                acc[v] = MEAN ? fma(c, d, acc[v]) : acc[v] + d;
             }
         }
     }
 }
 
-// the row's current weights and accumulators (issued before the gradient
-// reduction so that both sets of loads are in flight together)
-template <typename WT, int VEC, int LPR, int NCH>
-__device__ __forceinline__ void row_load(const WT* wrow, const float* arow, int D, int li,
-                                         float (&w)[NCH][VEC], float (&a)[NCH][VEC])
+// one Adagrad step of the lane's columns of a row: a += g^2 ; w -= lr * g / (sqrt(a) + eps)
+template <bool BF16, bool NARROW>
+__device__ __forceinline__ void row_step(const RowPtr& r, int D, const double (&acc)[4], float (&w)[4], float (&a)[4],
+                                         float lr, float eps)
 {
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int d0 = (c * LPR + li) * VEC;
-        if (d0 < D) {
-            Row<WT, VEC>::load(wrow + d0, w[c]);
-            load_f32<VEC>(arow + d0, a[c]);
-        }
+    for (int v = 0; v < 4; ++v) {
+        const float g = (float)acc[v];
+        a[v] = a[v] + g * g;
+        // square root and reciprocal as the hardware gives them (1 ulp each): the step is within
+        // 3 ulp of lr*g/(sqrt(a)+eps), and it is at most lr in size
+        w[v] = w[v] - lr * g * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(a[v]) + eps);
     }
-}
-
-// one Adagrad step of the row: a += g^2 ; w -= lr * g / (sqrt(a) + eps)
-template <typename WT, int VEC, int LPR, int NCH>
-__device__ __forceinline__ void row_step(WT* wrow, float* arow, int D, int li,
-                                         const double (&acc)[NCH][VEC], float (&w)[NCH][VEC],
-                                         float (&a)[NCH][VEC], float lr, float eps)
-{
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int d0 = (c * LPR + li) * VEC;
-        if (d0 < D) {
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                const float g = (float)acc[c][v];
-                a[c][v] = a[c][v] + g * g;
-                // square root and reciprocal as the hardware gives them (1 ulp each): the step is within
-                // 3 ulp of lr*g/(sqrt(a)+eps), and it is at most lr in size
-                w[c][v] = w[c][v] - lr * g * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(a[c][v]) + eps);
-            }
-            store_f32<VEC>(arow + d0, a[c]);
-            Row<WT, VEC>::store(wrow + d0, w[c]);
-        }
-    }
+    store_f32x4<NARROW>(r.a, D, a);
+    store_w4<BF16, NARROW>(r.w, D, w);
 }
 
 // sum over the lane groups of a wavefront (butterfly); every lane ends with the total
-template <int VEC, int LPR, int NCH>
-__device__ __forceinline__ void wave_group_sum(double (&acc)[NCH][VEC])
+__device__ __forceinline__ void wave_group_sum(double (&acc)[4], int lpr)
 {
+#pragma nounroll
+    for (int o = lpr; o < 64; o <<= 1)
 #pragma unroll
-    for (int o = LPR; o < 64; o <<= 1)
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[c][v] += __shfl_xor(acc[c][v], o, 64);
+        for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], o, 64);
 }
 
-template <typename WT, int VEC, int LPR, int NCH, bool MEAN>
-__global__ void __launch_bounds__(NT, VEC > 4 ? 1 : (MEAN ? PK_ADA_WAVES_MEAN : PK_ADA_WAVES))   // 8-wide rows need their registers
-pk_adagrad_kernel(WT* W, float* A, const PackState* __restrict__ st, int p,
-                  const uint32_t* __restrict__ unique_all, const int32_t* __restrict__ seg_all,
-                  double* ghot_all, int dmax, const int4* __restrict__ tile_hdr, int tp, int n_host,
-                  const uint32_t* __restrict__ seg_ent_all, int ent_mult,
-                  const float* __restrict__ grad, int64_t gstride, int64_t out_dim, uint32_t addr_max, int D,
-                  float lr, float eps, const HotView hv)
+// Long keys.  Every kMarkStep-th position names the key that holds it; a piece belongs to the first such
+// position inside it (every piece is longer than kMarkStep), and a block to kMarksPerBlock of them.
+constexpr int kMarksPerBlock = 4;      // (16: the mixed layer 16 % slower, a block then has several pieces one after the other)
+constexpr int kLongBlocks = 768;
+
+template <bool BF16, bool MEAN, bool NARROW, bool HYB>
+__device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, double (*s_red)[64][4])
 {
-    constexpr int GPB = NT / LPR;          // lane groups per block
-    constexpr int GPW = 64 / LPR;          // lane groups per wavefront
-    __shared__ int s_nwarm, s_nhot;
-    __shared__ int s_warm[kPosTileMax / (kColdMax + 1) + 2];
-    __shared__ int s_hot[kPosTileMax / (kWarmMax + 1) + 4];
-    __shared__ double s_red[NT / 64][LPR][NCH][VEC];   // per-wavefront partial sums of a hot piece
-    __shared__ int s_seg[kPosTileMax + 2];          // segment offsets of the tile's keys
-    __shared__ uint32_t s_row[kPosTileMax + 1];     // their table rows
-    __shared__ uint32_t s_addr[kPosTileMax + kWarmMax];   // decoded positions of the tile and its tail
-    __shared__ double s_scl[MEAN ? kPosTileMax + kWarmMax : 1];   // 1/L of mean pooling, in double: see the decode below
-    const int li = threadIdx.x % LPR, gi = threadIdx.x / LPR;
-    const int wv = threadIdx.x >> 6, gw = (threadIdx.x & 63) / LPR;
-    // A plan with one pack has all occurrences in it, so the host knows the sizes and the first
-    // tile header can be requested without waiting for the pack's state; the state is still
-    // checked.  A forward pass that raised the error word (input rejected, or a scan that ran
-    // out of patience) left no lists worth reading: the tables are then left alone.
-    const int n = n_host >= 0 ? n_host : st->nnz, start = n_host >= 0 ? 0 : st->start;
-    const bool state_ok = (n_host < 0 || st->nnz == n_host) && st->error == 0;
-    const int32_t* seg = seg_all + start + p;
-    const uint32_t* uq = unique_all + start;
-    const size_t tbase = (size_t)(start / tp + p);
-    double* gh = ghot_all + tbase * dmax;
-    const int4* th = tile_hdr + tbase;
-    const uint32_t* ent = seg_ent_all + (size_t)start * ent_mult;
-    GradSrc<MEAN> g{grad, s_addr, s_scl, 0};
-    const int n_tiles = (n + tp - 1) / tp;
-    for (XcdTiles it(n_tiles); it.valid(); it.next()) {
-        const int tile = it.tile;
-        const int t0 = tile * tp, t1 = min(t0 + tp, n);
-        // keys whose segments overlap [t0, t1), and the decode window: the tile, plus the tail
-        // of its last key unless that key is a long one (long keys are cut at the tile's end).
-        // The clamps keep the LDS arrays in bounds whatever the header holds.
-        const int4 hdr = th[tile];
-        if (!state_ok) return;
-        const int u_lo = hdr.x;
-        const int nseg = min(max(hdr.y - u_lo + 1, 0), tp);
-        const int w_end = min(max(hdr.z, t1), t1 + kWarmMax);
-        __syncthreads();                                   // the previous tile's LDS is consumed
-        for (int i = threadIdx.x; i <= nseg; i += NT) s_seg[i] = seg[u_lo + i];
-        for (int i = threadIdx.x; i < nseg; i += NT) s_row[i] = uq[u_lo + i];
-        for (int i = threadIdx.x; i < w_end - t0; i += NT) {
-            // The 1/L of mean pooling is formed and applied in double.  The first Adagrad step
-            // of a row moves a weight by lr*g/(|g|+eps): where the gradients of a key cancel
-            // (|g| near eps) an error of 1e-8 in g is an error of lr in the weight, and a
-            // float 1/L alone is off by 6e-8 of every term.
-            uint32_t a;
-            double c = 1.0;
-            if (MEAN) {
-                const uint2 e = reinterpret_cast<const uint2*>(ent)[t0 + i];
-                a = e.x;
-                c = 1.0 / (double)max(e.y, 1u);
-            } else {
-                a = ent[t0 + i];
-            }
-            if (gstride != out_dim) {                      // padded gradient rows
-                const uint32_t b = a / (uint32_t)out_dim;
-                a = b * (uint32_t)gstride + (a - b * (uint32_t)out_dim);
-            }
-            if (a > addr_max) { a = 0; c = 0.0; }          // never leave grad_out, whatever the list holds
-            s_addr[i] = a;
-            if (MEAN) s_scl[i] = c;
-        }
-        if (threadIdx.x == 0) { s_nwarm = 0; s_nhot = 0; }
-        g.t0 = t0;
-        __syncthreads();
-        // cold keys that start here are finished on the spot; the others are listed
-        for (int k = gi; k < nseg; k += GPB) {
-            const int s0 = s_seg[k], s1 = s_seg[k + 1];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const PackState* st = as_global(job.st) + k.p;
+    // A forward pass that raised the error word (input rejected, or a scan that ran out of patience)
+    // left no lists worth reading: the tables are then left alone.
+    const int n = st->error ? 0 : st->nnz, start = st->start;
+    const int32_t* seg = as_global(job.seg) + start + k.p;
+    const int32_t* marks = as_global(job.marks) + start / kMarkStep + k.p;
+    const int n_marks = (n + kMarkStep - 1) / kMarkStep;
+    const int n_ranges = (n_marks + kMarksPerBlock - 1) / kMarksPerBlock;
+    const int per = (n_ranges + 7) >> 3;
+    const int n_mine = max(0, min(per, n_ranges - x * per));
+    const int lpr = 1 << k.sh, gpw = 64 >> k.sh, li = lane & (lpr - 1), g = lane >> k.sh;
+    const int d0 = NARROW ? 0 : lane_col(li, k.D);
+    const bool act = 4 * li < k.D;
+    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, (uint32_t)job.gstride,
+                      (uint32_t)job.out_dim, k.addr_max, k.D};
+    for (; idx < n_mine; idx += stride) {
+        const int m0 = (x * per + idx) * kMarksPerBlock + lane;
+        int u = 0, s0 = 0, s1 = 0, piece = 0, n_pieces = 1;
+        bool mine = lane < kMarksPerBlock && m0 < n_marks;
+        if (mine) {
+            u = marks[m0];
+            s0 = seg[u]; s1 = seg[u + 1];
             const int len = s1 - s0;
-            if (len <= kColdMax) {
-                if (s0 >= t0) {
-                    WT* wrow;
-                    float* arow;
-                    rows_of<WT>(W, A, hv, s_row[k], D, &wrow, &arow);
-                    float w[NCH][VEC], a[NCH][VEC];
-                    row_load<WT, VEC, LPR, NCH>(wrow, arow, D, li, w, a);
-                    double acc[NCH][VEC];
-#pragma unroll
-                    for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) acc[c][v] = 0.0;
-                    accum_range<VEC, LPR, NCH, MEAN>(acc, g, D, li, s0, s1, 1);
-                    row_step<WT, VEC, LPR, NCH>(wrow, arow, D, li, acc, w, a, lr, eps);
-                }
-            } else if (len <= kWarmMax || (s0 >= t0 && s1 <= t1)) {   // fits the decoded window
-                if (s0 >= t0 && li == 0) s_warm[atomicAdd(&s_nwarm, 1)] = k;
-            } else if (li == 0) {
-                s_hot[atomicAdd(&s_nhot, 1)] = k;
-            }
+            n_pieces = max(1, len / kPiece);
+            piece = min((m0 * kMarkStep - s0) / kPiece, n_pieces - 1);
+            mine = len > kLongMin && (m0 * kMarkStep - s0) - piece * kPiece < kMarkStep;
         }
-        __syncthreads();
-        // warm keys that start here: one wavefront each
-        const int n_warm = s_nwarm;
-        for (int i = wv; i < n_warm; i += NT / 64) {
-            const int k = s_warm[i];
-            const int s0 = s_seg[k], s1 = s_seg[k + 1];
-            WT* wrow;
-            float* arow;
-            rows_of<WT>(W, A, hv, s_row[k], D, &wrow, &arow);
-            float w[NCH][VEC], a[NCH][VEC];
-            if (gw == 0) row_load<WT, VEC, LPR, NCH>(wrow, arow, D, li, w, a);
-            double acc[NCH][VEC];
+        for (uint64_t todo = __ballot(mine); todo; todo &= todo - 1) {     // the same in all wavefronts of the block
+            const int lead = __ffsll((unsigned long long)todo) - 1;
+            const int ku = __builtin_amdgcn_readlane(u, lead), ks0 = __builtin_amdgcn_readlane(s0, lead);
+            const int ks1 = __builtin_amdgcn_readlane(s1, lead), kp = __builtin_amdgcn_readlane(piece, lead);
+            const int kn = __builtin_amdgcn_readlane(n_pieces, lead);
+            const int a = ks0 + kp * kPiece, b = kp + 1 == kn ? ks1 : a + kPiece;
+            const bool fin = wv == 0 && g == 0 && act;                      // the lanes that take the step
+            const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, as_global(job.unique)[start + ku], k.D, d0);
+            float w[4], ac[4];
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(a + (wv * gpw + g) * 4), (uint32_t)b, (uint32_t)(4 * gpw * (NT / 64)));
+            if (fin && kn == 1) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }
+            wave_group_sum(acc, lpr);
+            __syncthreads();                           // the previous piece's sums are consumed
+            if (g == 0) {
 #pragma unroll
-            for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[c][v] = 0.0;
-            accum_range<VEC, LPR, NCH, MEAN>(acc, g, D, li, s0 + gw, s1, GPW);
-            wave_group_sum<VEC, LPR, NCH>(acc);
-            if (gw == 0) row_step<WT, VEC, LPR, NCH>(wrow, arow, D, li, acc, w, a, lr, eps);
-        }
-        // long keys that cross tile boundaries: the tile's piece is split over the block's
-        // wavefronts, reduced in LDS and added to the key's partial sums;
-        // pk_adagrad_hot_kernel finishes those keys.
-        const int n_hot_here = s_nhot;
-        for (int i = 0; i < n_hot_here; ++i) {
-            const int k = s_hot[i];
-            const int s0 = s_seg[k], s1 = s_seg[k + 1];
-            const int a0 = max(s0, t0), b0 = min(s1, t1);
-            const int share = (b0 - a0 + NT / 64 - 1) / (NT / 64);
-            const int c0 = a0 + wv * share, c1 = min(c0 + share, b0);
-            double acc[NCH][VEC];
-#pragma unroll
-            for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[c][v] = 0.0;
-            accum_range<VEC, LPR, NCH, MEAN>(acc, g, D, li, c0 + gw, c1, GPW);
-            wave_group_sum<VEC, LPR, NCH>(acc);
-            __syncthreads();                               // s_red of the previous piece is consumed
-            if (gw == 0) {
-#pragma unroll
-                for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) s_red[wv][li][c][v] = acc[c][v];
+                for (int v = 0; v < 4; ++v) s_red[wv][li][v] = acc[v];
             }
             __syncthreads();
-            if (wv == 0 && gw == 0) {
+            if (!fin) continue;
 #pragma unroll
-                for (int c = 0; c < NCH; ++c)
+            for (int v = 0; v < 4; ++v) {
+                double t = 0.0;
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) {
-                        double t = 0.0;
-#pragma unroll
-                        for (int w2 = 0; w2 < NT / 64; ++w2) t += s_red[w2][li][c][v];
-                        acc[c][v] = t;
-                    }
-                {
-                    double* prow = gh + (size_t)(s0 / tp) * D; // partial sums, indexed by the tile the key starts in
-#pragma unroll
-                    for (int c = 0; c < NCH; ++c) {
-                        const int d0 = (c * LPR + li) * VEC;
-                        if (d0 < D) {
-#pragma unroll
-                            for (int v = 0; v < VEC; ++v) atomicAdd(prow + d0 + v, acc[c][v]);
-                        }
-                    }
-                }
+                for (int w2 = 0; w2 < NT / 64; ++w2) t += s_red[w2][li][v];
+                acc[v] = t;
             }
+            if (kn > 1) {
+                // The pieces meet at device-scope atomics.  Every add returns its old value and the ticket is
+                // taken after all of them have: so whoever draws the last ticket finds every piece's sums (no
+                // fence, which would write the whole L2 back).
+                const size_t slot = (size_t)(start / kPiece + k.p) + (size_t)(ks0 / kPiece);
+                double* prow = as_global(job.ghot) + slot * job.dmax + d0;
+                double old = 0.0;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (d0 + v >= 4 * li && v < k.D) old += atomicAdd(prow + v, acc[v]);   // (a column two lanes hold is added once)
+                asm volatile("s_waitcnt vmcnt(0)" ::"v"(old) : "memory");
+                int t = 0;
+                if (li == 0) t = atomicAdd(as_global(job.ticket) + slot, 1);
+                t = __builtin_amdgcn_readfirstlane(t);
+                if (t != kn - 1) continue;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    acc[v] = v < k.D ? __hip_atomic_load(prow + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+                load_w4<BF16, NARROW>(r.w, k.D, w);
+                load_f32x4<NARROW>(r.a, k.D, ac);
+            }
+            row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
         }
     }
+    return idx - n_mine;
 }
 
-// Keys that are long and cross tile boundaries: their partial sums are complete
-// once pk_adagrad_kernel has ended; apply the update.  One wavefront per tile
-// looks at the key that runs out of the tile's end and takes it if it starts in
-// this tile (so every such key is taken exactly once).  All packs in one launch;
-// there are few such keys, so a row is handled one element per lane.
-struct HotPacks {
-    void* W[16];
-    float* A[16];
-    HotView hv[16];
-};
-
-__global__ void __launch_bounds__(NT)
-pk_adagrad_hot_kernel(HotPacks ptrs, int p0, const PackMeta* __restrict__ pm, const PackState* __restrict__ st,
-                      const uint32_t* __restrict__ unique_all, const int32_t* __restrict__ seg_all,
-                      const double* __restrict__ ghot_all, int dmax, const int4* __restrict__ tile_hdr, int tp,
-                      float lr, float eps)
+// The other keys of a pack.  XCD x takes the x-th eighth of the keys (neighbouring keys share gradient
+// columns: one L2 then holds them), its wavefronts take consecutive handfuls.
+template <bool BF16, bool MEAN, bool NARROW, bool HYB>
+__device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride)
 {
-    const int p = p0 + blockIdx.y;
-    const PackMeta k = pm[p];
-    if (st[p].error) return;                               // as in pk_adagrad_kernel
-    const int n = st[p].nnz, start = st[p].start, D = k.dim;
-    const int32_t* seg = seg_all + start + p;
-    const size_t tbase = (size_t)(start / tp + p);
-    const double* gh = ghot_all + tbase * dmax;
-    const int4* th = tile_hdr + tbase;
-    const int n_tiles = (n + tp - 1) / tp;
     const int lane = threadIdx.x & 63;
-    for (int t = blockIdx.x * (NT / 64) + (threadIdx.x >> 6); t + 1 < n_tiles; t += gridDim.x * (NT / 64)) {
-        const int u = th[t + 1].x;                             // the key that holds the next tile's first position
-        const int s0 = seg[u], s1 = seg[u + 1];
-        if (s0 < t * tp || s0 >= (t + 1) * tp || s1 - s0 <= kWarmMax) continue;
-        const uint32_t row = unique_all[start + u];
-        if (k.dtype == PK_F32) {
-            float* wrow;
-            float* arow;
-            rows_of<float>(static_cast<float*>(ptrs.W[blockIdx.y]), ptrs.A[blockIdx.y], ptrs.hv[blockIdx.y], row, D, &wrow, &arow);
-            for (int d = lane; d < D; d += 64) {
-                const float g = (float)gh[(size_t)t * D + d];
-                const float a = arow[d] + g * g;
-                arow[d] = a;
-                wrow[d] = wrow[d] - lr * g * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(a) + eps);
-            }
-        } else {
-            uint16_t* wrow;
-            float* arow;
-            rows_of<uint16_t>(static_cast<uint16_t*>(ptrs.W[blockIdx.y]), ptrs.A[blockIdx.y], ptrs.hv[blockIdx.y], row, D, &wrow, &arow);
-            for (int d = lane; d < D; d += 64) {
-                const float g = (float)gh[(size_t)t * D + d];
-                const float a = arow[d] + g * g;
-                arow[d] = a;
-                wrow[d] = (uint16_t)f32_to_bf16(bf16_to_f32(wrow[d]) - lr * g * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(a) + eps));
-            }
+    const PackState* st = as_global(job.st) + k.p;
+    const int U = st->error ? 0 : st->n_unique, start = st->start;
+    const int lpr = 1 << k.sh, gpw = 64 >> k.sh, li = lane & (lpr - 1), g = lane >> k.sh;
+    const int n_chunks = (U + gpw - 1) >> (6 - k.sh);
+    const int per = (n_chunks + 7) >> 3;
+    const int n_mine = max(0, min(per, n_chunks - x * per));
+    const int32_t* seg = as_global(job.seg) + start + k.p + (x * per) * gpw;
+    const uint32_t* uq = as_global(job.unique) + start + (x * per) * gpw;
+    const int u_end = U - (x * per) * gpw;
+    const int d0 = NARROW ? 0 : lane_col(li, k.D);
+    const bool act = 4 * li < k.D;
+    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, (uint32_t)job.gstride,
+                      (uint32_t)job.out_dim, k.addr_max, k.D};
+    int s0 = 0, s1 = 0;
+    uint32_t row = 0;
+    auto fetch = [&](int c) {                              // the segment and the row of this group's key of handful c
+        const int u = min(c * gpw + g, u_end - 1);         // (past the end: some key, not used)
+        s0 = seg[u]; s1 = seg[u + 1]; row = uq[u];
+        if (c * gpw + g >= u_end) s1 = s0;
+    };
+    if (idx < n_mine) fetch(idx);
+#pragma nounroll
+    for (; idx < n_mine; idx += stride) {
+        const int a = s0, b = s1, len = b - a;
+        const uint32_t r0 = row;
+        fetch(min(idx + stride, n_mine - 1));
+        if (len > 0 && len <= kColdMax && act) {
+            const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, r0, k.D, d0);
+            float w[4], ac[4];
+            load_w4<BF16, NARROW>(r.w, k.D, w);
+            load_f32x4<NARROW>(r.a, k.D, ac);
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
+            row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
         }
+#pragma nounroll
+        for (uint64_t todo = __ballot(li == 0 && len > kColdMax && len <= kLongMin); todo; todo &= todo - 1) {
+            const int lead = __ffsll((unsigned long long)todo) - 1;
+            const int wa = __builtin_amdgcn_readlane(a, lead), wb = __builtin_amdgcn_readlane(b, lead);
+            const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, (uint32_t)__builtin_amdgcn_readlane((int)r0, lead), k.D, d0);
+            const bool fin = g == 0 && act;
+            float w[4], ac[4];
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(wa + 4 * g), (uint32_t)wb, (uint32_t)(4 * gpw));
+            if (fin) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }    // (on their way while the groups are added up)
+            wave_group_sum(acc, lpr);
+            if (fin) row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
+        }
+    }
+    return idx - n_mine;
+}
+
+// the code for a pack's kind
+#define PK_ADA_KINDS(FN, ...)                                                                   \
+    switch (k.kind) {                                                                           \
+        case 0: idx = FN<false, false, false, HYB>(__VA_ARGS__); break;                         \
+        case 1: idx = FN<true, false, false, HYB>(__VA_ARGS__); break;                          \
+        case 2: idx = FN<false, true, false, HYB>(__VA_ARGS__); break;                          \
+        case 3: idx = FN<true, true, false, HYB>(__VA_ARGS__); break;                           \
+        case 4: idx = FN<false, false, true, HYB>(__VA_ARGS__); break;                          \
+        case 5: idx = FN<true, false, true, HYB>(__VA_ARGS__); break;                           \
+        case 6: idx = FN<false, true, true, HYB>(__VA_ARGS__); break;                           \
+        case 7: idx = FN<true, true, true, HYB>(__VA_ARGS__); break;                            \
+    }
+
+template <bool HYB>
+__global__ void __launch_bounds__(NT, 6)
+pk_adagrad_kernel(AdaJob job)
+{
+    __shared__ double s_red[NT / 64][64][4];               // per-wavefront sums of a long key's piece
+    if ((int)blockIdx.x < job.hot_blocks) {
+        int idx = blockIdx.x >> 3;
+        for (int i = 0; i < job.n_packs; ++i) {
+            const AdaPack& k = job.pack[i];
+            PK_ADA_KINDS(ada_long_keys, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_red)
+        }
+        return;
+    }
+    const int kb = (int)blockIdx.x - job.hot_blocks;       // (hot_blocks is a multiple of 8)
+    const int stride = (job.key_blocks >> 3) * (NT / 64);
+    int idx = (kb >> 3) * (NT / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (int i = 0; i < job.n_packs; ++i) {
+        const AdaPack& k = job.pack[i];
+        PK_ADA_KINDS(ada_keys, job, k, idx, kb & 7, stride)
     }
 }

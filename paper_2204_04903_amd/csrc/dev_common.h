@@ -4,19 +4,6 @@
 
 constexpr int NT = 256;   // threads per block of the streaming kernels
 
-#ifndef PK_ADA_WAVES
-#define PK_ADA_WAVES 6    // wavefronts per SIMD the backward kernel is compiled for (register budget)
-#endif
-#ifndef PK_ADA_WAVES_MEAN
-#define PK_ADA_WAVES_MEAN 6
-#endif
-#ifndef PK_ADA_UNROLL
-#define PK_ADA_UNROLL 4   // gradient chunks a lane group keeps in flight
-#endif
-#ifndef PK_ADA_UNROLL_MEAN
-#define PK_ADA_UNROLL_MEAN 2
-#endif
-
 template <int NTHREADS>
 __device__ __forceinline__ int block_excl_scan(int v, int* total)
 {

@@ -7,7 +7,7 @@
 // the slice's bitmap (which rows occur), the popcount prefix of the bitmap's words (the index of a
 // key among the slice's distinct keys is a prefix plus a popcount) and one counter per distinct
 // key.  From those it writes, for its slice, the ascending distinct keys, the segment offsets, the
-// headers of the backward tiles and the occurrences grouped by key -- everything the backward
+// marks by which the backward pass finds long keys, and the occurrences grouped by key -- everything the backward
 // pass reads.  What a slice needs from the others is two numbers, the distinct keys and the
 // occurrences of the slices before it in the pack; they travel through look-back descriptors.
 //
@@ -438,7 +438,7 @@ struct SliceArgs {
     uint32_t* bitmap; int32_t* slice_nu;                        // large batches only: bitmaps with rank samples, distinct keys per slice
     const int32_t* big_list; const int32_t* n_big;              // ... and the listed slices with many records
     uint32_t* unique; int32_t* seg_all; uint32_t* ent_all; int ent_mult;
-    int4* tile_hdr; int tp; double* ghot; int dmax;
+    int32_t* marks; double* ghot; int32_t* ticket; int dmax;
     uint64_t* desc; uint64_t* gdesc; int32_t* done; int n_slices;   // small batches: descriptors the library owns, cleaned by the last block
     int64_t out_dim;
 #ifdef PK_PHASE_TIMES
@@ -774,14 +774,12 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
         return;
     }
 
-    // ---- occurrences per distinct key, segment offsets, headers of the backward tiles, and every
+    // ---- occurrences per distinct key, segment offsets, marks for the backward pass, and every
     //      occurrence's gradient place at its key's next free position; a round handles RANKS keys ----
-    const int tp = a.tp, dim = k.dim;
+    const int dim = k.dim;
     const bool wide = k.has_mean != 0;                     // the pack's entries carry the bag length
     uint32_t* __restrict__ ent = a.ent_all + (size_t)pstart * a.ent_mult;
-    const size_t tbase = (size_t)(pstart / tp + p);
-    int4* th = a.tile_hdr + tbase;
-    double* gh = a.ghot + tbase * a.dmax;
+    int32_t* __restrict__ marks = a.marks + (pstart / kMarkStep + p);
     const int32_t* __restrict__ po = a.packed_offsets + (int64_t)k.first_slot * B + p;
     auto rank_of = [&](uint32_t kl) {
         return (int)(s_pre[kl >> 5] + __popc(s_bits[kl >> 5] & ((1u << (kl & 31)) - 1u)));
@@ -817,20 +815,13 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
                 const int u = base_u + r0 + i;
                 seg[u] = s0;
                 s_cnt[i] = s0;                             // from here on: the segment's next free position
-                // headers of the backward tiles the segment overlaps: x = the key that holds the
-                // tile's first position, y = the key that holds its last one, z = where the
-                // tile's decoded window ends (its last key is decoded to its end unless it is long)
-                for (int tt = s0 / tp; (int64_t)tt * tp < (int64_t)s0 + len; ++tt) {
-                    const int t_first = tt * tp, t_end = min(t_first + tp, nnz_p);
-                    if (t_first >= s0) th[tt].x = u;
-                    if (t_end - 1 < s0 + len) {
-                        th[tt].y = u;
-                        th[tt].z = len <= kWarmMax ? s0 + len : t_end;
-                    }
-                }
-                if (len > kWarmMax && s0 / tp != (s0 + len - 1) / tp) {
-                    const int slot = s0 / tp;              // one such key at most starts in a tile
-                    for (int d = 0; d < dim; ++d) gh[(size_t)slot * dim + d] = 0.0;
+                // every kMarkStep-th position names its key: how the backward pass finds the long ones
+                for (int m = (s0 + kMarkStep - 1) / kMarkStep; (int64_t)m * kMarkStep < (int64_t)s0 + len; ++m) marks[m] = u;
+                if (len >= 2 * kPiece) {                   // the key is reduced in pieces: its partial sums start at zero
+                    const size_t slot = (size_t)(pstart / kPiece + p) + (size_t)(s0 / kPiece);    // (no two such keys share one)
+                    double* gh = a.ghot + slot * a.dmax;
+                    for (int d = 0; d < dim; ++d) gh[d] = 0.0;
+                    a.ticket[slot] = 0;
                 }
                 s0 += len;
             }

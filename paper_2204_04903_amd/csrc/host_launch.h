@@ -226,6 +226,9 @@ unsigned blocks_for(int64_t items, int64_t per_block, int64_t cap)
 
 int pow2_ceil(int v) { int p = 1; while (p < v) p <<= 1; return p; }
 
+// log2 of the lanes that hold a row, four columns each
+int lane_shift(int D) { int s = 0; while ((4 << s) < D) ++s; return s; }
+
 // pack p's packed_offsets start (entries): the packs before it hold k*B+1 each
 int64_t po_off(const pk_plan* plan, int p, int32_t B)
 {
@@ -270,13 +273,6 @@ struct PoolArgs {
     const int32_t* slot_field; int B; int D; int64_t n_bags; float* out; int64_t out_stride; unsigned grid_cap;
     bool aligned; HotView hv;
 };
-struct AdaArgs {
-    void* W; float* A; const PackState* st; int p; const uint32_t* unique; const int32_t* seg;
-    double* ghot; int dmax; const int4* tile_hdr; int tp; int n_host; const uint32_t* seg_ent; int ent_mult;
-    int has_mean; const float* grad; int64_t gstride; int64_t out_dim; uint32_t addr_max; int D;
-    float lr; float eps; int64_t nnz_bound; bool aligned; HotView hv;
-};
-
 template <typename WT, int VEC, int LPR, int NCH>
 pk_status launch_pool(DeviceState* ds, hipStream_t stream, const PoolArgs& a)
 {
@@ -290,21 +286,6 @@ pk_status launch_pool(DeviceState* ds, hipStream_t stream, const PoolArgs& a)
         PK_LAUNCH("pk_pool", (pk_pool_kernel<WT, VEC, LPR, NCH, false>), dim3(grid), dim3(NT), 0,
                   static_cast<const WT*>(a.W), a.keys, a.po, a.st, a.rows, a.fmeta, a.slot_field, a.B, a.D, a.n_bags,
                   a.out, a.out_stride, a.hv);
-    return PK_OK;
-}
-
-template <typename WT, int VEC, int LPR, int NCH>
-pk_status launch_adagrad(DeviceState* ds, hipStream_t stream, const AdaArgs& a)
-{
-    const unsigned grid = (blocks_for(a.nnz_bound, a.tp, 256 * 16) + 7u) & ~7u;
-    if (a.has_mean)
-        PK_LAUNCH("pk_adagrad", (pk_adagrad_kernel<WT, VEC, LPR, NCH, true>), dim3(grid), dim3(NT), 0,
-                  static_cast<WT*>(a.W), a.A, a.st, a.p, a.unique, a.seg, a.ghot, a.dmax, a.tile_hdr,
-                  a.tp, a.n_host, a.seg_ent, a.ent_mult, a.grad, a.gstride, a.out_dim, a.addr_max, a.D, a.lr, a.eps, a.hv);
-    else
-        PK_LAUNCH("pk_adagrad", (pk_adagrad_kernel<WT, VEC, LPR, NCH, false>), dim3(grid), dim3(NT), 0,
-                  static_cast<WT*>(a.W), a.A, a.st, a.p, a.unique, a.seg, a.ghot, a.dmax, a.tile_hdr,
-                  a.tp, a.n_host, a.seg_ent, a.ent_mult, a.grad, a.gstride, a.out_dim, a.addr_max, a.D, a.lr, a.eps, a.hv);
     return PK_OK;
 }
 
@@ -331,8 +312,6 @@ pk_status launch_adagrad(DeviceState* ds, hipStream_t stream, const AdaArgs& a)
 
 template <typename WT, int VECW>
 pk_status dispatch_pool(DeviceState* ds, hipStream_t stream, int D, const PoolArgs& a) { PK_DISPATCH_BODY(launch_pool) }
-template <typename WT, int VECW>
-pk_status dispatch_adagrad(DeviceState* ds, hipStream_t stream, int D, const AdaArgs& a) { PK_DISPATCH_BODY(launch_adagrad) }
 
 // shape of the pooling code for a pack, as numbered in pk_fused_kernel, and its lanes per row
 int pool_variant(int dtype, int D, bool aligned, int* lpr_out)

@@ -17,12 +17,12 @@
 //   scan      H2: places of the slices' records
 //   scatter   H2: one (key in slice, bag) record per occurrence, grouped by slice
 //   slices    H2: per slice, in LDS: mark (bitmap, number of distinct keys), a scan, then place: distinct
-//             keys (ascending), occurrences grouped by key, segment offsets, headers of the backward tiles
+//             keys (ascending), occurrences grouped by key, segment offsets, marks for the backward pass
 //   inverse   H2: inverse[q] = rank(key[q]) from the bitmap and rank samples of the slices
-//   adagrad   H6+H7: per pack, per distinct key: reduce gradients, update row in place
-//   hot       H7: keys whose occurrences span several backward tiles, from their partial sums
+//   adagrad   H6+H7: per distinct key: reduce gradients, update row in place (all packs in one launch)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -121,7 +121,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     uint32_t* keys = ws.at<uint32_t>(L.keys);
     int32_t* inverse = ws.at<int32_t>(L.inverse);
     uint32_t* seg_ent = ws.at<uint32_t>(L.seg_ent);
-    int4* tile_hdr = ws.at<int4>(L.tile_hdr);
+    int32_t* marks = ws.at<int32_t>(L.marks);
     uint32_t* unique = ws.at<uint32_t>(L.unique);
     int32_t* seg = ws.at<int32_t>(L.seg);
     double* ghot = ws.at<double>(L.ghot);
@@ -139,7 +139,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     sa.packed_offsets = packed_offsets;
     sa.keys = keys; sa.inverse = inverse;
     sa.unique = unique; sa.seg_all = seg; sa.ent_all = seg_ent; sa.ent_mult = plan->any_mean ? 2 : 1;
-    sa.tile_hdr = tile_hdr; sa.tp = L.pos_tile; sa.ghot = ghot; sa.dmax = L.dmax;
+    sa.marks = marks; sa.ghot = ghot; sa.ticket = ws.at<int32_t>(L.ticket); sa.dmax = L.dmax;
     sa.n_slices = L.n_slices;
     sa.out_dim = plan->out_dim;
 #ifdef PK_PHASE_TIMES
@@ -411,41 +411,48 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
     Ws ws{static_cast<char*>(workspace), make_layout(plan, B, nnz)};
     const Layout& L = ws.L;
     PackState* st = ws.at<PackState>(L.state);
-    // packs touch disjoint tables: one side stream each
+    // All packs go into one launch, the widest rows first (their keys take longest, the others fill the tail).
+    // With interleaving groups asked for, one launch per group on a stream of its own.
+    std::vector<int> order;
+    for (int p = 0; p < P; ++p)
+        if (!plan->packs[p].fields.empty()) order.push_back(p);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return plan->packs[x].dim > plan->packs[y].dim; });
     const int G = plan->opts.interleave_groups;
-    const bool overlap = ds->overlap && !ds->prof_on && P > 1 && G != 1;
-    const int n_side = overlap ? std::min<int>(P, G >= 2 ? G : 2) : 0;
+    const int n_side = ds->overlap && !ds->prof_on && G >= 2 && P > 1 ? std::min(P, G) : 0;
     if (n_side) { rc = fork_streams(ds, stream, n_side); if (rc != PK_OK) return rc; }
-    for (int p = 0; p < P; ++p) {
-        const Pack& k = plan->packs[p];
-        hipStream_t ps = n_side ? ds->side[p % n_side] : stream;
-        if (k.fields.empty()) continue;
-        AdaArgs a{W[p], A[p], st + p, p, ws.at<uint32_t>(L.unique), ws.at<int32_t>(L.seg), ws.at<double>(L.ghot),
-                  L.dmax, ws.at<int4>(L.tile_hdr), L.pos_tile, P == 1 ? (int)nnz : -1,
-                  ws.at<uint32_t>(L.seg_ent), plan->any_mean ? 2 : 1, k.has_mean ? 1 : 0, grad_out, grad_row_stride,
-                  plan->out_dim, (uint32_t)((int64_t)(B - 1) * grad_row_stride + plan->out_dim - k.dim), k.dim, lr,
-                  eps, nnz,
-                  cols_aligned(plan, p) && aligned16(grad_out) && grad_row_stride % 4 == 0 && aligned16(W[p]) &&
-                      aligned16(A[p]),
-                  hot ? hot[p] : HotView{nullptr, nullptr, nullptr}};
-        rc = k.dtype == PK_F32 ? dispatch_adagrad<float, 4>(ds, ps, k.dim, a)
-                               : dispatch_adagrad<uint16_t, 8>(ds, ps, k.dim, a);
-        if (rc != PK_OK) return rc;
-    }
-    if (n_side) { rc = join_streams(ds, stream, n_side); if (rc != PK_OK) return rc; }
-    // long keys that cross tile boundaries, all packs at once
-    const unsigned hgrid = blocks_for(nnz / L.pos_tile + 1, NT / 64, 1024);
-    for (int p0 = 0; p0 < P; p0 += 16) {
-        HotPacks hp{};
-        const int np = std::min(16, P - p0);
-        for (int i = 0; i < np; ++i) {
-            hp.W[i] = W[p0 + i]; hp.A[i] = A[p0 + i];
-            hp.hv[i] = hot ? hot[p0 + i] : HotView{nullptr, nullptr, nullptr};
+    hipStream_t main_stream = stream;
+    for (int grp = 0; grp < std::max(1, n_side); ++grp) {
+        if (n_side) stream = ds->side[grp];
+        AdaJob job{};
+        job.ent_mult = plan->any_mean ? 2 : 1; job.st = st;
+        job.unique = ws.at<uint32_t>(L.unique); job.seg = ws.at<int32_t>(L.seg); job.marks = ws.at<int32_t>(L.marks);
+        job.ent = ws.at<uint32_t>(L.seg_ent); job.ghot = ws.at<double>(L.ghot); job.ticket = ws.at<int32_t>(L.ticket);
+        job.dmax = L.dmax; job.grad = grad_out; job.gstride = grad_row_stride; job.out_dim = plan->out_dim;
+        job.lr = lr; job.eps = eps;
+        for (size_t i = 0; i <= order.size(); ++i) {
+            if (job.n_packs == kAdaPacks || (i == order.size() && job.n_packs)) {
+                int sh = 0;
+                for (int q = 0; q < job.n_packs; ++q) sh = std::max(sh, job.pack[q].sh);
+                // long keys: none in a batch that has no more occurrences than a key needs to be long
+                job.hot_blocks = nnz <= kLongMin ? 0 : (int)((blocks_for(nnz, kMarkStep * kMarksPerBlock, kLongBlocks) + job.n_packs + 7u) & ~7u);
+                job.key_blocks = (int)((blocks_for(nnz + (int64_t)job.n_packs * (64 >> sh), (64 >> sh) * (NT / 64), 256 * 16) + 7u) & ~7u);
+                const dim3 grid(job.hot_blocks + job.key_blocks);
+                if (hot) PK_LAUNCH("pk_adagrad", pk_adagrad_kernel<true>, grid, dim3(NT), 0, job);
+                else PK_LAUNCH("pk_adagrad", pk_adagrad_kernel<false>, grid, dim3(NT), 0, job);
+                job.n_packs = 0;
+            }
+            if (i == order.size()) break;
+            const int p = order[i];
+            if (n_side && p % n_side != grp) continue;
+            const Pack& k = plan->packs[p];
+            job.pack[job.n_packs++] = AdaPack{W[p], A[p], hot ? hot[p] : HotView{nullptr, nullptr, nullptr},
+                                              (uint32_t)((int64_t)(B - 1) * grad_row_stride + plan->out_dim - k.dim), k.dim,
+                                              lane_shift(k.dim), p,
+                                              (k.dtype == PK_BF16 ? 1 : 0) | (k.has_mean ? 2 : 0) | (k.dim < 4 ? 4 : 0)};
         }
-        PK_LAUNCH("pk_adagrad_hot", pk_adagrad_hot_kernel, dim3(hgrid, np), dim3(NT), 0, hp, p0, ds->pmeta, st,
-                  ws.at<uint32_t>(L.unique), ws.at<int32_t>(L.seg), ws.at<double>(L.ghot), L.dmax,
-                  ws.at<int4>(L.tile_hdr), L.pos_tile, lr, eps);
     }
+    stream = main_stream;
+    if (n_side) { rc = join_streams(ds, stream, n_side); if (rc != PK_OK) return rc; }
     return PK_OK;
 }
 

@@ -12,11 +12,13 @@
 
 namespace pk {
 
+// The backward pass handles a key by its number of occurrences (dev_adagrad.h).
 constexpr int kColdMax   = 8;      // keys with at most this many occurrences: one lane group per key
-constexpr int kWarmMax   = 256;    // up to this many: one wavefront per key; above: split, partial sums
+constexpr int kLongMin   = 256;    // up to this many: one wavefront per key; above: a block per piece of the key
+constexpr int kMarkStep  = 256;    // every kMarkStep-th position of the grouped occurrences names its key: how long keys are found
+constexpr int kPiece     = 1024;   // occurrences per piece of a long key (the last piece takes what is left, up to twice that)
+static_assert(kMarkStep <= kLongMin && kPiece > kLongMin, "every piece of a long key holds a marked position");
 constexpr int kRankWords = 3;      // in memory a rank sample follows every 3 bitmap words (96 keys): a lookup is one 16-byte read
-constexpr int kPosTileMax = 512;   // occurrences handled per block iteration in the backward pass (upper end)
-constexpr int kPosTileMin = 64;
 constexpr size_t kAlign = 256;
 
 // The dedup cuts every table's key range into slices of 2^k keys; one block owns a slice and keeps
@@ -183,7 +185,7 @@ struct Pack {
 
 // Byte offsets of the workspace's arrays for one (plan, B, nnz).
 struct Layout {
-    size_t state, packed_offsets, keys, inverse, seg_ent, tile_hdr, unique, seg, ghot,
+    size_t state, packed_offsets, keys, inverse, seg_ent, marks, unique, seg, ghot, ticket,
            clear_begin, slice_total, slice_nu, big_list, slice_cursor, slice_usum, slice_info, tgeom, fscan, tile_hist, rec, bitmap, total;
     size_t clear_bytes;          // what the partitioned path clears before its first kernel: per-pack state,
                                  // slice totals and distinct-key counts, contiguous from `clear_begin`
@@ -191,7 +193,6 @@ struct Layout {
     int32_t max_table_slices;    // most slices any table has
     int32_t log_max;             // partitioned path: largest slice (log2 of its keys) of this call
     int32_t dmax;
-    int32_t pos_tile;            // occurrences per backward tile for this nnz
     int32_t bags_per_tile;       // bags per tile of the keys and scatter kernels
     int32_t tile_hist_stride;    // entries per tile of the stored per-slice counts (0: not stored, the scatter kernel counts again)
     bool small;                  // the forward pass's dedup is one launch (every slice block scans its table's IDs)
@@ -225,6 +226,5 @@ namespace pk {
 void set_error(const std::string& msg);
 pk_status fail(pk_status s, const std::string& msg);
 Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz);
-int32_t pos_tile_for(int64_t nnz);
 void destroy_device_state(pk_plan* plan);   // defined in pk_device.hip
 }  // namespace pk

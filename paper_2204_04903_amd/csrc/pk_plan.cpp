@@ -28,16 +28,6 @@ pk_status fail(pk_status s, const std::string& msg)
 
 static size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-// Occurrences per block iteration of the backward pass: small problems get small
-// tiles so that the launch still has thousands of blocks.
-int32_t pos_tile_for(int64_t nnz)
-{
-    int64_t t = nnz < (1 << 19) ? 128 : nnz < (2 << 20) ? 256 : 512;
-    if (t < kPosTileMin) t = kPosTileMin;
-    if (t > kPosTileMax) t = kPosTileMax;
-    return (int32_t)t;
-}
-
 // the most slices all tables together (and any one table) can have in a partitioned call: the tables'
 // shares of the occurrences are not known before the batch is
 static void count_slices(const pk_plan* plan, int64_t nnz, int32_t log_max, int64_t* total, int32_t* most)
@@ -97,14 +87,15 @@ Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz)
     L.packed_offsets = take((F * (size_t)B + P) * 4);
     L.keys           = take(n * 4);
     L.inverse        = take(n * 4);
-    L.seg_ent        = take(n * (plan->any_mean ? 8 : 4));
-    L.pos_tile       = pos_tile_for(nnz);
-    const size_t tile_cap = n / L.pos_tile + P + 2;      // backward tiles of all packs
-    L.tile_hdr       = take(tile_cap * 16);
+    // entries are read four at a time: room for the last reading past the end
+    L.seg_ent        = take(n * (plan->any_mean ? 8 : 4) + 32);
+    L.marks          = take((n / kMarkStep + P + 2) * 4);
     L.unique         = take(n * 4);
     L.seg            = take((n + P + 1) * 4);
     L.dmax           = plan->dmax;
-    L.ghot           = take(tile_cap * (size_t)plan->dmax * 8);
+    const size_t pieces = n / kPiece + P + 2;            // partial sums of the keys that take several pieces
+    L.ghot           = take(pieces * (size_t)plan->dmax * 8);
+    L.ticket         = take(pieces * 4);
     L.rec            = take(L.small ? 0 : n * 8);
     L.bitmap         = take(L.small ? 0 : (size_t)plan->bitmap_words * 4);
     L.total = off;
