@@ -190,16 +190,16 @@ struct TileOf {
     }
 };
 
-template <int BT>
 __global__ void __launch_bounds__(NT)
-pk_keys_kernel(const int64_t* __restrict__ ids, const int32_t* __restrict__ offsets, int B, int F,
+pk_keys_kernel(const int64_t* __restrict__ ids, const int32_t* __restrict__ offsets, int B, int F, int BT,
                const FieldMeta* __restrict__ fmeta, const PackMeta* __restrict__ pm, PackState* st,
                uint32_t* __restrict__ keys, int32_t* __restrict__ packed_offsets, int32_t* slice_total,
                const TableCut* __restrict__ cut, const int32_t* __restrict__ fscan, int32_t* __restrict__ tile_hist,
                int tile_hist_stride)
 {
-    extern __shared__ int32_t s_hist[];                    // the tile's counts per slice of its table
-    __shared__ int32_t s_po[BT + 1];
+    extern __shared__ int32_t s_dyn[];                     // the tile's bag offsets | its counts per slice of its table
+    int32_t* s_po = s_dyn;
+    int32_t* s_hist = s_po + BT + 1;
     __shared__ int s_flag;
     const int tid = threadIdx.x;
     if (fscan[3 * F + 2]) return;                          // the field boundaries are unusable: the packs' error words say so
@@ -311,17 +311,16 @@ pk_slice_scan_kernel(const TableCut* __restrict__ cut, int T,
 // Large batches: one record per occurrence, (key inside its slice, place of its bag's gradient chunk), written to
 // the slice's place.  A tile counts its occurrences per slice in LDS, reserves room in every
 // touched slice with one global add, and then places its records from block-local cursors.
-template <int BT>
 __global__ void __launch_bounds__(NT)
-pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int64_t nnz, int log_max,
+pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int64_t nnz, int log_max,
                   const FieldMeta* __restrict__ fmeta, const TableCut* __restrict__ cut,
                   const PackState* __restrict__ st, const uint32_t* __restrict__ keys, int32_t* slice_cursor,
                   uint2* __restrict__ rec, int hist_words, int64_t out_dim, const int32_t* __restrict__ fscan,
                   const int32_t* __restrict__ tile_hist, int tile_hist_stride)
 {
-    extern __shared__ int32_t s_dyn[];                     // counts | places, per slice of the tile's table
-    __shared__ int32_t s_po[BT + 1];
-    int32_t* s_hist = s_dyn;
+    extern __shared__ int32_t s_dyn[];                     // the tile's bag offsets | counts | places, per slice of its table
+    int32_t* s_po = s_dyn;
+    int32_t* s_hist = s_po + BT + 1;
     int32_t* s_place = s_hist + hist_words;
     const int tid = threadIdx.x;
     if (fscan[3 * F + 2]) return;

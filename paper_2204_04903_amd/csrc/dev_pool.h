@@ -1,150 +1,249 @@
-// H3-H5: gather + pool + concatenate, and the kernel in which small batches share the sort's launch.
+// H3-H5: gather + pool + concatenate, and the kernel in which small batches share the dedup's launch.
 // Part of pk_device.hip: included there, in this order, inside its anonymous namespace.
 
 // ---------------------------------------------------------------------------
-// H3+H4+H5: Gather and SegmentReduction (Sec. II-D) fused (K-Packing, Sec.
-// III-B: both are memory-bound), one launch per pack.  A group of LPR lanes owns
-// one bag; each lane covers VEC (x NCH) columns, so a row is read with one
-// coalesced access.  The concatenation of the fields of a sample is the write
-// address.
+// H3+H4+H5: Gather and SegmentReduction (Sec. II-D) fused (K-Packing, Sec. III-B: both are memory-bound), all
+// packs in one launch.  A lane group holds a row, four columns a lane (dev_rows.h); the concatenation of the
+// fields of a sample is the write address.
+//
+// A wavefront takes a tile of consecutive bags of one field, a lane group a run of consecutive bags of it.
+// The group walks the run's POSITIONS, R at a time, whatever bags they belong to: the keys of a round are two
+// 16-byte reads, its R rows are in flight together, and a bag's sum is written when its last position has been
+// added.  So one-hot bags keep as many rows in flight as long ones, and what a group waits for in vain is
+// only the unevenness of whole runs.  The next round's keys are asked for before this round's rows are used.
+// A field of sequences (kSeqAvg IDs per bag or more on average) is left to the cooperating wavefronts at the
+// end of the grid: there all groups of a wavefront share a bag.
 // ---------------------------------------------------------------------------
-// What the pooling of a pack reads its rows' keys from: the packed keys and packed bag offsets the
-// dedup stage left in the workspace, or (small batches, where the pooling runs beside the dedup in
-// one launch) the caller's IDs and offsets, hashed here the same way.
-struct PoolSrc {
-    const uint32_t* keys_all; const int32_t* po; const PackState* st;      // from the workspace
-    const int64_t* ids; const int32_t* offsets; int64_t nnz;               // from the caller's inputs
-    uint32_t rows;                                                         // rows of the pack's table
+constexpr int kSeqAvg = 64;      // IDs per bag from which a field's bags take a whole wavefront each
+constexpr int kRunMax = 8;       // most bags in a lane group's run
+constexpr int kPoolPacks = 16;   // packs of one launch
+
+struct PoolPack {
+    const void* W; HotView hv; const int32_t* slot_field;
+    uint32_t rows, po_begin;         // rows of the pack's table; where its packed offsets start
+    int32_t D, sh, kind;             // dimension; log2 of the lanes per row; 1: bf16, 2: dimension below four
+    int32_t n_fields, run, tiles;    // fields; bags per group; tiles per field
+    int32_t item_begin, p;           // first tile of the pack among the launch's; pack
+};
+struct PoolJob {
+    PoolPack pack[kPoolPacks];
+    int32_t n_packs, B, n_items, coop_waves;
+    float* out; int64_t out_stride;
+    const FieldMeta* fmeta;
+    const uint32_t* keys; const int32_t* po; const PackState* st;          // from the workspace, or (small batches,
+    const int64_t* ids; const int32_t* offsets; int64_t nnz;               // where the pooling runs beside the dedup)
+};                                                                         // the caller's IDs, hashed here the same way
+
+// keys of R consecutive positions from q on, without those past the pack's (or the IDs') end
+template <bool IDS, int R>
+struct KeySrc {
+    const uint32_t* keys; const int64_t* ids; int n;
+    uint32_t base, rows, last_row; uint64_t magic;
+    __device__ __forceinline__ KeySrc(const PoolJob& job, const PoolPack& k, const FieldMeta& m)
+    {
+        const PackState* st = IDS ? nullptr : as_global(job.st) + k.p;
+        n = IDS ? (int)job.nnz : st->nnz;
+        keys = IDS ? nullptr : as_global(job.keys) + st->start;
+        ids = as_global(job.ids);
+        base = m.base_row; rows = m.rows; magic = m.magic; last_row = k.rows - 1;
+    }
+    __device__ __forceinline__ void raw(int q, uint32_t (&v)[IDS ? 2 * R : R]) const
+    {
+        if constexpr (IDS) {
+            if (q + R <= n) {
+#pragma unroll
+                for (int i = 0; i < 2 * R; i += 4) load_u32<4>(reinterpret_cast<const uint32_t*>(ids + q) + i, v + i);
+            } else {                                       // the last positions of all: nothing is read past the IDs' end
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const uint64_t id = (uint64_t)ids[min(q + i, n - 1)];
+                    v[2 * i] = (uint32_t)id; v[2 * i + 1] = (uint32_t)(id >> 32);
+                }
+            }
+        } else {                                           // (the workspace has room past the last key)
+#pragma unroll
+            for (int i = 0; i < R; i += 4) load_u32<4>(keys + q + i, v + i);
+        }
+    }
+    // a key that is no row of the pack (only possible after rejected offsets, which raise the error word) is
+    // bent to the last row so that no read leaves the table
+    __device__ __forceinline__ uint32_t key(const uint32_t (&v)[IDS ? 2 * R : R], int i) const
+    {
+        if constexpr (IDS) return base + fold_id((int64_t)((uint64_t)v[2 * i] | (uint64_t)v[2 * i + 1] << 32), rows, magic);
+        else return min(v[i], last_row);
+    }
 };
 
-// `block` of `nblocks` blocks of `nthreads` threads; HYB: rows may live in a Hot-storage;
-// DEEP: eight rows of a bag in flight instead of four (the kernel that shares the dedup's
-// launch has no registers for that); IDS: keys are formed from the caller's IDs
-template <typename WT, int VEC, int LPR, int NCH, bool HYB, bool DEEP, bool IDS>
-__device__ __forceinline__ void pool_body(const WT* __restrict__ W, const PoolSrc& src,
-                                          const FieldMeta* __restrict__ fmeta, const int32_t* __restrict__ slot_field,
-                                          int B, int D, int64_t n_bags, float* __restrict__ out, int64_t out_stride,
-                                          int block, int nblocks, int nthreads, const HotView hv)
+template <bool BF16, bool HYB>
+__device__ __forceinline__ const char* pool_row(const PoolPack& k, uint32_t row, int d0)
 {
-    const int GPB = nthreads / LPR;
-    const int li = threadIdx.x % LPR, gi = threadIdx.x / LPR;
-    const int n = IDS ? (int)src.nnz : src.st->nnz;
-    const uint32_t* __restrict__ keys = IDS ? nullptr : src.keys_all + src.st->start;
-    const int64_t* __restrict__ ids = src.ids;
-    const uint32_t last_row = src.rows - 1;
-    for (int64_t bag = (int64_t)block * GPB + gi; bag < n_bags; bag += (int64_t)nblocks * GPB) {
-        const int j = (int)(bag / B);
-        const int b = (int)(bag - (int64_t)j * B);
-        const int f = slot_field[j];
-        const FieldMeta m = fmeta[f];
-        int q0, q1;
-        if (IDS) {
-            const int32_t* offs = src.offsets + (int64_t)f * B;
-            q0 = min(max(offs[b], 0), n);                  // whatever the offsets hold, no read leaves ids
-            q1 = min(max(offs[b + 1], q0), n);
-        } else {
-            q0 = min(max(src.po[bag], 0), n);
-            q1 = min(max(src.po[bag + 1], q0), n);
+    const char* w = as_global(static_cast<const char*>(k.W));
+    if (HYB) {
+        const int s = as_global(k.hv.slot_of)[row];
+        if (s >= 0) { w = as_global(static_cast<const char*>(k.hv.W_hot)); row = (uint32_t)s; }
+    }
+    return w + (((size_t)((uint64_t)row * (uint32_t)k.D) + (size_t)d0) << (BF16 ? 1 : 2));
+}
+
+__device__ __forceinline__ const int32_t* pool_offsets(const PoolJob& job, const PoolPack& k, bool ids, int j, int f)
+{
+    return ids ? as_global(job.offsets) + (int64_t)f * job.B : as_global(job.po) + k.po_begin + (int64_t)j * job.B;
+}
+
+__device__ __forceinline__ bool pool_is_seq(const int32_t* offs, int B)
+{
+    return (int64_t)offs[B] - offs[0] >= (int64_t)kSeqAvg * B;
+}
+
+// s_off: the wavefront's own LDS, 64 * kRunMax + 1 words
+template <bool BF16, bool NARROW, bool HYB, bool IDS, int R>
+__device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k, int item, int32_t* s_off)
+{
+    const int lane = threadIdx.x & 63, B = job.B;
+    const int j = item / k.tiles;
+    const int f = as_global(k.slot_field)[j];
+    const FieldMeta m = as_global(job.fmeta)[f];
+    const int32_t* offs = pool_offsets(job, k, IDS, j, f);
+    if (pool_is_seq(offs, B)) return;
+    const KeySrc<IDS, R> src(job, k, m);
+    const int b0 = (item - j * k.tiles) * ((64 >> k.sh) * k.run);
+    const int nb = min((64 >> k.sh) * k.run, B - b0);
+    for (int i = lane; i <= nb; i += 64) s_off[i] = min(max(offs[b0 + i], 0), src.n);   // whatever the offsets hold, no read leaves the keys
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int li = lane & ((1 << k.sh) - 1);
+    int cb = (lane >> k.sh) * k.run;                       // the bag being added up ...
+    const int last = min(cb + k.run, nb);
+    if (cb >= last || 4 * li >= k.D) return;
+    const int d0 = NARROW ? 0 : lane_col(li, k.D);
+    int q = s_off[cb], c0 = q, ce = s_off[cb + 1];         // ... its first position and its end
+    const int qe = s_off[last];
+    float* o = as_global(job.out) + (size_t)(b0 + cb) * (size_t)job.out_stride + m.col + d0;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    auto flush = [&]() {
+        const int len = ce - c0;
+        const float scale = m.pool == PK_MEAN && len > 0 ? 1.0f / (float)len : 1.0f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] *= scale;
+        store_f32x4<NARROW>(o, k.D, acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = 0.f;
+        o += job.out_stride;
+        c0 = ce;
+        ce = ++cb < last ? s_off[cb + 1] : -1;
+    };
+    while (ce == q) flush();                               // empty bags before the first position
+    uint32_t kv[IDS ? 2 * R : R];
+    if (q < qe) src.raw(q, kv);
+#pragma nounroll
+    for (; q < qe; q += R) {
+        float x[R][4];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const uint32_t first = src.key(kv, 0);
+            const uint32_t row = i == 0 || q + i < qe ? src.key(kv, i) : first;      // past the run: a row that is there anyway, not used
+            load_w4<BF16, NARROW>(pool_row<BF16, HYB>(k, row, d0), k.D, x[i]);
         }
-        // the key of position q; a key that is no row of the pack (only possible after rejected
-        // offsets, which raise the error word) is bent to the last row so that no read leaves the table
-        auto key_at = [&](int q) -> uint32_t {
-            if (IDS) return m.base_row + fold_id(ids[q], m.rows, m.magic);
-            return min(keys[q], last_row);
-        };
-        float acc[NCH][VEC];
+        src.raw(min(q + R, qe - 1), kv);
 #pragma unroll
-        for (int c = 0; c < NCH; ++c)
+        for (int i = 0; i < R; ++i) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[c][v] = 0.f;
-        int q = q0;
-        if (DEEP) {                                        // eight rows in flight where the registers allow it
-            for (; q + 8 <= q1; q += 8) {
-                const WT* r[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) r[k] = row_of<const WT, HYB>(W, hv, key_at(q + k), D);
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) {
-                    const int d0 = (c * LPR + li) * VEC;
-                    if (d0 < D) {
-                        float x[8][VEC];
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) Row<WT, VEC>::load(r[k] + d0, x[k]);
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) {        // the order of additions of two rounds of four
-                            acc[c][v] += (x[0][v] + x[1][v]) + (x[2][v] + x[3][v]);
-                            acc[c][v] += (x[4][v] + x[5][v]) + (x[6][v] + x[7][v]);
-                        }
-                    }
-                }
-            }
-        }
-        for (; q + 4 <= q1; q += 4) {
-            const WT* r0 = row_of<const WT, HYB>(W, hv, key_at(q), D);
-            const WT* r1 = row_of<const WT, HYB>(W, hv, key_at(q + 1), D);
-            const WT* r2 = row_of<const WT, HYB>(W, hv, key_at(q + 2), D);
-            const WT* r3 = row_of<const WT, HYB>(W, hv, key_at(q + 3), D);
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const int d0 = (c * LPR + li) * VEC;
-                if (d0 < D) {
-                    float x0[VEC], x1[VEC], x2[VEC], x3[VEC];
-                    Row<WT, VEC>::load(r0 + d0, x0);
-                    Row<WT, VEC>::load(r1 + d0, x1);
-                    Row<WT, VEC>::load(r2 + d0, x2);
-                    Row<WT, VEC>::load(r3 + d0, x3);
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[c][v] += (x0[v] + x1[v]) + (x2[v] + x3[v]);
-                }
-            }
-        }
-        // What is left of the bag (up to three rows) in one round: the rows that are there are asked for
-        // together, the others count as zeros.  (One row after the other is a wait per row.)
-        if (q < q1) {
-            const int rem = q1 - q;
-            const WT* r[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) r[k] = row_of<const WT, HYB>(W, hv, k < rem ? key_at(q + k) : key_at(q), D);
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const int d0 = (c * LPR + li) * VEC;
-                if (d0 < D) {
-                    float x[3][VEC];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) x[k][v] = 0.f;
-                        if (k < rem) Row<WT, VEC>::load(r[k] + d0, x[k]);
-                    }
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[c][v] += (x[0][v] + x[1][v]) + x[2][v];
-                }
-            }
-        }
-        const float scale = (m.pool == PK_MEAN && q1 > q0) ? 1.0f / (float)(q1 - q0) : 1.0f;
-        float* o = out + (size_t)b * out_stride + m.col;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int d0 = (c * LPR + li) * VEC;
-            if (d0 < D) {
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[c][v] *= scale;
-                store_f32<VEC>(o + d0, acc[c]);
-            }
+            for (int v = 0; v < 4; ++v) acc[v] += x[i][v];
+            while (ce == q + i + 1) flush();               // its bag is complete (and the empty ones after it)
         }
     }
 }
 
-template <typename WT, int VEC, int LPR, int NCH, bool HYB>
-__global__ void __launch_bounds__(NT)
-pk_pool_kernel(const WT* __restrict__ W, const uint32_t* __restrict__ keys_all, const int32_t* __restrict__ po,
-               const PackState* __restrict__ st, uint32_t rows, const FieldMeta* __restrict__ fmeta,
-               const int32_t* __restrict__ slot_field, int B, int D, int64_t n_bags,
-               float* __restrict__ out, int64_t out_stride, const HotView hv)
+// Sequence fields: a wavefront per bag, R positions per group and round.
+template <bool BF16, bool NARROW, bool HYB, bool IDS, int R>
+__device__ __forceinline__ int pool_coop(const PoolJob& job, const PoolPack& k, int idx)
 {
-    const PoolSrc src{keys_all, po, st, nullptr, nullptr, 0, rows};
-    pool_body<WT, VEC, LPR, NCH, HYB, true, false>(W, src, fmeta, slot_field, B, D, n_bags, out, out_stride,
-                                                   blockIdx.x, gridDim.x, NT, hv);
+    const int lane = threadIdx.x & 63, B = job.B;
+    const int lpr = 1 << k.sh, gpw = 64 >> k.sh, li = lane & (lpr - 1), g = lane >> k.sh;
+    const int d0 = NARROW ? 0 : lane_col(li, k.D);
+    for (int j0 = 0; j0 < k.n_fields; j0 += 64) {
+        bool seq = false;
+        if (j0 + lane < k.n_fields)
+            seq = pool_is_seq(pool_offsets(job, k, IDS, j0 + lane, IDS ? as_global(k.slot_field)[j0 + lane] : 0), B);
+        for (uint64_t todo = __ballot(seq); todo; todo &= todo - 1) {
+            const int j = j0 + __ffsll((unsigned long long)todo) - 1;
+            const int f = as_global(k.slot_field)[j];
+            const FieldMeta m = as_global(job.fmeta)[f];
+            const int32_t* offs = pool_offsets(job, k, IDS, j, f);
+            const KeySrc<IDS, R> src(job, k, m);
+            for (; idx < B; idx += job.coop_waves) {
+                const int q0 = min(max(offs[idx], 0), src.n), q1 = min(max(offs[idx + 1], q0), src.n);
+                float acc[4] = {0.f, 0.f, 0.f, 0.f};
+                int q = q0 + g * R;
+                uint32_t kv[IDS ? 2 * R : R];
+                if (q < q1) src.raw(q, kv);
+#pragma nounroll
+                for (; q < q1; q += R * gpw) {
+                    float x[R][4];
+#pragma unroll
+                    for (int i = 0; i < R; ++i) {
+                        const uint32_t row = i == 0 || q + i < q1 ? src.key(kv, i) : src.key(kv, 0);
+                        load_w4<BF16, NARROW>(pool_row<BF16, HYB>(k, row, d0), k.D, x[i]);
+                    }
+                    src.raw(min(q + R * gpw, q1 - 1), kv);
+#pragma unroll
+                    for (int i = 0; i < R; ++i)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[v] += i == 0 || q + i < q1 ? x[i][v] : 0.f;
+                }
+#pragma nounroll
+                for (int s = lpr; s < 64; s <<= 1)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], s, 64);
+                if (g == 0 && 4 * li < k.D) {
+                    const float scale = m.pool == PK_MEAN && q1 > q0 ? 1.0f / (float)(q1 - q0) : 1.0f;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[v] *= scale;
+                    store_f32x4<NARROW>(as_global(job.out) + (size_t)idx * (size_t)job.out_stride + m.col + d0, k.D, acc);
+                }
+            }
+            idx -= B;
+        }
+    }
+    return idx;
+}
+
+// the code for a pack's kind
+#define PK_POOL_KINDS(FN, RES, ...)                                                             \
+    switch (k.kind) {                                                                           \
+        case 0: RES FN<false, false, HYB, IDS, R>(__VA_ARGS__); break;                          \
+        case 1: RES FN<true, false, HYB, IDS, R>(__VA_ARGS__); break;                           \
+        case 2: RES FN<false, true, HYB, IDS, R>(__VA_ARGS__); break;                           \
+        case 3: RES FN<true, true, HYB, IDS, R>(__VA_ARGS__); break;                            \
+    }
+
+// one wavefront's share of a launch's pooling: `wave` counts its wavefronts
+template <bool HYB, bool IDS, int R>
+__device__ __forceinline__ void pool_wave(const PoolJob& job, int wave, int32_t* s_off)
+{
+    if (wave < job.n_items) {
+        int i = 0;
+        while (i + 1 < job.n_packs && wave >= job.pack[i + 1].item_begin) ++i;
+        const PoolPack& k = job.pack[i];
+        const int item = wave - k.item_begin;
+        PK_POOL_KINDS(pool_tile, , job, k, item, s_off)
+        return;
+    }
+    int idx = wave - job.n_items;
+    if (idx >= job.coop_waves) return;
+    for (int i = 0; i < job.n_packs; ++i) {
+        const PoolPack& k = job.pack[i];
+        PK_POOL_KINDS(pool_coop, idx =, job, k, idx)
+    }
+}
+
+template <bool HYB>
+__global__ void __launch_bounds__(NT, 6)
+pk_pool_kernel(PoolJob job)
+{
+    __shared__ int32_t s_off[NT / 64][64 * kRunMax + 1];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    pool_wave<HYB, false, 8>(job, (int)blockIdx.x * (NT / 64) + wv, s_off[wv]);
 }
 
 // Small batches: the whole forward pass is ONE launch.  The first blocks are the slices of the
@@ -152,35 +251,6 @@ pk_pool_kernel(const WT* __restrict__ W, const uint32_t* __restrict__ keys_all, 
 // per pack, and the rest pool: the pooling needs the rows' keys only, which it forms from the IDs
 // itself, so it depends on nothing the other blocks write.  (With few occurrences a launch is
 // mostly latency, and a second launch would wait for the first.)
-constexpr int kFusedPacks = 16;
-struct PoolPack {
-    const void* W; const int32_t* slot_field;
-    int64_t n_bags; int32_t D; int32_t variant; int32_t block_begin; uint32_t rows;
-};
-struct PoolJob {
-    PoolPack pack[kFusedPacks];
-    int32_t n_packs; int32_t B; int32_t n_blocks; int32_t pad;
-    float* out; int64_t out_stride;
-};
-
-// variant = 12 * dtype + shape; the shapes in the order of the host's dispatch
-#define PK_POOL_SHAPES(WT, VECW, base)                                                          \
-    case base + 0:  pool_body<WT, VECW, 1, 1, false, false, true>(PK_POOL_ARGS); break;                 \
-    case base + 1:  pool_body<WT, VECW, 2, 1, false, false, true>(PK_POOL_ARGS); break;                 \
-    case base + 2:  pool_body<WT, VECW, 4, 1, false, false, true>(PK_POOL_ARGS); break;                 \
-    case base + 3:  pool_body<WT, VECW, 8, 1, false, false, true>(PK_POOL_ARGS); break;                 \
-    case base + 4:  pool_body<WT, VECW, 16, 1, false, false, true>(PK_POOL_ARGS); break;                \
-    case base + 5:  pool_body<WT, VECW, 32, 1, false, false, true>(PK_POOL_ARGS); break;                \
-    case base + 6:  pool_body<WT, VECW, 64, 1, false, false, true>(PK_POOL_ARGS); break;                \
-    case base + 7:  pool_body<WT, 1, 4, 1, false, false, true>(PK_POOL_ARGS); break;                    \
-    case base + 8:  pool_body<WT, 1, 16, 1, false, false, true>(PK_POOL_ARGS); break;                   \
-    case base + 9:  pool_body<WT, 1, 64, 1, false, false, true>(PK_POOL_ARGS); break;                   \
-    case base + 10: pool_body<WT, 1, 64, 2, false, false, true>(PK_POOL_ARGS); break;                   \
-    case base + 11: pool_body<WT, 1, 64, 4, false, false, true>(PK_POOL_ARGS); break;
-#define PK_POOL_ARGS                                                                            \
-    static_cast<const WT_*>(k.W), src, a.fmeta, k.slot_field, pj.B, k.D, k.n_bags, pj.out, pj.out_stride, local,  \
-        n_local, kSliceThreads, HotView{nullptr, nullptr, nullptr}
-
 // WAVES: wavefronts per SIMD the kernel is compiled for.  8 lets two blocks share a compute unit, which a
 // launch with more blocks than compute units needs; 4 gives a block twice the registers (nothing is then
 // kept in scratch memory), which is faster when every block has a compute unit to itself.
@@ -190,6 +260,7 @@ pk_fused_kernel(SliceArgs a, PoolJob pj, int slice_blocks, int meta_blocks)
 {
     extern __shared__ int32_t s_dyn[];                     // kSliceTfWords words per field of a table
     __shared__ int32_t s_main[slice_lds_words(kSliceLogMax, kSliceRanks)];
+    static_assert(slice_lds_words(kSliceLogMax, kSliceRanks) >= kSliceThreads / 64 * (64 * kRunMax + 1), "the pooling's offsets must fit the block's LDS");
     if ((int)blockIdx.x < slice_blocks) {
         slice_body<kSliceFused, kSliceThreads, kSliceLogMax, kSliceRanks>(a, blockIdx.x, s_main, s_dyn);
         return;
@@ -200,23 +271,8 @@ pk_fused_kernel(SliceArgs a, PoolJob pj, int slice_blocks, int meta_blocks)
         PK_PT(a, blockIdx.x, 8);
         return;
     }
-    const int pb = (int)blockIdx.x - slice_blocks - meta_blocks;
-    int p = 0;
-    while (p + 1 < pj.n_packs && pb >= pj.pack[p + 1].block_begin) ++p;
-    const PoolPack k = pj.pack[p];
-    const int local = pb - k.block_begin;
-    const int n_local = (p + 1 < pj.n_packs ? pj.pack[p + 1].block_begin : pj.n_blocks) - k.block_begin;
-    const PoolSrc src{nullptr, nullptr, nullptr, a.ids, a.offsets, a.nnz, k.rows};
-    switch (k.variant) {
-        {
-            using WT_ = float;
-            PK_POOL_SHAPES(float, 4, 0)
-        }
-        {
-            using WT_ = uint16_t;
-            PK_POOL_SHAPES(uint16_t, 8, 12)
-        }
-    }
-    __syncthreads();
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    pool_wave<false, true, 4>(pj, ((int)blockIdx.x - slice_blocks - meta_blocks) * (kSliceThreads / 64) + wv,
+                              s_main + wv * (64 * kRunMax + 1));
     PK_PT(a, blockIdx.x, 8);
 }

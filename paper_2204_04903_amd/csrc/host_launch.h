@@ -257,76 +257,36 @@ pk_status check_common(const pk_plan* plan, int32_t B, int64_t nnz, const void* 
     return PK_OK;
 }
 
-// ---- per-pack template dispatch ------------------------------------------------
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
-// every field of the pack starts at an output column that is a multiple of 4
-bool cols_aligned(const pk_plan* plan, int p)
+// The pooling of the packs in `packs` (indices, widest rows first) as one launch's work, from `job`'s sources.
+// Runs of up to kRunMax bags per lane group, shorter ones where the launch would have too few wavefronts
+// to fill the chip (256 CUs x 16).
+void fill_pool_job(const pk_plan* plan, const DeviceState* ds, const std::vector<int>& packs, void* const* W, const HotView* hot,
+                   int32_t B, PoolJob* job)
 {
-    for (int32_t f : plan->packs[p].fields)
-        if (plan->field_col[f] % 4) return false;
-    return true;
-}
-
-struct PoolArgs {
-    const void* W; const uint32_t* keys; const int32_t* po; const PackState* st; uint32_t rows; const FieldMeta* fmeta;
-    const int32_t* slot_field; int B; int D; int64_t n_bags; float* out; int64_t out_stride; unsigned grid_cap;
-    bool aligned; HotView hv;
-};
-template <typename WT, int VEC, int LPR, int NCH>
-pk_status launch_pool(DeviceState* ds, hipStream_t stream, const PoolArgs& a)
-{
-    constexpr int GPB = NT / LPR;
-    const unsigned grid = blocks_for(a.n_bags, GPB, a.grid_cap);
-    if (a.hv.slot_of)
-        PK_LAUNCH("pk_pool", (pk_pool_kernel<WT, VEC, LPR, NCH, true>), dim3(grid), dim3(NT), 0,
-                  static_cast<const WT*>(a.W), a.keys, a.po, a.st, a.rows, a.fmeta, a.slot_field, a.B, a.D, a.n_bags,
-                  a.out, a.out_stride, a.hv);
-    else
-        PK_LAUNCH("pk_pool", (pk_pool_kernel<WT, VEC, LPR, NCH, false>), dim3(grid), dim3(NT), 0,
-                  static_cast<const WT*>(a.W), a.keys, a.po, a.st, a.rows, a.fmeta, a.slot_field, a.B, a.D, a.n_bags,
-                  a.out, a.out_stride, a.hv);
-    return PK_OK;
-}
-
-// Picks lanes-per-row so that one row is one coalesced access: 16 bytes per
-// lane when the dimension allows it, else one element per lane.
-#define PK_DISPATCH_BODY(FN)                                                                    \
-    if (D % VECW == 0 && a.aligned) {                                                           \
-        switch (pow2_ceil(D / VECW)) {                                                          \
-            case 1:  return FN<WT, VECW, 1, 1>(ds, stream, a);                                  \
-            case 2:  return FN<WT, VECW, 2, 1>(ds, stream, a);                                  \
-            case 4:  return FN<WT, VECW, 4, 1>(ds, stream, a);                                  \
-            case 8:  return FN<WT, VECW, 8, 1>(ds, stream, a);                                  \
-            case 16: return FN<WT, VECW, 16, 1>(ds, stream, a);                                 \
-            case 32: return FN<WT, VECW, 32, 1>(ds, stream, a);                                 \
-            case 64: return FN<WT, VECW, 64, 1>(ds, stream, a);                                 \
-        }                                                                                       \
-    }                                                                                           \
-    if (D <= 4)   return FN<WT, 1, 4, 1>(ds, stream, a);                                        \
-    if (D <= 16)  return FN<WT, 1, 16, 1>(ds, stream, a);                                       \
-    if (D <= 64)  return FN<WT, 1, 64, 1>(ds, stream, a);                                       \
-    if (D <= 128) return FN<WT, 1, 64, 2>(ds, stream, a);                                       \
-    if (D <= 256) return FN<WT, 1, 64, 4>(ds, stream, a);                                       \
-    return fail(PK_EOVERFLOW, "dim above 256");
-
-template <typename WT, int VECW>
-pk_status dispatch_pool(DeviceState* ds, hipStream_t stream, int D, const PoolArgs& a) { PK_DISPATCH_BODY(launch_pool) }
-
-// shape of the pooling code for a pack, as numbered in pk_fused_kernel, and its lanes per row
-int pool_variant(int dtype, int D, bool aligned, int* lpr_out)
-{
-    static const int lanes[12] = {1, 2, 4, 8, 16, 32, 64, 4, 16, 64, 64, 64};
-    const int vecw = dtype == PK_F32 ? 4 : 8;
-    int shape;
-    if (D % vecw == 0 && aligned && pow2_ceil(D / vecw) <= 64) {
-        shape = 0;
-        while ((1 << shape) < pow2_ceil(D / vecw)) ++shape;
-    } else {
-        shape = D <= 4 ? 7 : D <= 16 ? 8 : D <= 64 ? 9 : D <= 128 ? 10 : 11;
+    int run = kRunMax;
+    for (; run > 1; run /= 2) {
+        int64_t waves = 0;
+        for (int p : packs) {
+            const int64_t tile = (int64_t)(64 >> lane_shift(plan->packs[p].dim)) * run;
+            waves += (int64_t)plan->packs[p].fields.size() * ((B + tile - 1) / tile);
+        }
+        if (waves >= 256 * 16) break;
     }
-    *lpr_out = lanes[shape];
-    return (dtype == PK_F32 ? 0 : 12) + shape;
+    int64_t items = 0;
+    job->n_packs = 0;
+    for (int p : packs) {
+        const Pack& k = plan->packs[p];
+        PoolPack& q = job->pack[job->n_packs++];
+        q = PoolPack{};
+        q.W = W[p]; q.hv = hot ? hot[p] : HotView{nullptr, nullptr, nullptr}; q.slot_field = ds->slot_field + k.first_slot;
+        q.rows = (uint32_t)k.rows; q.po_begin = (uint32_t)po_off(plan, p, B);
+        q.D = k.dim; q.sh = lane_shift(k.dim); q.kind = (k.dtype == PK_BF16 ? 1 : 0) | (k.dim < 4 ? 2 : 0);
+        const int tile = (64 >> q.sh) * run;
+        q.n_fields = (int32_t)k.fields.size(); q.run = run; q.tiles = (B + tile - 1) / tile;
+        q.item_begin = (int32_t)items; q.p = p;
+        items += (int64_t)q.n_fields * q.tiles;
+    }
+    job->B = B; job->fmeta = ds->fmeta; job->n_items = (int32_t)items;
 }
 
 template <typename WT>

@@ -128,9 +128,13 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     const int T = (int)plan->sort_tables.size();
     const int64_t n_bags = (int64_t)F * B;
 
-    auto pool_aligned = [&](int p) {
-        return cols_aligned(plan, p) && aligned16(out) && out_row_stride % 4 == 0 && aligned16(W[p]);
-    };
+    // the packs by the width of their rows, widest first: their work comes first in a launch, the others' fills its tail
+    std::vector<int> order;
+    for (int p = 0; p < P; ++p)
+        if (!plan->packs[p].fields.empty()) order.push_back(p);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return plan->packs[x].dim > plan->packs[y].dim; });
+    // wavefronts for the bags of sequence fields; there can be none where the batch is too small for it
+    const int coop_waves = nnz >= (int64_t)kSeqAvg * B ? (int)std::min<int64_t>(4096, std::max<int64_t>(nnz / kSeqAvg, 1)) : 0;
     SliceArgs sa{};
     sa.tmeta = ds->sort_tables; sa.tfields = ds->tfields; sa.T = T;
     sa.fmeta = ds->fmeta; sa.pm = ds->pmeta; sa.slot_field = ds->slot_field; sa.st = st; sa.P = P;
@@ -152,23 +156,17 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
 
     // ---- small batches: dedup (and pooling) in one launch ----
     if (L.small && do_dedup) {
-        const bool fuse_pool = do_pool && !hot && P <= kFusedPacks;
+        const bool fuse_pool = do_pool && !hot && (int)order.size() <= kPoolPacks;
         sa.target = 0; sa.log_max = kSliceLogMax;
         sa.desc = ds->small_desc; sa.gdesc = ds->small_desc + kSmallSlicesMax; sa.done = ds->small_done;
         PoolJob pj{};
-        int nb = 0, np = 0;
-        for (int p = 0; p < P && fuse_pool; ++p) {
-            const Pack& k = plan->packs[p];
-            if (k.fields.empty()) continue;
-            int lpr = 1;
-            PoolPack& q = pj.pack[np++];
-            q.W = W[p]; q.slot_field = ds->slot_field + k.first_slot;
-            q.n_bags = (int64_t)k.fields.size() * B; q.D = k.dim; q.rows = (uint32_t)k.rows;
-            q.variant = pool_variant(k.dtype, k.dim, pool_aligned(p), &lpr);
-            q.block_begin = nb;
-            nb += (int)blocks_for(q.n_bags, kSliceThreads / lpr, 2048);
+        int nb = 0;
+        if (fuse_pool) {
+            fill_pool_job(plan, ds, order, W, nullptr, B, &pj);
+            pj.coop_waves = coop_waves; pj.out = out; pj.out_stride = out_row_stride;
+            pj.ids = ids; pj.offsets = offsets; pj.nnz = nnz;
+            nb = (int)blocks_for((int64_t)pj.n_items + coop_waves, kSliceThreads / 64, 1 << 30);
         }
-        pj.n_packs = np; pj.B = B; pj.n_blocks = nb; pj.out = out; pj.out_stride = out_row_stride;
         const int meta_blocks = (int)blocks_for(n_bags, kSliceThreads * 4, 64);
         const size_t dyn = (size_t)std::max(1, plan->max_table_fields) * kSliceTfWords * 4;
         const unsigned fused_blocks = (unsigned)(L.n_slices + meta_blocks + nb);
@@ -185,7 +183,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     const int64_t n_tiles = (int64_t)F * ((B + bt - 1) / bt);
     const size_t scan_words = field_scan_words(F) + 2 * (size_t)T + 1;
     if (do_dedup && !L.small &&
-        std::max({scan_words, 2 * (size_t)L.max_table_slices, field_scan_words(F) + 4 * (size_t)F}) * 4 > 64 * 1024)
+        std::max({scan_words, (size_t)bt + 1 + 2 * (size_t)L.max_table_slices, field_scan_words(F) + 4 * (size_t)F}) * 4 > 64 * 1024)
         return fail(PK_EOVERFLOW, std::string(who) + ": fields, tables and slices per table together exceed what the "
                                   "dedup kernels stage in LDS");
     if (do_dedup && !L.small) {
@@ -204,39 +202,36 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
                   ds->sort_tables, ds->slot_field, st, packed_offsets, seg, ws.at<TableCut>(L.tgeom), L.n_slices,
                   ws.at<int32_t>(L.fscan));
         const dim3 key_grid(blocks_for(n_tiles, 1, 256 * 8));
-        const size_t keys_lds = (size_t)L.max_table_slices * 4;
-#define PK_KEYS_LAUNCH(BT)                                                                                      \
-    PK_LAUNCH("pk_keys", pk_keys_kernel<BT>, key_grid, dim3(NT), keys_lds, ids, offsets, B, F, ds->fmeta, ds->pmeta, st,  \
-              keys, packed_offsets, slice_total, ws.at<TableCut>(L.tgeom), ws.at<int32_t>(L.fscan),                    \
-              L.tile_hist_stride ? ws.at<int32_t>(L.tile_hist) : nullptr, L.tile_hist_stride)
-        switch (bt) {
-            case 32: PK_KEYS_LAUNCH(32); break;
-            case 128: PK_KEYS_LAUNCH(128); break;
-            case 512: PK_KEYS_LAUNCH(512); break;
-            default: PK_KEYS_LAUNCH(1024); break;
-        }
-#undef PK_KEYS_LAUNCH
+        const size_t keys_lds = ((size_t)bt + 1 + (size_t)L.max_table_slices) * 4;
+        PK_LAUNCH("pk_keys", pk_keys_kernel, key_grid, dim3(NT), keys_lds, ids, offsets, B, F, bt, ds->fmeta, ds->pmeta, st,
+                  keys, packed_offsets, slice_total, ws.at<TableCut>(L.tgeom), ws.at<int32_t>(L.fscan),
+                  L.tile_hist_stride ? ws.at<int32_t>(L.tile_hist) : nullptr, L.tile_hist_stride);
     }
 
-    // Pooling needs the keys only.  Large batches: it runs on side streams beside the rest of
-    // the dedup chain.  Interleaving groups (Sec. III-C, K-Interleaving): pack p belongs to group
-    // p mod G; a group's packed operations follow one another on the group's stream, the groups
-    // run side by side.  G = 0 lets the size decide (2 groups for large batches: a process has 4 hardware queues and the dedup chain uses two; none for small).
+    // Pooling needs the keys only.  Interleaving groups (Sec. III-C, K-Interleaving), when asked for: pack p belongs to
+    // group p mod G, every group pools on a stream of its own beside the rest of the dedup chain.
     const int G = plan->opts.interleave_groups;
-    const bool overlap = ds->overlap && !ds->prof_on && !L.small &&
-                         (G >= 2 || (G == 0 && (P > 1 || nnz >= (1 << 20)) && nnz >= (1 << 18)));
-    const int n_side = overlap && do_pool ? std::min<int>(P, G >= 2 ? G : 2) : 0;
+    const int n_side = ds->overlap && !ds->prof_on && !L.small && do_pool && G >= 2 ? std::min<int>(P, G) : 0;
     if (n_side) { rc = fork_streams(ds, stream, n_side); if (rc != PK_OK) return rc; }
-    for (int p = 0; p < P && do_pool; ++p) {
-        const Pack& k = plan->packs[p];
-        if (k.fields.empty()) continue;
-        PoolArgs a{W[p], keys, packed_offsets + po_off(plan, p, B), st + p, (uint32_t)k.rows, ds->fmeta,
-                   ds->slot_field + k.first_slot, B, k.dim, (int64_t)k.fields.size() * B, out, out_row_stride, 256 * 32,
-                   pool_aligned(p), hot ? hot[p] : HotView{nullptr, nullptr, nullptr}};
-        hipStream_t ps = n_side ? ds->side[p % n_side] : stream;
-        rc = k.dtype == PK_F32 ? dispatch_pool<float, 4>(ds, ps, k.dim, a)
-                               : dispatch_pool<uint16_t, 8>(ds, ps, k.dim, a);
-        if (rc != PK_OK) return rc;
+    if (do_pool) {
+        hipStream_t main_stream = stream;
+        for (int grp = 0; grp < std::max(1, n_side); ++grp) {
+            std::vector<int> mine;
+            for (int p : order)
+                if (!n_side || p % n_side == grp) mine.push_back(p);
+            if (n_side) stream = ds->side[grp];
+            for (size_t i = 0; i < mine.size(); i += kPoolPacks) {
+                PoolJob pj{};
+                fill_pool_job(plan, ds, std::vector<int>(mine.begin() + i, mine.begin() + std::min(mine.size(), i + kPoolPacks)), W, hot, B, &pj);
+                pj.coop_waves = coop_waves; pj.out = out; pj.out_stride = out_row_stride;
+                pj.keys = keys; pj.po = packed_offsets; pj.st = st;
+                // (the cooperating wavefronts follow the tiles in the same blocks)
+                const dim3 grid(blocks_for((int64_t)pj.n_items + coop_waves, NT / 64, 1 << 30));
+                if (hot) PK_LAUNCH("pk_pool", pk_pool_kernel<true>, grid, dim3(NT), 0, pj);
+                else PK_LAUNCH("pk_pool", pk_pool_kernel<false>, grid, dim3(NT), 0, pj);
+            }
+        }
+        stream = main_stream;
     }
     if (do_dedup && !L.small) {
         int32_t* slice_total = ws.at<int32_t>(L.slice_total);
@@ -246,19 +241,11 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
                   dim3(kScanThreads), (size_t)(T + 1) * 4,
                   ws.at<TableCut>(L.tgeom), T, slice_total, slice_cursor, ws.at<SliceInfo>(L.slice_info),
                   L.n_slices, L.log_max == kSliceLogFine ? kBigSliceCount : 0x7FFFFFFF, big_list + kBigSlicesMax, big_list);
-        const size_t sc_lds = 2 * (size_t)L.max_table_slices * 4;
+        const size_t sc_lds = ((size_t)bt + 1 + 2 * (size_t)L.max_table_slices) * 4;
         const dim3 tile_grid(blocks_for(n_tiles, 1, 256 * 8));
-#define PK_SCATTER_LAUNCH(BT)                                                                                   \
-    PK_LAUNCH("pk_scatter", pk_scatter_kernel<BT>, tile_grid, dim3(NT), sc_lds, offsets, B, F, nnz, sa.log_max, ds->fmeta,  \
-              ws.at<TableCut>(L.tgeom), st, keys, slice_cursor, ws.at<uint2>(L.rec), L.max_table_slices, plan->out_dim,     \
-              ws.at<int32_t>(L.fscan), L.tile_hist_stride ? ws.at<int32_t>(L.tile_hist) : nullptr, L.tile_hist_stride)
-        switch (bt) {
-            case 32: PK_SCATTER_LAUNCH(32); break;
-            case 128: PK_SCATTER_LAUNCH(128); break;
-            case 512: PK_SCATTER_LAUNCH(512); break;
-            default: PK_SCATTER_LAUNCH(1024); break;
-        }
-#undef PK_SCATTER_LAUNCH
+        PK_LAUNCH("pk_scatter", pk_scatter_kernel, tile_grid, dim3(NT), sc_lds, offsets, B, F, bt, nnz, sa.log_max, ds->fmeta,
+                  ws.at<TableCut>(L.tgeom), st, keys, slice_cursor, ws.at<uint2>(L.rec), L.max_table_slices, plan->out_dim,
+                  ws.at<int32_t>(L.fscan), L.tile_hist_stride ? ws.at<int32_t>(L.tile_hist) : nullptr, L.tile_hist_stride);
         const size_t tf_lds = (size_t)std::max(1, plan->max_table_fields) * kSliceTfWords * 4;
         if (L.n_slices > 0) {
             SliceArgs sm = sa, sp = sa;
@@ -268,31 +255,20 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
             sm.n_big = sp.n_big = big_list + kBigSlicesMax;
             const dim3 sgrid((unsigned)L.n_slices);
             const bool fine = L.log_max == kSliceLogFine;
-            // the listed slices run beside the others, on a stream of their own (not while kernels are timed one by one)
-            const bool beside = fine && ds->overlap && !ds->prof_on && do_pool;   // (a dedup on its own is itself running beside other work: a process has four hardware queues)
-            hipStream_t main_stream = stream;
-            if (beside) { rc = fork_streams(ds, main_stream, 1, DeviceState::kSide - 1); if (rc != PK_OK) return rc; }
             if (fine) {
-                stream = beside ? ds->side[DeviceState::kSide - 1] : main_stream;
                 PK_LAUNCH("pk_slices_mark_big", pk_slices_big_kernel<kSliceMark>, dim3(kBigSlicesMax), dim3(kSliceThreads), tf_lds, sm);
-                stream = main_stream;
                 PK_LAUNCH("pk_slices_mark", pk_slices_kernel<kSliceMark>, sgrid, dim3(kFineThreads), tf_lds, sm);
             } else {
                 PK_LAUNCH("pk_slices_mark", pk_slices_wide_kernel<kSliceMark>, sgrid, dim3(kSliceThreads), tf_lds, sm);
             }
-            if (beside) { rc = join_streams(ds, main_stream, 1, DeviceState::kSide - 1); if (rc != PK_OK) return rc; }
             PK_LAUNCH("pk_unique_scan", pk_unique_scan_kernel, dim3(blocks_for(L.n_slices, kScanThreads, 1 << 20)),
                       dim3(kScanThreads), 0, sm.slice_nu, L.n_slices, sp.slice_nu);
-            if (beside) { rc = fork_streams(ds, main_stream, 1, DeviceState::kSide - 1); if (rc != PK_OK) return rc; }
             if (fine) {
-                stream = beside ? ds->side[DeviceState::kSide - 1] : main_stream;
                 PK_LAUNCH("pk_slices_place_big", pk_slices_big_kernel<kSlicePlace>, dim3(kBigSlicesMax), dim3(kSliceThreads), tf_lds, sp);
-                stream = main_stream;
                 PK_LAUNCH("pk_slices_place", pk_slices_kernel<kSlicePlace>, sgrid, dim3(kFineThreads), tf_lds, sp);
             } else {
                 PK_LAUNCH("pk_slices_place", pk_slices_wide_kernel<kSlicePlace>, sgrid, dim3(kSliceThreads), tf_lds, sp);
             }
-            if (beside) { rc = join_streams(ds, main_stream, 1, DeviceState::kSide - 1); if (rc != PK_OK) return rc; }
         }
         const size_t inv_lds = (field_scan_words(F) + 4 * (size_t)F) * 4;
         // (every block stages the field scan and the slots' metadata: with many fields fewer blocks take more tiles each)

@@ -32,6 +32,7 @@ constexpr int kSliceLogMax = 17;           // 128 K keys: 4096 bitmap words
 constexpr int kSliceLogFine = 15;          // 32 K keys: 1024 bitmap words
 constexpr int kSliceWordsMax = 1 << (kSliceLogMax - 5);
 constexpr int kSliceOccLarge = 2048;       // occurrences per slice aimed at when the occurrences are partitioned
+constexpr int64_t kTilesMin = 1024;         // tiles that a launch of the keys and scatter kernels should have at least
 constexpr int64_t kSmallNnz = 1 << 19;     // below this many occurrences the forward pass is one launch
 constexpr int kSmallSlicesMax = 4096;      // ... if it has no more slices than this (descriptors the library owns)
 constexpr int kTableSlicesMax = 8192;      // slices per table (their counters are staged in LDS): rows <= 2^30
