@@ -9,12 +9,12 @@
 // key.  From those it writes, for its slice, the ascending distinct keys, the segment offsets, the
 // marks by which the backward pass finds long keys, and the occurrences grouped by key -- everything the backward
 // pass reads.  What a slice needs from the others is two numbers, the distinct keys and the
-// occurrences of the slices before it in the pack; they travel through look-back descriptors.
+// occurrences of the slices before it in the pack.
 //
 // Which occurrences belong to a slice:
 //   small batches   every slice block scans the IDs of its table's fields and keeps those whose
-//                   row falls into its slice (the IDs of a table are few and sit in L2), so the
-//                   whole dedup, with the pooling beside it, is ONE launch;
+//                   row falls into its slice, so the whole dedup, with the pooling beside it, is ONE
+//                   launch (dev_small.h);
 //   large batches   the occurrences are partitioned by slice first: the keys kernel counts them
 //                   per slice (block-local counts in LDS, one global add per touched slice), a
 //                   one-block scan turns the counts into places, a scatter kernel writes a
@@ -428,7 +428,7 @@ struct SliceArgs {
     const TableMeta* tmeta; const TableField* tfields; int T;
     const PackMeta* pm; const int32_t* slot_field; PackState* st; int P;
     int F, B; int64_t nnz; int target, log_max;
-    const int64_t* ids; const int32_t* offsets; const SmallSlice* small_slices;   // small batches: the block finds its occurrences itself
+    const int64_t* ids; const int32_t* offsets; const SmallSlice* small_slices; const int2* slot_info;   // small batches: the block finds its occurrences itself
     const SliceInfo* slice_info; const uint2* rec;              // large batches: the slice's records
     const TableCut* cut;                                        // ... and the tables' cuts for this batch
     const FieldMeta* fmeta;
@@ -450,226 +450,114 @@ struct SliceArgs {
 #define PK_PT(a, blk, k) do { } while (0)
 #endif
 
-// LDS words of a slice block: bitmap words | their popcount prefix | counters of a round of distinct keys.
-// Small batches: the same words first hold the field scan, and the upper three quarters of the
-// counters hold the slice's occurrences when they are few (12 bytes each, kept from the first pass over the IDs,
-// so that the IDs are read once).
+// LDS words of a slice block: bitmap words | their popcount prefix | counters of a round of distinct keys
 constexpr int slice_lds_words(int log_max, int ranks) { return 2 * (1 << (log_max - 5)) + ranks; }
 constexpr int kSliceTfWords = 5;           // dynamic LDS words per field of a table
 
-// one occurrence of a slice
-struct SliceRec {
-    uint32_t kl;       // key minus the slice's first key
-    int32_t x;         // small batches: the field's index in the table's field list; large: the place of the gradient chunk
-    int32_t q;         // small batches: position in ids
-    int32_t b, L;      // small batches: bag of the field and its length, if known (b >= 0); large: L = the record's scale
-};
+// one occurrence of a slice: key minus the slice's first key, the place of its gradient chunk, the chunk's scale
+struct SliceRec { uint32_t kl, ref, L; };
 
-// MODE: what the block does with its slice
-//   kSliceFused  small batches: everything, occurrences found in the IDs, sums of the slices before it by look-back
-//   kSliceMark   large batches, first half: which keys occur -> the slice's bitmap and its number of distinct keys
-//   kSlicePlace  large batches, second half (after a scan of those numbers): everything else
+// MODE: what the block does with its slice of a large batch
+//   kSliceMark   first half: which keys occur -> the slice's bitmap and its number of distinct keys
+//   kSlicePlace  second half (after a scan of those numbers): everything else
 // (With thousands of slices in flight a look-back makes every block wait for the slowest slice before it;
 // two launches with a scan between them let every block run without waiting.)
-enum { kSliceFused = 0, kSliceMark = 1, kSlicePlace = 2 };
+enum { kSliceMark = 1, kSlicePlace = 2 };
 
 template <int MODE, int NTH, int LOGMAX, int RANKS, bool BIG = false>
 __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_t* s_main, int32_t* s_tf)
 {
-    constexpr bool FROM_IDS = MODE == kSliceFused;
-    constexpr bool GROUPED = FROM_IDS || BIG || NTH > 256;          // lanes that share a key combine their counter updates
+    constexpr bool GROUPED = BIG || NTH > 256;             // lanes that share a key combine their counter updates
     constexpr int WMAX = 1 << (LOGMAX - 5);
-    constexpr int CACHE = FROM_IDS ? (RANKS * 3 / 4) / 3 : 0;      // occurrences kept in LDS (12 bytes each)
-    static_assert(!FROM_IDS || (RANKS - 3 * CACHE >= CACHE), "cached occurrences need as many counters");
-    constexpr int kBagBits = 20;                                   // of a cached occurrence's third word: its bag; above them its length
-    constexpr uint32_t kLenMany = (1u << (32 - kBagBits)) - 1u;    // ... a length of this or more is looked up again
-    static_assert(!FROM_IDS || slice_lds_words(LOGMAX, RANKS) >= 3 * 4096 + 2, "the field scan must fit the block's LDS");
+    constexpr int KEEP = NTH > 256 ? 0 : 12;               // records per thread whose rank and place stay in a register
     const int tid = threadIdx.x;
     uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_main);
     uint32_t* s_pre = s_bits + WMAX;
     int32_t* s_cnt = s_main + 2 * WMAX;
-    uint32_t* s_ckey = reinterpret_cast<uint32_t*>(s_cnt + (RANKS - 3 * CACHE));   // key inside the slice | field of the table
-    uint32_t* s_cpos = s_ckey + CACHE;                                             // position in ids
-    uint32_t* s_cbag = s_cpos + CACHE;                                             // bag | its length
-    __shared__ uint32_t s_bc[4];
-    __shared__ int s_ncache;
-    const int F = a.F, B = a.B;
+    const int B = a.B;
     const int64_t out_dim = a.out_dim;
 
-    PK_PT(a, slice, 0);
     // ---- which slice, of which table; where the pack's arrays start ----
-    int t, idx, lg, n_tslices, pack_first, is_last, p, nf, field_begin, pstart, nnz_p, rec_start = 0, rec_count = 0;
-    uint32_t key_lo, rows, own_flags = 0;
-    if (FROM_IDS) {
-        const SmallSlice ss = a.small_slices[slice];
-        t = ss.table; idx = ss.idx; lg = ss.log_keys; n_tslices = ss.n_table_slices; pack_first = ss.pack_first;
-        is_last = ss.is_last; p = ss.pack; field_begin = ss.field_begin; nf = ss.field_end - ss.field_begin;
-        key_lo = ss.key_lo; rows = ss.rows;
-    } else {
-        const SliceInfo si = a.slice_info[slice];
-        if (si.table < 0) return;                                      // room for a slice this batch does not have
-        if (BIG != ((si.table & kBigSliceFlag) != 0)) return;          // listed slices belong to the launch that takes the list
-        t = si.table & ~kBigSliceFlag; idx = si.idx; rec_start = si.start; rec_count = si.count;
-        const TableMeta tm = a.tmeta[t];
-        p = tm.pack; field_begin = tm.field_begin; nf = tm.field_end - tm.field_begin; key_lo = tm.key_lo; rows = tm.rows;
-        const TableCut tc = a.cut[t];
-        lg = tc.log_keys; n_tslices = tc.n;
-        pack_first = 0; is_last = 0;
-    }
+    const SliceInfo si = a.slice_info[slice];
+    if (si.table < 0) return;                              // room for a slice this batch does not have
+    if (BIG != ((si.table & kBigSliceFlag) != 0)) return;  // listed slices belong to the launch that takes the list
+    const int t = si.table & ~kBigSliceFlag, idx = si.idx, rec_start = si.start, n_rec = si.count;
+    const TableMeta tm = a.tmeta[t];
+    const int p = tm.pack, nf = tm.field_end - tm.field_begin;
+    const uint32_t key_lo = tm.key_lo, rows = tm.rows;
+    const TableCut tc = a.cut[t];
+    const int lg = tc.log_keys;
     const PackMeta k = a.pm[p];
-    if (FROM_IDS) {
-        int32_t* s_fb = s_main;
-        int32_t* s_delta = s_fb + (F + 1);
-        int32_t* s_slotpos = s_delta + F;
-        const int bad = field_scan<NTH>(a.offsets, B, F, a.nnz, a.slot_field, s_fb, s_delta, s_slotpos);
-        pstart = s_slotpos[k.first_slot];
-        nnz_p = s_slotpos[k.first_slot + k.n_fields] - pstart;
+    const int pstart = a.st[p].start, nnz_p = a.st[p].nnz, pack_first = a.st[p].first_slice;
+    const bool is_last = t == k.first_stable + k.n_stables - 1 && idx + 1 == tc.n;     // last slice of the pack's last table
+    if (a.st[p].error) return;                             // offsets of this pack were rejected
+    if (MODE == kSlicePlace)
         for (int j = tid; j < nf; j += NTH) {
-            const TableField tf = a.tfields[field_begin + j];
-            s_tf[kSliceTfWords * j] = s_fb[tf.field];
-            s_tf[kSliceTfWords * j + 1] = s_fb[tf.field + 1];
-            s_tf[kSliceTfWords * j + 2] = s_delta[tf.field];
-            s_tf[kSliceTfWords * j + 3] = tf.col;
-            s_tf[kSliceTfWords * j + 4] = tf.pool | (tf.field << 1);
-        }
-        __syncthreads();
-        if (bad) {                                         // every block sees the same boundaries: nobody publishes, nobody waits
-            if (is_last && tid == 0) { a.st[p].n_unique = 0; a.st[p].error = 1; }
-            return;
-        }
-        // the offsets of this slice's share of the table's bags: inside the field and not decreasing
-        int viol = 0;
-        const int b_lo = (int)((int64_t)B * idx / n_tslices), b_hi = (int)((int64_t)B * (idx + 1) / n_tslices);
-        for (int j = 0; j < nf; ++j) {
-            const int32_t* offs = a.offsets + (int64_t)(s_tf[kSliceTfWords * j + 4] >> 1) * B;
-            for (int b = b_lo + tid; b < b_hi; b += NTH) {
-                const int o0 = offs[b], o1 = offs[b + 1];
-                viol |= o0 > o1 || o0 < s_tf[kSliceTfWords * j] || o1 > s_tf[kSliceTfWords * j + 1];
-            }
-        }
-        if (__syncthreads_or(viol)) own_flags |= 1u;
-    } else {
-        pstart = a.st[p].start;
-        nnz_p = a.st[p].nnz;
-        pack_first = a.st[p].first_slice;
-        is_last = t == k.first_stable + k.n_stables - 1 && idx + 1 == n_tslices;   // last slice of the pack's last table
-        if (a.st[p].error) return;                         // offsets of this pack were rejected: no block of it publishes or waits
-        for (int j = tid; j < nf; j += NTH) {
-            const TableField tf = a.tfields[field_begin + j];
+            const TableField tf = a.tfields[tm.field_begin + j];
             s_tf[kSliceTfWords * j] = tf.slot;
             s_tf[kSliceTfWords * j + 3] = tf.col;
-            s_tf[kSliceTfWords * j + 4] = tf.pool;
         }
-    }
-    PK_PT(a, slice, 1);
-    const uint64_t magic = FROM_IDS ? fold_magic(rows) : 0;  // (one division per block; the IDs are folded without)
     const uint32_t lo = (uint32_t)idx << lg;               // first key of the slice inside its table
     const uint32_t nkeys = min((uint32_t)1 << lg, rows - lo);
     const int words = 1 << (lg - 5);
-    bool cached = false;
-    int n_rec = 0;
 
-    // all occurrences of the slice, in any order: fn(SliceRec, on).  Every lane makes the same trips and
-    // calls fn every time, with on = false where it has no occurrence, so that fn may combine lanes.
+    // all records of the slice: fn(SliceRec, on).  Every lane makes the same trips and calls fn every time, with
+    // on = false where it has none, so that fn may combine lanes.
+    const uint2* __restrict__ rec = a.rec + rec_start;
+    auto unpack = [&](uint2 r, bool valid, bool* on) {
+        const uint32_t kl = r.x & ((1u << LOGMAX) - 1u);
+        *on = valid && kl < nkeys;
+        return SliceRec{*on ? kl : 0u, r.y, r.x >> LOGMAX};
+    };
     auto for_records = [&](auto&& fn) {
-        if (FROM_IDS && cached) {
-            for (int base = 0; base < n_rec; base += NTH) {
-                const int i = base + tid;
-                const bool on = i < n_rec;
-                const uint32_t ek = on ? s_ckey[i] : 0u, eq = on ? s_cpos[i] : 0u, eb = on ? s_cbag[i] : 0u;
-                const uint32_t L = eb >> kBagBits;
-                fn(SliceRec{ek & ((1u << LOGMAX) - 1u), (int32_t)(ek >> LOGMAX), (int32_t)eq,
-                            L == kLenMany ? -1 : (int32_t)(eb & ((1u << kBagBits) - 1u)), (int32_t)L}, on);
+        constexpr int UN = BIG ? 8 : 4;                    // records per thread in flight: a listed slice is long
+        for (int base = 0; base < n_rec; base += UN * NTH) {
+            uint2 r[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int i = base + tid + u * NTH;
+                r[u] = i < n_rec ? rec[i] : make_uint2(0, 0);
             }
-        } else if (FROM_IDS) {
-            for (int j = 0; j < nf; ++j) {
-                const int q0 = s_tf[kSliceTfWords * j], q1 = s_tf[kSliceTfWords * j + 1];
-                for (int base = q0; base < q1; base += 4 * NTH) {
-                    int64_t idv[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int i = base + tid + u * NTH;
-                        idv[u] = i < q1 ? a.ids[i] : 0;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int i = base + tid + u * NTH;
-                        const uint32_t kk = i < q1 ? fold_id(idv[u], rows, magic) : 0xFFFFFFFFu;
-                        const bool on = i < q1 && (kk >> lg) == (uint32_t)idx;
-                        fn(SliceRec{on ? kk - lo : 0u, j, i, -1, 0}, on);
-                    }
-                }
-            }
-        } else {
-            const uint2* __restrict__ rec = a.rec + rec_start;
-            constexpr int UN = BIG ? 8 : 4;                // records per thread in flight: a listed slice is long
-            for (int base = 0; base < rec_count; base += UN * NTH) {
-                uint2 r[UN];
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    const int i = base + tid + u * NTH;
-                    r[u] = i < rec_count ? rec[i] : make_uint2(0xFFFFFFFFu, 0);
-                }
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    const uint32_t kl = r[u].x & ((1u << LOGMAX) - 1u);
-                    const bool on = r[u].x != 0xFFFFFFFFu && kl < nkeys;
-                    fn(SliceRec{on ? kl : 0u, (int32_t)r[u].y, 0, -1, (int32_t)(r[u].x >> LOGMAX)}, on);
-                }
+            for (int u = 0; u < UN; ++u) {
+                bool on;
+                const SliceRec x = unpack(r[u], base + tid + u * NTH < n_rec, &on);
+                fn(x, on);
             }
         }
-    };
-    // the bag of an occurrence found in the IDs, and its length
-    auto bag_of = [&](int j, int q, int* L) {
-        const int32_t* offs = a.offsets + (int64_t)(s_tf[kSliceTfWords * j + 4] >> 1) * B;
-        const int b = find_bag(offs, B, q, q - s_tf[kSliceTfWords * j]);
-        *L = offs[b + 1] - offs[b];
-        return b;
     };
 
     // ---- which keys occur ----
     // The slice's bitmap in memory: word w of the table's bitmap stands at w + w / 3 of the table's
     // region, so that every 16 bytes hold three words and, in the fourth, the rank of their first key.
-    uint32_t* bmw = FROM_IDS ? nullptr : a.bitmap + a.tmeta[t].word_base;
+    uint32_t* bmw = a.bitmap + tm.word_base;
     const uint32_t tw0 = (uint32_t)idx * (uint32_t)words;
-    if (MODE == kSlicePlace) {
-        for (int w = tid; w < words; w += NTH) s_bits[w] = bmw[tw0 + w + (tw0 + w) / 3u];
-    } else {
+    if (MODE == kSliceMark) {
         for (int w = tid; w < words; w += NTH) s_bits[w] = 0;
-    }
-    if (tid == 0) s_ncache = 0;
-    __syncthreads();
-    int mine = 0;
-    if (MODE != kSlicePlace)
-    for_records([&](const SliceRec& r, bool on) {
-        if (on) {
-            const uint32_t bit = 1u << (r.kl & 31);
-            if (!(s_bits[r.kl >> 5] & bit)) atomicOr(&s_bits[r.kl >> 5], bit);
-            ++mine;
-        }
-        if (FROM_IDS) {                                    // keep the occurrence while it is at hand
-            const uint64_t m = __ballot(on);
-            if (m) {
-                const int lane = tid & 63, leader = __ffsll((unsigned long long)m) - 1;
-                int base = 0;
-                if (lane == leader) base = atomicAdd(&s_ncache, __popcll(m));
-                base = __shfl(base, leader, 64);
-                const int at = base + __popcll(m & ((1ull << lane) - 1ull));
-                if (on && at < CACHE) { s_ckey[at] = r.kl | ((uint32_t)r.x << LOGMAX); s_cpos[at] = (uint32_t)r.q; }
+        __syncthreads();
+        for_records([&](const SliceRec& r, bool on) {
+            if (on) {
+                const uint32_t bit = 1u << (r.kl & 31);
+                if (!(s_bits[r.kl >> 5] & bit)) atomicOr(&s_bits[r.kl >> 5], bit);
             }
+        });
+        __syncthreads();
+        int c = 0;
+        for (int w = tid; w < words; w += NTH) {
+            const uint32_t x = s_bits[w];
+            bmw[tw0 + w + (tw0 + w) / 3u] = x;             // the bitmap and the count go to memory; the rest follows the scan
+            c += __popc(x);
         }
-    });
-    (void)block_excl_scan<NTH>(mine, &n_rec);              // its barriers also complete the bitmap
-    if (!FROM_IDS) n_rec = rec_count;
-    cached = FROM_IDS && n_rec <= CACHE && B <= (1 << kBagBits);
-    if (cached) {                                          // the bags of the kept occurrences, all lookups in flight together
-        for (int i = tid; i < n_rec; i += NTH) {
-            int L;
-            const int b = bag_of((int)(s_ckey[i] >> LOGMAX), (int)s_cpos[i], &L);
-            s_cbag[i] = (uint32_t)b | (min((uint32_t)max(L, 0), kLenMany) << kBagBits);
-        }
+        int n_u;
+        (void)block_excl_scan<NTH>(c, &n_u);
+        if (tid == 0) a.slice_nu[slice] = n_u;
+        return;
     }
-    PK_PT(a, slice, 2);
+    for (int w = tid; w < words; w += NTH) s_bits[w] = bmw[tw0 + w + (tw0 + w) / 3u];
+    for (int i = tid; i < RANKS; i += NTH) s_cnt[i] = 0;
+    const int base_u = a.slice_nu[slice] - a.slice_nu[pack_first];     // scanned: distinct keys of the pack's slices before
+    const int rec_before = rec_start - pstart;
+    __syncthreads();
     // popcount prefix of the words: thread i owns words [i * wpt, (i + 1) * wpt)
     const int wpt = max(1, words / NTH);
     int c = 0;
@@ -677,101 +565,35 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
         for (int j = 0; j < wpt; ++j) c += __popc(s_bits[tid * wpt + j]);
     int n_u;
     const int ex = block_excl_scan<NTH>(c, &n_u);
-    if (tid * wpt < words) {
-        int run = ex;
-        for (int j = 0; j < wpt; ++j) {
-            s_pre[tid * wpt + j] = (uint32_t)run;
-            run += __popc(s_bits[tid * wpt + j]);
-        }
-    }
-    if (MODE == kSliceMark) {                              // the bitmap and the count go to memory; the rest follows the scan
-        for (int w = tid; w < words; w += NTH) bmw[tw0 + w + (tw0 + w) / 3u] = s_bits[w];
-        if (tid == 0) a.slice_nu[slice] = n_u;
+    // whatever the sums hold, no write below leaves the pack's arrays
+    if (base_u < 0 || rec_before < 0 || (int64_t)base_u + n_u > (int64_t)nnz_p || (int64_t)rec_before + n_rec > (int64_t)nnz_p) {
+        if (tid == 0) atomicOr(&a.st[p].error, 2);
         return;
     }
-    // the counts of this slice are out early: the slices after it add them up while it goes on
-    if (FROM_IDS && tid == 0)
-        publish_desc(a.desc + slice, make_desc(slice == pack_first ? kDescPfx : kDescAgg, (uint32_t)n_u, (uint32_t)n_rec, own_flags));
-    PK_PT(a, slice, 3);
-
-    int base_u = 0, rec_before = 0;
     uint32_t* __restrict__ uq = a.unique + pstart;
     int32_t* __restrict__ seg = a.seg_all + pstart + p;
-    // Distinct keys and occurrences of the pack's slices before this one; then what needs them: the slice's
-    // distinct keys (ascending) in their place, bitmap and rank samples for the inverse kernel, the pack's
-    // totals.  Returns false when the sums cannot be right (then nothing is written).
-    auto after_lookback = [&]() -> bool {
-        if (!FROM_IDS) {
-            if (tid == 0) { s_bc[0] = (uint32_t)(a.slice_nu[slice] - a.slice_nu[pack_first]); s_bc[2] = 0; }   // scanned: distinct keys before
-        } else if (tid < 64) {
-            uint32_t pa = 0, pb = 0, pf = 0;
-            if (slice != pack_first) {
-                const int g0 = (pack_first >> 6) + p;      // the pack's first group descriptor (packs never share one)
-                lookback_grouped(a.desc, a.gdesc, pack_first, g0, slice, (uint32_t)n_u, (uint32_t)n_rec, own_flags, &pa, &pb, &pf);
-                if (tid == 0) {
-                    const uint64_t incl = make_desc(kDescPfx, pa + (uint32_t)n_u, pb + (uint32_t)n_rec, pf | own_flags);
-                    publish_desc(a.desc + slice, incl);
-                    if (((slice - pack_first) & 63) == 63) publish_desc(a.gdesc + g0 + ((slice - pack_first) >> 6), incl);
-                }
-            }
-            if (tid == 0) {
-                s_bc[0] = pa; s_bc[1] = pb; s_bc[2] = pf | own_flags;
-                if (FROM_IDS) {
-                    // The descriptors belong to the library and must be zero when the next call starts: the
-                    // block that finishes its look-back last (every block has then published, and read what
-                    // it needed) clears them.  Reading the own descriptor back first makes sure that the
-                    // store has arrived before this block counts as finished (same address: same order).
-                    const uint64_t back = __hip_atomic_load(a.desc + slice, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    s_bc[3] = ((back >> 62) == kDescPfx && atomicAdd(a.done, 1) == a.n_slices - 1) ? 1u : 0u;
-                }
+    if (tid * wpt < words) {                               // prefix, and the slice's distinct keys (ascending) in their place
+        int run = ex;
+        for (int j = 0; j < wpt; ++j) {
+            const int w = tid * wpt + j;
+            s_pre[w] = (uint32_t)run;
+            uint32_t x = s_bits[w];
+            const uint32_t key0 = key_lo + lo + (uint32_t)w * 32u;
+            while (x) {
+                const int bit = __ffs(x) - 1;
+                x &= x - 1;
+                uq[base_u + run++] = key0 + bit;
             }
         }
-        __syncthreads();
-        PK_PT(a, slice, 4);
-        base_u = (int)s_bc[0];
-        rec_before = FROM_IDS ? (int)s_bc[1] : rec_start - pstart;
-        const uint32_t flags = s_bc[2];
-        if (FROM_IDS && s_bc[3]) {
-            for (int i = tid; i < a.n_slices; i += NTH) publish_desc(a.desc + i, 0);
-            for (int i = tid; i < (a.n_slices >> 6) + a.P + 2; i += NTH) publish_desc(a.gdesc + i, 0);
-            if (tid == 0) *a.done = 0;
-        }
-        // whatever the descriptors held, no write below leaves the pack's arrays
-        if (base_u < 0 || rec_before < 0 || (int64_t)base_u + n_u > (int64_t)nnz_p ||
-            (int64_t)rec_before + n_rec > (int64_t)nnz_p) {
-            if (tid == 0) atomicOr(&a.st[p].error, 2);
-            return false;
-        }
-        if (tid * wpt < words) {
-            for (int j = 0; j < wpt; ++j) {
-                const int w = tid * wpt + j;
-                uint32_t x = s_bits[w];
-                int at = base_u + (int)s_pre[w];
-                const uint32_t key0 = key_lo + lo + (uint32_t)w * 32u;
-                while (x) {
-                    const int bit = __ffs(x) - 1;
-                    x &= x - 1;
-                    uq[at++] = key0 + bit;
-                }
-            }
-        }
-        if (!FROM_IDS) {                                   // rank samples beside the bitmap, for the inverse kernel
-            for (uint32_t u = (tw0 + 2u) / 3u + tid; 3u * u < tw0 + (uint32_t)words; u += NTH)
-                bmw[4u * u + 3u] = (uint32_t)(base_u + (int)s_pre[3u * u - tw0]);
-        }
-        if (is_last && tid == 0) {
-            a.st[p].n_unique = base_u + n_u;
-            seg[base_u + n_u] = nnz_p;
-            if (FROM_IDS) a.st[p].error = (int32_t)flags;
-            else if (flags) atomicOr(&a.st[p].error, (int32_t)flags);
-        }
-        PK_PT(a, slice, 5);
-        return true;
-    };
-    if (n_u == 0) {
-        (void)after_lookback();
-        return;
     }
+    if (is_last && tid == 0) {
+        a.st[p].n_unique = base_u + n_u;
+        seg[base_u + n_u] = nnz_p;
+    }
+    __syncthreads();
+    for (uint32_t u = (tw0 + 2u) / 3u + tid; 3u * u < tw0 + (uint32_t)words; u += NTH)     // rank samples beside the bitmap, for the inverse kernel
+        bmw[4u * u + 3u] = (uint32_t)(base_u + (int)s_pre[3u * u - tw0]);
+    if (n_u == 0) return;
 
     // ---- occurrences per distinct key, segment offsets, marks for the backward pass, and every
     //      occurrence's gradient place at its key's next free position; a round handles RANKS keys ----
@@ -783,20 +605,22 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
     auto rank_of = [&](uint32_t kl) {
         return (int)(s_pre[kl >> 5] + __popc(s_bits[kl >> 5] & ((1u << (kl & 31)) - 1u)));
     };
-    const int rounds_cap = cached ? RANKS - 3 * CACHE : RANKS;      // cached occurrences take the upper counters' room
+    auto put = [&](const SliceRec& r, int pos) {
+        if ((unsigned)pos >= (unsigned)nnz_p) return;
+        if (!wide) { ent[pos] = r.ref; return; }
+        uint32_t len = r.L;
+        if (len == 0) {                                    // a bag too long for the record's bits: its length from the bag
+            const uint32_t b = r.ref / (uint32_t)out_dim, col = r.ref - b * (uint32_t)out_dim;
+            int j = 0;
+            while (j + 1 < nf && (uint32_t)s_tf[kSliceTfWords * j + 3] != col) ++j;
+            const uint32_t g = (uint32_t)s_tf[kSliceTfWords * j] * (uint32_t)B + b;
+            len = (uint32_t)max(po[g + 1] - po[g], 1);
+        }
+        reinterpret_cast<uint2*>(ent)[pos] = make_uint2(r.ref, len);
+    };
+    // counters of keys [r0, r0 + width) become the keys' first places; segment offsets and marks go out
     int placed = 0;                                        // occurrences of the keys of earlier rounds
-    for (int r0 = 0; r0 < n_u; r0 += rounds_cap) {
-        const int width = min(rounds_cap, n_u - r0);
-        __syncthreads();
-        for (int i = tid; i < width; i += NTH) s_cnt[i] = 0;
-        __syncthreads();
-        for_records([&](const SliceRec& r, bool on) {
-            const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
-            if (GROUPED) (void)lds_inc_grouped(s_cnt, rr, on && rr < (uint32_t)width);
-            else if (on && rr < (uint32_t)width) atomicAdd(&s_cnt[rr], 1);
-        });
-        __syncthreads();
-        PK_PT(a, slice, 6);
+    auto starts = [&](int r0, int width) {
         const int per = (width + NTH - 1) / NTH;           // consecutive counters per thread
         int sum = 0;
         for (int j = 0; j < per; ++j) {
@@ -805,7 +629,6 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
         }
         int tot;
         const int ex_occ = block_excl_scan<NTH>(sum, &tot);
-        if (r0 == 0 && !after_lookback()) return;          // the same for every thread
         int s0 = rec_before + placed + ex_occ;
         for (int j = 0; j < per; ++j) {
             const int i = tid * per + j;
@@ -813,7 +636,7 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
                 const int len = s_cnt[i];
                 const int u = base_u + r0 + i;
                 seg[u] = s0;
-                s_cnt[i] = s0;                             // from here on: the segment's next free position
+                s_cnt[i] = s0;
                 // every kMarkStep-th position names its key: how the backward pass finds the long ones
                 for (int m = (s0 + kMarkStep - 1) / kMarkStep; (int64_t)m * kMarkStep < (int64_t)s0 + len; ++m) marks[m] = u;
                 if (len >= 2 * kPiece) {                   // the key is reduced in pieces: its partial sums start at zero
@@ -825,50 +648,74 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
                 s0 += len;
             }
         }
+        placed += tot;
+    };
+    if (KEEP && n_rec <= KEEP * NTH && n_u <= RANKS) {
+        // The counting pass gives every record its key's rank and its place among the key's occurrences: both fit a
+        // register, and the placing pass needs no counter.
+        uint32_t rp[KEEP ? KEEP : 1];
+#pragma unroll
+        for (int u0 = 0; u0 < KEEP; u0 += 4) {
+            if (u0 * NTH >= n_rec) break;
+            uint2 r[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = tid + (u0 + u) * NTH;
+                r[u] = i < n_rec ? rec[i] : make_uint2(0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                bool on;
+                const SliceRec x = unpack(r[u], tid + (u0 + u) * NTH < n_rec, &on);
+                const uint32_t rk = (uint32_t)rank_of(x.kl);
+                rp[u0 + u] = on ? rk | ((uint32_t)atomicAdd(&s_cnt[rk], 1) << 16) : 0xFFFFFFFFu;
+            }
+        }
         __syncthreads();
-        PK_PT(a, slice, 7);
+        starts(0, n_u);
+        __syncthreads();
+#pragma unroll
+        for (int u0 = 0; u0 < KEEP; u0 += 4) {
+            if (u0 * NTH >= n_rec) break;
+            uint2 r[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = tid + (u0 + u) * NTH;
+                r[u] = i < n_rec ? rec[i] : make_uint2(0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                bool on;
+                const SliceRec x = unpack(r[u], tid + (u0 + u) * NTH < n_rec, &on);
+                if (on) put(x, s_cnt[rp[u0 + u] & 0xFFFFu] + (int)(rp[u0 + u] >> 16));
+            }
+        }
+        return;
+    }
+    for (int r0 = 0; r0 < n_u; r0 += RANKS) {
+        const int width = min(RANKS, n_u - r0);
+        if (r0) {
+            __syncthreads();
+            for (int i = tid; i < width; i += NTH) s_cnt[i] = 0;
+            __syncthreads();
+        }
         for_records([&](const SliceRec& r, bool on) {
-            const int rk = rank_of(r.kl);
-            const uint32_t rr = (uint32_t)(rk - r0);
+            const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
+            if (GROUPED) (void)lds_inc_grouped(s_cnt, rr, on && rr < (uint32_t)width);
+            else if (on && rr < (uint32_t)width) atomicAdd(&s_cnt[rr], 1);
+        });
+        __syncthreads();
+        starts(r0, width);
+        __syncthreads();
+        for_records([&](const SliceRec& r, bool on) {
+            const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
             on = on && rr < (uint32_t)width;
             int pos = 0;
             if (GROUPED) pos = lds_inc_grouped(s_cnt, rr, on);
-            if (!on) return;
-            if (!GROUPED) pos = atomicAdd(&s_cnt[rr], 1);
-            uint32_t ref, len = 1u;
-            if (FROM_IDS) {
-                int L = r.L, b = r.b;
-                if (b < 0) b = bag_of(r.x, r.q, &L);
-                ref = (uint32_t)((int64_t)b * out_dim + s_tf[kSliceTfWords * r.x + 3]);
-                if ((s_tf[kSliceTfWords * r.x + 4] & 1) == PK_MEAN && L > 0) len = (uint32_t)L;
-                const int qp = r.q + s_tf[kSliceTfWords * r.x + 2];
-                if ((unsigned)qp < (unsigned)a.nnz) {
-                    a.keys[qp] = key_lo + lo + r.kl;
-                    a.inverse[qp] = base_u + rk;
-                }
-            } else {
-                ref = (uint32_t)r.x;                       // the record holds the place of the gradient chunk
-                if (wide) {
-                    len = (uint32_t)r.L;
-                    if (len == 0) {                        // a bag too long for the record's bits: its length from the bag
-                        const uint32_t b = ref / (uint32_t)out_dim, col = ref - b * (uint32_t)out_dim;
-                        int j = 0;
-                        while (j + 1 < nf && (uint32_t)s_tf[kSliceTfWords * j + 3] != col) ++j;
-                        const uint32_t g = (uint32_t)s_tf[kSliceTfWords * j] * (uint32_t)B + b;
-                        len = (uint32_t)max(po[g + 1] - po[g], 1);
-                    }
-                }
-            }
-            if ((unsigned)pos < (unsigned)nnz_p) {
-                if (wide) reinterpret_cast<uint2*>(ent)[pos] = make_uint2(ref, len);
-                else ent[pos] = ref;
-            }
+            else if (on) pos = atomicAdd(&s_cnt[rr], 1);
+            if (on) put(r, pos);
         });
-        placed += tot;
     }
-
-    __syncthreads();
-    PK_PT(a, slice, 8);
 }
 
 // Large batches: one block per slice, in two launches with a scan between them.

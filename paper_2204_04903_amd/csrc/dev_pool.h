@@ -259,10 +259,11 @@ __global__ void __launch_bounds__(kSliceThreads, WAVES)
 pk_fused_kernel(SliceArgs a, PoolJob pj, int slice_blocks, int meta_blocks)
 {
     extern __shared__ int32_t s_dyn[];                     // kSliceTfWords words per field of a table
-    __shared__ int32_t s_main[slice_lds_words(kSliceLogMax, kSliceRanks)];
-    static_assert(slice_lds_words(kSliceLogMax, kSliceRanks) >= kSliceThreads / 64 * (64 * kRunMax + 1), "the pooling's offsets must fit the block's LDS");
+    __shared__ int32_t s_main[kSmallLdsWords];
+    static_assert(kSmallLdsWords >= kSliceThreads / 64 * (64 * kRunMax + 1), "the pooling's offsets must fit the block's LDS");
+    static_assert(kSmallLdsWords >= 3 * 4096 + 2, "the field scan must fit the block's LDS");
     if ((int)blockIdx.x < slice_blocks) {
-        slice_body<kSliceFused, kSliceThreads, kSliceLogMax, kSliceRanks>(a, blockIdx.x, s_main, s_dyn);
+        small_slice_body(a, blockIdx.x, s_main, s_dyn);
         return;
     }
     PK_PT(a, blockIdx.x, 0);

@@ -35,10 +35,6 @@ __device__ __forceinline__ void load_u32(const uint32_t* p, uint32_t* v)
 
 __device__ __forceinline__ int lane_col(int li, int D) { return D >= 4 ? min(4 * li, D - 4) : 0; }
 
-// a pointer that came out of a struct, known to be a global one (the compiler cannot see it: it would use flat accesses)
-template <typename T>
-__device__ __forceinline__ T* as_global(T* p) { return (T*)(__attribute__((address_space(1))) T*)p; }
-
 template <bool NARROW>
 __device__ __forceinline__ void load_f32x4(const float* p, int D, float (&v)[4])
 {

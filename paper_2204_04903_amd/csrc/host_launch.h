@@ -13,7 +13,8 @@ struct DeviceState {
     int32_t* slot_field = nullptr;
     uint64_t* small_desc = nullptr;       // look-back descriptors of the one-launch forward pass (zero between calls)
     int32_t* small_done = nullptr;        // ... and its count of blocks that are through their look-back
-    SmallSlice* small_slices = nullptr;   // the cut of the one-launch forward pass
+    SmallSlice* small_slices[kSmallCuts] = {};   // the cuts of the one-launch forward pass
+    int2* slot_info = nullptr;            // per slot (over all packs): its field, the field's table in the table list
     TableField* tfields = nullptr;        // the table field list with what the slice blocks need of a field
     TableMeta* sort_tables = nullptr;
     int32_t* table_fields = nullptr;
@@ -48,7 +49,8 @@ struct MetaImage {
     std::vector<PackMeta> pmv;
     std::vector<TableField> tfi;
     std::vector<SlotMeta> slm;
-    size_t o_desc, o_done, o_fm, o_pm, o_slot, o_ss, o_tfi, o_tab, o_tf, o_slm, total;
+    std::vector<int2> sli;
+    size_t o_desc, o_done, o_fm, o_pm, o_slot, o_sli, o_ss[kSmallCuts], o_tfi, o_tab, o_tf, o_slm, total;
 };
 
 void build_meta_image(const pk_plan* plan, MetaImage* mi)
@@ -88,15 +90,18 @@ void build_meta_image(const pk_plan* plan, MetaImage* mi)
         const TableMeta& tm = plan->sort_tables[m.stable];
         mi->slm[j] = SlotMeta{tm.key_lo, tm.word_base, tm.rows, m.pack};
     }
+    mi->sli.resize(F);
+    for (size_t j = 0; j < F; ++j) mi->sli[j] = make_int2(plan->slot_field[j], mi->fm[plan->slot_field[j]].stable);
     auto pad = [](size_t b) { return (b + 255) / 256 * 256; };
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += pad(bytes); return o; };
-    mi->o_desc = take(((size_t)kSmallSlicesMax + kSmallSlicesMax / 64 + 4096 + 2) * 8);   // per slice, then per group of 64
+    mi->o_desc = take(((size_t)kSmallSlicesMax + kSmallSlicesMax / kDescGroup + 4096 + 2) * 8);   // per slice, then per group
     mi->o_done = take(256);
     mi->o_fm   = take(F * sizeof(FieldMeta));
     mi->o_pm   = take(P * sizeof(PackMeta));
     mi->o_slot = take(F * 4);
-    mi->o_ss   = take(plan->small_slices.size() * sizeof(SmallSlice));
+    mi->o_sli  = take(F * sizeof(int2));
+    for (int c = 0; c < kSmallCuts; ++c) mi->o_ss[c] = take(plan->small_slices[c].size() * sizeof(SmallSlice));
     mi->o_tfi  = take(mi->tfi.size() * sizeof(TableField));
     mi->o_tab  = take(plan->sort_tables.size() * sizeof(TableMeta));
     mi->o_tf   = take(plan->table_fields.size() * 4);
@@ -111,7 +116,8 @@ void point_into(DeviceState* ds, char* base, const MetaImage& mi)
     ds->fmeta = reinterpret_cast<FieldMeta*>(base + mi.o_fm);
     ds->pmeta = reinterpret_cast<PackMeta*>(base + mi.o_pm);
     ds->slot_field = reinterpret_cast<int32_t*>(base + mi.o_slot);
-    ds->small_slices = reinterpret_cast<SmallSlice*>(base + mi.o_ss);
+    ds->slot_info = reinterpret_cast<int2*>(base + mi.o_sli);
+    for (int c = 0; c < kSmallCuts; ++c) ds->small_slices[c] = reinterpret_cast<SmallSlice*>(base + mi.o_ss[c]);
     ds->tfields = reinterpret_cast<TableField*>(base + mi.o_tfi);
     ds->sort_tables = reinterpret_cast<TableMeta*>(base + mi.o_tab);
     ds->table_fields = reinterpret_cast<int32_t*>(base + mi.o_tf);
@@ -125,7 +131,8 @@ void for_meta_pieces(const pk_plan* plan, const MetaImage& mi, Fn&& fn)
     fn(mi.o_fm, mi.fm.data(), mi.fm.size() * sizeof(FieldMeta));
     fn(mi.o_pm, mi.pmv.data(), mi.pmv.size() * sizeof(PackMeta));
     fn(mi.o_slot, plan->slot_field.data(), plan->slot_field.size() * 4);
-    fn(mi.o_ss, plan->small_slices.data(), plan->small_slices.size() * sizeof(SmallSlice));
+    fn(mi.o_sli, mi.sli.data(), mi.sli.size() * sizeof(int2));
+    for (int c = 0; c < kSmallCuts; ++c) fn(mi.o_ss[c], plan->small_slices[c].data(), plan->small_slices[c].size() * sizeof(SmallSlice));
     fn(mi.o_tfi, mi.tfi.data(), mi.tfi.size() * sizeof(TableField));
     fn(mi.o_tab, plan->sort_tables.data(), plan->sort_tables.size() * sizeof(TableMeta));
     fn(mi.o_tf, plan->table_fields.data(), plan->table_fields.size() * 4);

@@ -41,7 +41,8 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 // One translation unit; the kernels and their launch helpers are kept in section files:
 //   dev_common.h   block scans, folding hash, look-back prefix sums, tile order
-//   dev_dedup.h    keys, slice scan, scatter, slices, inverse (H1, H2)
+//   dev_dedup.h    keys, slice scan, scatter, slices, inverse (H1, H2), large batches
+//   dev_small.h    H1 and H2 of small batches
 //   dev_rows.h     row access, plain or hybrid row addressing
 //   dev_pool.h     pooling (H3-H5) and the one launch of the forward pass for small batches
 //   dev_adagrad.h  gradient reduction + Adagrad (H6, H7)
@@ -52,6 +53,7 @@ namespace {
 
 #include "dev_common.h"
 #include "dev_dedup.h"
+#include "dev_small.h"
 #include "dev_rows.h"
 #include "dev_pool.h"
 #include "dev_adagrad.h"
@@ -139,7 +141,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     sa.tmeta = ds->sort_tables; sa.tfields = ds->tfields; sa.T = T;
     sa.fmeta = ds->fmeta; sa.pm = ds->pmeta; sa.slot_field = ds->slot_field; sa.st = st; sa.P = P;
     sa.F = F; sa.B = B; sa.nnz = nnz;
-    sa.ids = ids; sa.offsets = offsets; sa.small_slices = ds->small_slices;
+    sa.ids = ids; sa.offsets = offsets; sa.small_slices = ds->small_slices[L.small_cut]; sa.slot_info = ds->slot_info;
     sa.packed_offsets = packed_offsets;
     sa.keys = keys; sa.inverse = inverse;
     sa.unique = unique; sa.seg_all = seg; sa.ent_all = seg_ent; sa.ent_mult = plan->any_mean ? 2 : 1;

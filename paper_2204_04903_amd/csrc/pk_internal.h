@@ -73,13 +73,12 @@ inline int32_t slice_count_max(uint32_t rows, int64_t nnz, int32_t target, int32
     return (int32_t)std::min(fine, std::max(coarse, want));
 }
 
-// Small batches: the cut depends on the plan alone (up to 8 slices per table, fewer when there are
-// many tables), so the list of slices is made once, on the host.
-inline SliceGeom slice_geom_small(int64_t rows, int32_t n_tables)
+// Small batches: a table's keys in about `want` slices, none longer than a block's LDS bitmap.  Lists for 1, 2, 4
+// and 8 are made once, on the host, and a call takes the one that its occurrences per table ask for (a slice
+// block scans all IDs of its table, so slices with few occurrences only add blocks to wait for).
+constexpr int kSmallCuts = 4;
+inline SliceGeom slice_geom_small(int64_t rows, int32_t want)
 {
-    int64_t want = 1024 / (n_tables > 0 ? n_tables : 1);
-    if (want > 8) want = 8;
-    if (want < 1) want = 1;
     const int64_t per = (rows + want - 1) / want;
     int lg = kSliceLogMin;
     while (lg < kSliceLogMax && ((int64_t)1 << lg) < per) ++lg;
@@ -88,8 +87,17 @@ inline SliceGeom slice_geom_small(int64_t rows, int32_t n_tables)
     g.n = (int32_t)((rows + ((int64_t)1 << lg) - 1) >> lg);
     return g;
 }
+// occurrences per slice aimed at, and slices of all tables together at most (beyond the tables' own number)
+constexpr int64_t kSmallSliceOcc = 1024;
+inline int small_cut(int64_t nnz, int64_t n_tables)
+{
+    int cut = 0;
+    while (cut + 1 < kSmallCuts && nnz > ((int64_t)kSmallSliceOcc * n_tables << cut) && ((int64_t)n_tables << (cut + 1)) <= 1024) ++cut;
+    return cut;
+}
 
-// One slice of the small-batch cut; static, device side, in (pack, table, slice) order.
+// One slice of the small-batch cut, with all that its block needs of the plan; static, device side, in
+// (pack, table, slice) order.
 struct SmallSlice {
     int32_t table;           // index in the table list
     int32_t idx;             // slice of the table
@@ -98,9 +106,13 @@ struct SmallSlice {
     int32_t pack_first;      // the pack's first slice
     int32_t is_last;         // the pack's last slice
     int32_t pack;
-    int32_t field_begin, field_end;   // the table's fields in the table field list
+    int32_t field_begin, n_fields;    // the table's fields in the table field list
     uint32_t key_lo, rows;   // the table's first key inside its pack, its rows
+    int32_t dim, wide;       // of the pack: dimension; entries carry bag lengths
+    int32_t first_slot, pack_fields;  // the pack's first slot, its fields
+    int32_t slot0, field0, col0, pool0;   // the table's first field: slot (over all packs), index, column, pooling
     int32_t pad;
+    uint64_t magic;          // FieldMeta::magic
 };
 
 // Per field, device side (indexed by field index).
@@ -196,6 +208,7 @@ struct Layout {
     int32_t dmax;
     int32_t bags_per_tile;       // bags per tile of the keys and scatter kernels
     int32_t tile_hist_stride;    // entries per tile of the stored per-slice counts (0: not stored, the scatter kernel counts again)
+    int32_t small_cut;           // the cut of a small batch
     bool small;                  // the forward pass's dedup is one launch (every slice block scans its table's IDs)
 };
 
@@ -213,7 +226,7 @@ struct pk_plan {
     std::vector<int32_t> slot_field;      // fields in (pack, slot) order
     std::vector<pk::TableMeta> sort_tables;   // tables with fields, in (pack, first key) order
     std::vector<int32_t> table_fields;        // per entry of sort_tables: the fields that read it
-    std::vector<pk::SmallSlice> small_slices; // the cut used by the one-launch forward pass
+    std::vector<pk::SmallSlice> small_slices[pk::kSmallCuts];   // the cuts the one-launch forward pass chooses from
     int64_t out_dim = 0;
     bool any_mean = false;
     int64_t bitmap_words = 0;             // all tables' bitmaps with their rank samples

@@ -49,7 +49,8 @@ Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz)
     const size_t F = plan->fields.size(), P = plan->packs.size();
     const size_t n = (size_t)std::max<int64_t>(nnz, 1);
     Layout L{};
-    int64_t slices = (int64_t)plan->small_slices.size();
+    L.small_cut = small_cut(nnz, (int64_t)plan->sort_tables.size());
+    int64_t slices = (int64_t)plan->small_slices[L.small_cut].size();
     int32_t most = 0;
     L.small = nnz < kSmallNnz && slices <= kSmallSlicesMax && !(plan->opts.debug & 2);
     L.log_max = kSliceLogMax;
@@ -266,20 +267,29 @@ pk_status pk_plan_create(const pk_table_desc* tables, int32_t n_tables, const pk
         delete pl;
         return fail(PK_EOVERFLOW, "pk_plan_create: the tables' bitmaps do not fit 2^32 words");
     }
-    // the cut of the one-launch forward pass
-    for (size_t p = 0; p < pl->packs.size(); ++p) {
-        const Pack& k = pl->packs[p];
-        const int32_t pack_first = (int32_t)pl->small_slices.size();
-        for (int32_t i = 0; i < k.n_stables; ++i) {
-            const TableMeta& tm = pl->sort_tables[k.first_stable + i];
-            const SliceGeom g = slice_geom_small(tm.rows, (int32_t)pl->sort_tables.size());
-            for (int32_t j = 0; j < g.n; ++j) {
-                SmallSlice ss{};
-                ss.table = k.first_stable + i; ss.idx = j; ss.log_keys = g.log_keys; ss.n_table_slices = g.n;
-                ss.pack_first = pack_first; ss.is_last = (i + 1 == k.n_stables && j + 1 == g.n) ? 1 : 0;
-                ss.pack = (int32_t)p; ss.field_begin = tm.field_begin; ss.field_end = tm.field_end;
-                ss.key_lo = tm.key_lo; ss.rows = tm.rows;
-                pl->small_slices.push_back(ss);
+    // the cuts of the one-launch forward pass
+    for (int cut = 0; cut < kSmallCuts; ++cut) {
+        std::vector<SmallSlice>& list = pl->small_slices[cut];
+        for (size_t p = 0; p < pl->packs.size(); ++p) {
+            const Pack& k = pl->packs[p];
+            const int32_t pack_first = (int32_t)list.size();
+            for (int32_t i = 0; i < k.n_stables; ++i) {
+                const TableMeta& tm = pl->sort_tables[k.first_stable + i];
+                const SliceGeom g = slice_geom_small(tm.rows, 1 << cut);
+                const int32_t f0 = pl->table_fields[tm.field_begin];
+                for (int32_t j = 0; j < g.n; ++j) {
+                    SmallSlice ss{};
+                    ss.table = k.first_stable + i; ss.idx = j; ss.log_keys = g.log_keys; ss.n_table_slices = g.n;
+                    ss.pack_first = pack_first; ss.is_last = (i + 1 == k.n_stables && j + 1 == g.n) ? 1 : 0;
+                    ss.pack = (int32_t)p; ss.field_begin = tm.field_begin; ss.n_fields = tm.field_end - tm.field_begin;
+                    ss.key_lo = tm.key_lo; ss.rows = tm.rows;
+                    ss.dim = k.dim; ss.wide = k.has_mean ? 1 : 0;
+                    ss.first_slot = k.first_slot; ss.pack_fields = (int32_t)k.fields.size();
+                    ss.slot0 = k.first_slot + pl->field_slot[f0]; ss.field0 = f0;
+                    ss.col0 = (int32_t)pl->field_col[f0]; ss.pool0 = fields[f0].pool;
+                    ss.magic = ~(uint64_t)0 / (uint64_t)tm.rows;
+                    list.push_back(ss);
+                }
             }
         }
     }
