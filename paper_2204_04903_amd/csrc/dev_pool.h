@@ -263,7 +263,8 @@ pk_fused_kernel(SliceArgs a, PoolJob pj, int slice_blocks, int meta_blocks)
     static_assert(kSmallLdsWords >= kSliceThreads / 64 * (64 * kRunMax + 1), "the pooling's offsets must fit the block's LDS");
     static_assert(kSmallLdsWords >= 3 * 4096 + 2, "the field scan must fit the block's LDS");
     if ((int)blockIdx.x < slice_blocks) {
-        small_slice_body(a, blockIdx.x, s_main, s_dyn);
+        // (the kernel's arguments where they stand: `a` is the first of them)
+        small_slice_body<(WAVES > 4)>((SliceArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x, s_main, s_dyn);
         return;
     }
     PK_PT(a, blockIdx.x, 0);

@@ -23,7 +23,111 @@ constexpr int kDescGroup = 16;           // slices whose distinct keys also add 
 
 __device__ __forceinline__ uint64_t small_load(const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-__device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, int32_t* s_main, int32_t* s_tf)
+// LEAN (two blocks per CU): the kernel's arguments and the slice's description are read where they are used,
+// through pointers that the compiler loses track of between the phases: held from the start they are forty scalar
+// registers more than there are, and with the spills of those the 26-field launch is 5 us slower.  A block that has
+// its CU to itself has the registers and would only wait for the reads.
+typedef const __attribute__((address_space(4))) SliceArgs* SliceArgsPtr;
+typedef const __attribute__((address_space(4))) SmallSlice* SmallSlicePtr;
+template <bool LEAN>
+__device__ __forceinline__ SliceArgsPtr forget(SliceArgsPtr p)
+{
+    if (LEAN) asm volatile("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ SmallSlicePtr slice_at(SliceArgsPtr a, int slice) { return (SmallSlicePtr)a->small_slices + slice; }
+
+// what the phases of a block hand on, in LDS
+struct SmallCtx { int32_t pstart, nnz_p, rec_before, n_rec, n_u, q0; };
+
+// writes of one occurrence: its key and inverse, its entry in its key's segment
+__device__ __forceinline__ void small_place(SliceArgsPtr a, SmallSlicePtr ss, const int32_t* tf, int pstart, int nnz_p, int base_u,
+                                            uint32_t kl, int q, int rk, int pos, int b, int L)
+{
+    const uint32_t ref = (uint32_t)((int64_t)b * a->out_dim + tf[3]);
+    const int qp = q + tf[2];
+    if ((unsigned)qp < (unsigned)a->nnz) {
+        as_global(a->keys)[qp] = ss->key_lo + ((uint32_t)ss->idx << ss->log_keys) + kl;
+        as_global(a->inverse)[qp] = base_u + rk;
+    }
+    if ((unsigned)pos < (unsigned)nnz_p) {
+        uint32_t* ent = as_global(a->ent_all) + (size_t)pstart * a->ent_mult;
+        if (ss->wide) reinterpret_cast<uint2*>(ent)[pos] = make_uint2(ref, (tf[4] & 1) == PK_MEAN && L > 0 ? (uint32_t)L : 1u);   // the pack's entries carry the bag length
+        else ent[pos] = ref;
+    }
+}
+
+// counters of keys [r0, r0 + width) become the keys' first places; segment offsets and marks go out
+__device__ __forceinline__ void small_starts(SliceArgsPtr a, SmallSlicePtr ss, int32_t* s_cnt, int pstart, int base_u, int r0, int width, int s0, int per)
+{
+    const int p = ss->pack;
+    int32_t* seg = as_global(a->seg_all) + pstart + p + base_u + r0;
+    int32_t* marks = as_global(a->marks) + (pstart / kMarkStep + p);
+    for (int j = 0; j < per; ++j) {
+        const int i = (int)threadIdx.x * per + j;
+        if (i < width) {
+            const int len = s_cnt[i];
+            seg[i] = s0;
+            s_cnt[i] = s0;
+            for (int m = (s0 + kMarkStep - 1) / kMarkStep; (int64_t)m * kMarkStep < (int64_t)s0 + len; ++m) marks[m] = base_u + r0 + i;
+            if (len >= 2 * kPiece) {                       // the key is reduced in pieces: its partial sums start at zero
+                const size_t slot = (size_t)(pstart / kPiece + p) + (size_t)(s0 / kPiece);
+                double* gh = as_global(a->ghot) + slot * a->dmax;
+                for (int d = 0; d < ss->dim; ++d) gh[d] = 0.0;
+                as_global(a->ticket)[slot] = 0;
+            }
+            s0 += len;
+        }
+    }
+}
+
+__device__ __forceinline__ int small_sum(const int32_t* s_cnt, int width, int per)
+{
+    int s = 0;
+    for (int j = 0; j < per; ++j) {
+        const int i = (int)threadIdx.x * per + j;
+        s += i < width ? s_cnt[i] : 0;
+    }
+    return s;
+}
+
+__device__ __forceinline__ int small_rank(const uint32_t* s_bits, const uint32_t* s_pre, uint32_t kl)
+{
+    return (int)(s_pre[kl >> 5] + __popc(s_bits[kl >> 5] & ((1u << (kl & 31)) - 1u)));
+}
+
+// bag offsets in LDS: every 2^step_log-th
+__device__ __forceinline__ int small_step(int B)
+{
+    int k = 0;
+    while (((B + (1 << k) - 1) >> k) + 1 > kSmallOffs) ++k;
+    return k;
+}
+
+// the bag of position q and its length, for a table with one field: from the samples in LDS (where they are),
+// then the few bags between two of them
+__device__ __forceinline__ int small_bag(const int32_t* __restrict__ offs, int B, const int32_t* s_offs, bool sampled, int guess, int q, int* L)
+{
+    int b;
+    if (sampled) {
+        const int step_log = small_step(B), n_offs = ((B + (1 << step_log) - 1) >> step_log) + 1;
+        int k = upper_bound_i32(s_offs, n_offs, q) - 1;
+        if (step_log == 0) {
+            k = min(max(k, 0), B - 1);
+            *L = s_offs[k + 1] - s_offs[k];
+            return k;
+        }
+        k = max(k, 0) << step_log;
+        b = min(max(k + upper_bound_i32(offs + k, max(min(1 << step_log, B - k), 0), q) - 1, 0), B - 1);
+    } else {
+        b = find_bag(offs, B, q, guess);
+    }
+    *L = offs[b + 1] - offs[b];
+    return b;
+}
+
+template <bool LEAN>
+__device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int32_t* s_main, int32_t* s_tf)
 {
     constexpr int NTH = kSliceThreads, NW = NTH / 64;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -34,68 +138,71 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
     int32_t* s_cpos = s_cnt + kSmallRanks + kSmallCache;
     int32_t* s_offs = s_cpos + kSmallCache;
     __shared__ int4 s_red[NW];
-    __shared__ int s_wsum[NW];
-    __shared__ int s_n, s_before, s_flag, s_odd, s_base;
-    const int F = a.F, B = a.B;
-    const int64_t nnz = a.nnz, out_dim = a.out_dim;
-    const int32_t* __restrict__ offsets = as_global(a.offsets);
-    const int64_t* __restrict__ ids = as_global(a.ids);
-    PK_PT(a, slice, 0);
-    const SmallSlice ss = as_global(a.small_slices)[slice];
-    const int lg = ss.log_keys, p = ss.pack, nf = ss.n_fields;      // (fields of the table)
-    const uint32_t rows = ss.rows, lo = (uint32_t)ss.idx << lg;     // first key of the slice inside its table
+    __shared__ int s_n, s_before, s_flag, s_base;
+    __shared__ SmallCtx s_ctx;
+    const int F = a->F, B = a->B;
+    const int64_t nnz = a->nnz;
+    const int32_t* __restrict__ offsets = as_global(a->offsets);
+    const int64_t* __restrict__ ids = as_global(a->ids);
+    PK_PT(*a, slice, 0);
+    SmallSlicePtr ss = slice_at(a, slice);
+    const int lg = ss->log_keys, nf = ss->n_fields;        // (fields of the table)
+    const uint32_t lo = (uint32_t)ss->idx << lg;           // first key of the slice inside its table
     const int words = 1 << (lg - 5);
 
-    // ---- sizes: occurrences of the packs before, of the tables before, of the pack, of the slots before ----
-    int4 sum = make_int4(0, 0, 0, 0);
-    int bad = 0, viol = 0;
-    for (int i = tid; i < F; i += NTH) {
-        const int2 sf = as_global(a.slot_info)[i];         // field, its table in the (pack, first key) order
-        const int o0 = offsets[(int64_t)sf.x * B], o1 = offsets[(int64_t)(sf.x + 1) * B];
-        const int len = o1 - o0;
-        bad |= len < 0 || (sf.x == 0 && o0 != 0) || (sf.x == F - 1 && (int64_t)o1 != nnz);
-        sum.x += i < ss.first_slot ? len : 0;
-        sum.y += sf.y < ss.table ? len : 0;
-        sum.z += i >= ss.first_slot && i < ss.first_slot + ss.pack_fields ? len : 0;
-        sum.w += i < ss.slot0 ? len : 0;
-    }
-    // the table's (first) field: where its occurrences are; the first of them and of the offsets on their way
+    // ---- what can be asked for at once, in the order it is needed ----
+    // field sizes; the offsets of this slice's share of the table's bags; the first IDs
+    int2 sf = make_int2(0, 0);
+    if (tid < F) sf = as_global(a->slot_info)[tid];         // the slot's field, its table in the (pack, first key) order
     const int n_all = (int)nnz;
-    const int fb0 = offsets[(int64_t)ss.field0 * B];
-    const int q0 = min(max(fb0, 0), n_all), q1 = min(max(offsets[(int64_t)(ss.field0 + 1) * B], q0), n_all);
-    const int32_t* __restrict__ offs0 = offsets + (int64_t)ss.field0 * B;
+    const int32_t* __restrict__ offs0 = offsets + (int64_t)ss->field0 * B;
+    const int fb0 = offs0[0], fe0 = offs0[B];              // the table's (first) field: where its occurrences are
+    const int b_lo = (int)((int64_t)B * ss->idx / ss->n_table_slices), b_hi = (int)((int64_t)B * (ss->idx + 1) / ss->n_table_slices);
+    int share0 = 0, share1 = 0;
+    if (b_lo + tid < b_hi) { share0 = offs0[b_lo + tid]; share1 = offs0[b_lo + tid + 1]; }
+    int o0 = 0, o1 = 0;
+    if (tid < F) { o0 = offsets[(int64_t)sf.x * B]; o1 = offsets[(int64_t)(sf.x + 1) * B]; }
+    const int q0 = min(max(fb0, 0), n_all), q1 = min(max(fe0, q0), n_all);
     const bool onehot = nf == 1 && q1 - q0 == B;           // as many occurrences as bags: most likely one each
     int64_t idv[4];
-    int og[4], og1[4];
     auto fetch = [&](int base, int end) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = base + tid + u * NTH;
             idv[u] = i < end ? ids[i] : 0;
-            og[u] = onehot && i < end ? offs0[i - q0] : 0;
-            og1[u] = onehot && i < end ? offs0[i - q0 + 1] : 0;
         }
     };
     fetch(q0, q1);
-    int step_log = 0;                                      // every 2^step_log-th bag offset is kept in LDS
-    while (((B + (1 << step_log) - 1) >> step_log) + 1 > kSmallOffs) ++step_log;
-    const int n_offs = ((B + (1 << step_log) - 1) >> step_log) + 1;
+    // ---- sizes: occurrences of the packs before, of the tables before, of the pack, of the slots before ----
+    int4 sum = make_int4(0, 0, 0, 0);
+    int bad = 0, viol = 0;
+    for (int i = tid; i < F; i += NTH) {
+        if (i >= NTH) {
+            sf = as_global(a->slot_info)[i];
+            o0 = offsets[(int64_t)sf.x * B]; o1 = offsets[(int64_t)(sf.x + 1) * B];
+        }
+        const int len = o1 - o0;
+        bad |= len < 0 || (sf.x == 0 && o0 != 0) || (sf.x == F - 1 && (int64_t)o1 != nnz);
+        sum.x += i < ss->first_slot ? len : 0;
+        sum.y += sf.y < ss->table ? len : 0;
+        sum.z += i >= ss->first_slot && i < ss->first_slot + ss->pack_fields ? len : 0;
+        sum.w += i < ss->slot0 ? len : 0;
+    }
+    // the bags of this slice's share: inside the field and not decreasing
+    for (int b = b_lo + tid; b < b_hi; b += NTH) {
+        if (b >= b_lo + NTH) { share0 = offs0[b]; share1 = offs0[b + 1]; }
+        viol |= share0 > share1 || share0 < fb0 || share1 > fe0;
+    }
+    for (int j = 1; j < nf; ++j) {
+        const int32_t* offs = offsets + (int64_t)as_global(a->tfields)[ss->field_begin + j].field * B;
+        for (int b = b_lo + tid; b < b_hi; b += NTH) viol |= offs[b] > offs[b + 1] || offs[b] < offs[0] || offs[b + 1] > offs[B];
+    }
+    const int step_log = small_step(B), n_offs = ((B + (1 << step_log) - 1) >> step_log) + 1;
     if (nf == 1 && !onehot)
         for (int i = tid; i < n_offs; i += NTH) s_offs[i] = offs0[min(i << step_log, B)];
-    // the offsets of this slice's share of the table's bags: inside the field and not decreasing
-    const int b_lo = (int)((int64_t)B * ss.idx / ss.n_table_slices), b_hi = (int)((int64_t)B * (ss.idx + 1) / ss.n_table_slices);
-    for (int j = 0; j < nf; ++j) {
-        const int f = nf == 1 ? ss.field0 : as_global(a.tfields)[ss.field_begin + j].field;
-        const int32_t* offs = offsets + (int64_t)f * B;
-        const int lo_o = offs[0], hi_o = offs[B];
-        for (int b = b_lo + tid; b < b_hi; b += NTH) {
-            const int x = offs[b], y = offs[b + 1];
-            viol |= x > y || x < lo_o || y > hi_o;
-        }
-    }
     for (int w = tid; w < words; w += NTH) s_bits[w] = 0;
     for (int i = tid; i < kSmallRanks; i += NTH) s_cnt[i] = 0;
-    if (tid == 0) { s_n = 0; s_before = 0; s_flag = 0; s_odd = 0; }
+    if (tid == 0) { s_n = 0; s_before = 0; s_flag = 0; }
     if (wv * 64 < F) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
@@ -108,21 +215,21 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
     sum = make_int4(0, 0, 0, 0);
     for (int w = 0; w < NW && w * 64 < F; ++w) { const int4 x = s_red[w]; sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w; }
     if (bad) {                                             // every block sees the same boundaries: nobody publishes, nobody waits
-        if (ss.is_last && tid == 0) { a.st[p].n_unique = 0; a.st[p].error = 1; }
+        if (ss->is_last && tid == 0) { as_global(a->st)[ss->pack].n_unique = 0; as_global(a->st)[ss->pack].error = 1; }
         return;
     }
-    const int pstart = sum.x, nnz_p = sum.z;
-    PK_PT(a, slice, 1);
+    if (tid == 0) { s_ctx.pstart = sum.x; s_ctx.nnz_p = sum.z; s_ctx.rec_before = sum.y - sum.x; s_ctx.q0 = q0; }
+    PK_PT(*a, slice, 1);
     // the table's fields: where they begin and end, packed position minus position, column, pooling | field
     if (nf == 1) {
-        if (tid == 0) { s_tf[0] = q0; s_tf[1] = q1; s_tf[2] = sum.w - fb0; s_tf[3] = ss.col0; s_tf[4] = ss.pool0 | (ss.field0 << 1); }
+        if (tid == 0) { s_tf[0] = q0; s_tf[1] = q1; s_tf[2] = sum.w - fb0; s_tf[3] = ss->col0; s_tf[4] = ss->pool0 | (ss->field0 << 1); }
     } else {
         // (several fields: their packed positions from the sizes of the slots before each)
         for (int j = 0; j < nf; ++j) {
-            const TableField tf = as_global(a.tfields)[ss.field_begin + j];
+            const TableField tf = as_global(a->tfields)[ss->field_begin + j];
             int before = 0;
-            for (int i = tid; i < ss.first_slot + tf.slot; i += NTH) {
-                const int f = as_global(a.slot_info)[i].x;
+            for (int i = tid; i < ss->first_slot + tf.slot; i += NTH) {
+                const int f = as_global(a->slot_info)[i].x;
                 before += offsets[(int64_t)(f + 1) * B] - offsets[(int64_t)f * B];
             }
             int tot;
@@ -137,31 +244,36 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
     }
 
     // ---- which keys occur; the slice's occurrences are kept while they are at hand ----
-    auto fold = [&](int64_t id) { return fold_id(id, rows, ss.magic); };
+    const uint32_t rows = ss->rows;
+    const uint64_t magic = ss->magic;
     int before = 0;                                        // per wavefront: occurrences of the table in earlier slices
     for (int j = 0; j < nf; ++j) {
         const int j0 = nf == 1 ? q0 : s_tf[kSliceTfWords * j], j1 = nf == 1 ? q1 : s_tf[kSliceTfWords * j + 1];
         for (int base = j0; base < j1; base += 4 * NTH) {
             if (nf > 1 || base > j0) fetch(base, j1);
+            uint32_t kk[4];
+            uint64_t m[4];
+            int n = 0;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int i = base + tid + u * NTH;
-                const bool valid = i < j1;
-                const uint32_t kk = valid ? fold(idv[u]) : 0xFFFFFFFFu;
-                const bool on = valid && (kk >> lg) == (uint32_t)ss.idx;
-                before += __popcll(__ballot(valid && kk < lo));
-                if (onehot && valid && !(og[u] <= i && i < og1[u])) s_odd = 1;
-                const uint64_t m = __ballot(on);
-                if (m) {
-                    const int leader = __ffsll((unsigned long long)m) - 1;
-                    int at = 0;
-                    if (lane == leader) at = atomicAdd(&s_n, __popcll(m));
-                    at = __shfl(at, leader, 64) + __popcll(m & ((1ull << lane) - 1ull));
-                    if (on) {
-                        const uint32_t kl = kk - lo, bit = 1u << (kl & 31);
+                kk[u] = base + tid + u * NTH < j1 ? fold_id(idv[u], rows, magic) : 0xFFFFFFFFu;      // (no row: rows <= 2^30)
+                before += __popcll(__ballot(kk[u] < lo));
+                m[u] = __ballot((kk[u] >> lg) == (uint32_t)ss->idx);
+                n += __popcll(m[u]);
+            }
+            if (n) {                                       // room for the wavefront's finds in one add
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&s_n, n);
+                at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (m[u] >> lane & 1) {
+                        const uint32_t kl = kk[u] - lo, bit = 1u << (kl & 31);
                         if (!(s_bits[kl >> 5] & bit)) atomicOr(&s_bits[kl >> 5], bit);
-                        if (at < kSmallCache) { s_ckey[at] = kl; s_cpos[at] = i; }
+                        const int x = at + __popcll(m[u] & ((1ull << lane) - 1ull));
+                        if (x < kSmallCache) { s_ckey[x] = kl; s_cpos[x] = base + tid + u * NTH; }
                     }
+                    at += __popcll(m[u]);
                 }
             }
         }
@@ -169,11 +281,11 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
     if (lane == 0 && before) atomicAdd(&s_before, before);
     if (viol) s_flag = 1;
     __syncthreads();
-    PK_PT(a, slice, 2);
+    PK_PT(*a, slice, 2);
+    a = forget<LEAN>(a);
+    ss = slice_at(a, slice);
     const int n_rec = s_n;
     const uint32_t own_flags = s_flag ? 1u : 0u;
-    const bool cached = nf == 1 && n_rec <= kSmallCache;
-    const int rec_before = sum.y - sum.x + s_before;       // the pack's occurrences before this slice's
 
     // ---- popcount prefix of the words: thread i owns words [i * wpt, (i + 1) * wpt) ----
     const int wpt = max(1, words / NTH);
@@ -184,17 +296,18 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
     int run = block_excl_scan<NTH>(c, &n_u);
     // the number of this slice's distinct keys is out: in its own word and in its group's; and the words of the
     // slices before it are asked for (one lane each: those of the own group, and the earlier groups' sums)
-    uint64_t* desc = as_global(a.desc);
-    const int l = slice - ss.pack_first, g = l / kDescGroup, r = l % kDescGroup;
-    uint64_t* gd = as_global(a.gdesc) + (ss.pack_first / kDescGroup + p);  // the pack's groups (packs never share one)
-    uint64_t ack = 0, d_own = 0, d_grp = 0;
-    if (tid == 0) {
-        const uint64_t v = ((uint64_t)1 << 48) | ((uint64_t)own_flags << 40) | (uint32_t)n_u;     // count of slices | flags | distinct keys
-        ack = atomicExch((unsigned long long*)desc + slice, (unsigned long long)v);
-        ack += atomicAdd((unsigned long long*)gd + g, (unsigned long long)v);
-    }
+    const int l = slice - ss->pack_first, g = l / kDescGroup, r = l % kDescGroup;
+    uint64_t ack0 = 0, ack1 = 0, d_own = 0, d_grp = 0;     // (acks: old values, which say that the words have arrived)
+    int ack2 = 0, ack3 = 0;
     if (wv == 0) {
-        if (lane < r) d_own = small_load(desc + slice - 1 - lane);
+        uint64_t* desc = as_global(a->desc) + slice;
+        uint64_t* gd = as_global(a->gdesc) + (ss->pack_first / kDescGroup + ss->pack);     // the pack's groups (packs never share one)
+        if (lane == 0) {
+            const uint64_t v = ((uint64_t)1 << 48) | ((uint64_t)own_flags << 40) | (uint32_t)n_u;     // count of slices | flags | distinct keys
+            ack0 = atomicExch((unsigned long long*)desc, (unsigned long long)v);
+            ack1 = atomicAdd((unsigned long long*)gd + g, (unsigned long long)v);
+        }
+        if (lane < r) d_own = small_load(desc - 1 - lane);
         if (lane < g) d_grp = small_load(gd + lane);
     }
     if (tid * wpt < words)
@@ -202,20 +315,22 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
             s_pre[tid * wpt + j] = (uint32_t)run;
             run += __popc(s_bits[tid * wpt + j]);
         }
+    if (tid == 0) { s_ctx.rec_before += s_before; s_ctx.n_rec = n_rec; s_ctx.n_u = n_u; }
     __syncthreads();
-    PK_PT(a, slice, 3);
+    PK_PT(*a, slice, 3);
+    a = forget<LEAN>(a);
+    ss = slice_at(a, slice);
 
     // ---- what needs the slices before ----
-    int base_u = 0;
-    uint32_t* __restrict__ uq = as_global(a.unique) + pstart;
-    int32_t* __restrict__ seg = as_global(a.seg_all) + pstart + p;
     auto finish_wait = [&]() {                             // wavefront 0: distinct keys of the slices before
+        uint64_t* desc = as_global(a->desc) + slice;
+        uint64_t* gd = as_global(a->gdesc) + (ss->pack_first / kDescGroup + ss->pack);
         bool gave_up = false;
         int spins = 0;
         while (__any(lane < r && (d_own >> 48) == 0)) {
             if (++spins > kSpinLimit) { gave_up = true; break; }
             __builtin_amdgcn_s_sleep(1);
-            if (lane < r && (d_own >> 48) == 0) d_own = small_load(desc + slice - 1 - lane);
+            if (lane < r && (d_own >> 48) == 0) d_own = small_load(desc - 1 - lane);
         }
         uint32_t u = lane < r ? (uint32_t)d_own : 0u, fl = lane < r ? (uint32_t)(d_own >> 40) & 1u : 0u;
         for (int k0 = 0; k0 < g; k0 += 64) {               // a group is complete when all its slices have added themselves
@@ -231,25 +346,26 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) { u += __shfl_xor(u, o, 64); fl |= __shfl_xor(fl, o, 64); }
         if (lane == 0) {
-            if (gave_up) ack += atomicOr(a.done + 1, 2);
+            if (gave_up) ack2 = atomicOr(as_global(a->done) + 1, 2);
             s_base = gave_up ? -1 : (int)u;
             s_flag = (int)(fl | own_flags);
         }
     };
-    // Returns false when the sums cannot be right (then nothing is written): whatever the words held, no write
-    // below leaves the pack's arrays.
+    // The slice's distinct keys (ascending) in their place, the pack's totals.  Returns false when the sums cannot be
+    // right (then nothing is written): whatever the words held, no write below leaves the pack's arrays.
     auto after_wait = [&]() -> bool {
-        base_u = s_base;
+        const int base_u = s_base, pstart = s_ctx.pstart, nnz_p = s_ctx.nnz_p, rec_before = s_ctx.rec_before;
         if (base_u < 0 || rec_before < 0 || (int64_t)base_u + n_u > (int64_t)nnz_p || (int64_t)rec_before + n_rec > (int64_t)nnz_p) {
-            if (tid == 0) ack += atomicOr(a.done + 1, 2);
+            if (tid == 0) ack2 = atomicOr(as_global(a->done) + 1, 2);
             return false;
         }
+        uint32_t* uq = as_global(a->unique) + pstart + base_u;
         if (tid * wpt < words) {
+            int at = (int)s_pre[tid * wpt];
             for (int j = 0; j < wpt; ++j) {
                 const int w = tid * wpt + j;
                 uint32_t x = s_bits[w];
-                int at = base_u + (int)s_pre[w];
-                const uint32_t key0 = ss.key_lo + lo + (uint32_t)w * 32u;
+                const uint32_t key0 = ss->key_lo + lo + (uint32_t)w * 32u;
                 while (x) {
                     const int bit = __ffs(x) - 1;
                     x &= x - 1;
@@ -257,140 +373,86 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
                 }
             }
         }
-        if (ss.is_last && tid == 0) {
-            a.st[p].n_unique = base_u + n_u;
-            seg[base_u + n_u] = nnz_p;
-            ack += atomicExch(&a.st[p].error, s_flag);
+        if (ss->is_last && tid == 0) {
+            PackState* st = as_global(a->st) + ss->pack;
+            st->n_unique = base_u + n_u;
+            as_global(a->seg_all)[pstart + ss->pack + base_u + n_u] = nnz_p;
+            ack3 = atomicExch(&st->error, s_flag);
         }
-        PK_PT(a, slice, 5);
+        PK_PT(*a, slice, 5);
         return true;
     };
-    auto rank_of = [&](uint32_t kl) { return (int)(s_pre[kl >> 5] + __popc(s_bits[kl >> 5] & ((1u << (kl & 31)) - 1u))); };
-    // the bag of an occurrence and its length
-    const bool all_one = onehot && !s_odd;
-    auto bag_of = [&](int j, int q, int* L) {
-        if (all_one) { *L = 1; return q - q0; }
-        if (nf == 1 && !onehot) {                          // the samples in LDS, then the few bags between two of them
-            int k = upper_bound_i32(s_offs, n_offs, q) - 1;
-            if (step_log == 0) {
-                k = min(max(k, 0), B - 1);
-                *L = s_offs[k + 1] - s_offs[k];
-                return k;
-            }
-            k = max(k, 0) << step_log;
-            const int n = min(1 << step_log, B - k);
-            const int b = min(max(k + upper_bound_i32(offs0 + k, max(n, 0), q) - 1, 0), B - 1);
-            *L = offs0[b + 1] - offs0[b];
-            return b;
-        }
-        const int32_t* offs = offsets + (int64_t)(s_tf[kSliceTfWords * j + 4] >> 1) * B;
-        const int b = find_bag(offs, B, q, q - s_tf[kSliceTfWords * j]);
-        *L = offs[b + 1] - offs[b];
-        return b;
-    };
-    const bool wide = ss.wide != 0;                        // the pack's entries carry the bag length
-    uint32_t* __restrict__ ent = as_global(a.ent_all) + (size_t)pstart * a.ent_mult;
-    int32_t* __restrict__ marks = as_global(a.marks) + (pstart / kMarkStep + p);
-    auto place = [&](int j, uint32_t kl, int q, int rk, int pos) {
-        int L;
-        const int b = bag_of(j, q, &L);
-        const uint32_t ref = (uint32_t)((int64_t)b * out_dim + s_tf[kSliceTfWords * j + 3]);
-        const int qp = q + s_tf[kSliceTfWords * j + 2];
-        if ((unsigned)qp < (unsigned)nnz) {
-            as_global(a.keys)[qp] = ss.key_lo + lo + kl;
-            as_global(a.inverse)[qp] = base_u + rk;
-        }
-        if ((unsigned)pos < (unsigned)nnz_p) {
-            if (wide) reinterpret_cast<uint2*>(ent)[pos] = make_uint2(ref, (s_tf[kSliceTfWords * j + 4] & 1) == PK_MEAN && L > 0 ? (uint32_t)L : 1u);
-            else ent[pos] = ref;
-        }
-    };
-    // counters of keys [r0, r0 + width) become the keys' first places; segment offsets and marks go out
-    auto starts = [&](int r0, int width, int s0, int per) {
-        for (int j = 0; j < per; ++j) {
-            const int i = tid * per + j;
-            if (i < width) {
-                const int len = s_cnt[i], u = base_u + r0 + i;
-                seg[u] = s0;
-                s_cnt[i] = s0;
-                for (int m = (s0 + kMarkStep - 1) / kMarkStep; (int64_t)m * kMarkStep < (int64_t)s0 + len; ++m) marks[m] = u;
-                if (len >= 2 * kPiece) {                   // the key is reduced in pieces: its partial sums start at zero
-                    const size_t slot = (size_t)(pstart / kPiece + p) + (size_t)(s0 / kPiece);
-                    double* gh = as_global(a.ghot) + slot * a.dmax;
-                    for (int d = 0; d < ss.dim; ++d) gh[d] = 0.0;
-                    as_global(a.ticket)[slot] = 0;
-                }
-                s0 += len;
-            }
-        }
-    };
-    auto sum_of = [&](int width, int per) {
-        int s = 0;
-        for (int j = 0; j < per; ++j) {
-            const int i = tid * per + j;
-            s += i < width ? s_cnt[i] : 0;
-        }
-        return s;
-    };
 
-    bool ok = true;
-    if (cached && n_u <= kSmallRanks) {
+    if (nf == 1 && n_rec <= kSmallCache && n_u <= kSmallRanks) {
         // ---- occurrences per distinct key; every kept occurrence keeps its key's rank and its place among them ----
         constexpr int PER = kSmallCache / NTH;
-        uint32_t kl[PER];
-        int q[PER], rk[PER], at[PER];
+        const int q0 = s_ctx.q0;
+        const int32_t* __restrict__ offs = as_global(a->offsets) + (int64_t)ss->field0 * B;
+        int q[PER], ra[PER], g0[PER], g1[PER];             // ra: rank | place << 16
 #pragma unroll
         for (int e = 0; e < PER; ++e) {
             const int i = tid + e * NTH;
             const bool on = i < n_rec;
-            kl[e] = on ? s_ckey[i] : 0u;
             q[e] = on ? s_cpos[i] : 0;
-            rk[e] = rank_of(kl[e]);
-            at[e] = 0;
-            if (wv * 64 + e * NTH < n_rec) at[e] = lds_inc_grouped(s_cnt, (uint32_t)rk[e], on);
+            const int guess = min(max(q[e] - q0, 0), B - 1);
+            g0[e] = onehot ? offs[guess] : 0;              // the bag it is in if all hold one
+            g1[e] = onehot ? offs[guess + 1] : 0;
+            const int rk = small_rank(s_bits, s_pre, on ? s_ckey[i] : 0u);
+            ra[e] = rk;
+            if (wv * 64 + e * NTH < n_rec) ra[e] |= lds_inc_grouped(s_cnt, (uint32_t)rk, on) << 16;
         }
         __syncthreads();
-        PK_PT(a, slice, 6);
+        PK_PT(*a, slice, 6);
         const int per = (n_u + NTH - 1) / NTH;
-        const int s = sum_of(n_u, per);
+        const int s = small_sum(s_cnt, n_u, per);
         if (wv == 0) finish_wait();
         int tot;
         const int ex = block_excl_scan<NTH>(s, &tot);      // (its barriers also publish what wavefront 0 found)
-        PK_PT(a, slice, 4);
-        ok = after_wait();
-        if (ok) starts(0, n_u, rec_before + ex, per);
+        PK_PT(*a, slice, 4);
+        const bool ok = after_wait();
+        if (ok) small_starts(a, ss, s_cnt, s_ctx.pstart, s_base, 0, n_u, s_ctx.rec_before + ex, per);
         __syncthreads();
-        PK_PT(a, slice, 7);
+        PK_PT(*a, slice, 7);
+        a = forget<LEAN>(a);
+        ss = slice_at(a, slice);
         if (ok) {
+            const int pstart = s_ctx.pstart, nnz_p = s_ctx.nnz_p, base_u = s_base;
 #pragma unroll
             for (int e = 0; e < PER; ++e)
-                if (tid + e * NTH < n_rec) place(0, kl[e], q[e], rk[e], s_cnt[rk[e]] + at[e]);
+                if (tid + e * NTH < n_rec) {
+                    int L = g1[e] - g0[e], b = q[e] - q0;
+                    if (!onehot || q[e] < g0[e] || q[e] >= g1[e]) b = small_bag(offs, B, s_offs, !onehot, q[e] - q0, q[e], &L);
+                    const int rk = ra[e] & 0xFFFF;
+                    small_place(a, ss, s_tf, pstart, nnz_p, base_u, s_ckey[tid + e * NTH], q[e], rk, s_cnt[rk] + (ra[e] >> 16), b, L);
+                }
         }
     } else {
         // ---- more occurrences than are kept, or several fields: from the IDs again, kSmallRanks keys a round ----
+        if (wv == 0) finish_wait();
+        __syncthreads();
+        bool ok = after_wait();
+        a = forget<LEAN>(a);
+        ss = slice_at(a, slice);
         auto for_ids = [&](auto&& fn) {                    // fn(field of the table, key in slice, position, on): all lanes make every trip
             for (int j = 0; j < nf; ++j) {
                 const int j0 = s_tf[kSliceTfWords * j], j1 = s_tf[kSliceTfWords * j + 1];
-                for (int base = j0; base < j1; base += 4 * NTH) {
-                    int64_t v[4];
+                for (int base = j0; base < j1; base += 2 * NTH) {
+                    int64_t v[2];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < 2; ++u) {
                         const int i = base + tid + u * NTH;
-                        v[u] = i < j1 ? ids[i] : 0;
+                        v[u] = i < j1 ? as_global(a->ids)[i] : 0;
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < 2; ++u) {
                         const int i = base + tid + u * NTH;
-                        const uint32_t kk = i < j1 ? fold(v[u]) : 0xFFFFFFFFu;
-                        const bool on = i < j1 && (kk >> lg) == (uint32_t)ss.idx;
+                        const uint32_t kk = i < j1 ? fold_id(v[u], ss->rows, ss->magic) : 0xFFFFFFFFu;
+                        const bool on = (kk >> lg) == (uint32_t)ss->idx;
                         fn(j, on ? kk - lo : 0u, i, on);
                     }
                 }
             }
         };
-        if (wv == 0) finish_wait();
-        __syncthreads();
-        ok = after_wait();
         int placed = 0;
         for (int r0 = 0; ok && r0 < n_u; r0 += kSmallRanks) {
             const int width = min(kSmallRanks, n_u - r0);
@@ -400,42 +462,47 @@ __device__ __forceinline__ void small_slice_body(const SliceArgs& a, int slice, 
                 __syncthreads();
             }
             for_ids([&](int, uint32_t kl, int, bool on) {
-                const uint32_t rr = (uint32_t)(rank_of(kl) - r0);
+                const uint32_t rr = (uint32_t)(small_rank(s_bits, s_pre, kl) - r0);
                 (void)lds_inc_grouped(s_cnt, rr, on && rr < (uint32_t)width);
             });
             __syncthreads();
             const int per = (width + NTH - 1) / NTH;
             int tot;
-            const int ex = block_excl_scan<NTH>(sum_of(width, per), &tot);
-            starts(r0, width, rec_before + placed + ex, per);
+            const int ex = block_excl_scan<NTH>(small_sum(s_cnt, width, per), &tot);
+            small_starts(a, ss, s_cnt, s_ctx.pstart, s_base, r0, width, s_ctx.rec_before + placed + ex, per);
             __syncthreads();
             for_ids([&](int j, uint32_t kl, int i, bool on) {
-                const int rk = rank_of(kl);
+                const int rk = small_rank(s_bits, s_pre, kl);
                 const uint32_t rr = (uint32_t)(rk - r0);
                 on = on && rr < (uint32_t)width;
                 const int pos = lds_inc_grouped(s_cnt, rr, on);
-                if (on) place(j, kl, i, rk, pos);
+                if (on) {
+                    const int32_t* tf = s_tf + kSliceTfWords * j;
+                    int L;
+                    const int b = small_bag(as_global(a->offsets) + (int64_t)(tf[4] >> 1) * B, B, s_offs, nf == 1 && !onehot, i - tf[0], i, &L);
+                    small_place(a, ss, tf, s_ctx.pstart, s_ctx.nnz_p, s_base, kl, i, rk, pos, b, L);
+                }
             });
             placed += tot;
         }
     }
-    PK_PT(a, slice, 8);
+    PK_PT(*a, slice, 8);
     // The words belong to the library and must be zero when the next call starts: the block that is through its
     // wait last (every block has then published, and read what it needed) clears them.
     if (wv == 0) {
         int last = 0;
         if (lane == 0) {
-            asm volatile("s_waitcnt vmcnt(0)" ::"v"(ack) : "memory");      // this block's own words have arrived
-            last = atomicAdd(a.done, 1) == a.n_slices - 1;
+            asm volatile("s_waitcnt vmcnt(0)" ::"v"(ack0), "v"(ack1), "v"(ack2), "v"(ack3) : "memory");      // this block's own words have arrived
+            last = atomicAdd(as_global(a->done), 1) == a->n_slices - 1;
         }
         if (__builtin_amdgcn_readfirstlane(last)) {
-            for (int i = lane; i < a.n_slices; i += 64) publish_desc(a.desc + i, 0);
-            for (int i = lane; i < a.n_slices / kDescGroup + a.P + 2; i += 64) publish_desc(a.gdesc + i, 0);
+            for (int i = lane; i < a->n_slices; i += 64) publish_desc(as_global(a->desc) + i, 0);
+            for (int i = lane; i < a->n_slices / kDescGroup + a->P + 2; i += 64) publish_desc(as_global(a->gdesc) + i, 0);
             if (lane == 0) {
-                *a.done = 0;
+                *as_global(a->done) = 0;
                 // a block waited too long or found sums that cannot be: bit 1 of every pack's error word
-                if (atomicExch(a.done + 1, 0))
-                    for (int k = 0; k < a.P; ++k) atomicOr(&a.st[k].error, 2);
+                if (atomicExch(as_global(a->done) + 1, 0))
+                    for (int k = 0; k < a->P; ++k) atomicOr(&as_global(a->st)[k].error, 2);
             }
         }
     }

@@ -74,9 +74,10 @@ inline int32_t slice_count_max(uint32_t rows, int64_t nnz, int32_t target, int32
 }
 
 // Small batches: a table's keys in about `want` slices, none longer than a block's LDS bitmap.  Lists for 1, 2, 4
-// and 8 are made once, on the host, and a call takes the one that its occurrences per table ask for (a slice
-// block scans all IDs of its table, so slices with few occurrences only add blocks to wait for).
-constexpr int kSmallCuts = 4;
+// ... 64 are made once, on the host, and a call takes the one that its occurrences per table ask for: a slice
+// block scans all IDs of its table, so slices with few occurrences only add blocks to wait for, and one with
+// more occurrences than it keeps in LDS reads the IDs three times.
+constexpr int kSmallCuts = 7;
 inline SliceGeom slice_geom_small(int64_t rows, int32_t want)
 {
     const int64_t per = (rows + want - 1) / want;
@@ -87,12 +88,14 @@ inline SliceGeom slice_geom_small(int64_t rows, int32_t want)
     g.n = (int32_t)((rows + ((int64_t)1 << lg) - 1) >> lg);
     return g;
 }
-// occurrences per slice aimed at, and slices of all tables together at most (beyond the tables' own number)
+// Occurrences per slice aimed at, and blocks that the chip holds at once (two per CU): with more slices than those,
+// the later ones only start when the first are through.
 constexpr int64_t kSmallSliceOcc = 1024;
+constexpr int64_t kSmallBlocks = 512;
 inline int small_cut(int64_t nnz, int64_t n_tables)
 {
     int cut = 0;
-    while (cut + 1 < kSmallCuts && nnz > ((int64_t)kSmallSliceOcc * n_tables << cut) && ((int64_t)n_tables << (cut + 1)) <= 1024) ++cut;
+    while (cut + 1 < kSmallCuts && nnz > ((int64_t)kSmallSliceOcc * n_tables << cut) && (n_tables << (cut + 1)) <= kSmallBlocks) ++cut;
     return cut;
 }
 

@@ -270,6 +270,7 @@ pk_status pk_plan_create(const pk_table_desc* tables, int32_t n_tables, const pk
     // the cuts of the one-launch forward pass
     for (int cut = 0; cut < kSmallCuts; ++cut) {
         std::vector<SmallSlice>& list = pl->small_slices[cut];
+        if (cut > 0 && ((int64_t)pl->sort_tables.size() << cut) > kSmallBlocks) continue;      // small_cut does not choose it
         for (size_t p = 0; p < pl->packs.size(); ++p) {
             const Pack& k = pl->packs[p];
             const int32_t pack_first = (int32_t)list.size();
