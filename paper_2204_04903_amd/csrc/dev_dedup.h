@@ -884,85 +884,151 @@ pk_inverse_kernel(int F, const int32_t* __restrict__ fscan, const SlotMeta* __re
 // rows of a packed table dealt to n workers by row mod n, the distinct keys of a pack are regrouped by
 // owner -- owner 0 first, ascending inside an owner -- with the place of every key in `unique` beside it
 // (what Stitch needs for the rows that come back) and the offsets of the owners' groups.  A counting
-// sort in three small launches: counts per chunk of 512 keys and owner, a scan in owner-major order,
-// and the placing pass (a wavefront per chunk, so that the order inside an owner is the key order).
+// sort in two launches: counts per chunk and owner, and the placing pass, whose blocks add up the counts of the
+// chunks before their own (there are at most kPartChunks, so that is a few thousand numbers; a launch of one
+// block that scanned them took 4.7 us of a pack's 16.6).  A block owns a chunk and each of its wavefronts a
+// quarter, so that the order inside an owner is the key order; which lanes share an owner comes from one ballot
+// per bit of the owner's number.  Bound by the launches and their chains of loads, so all the loads of a step are
+// in flight at once.
 // ---------------------------------------------------------------------------
-constexpr int kPartChunk = 512;
+constexpr int kPartStep = 4 * NT, kPartChunks = 1024;   // a chunk is a multiple of kPartStep keys
 constexpr int kPartOwnersMax = 64;
+
+// keys per chunk: kPartStep, more where that gave more than kPartChunks chunks
+__device__ __forceinline__ int part_chunk(int U) { return ((U + kPartChunks - 1) / kPartChunks + kPartStep - 1) / kPartStep * kPartStep; }
+
+// key mod n: magic = floor((2^32 - 1) / n) gives the quotient or one below it
+__device__ __forceinline__ uint32_t part_owner(uint32_t key, uint32_t n, uint32_t magic)
+{
+    const uint32_t r = key - __umulhi(key, magic) * n;
+    return r >= n ? r - n : r;
+}
+
+// the lanes (of those with `on`) that have this lane's owner
+__device__ __forceinline__ uint64_t part_peers(uint32_t o, bool on, int bits)
+{
+    uint64_t m = __ballot(on);
+    for (int b = 0; b < bits; ++b) {
+        const uint64_t x = __ballot(o >> b & 1);
+        m &= (o >> b & 1) ? x : ~x;
+    }
+    return m;
+}
+
+// four keys of a lane at i, i + 64, ...: loaded without a condition (those at or past `end` are not used)
+__device__ __forceinline__ void part_load(uint32_t key[4], const uint32_t* __restrict__ uq, int i, int end)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) key[j] = uq[min(i + 64 * j, end - 1)];
+}
 
 __global__ void __launch_bounds__(NT)
 pk_partition_count_kernel(const PackState* __restrict__ st, int p, const uint32_t* __restrict__ unique_all,
-                          int n_owners, int32_t* __restrict__ chunk_counts)
+                          int n_owners, int bits, uint32_t magic, int32_t* __restrict__ chunk_counts)
 {
     __shared__ int s_cnt[kPartOwnersMax];
+    const int tid = threadIdx.x, lane = tid & 63;
     const int U = st[p].n_unique;
     const uint32_t* uq = unique_all + st[p].start;
-    const int n_chunks = (U + kPartChunk - 1) / kPartChunk;
-    for (int ch = blockIdx.x; ch < n_chunks; ch += gridDim.x) {
-        __syncthreads();
-        if (threadIdx.x < kPartOwnersMax) s_cnt[threadIdx.x] = 0;
-        __syncthreads();
-        for (int i = ch * kPartChunk + threadIdx.x; i < min((ch + 1) * kPartChunk, U); i += NT)
-            atomicAdd(&s_cnt[uq[i] % (uint32_t)n_owners], 1);
-        __syncthreads();
-        if ((int)threadIdx.x < n_owners) chunk_counts[(size_t)threadIdx.x * n_chunks + ch] = s_cnt[threadIdx.x];   // owner-major
-    }
-}
-
-// exclusive scan of the owner-major counts, in place; the owners' offsets on the way (one block)
-__global__ void __launch_bounds__(kScanThreads)
-pk_partition_scan_kernel(const PackState* __restrict__ st, int p, int n_owners, int32_t* chunk_counts,
-                         int32_t* __restrict__ offsets)
-{
-    const int U = st[p].n_unique;
-    const int n_chunks = (U + kPartChunk - 1) / kPartChunk;
-    const int total = n_owners * n_chunks;
-    int carry = 0;
-    for (int base = 0; base < total; base += kScanThreads) {
-        const int i = base + (int)threadIdx.x;
-        const int c = i < total ? chunk_counts[i] : 0;
-        int tot;
-        const int ex = block_excl_scan<kScanThreads>(c, &tot);
-        if (i < total) {
-            chunk_counts[i] = carry + ex;
-            if (i % n_chunks == 0) offsets[i / n_chunks] = carry + ex;
+    const int chunk = part_chunk(U), c0 = blockIdx.x * chunk, end = min(c0 + chunk, U);
+    if (c0 >= end) return;
+    if (tid < kPartOwnersMax) s_cnt[tid] = 0;
+    __syncthreads();
+    for (int i = c0 + (tid & ~63) * 4 + lane; i - lane < end; i += kPartStep) {
+        uint32_t key[4];
+        part_load(key, uq, i, end);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool on = i + 64 * j < end;
+            const uint32_t o = part_owner(key[j], (uint32_t)n_owners, magic);
+            const uint64_t m = part_peers(o, on, bits);
+            if (on && (m & ((1ull << lane) - 1ull)) == 0) atomicAdd(&s_cnt[o], __popcll(m));
         }
-        carry += tot;
     }
-    if (threadIdx.x == 0) {
-        offsets[n_owners] = U;
-        if (n_chunks == 0) for (int o = 0; o < n_owners; ++o) offsets[o] = 0;
-    }
+    __syncthreads();
+    if (tid < n_owners) chunk_counts[(size_t)blockIdx.x * n_owners + tid] = s_cnt[tid];
 }
 
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(NT)
 pk_partition_place_kernel(const PackState* __restrict__ st, int p, const uint32_t* __restrict__ unique_all,
-                          int n_owners, const int32_t* __restrict__ chunk_offsets, uint32_t* __restrict__ part_keys,
-                          int32_t* __restrict__ part_index)
+                          int n_owners, int bits, uint32_t magic, const int32_t* __restrict__ chunk_counts,
+                          uint32_t* __restrict__ part_keys, int32_t* __restrict__ part_index, int32_t* __restrict__ offsets)
 {
-    const int U = st[p].n_unique, lane = threadIdx.x;
+    constexpr int NW = NT / 64;
+    __shared__ int s_all[kPartOwnersMax], s_before[kPartOwnersMax], s_cur[NW][kPartOwnersMax];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int U = st[p].n_unique;
     const uint32_t* uq = unique_all + st[p].start;
-    const int n_chunks = (U + kPartChunk - 1) / kPartChunk;
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (int ch = blockIdx.x; ch < n_chunks; ch += gridDim.x) {
-        int cur = lane < n_owners ? chunk_offsets[(size_t)lane * n_chunks + ch] : 0;   // lane o: owner o's next place
-        for (int base = ch * kPartChunk; base < min((ch + 1) * kPartChunk, U); base += 64) {
-            const int i = base + lane;
-            const bool on = i < U;
-            const uint32_t key = on ? uq[i] : 0u;
-            const int o = on ? (int)(key % (uint32_t)n_owners) : -1;
-            int rank = 0, add = 0;
-            for (int ov = 0; ov < n_owners; ++ov) {        // lanes are in key order: rank among the owner's lanes
-                const uint64_t m = __ballot(o == ov);
-                if (o == ov) rank = __popcll(m & below);
-                if (lane == ov) add = __popcll(m);
+    const int chunk = part_chunk(U), n_chunks = chunk ? (U + chunk - 1) / chunk : 0;
+    const int c0 = blockIdx.x * chunk, end = min(c0 + chunk, U);
+    if (c0 >= end) {
+        if (blockIdx.x == 0 && tid <= n_owners) offsets[tid] = 0;     // no keys
+        return;
+    }
+    const int quarter = chunk / NW, w0 = c0 + wv * quarter, w1 = min(w0 + quarter, end);
+    uint32_t key[4];
+    if (w0 < w1) part_load(key, uq, w0 + lane, w1);
+    if (tid < kPartOwnersMax) { s_all[tid] = 0; s_before[tid] = 0; }
+    s_cur[wv][lane] = 0;
+    __syncthreads();
+    // every owner's keys, in all chunks and in those before this block's
+    const int per = NT / n_owners;                         // threads per owner
+    if (tid < per * n_owners) {
+        const int o = tid % n_owners;
+        int all = 0, before = 0;
+        for (int c = tid / n_owners; c < n_chunks; c += 8 * per) {
+            int x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = chunk_counts[(size_t)min(c + j * per, n_chunks - 1) * n_owners + o];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int y = c + j * per < n_chunks ? x[j] : 0;
+                all += y;
+                before += c + j * per < (int)blockIdx.x ? y : 0;
             }
-            const int at = __shfl(cur, on ? o : 0, 64) + rank;
+        }
+        if (all) { atomicAdd(&s_all[o], all); atomicAdd(&s_before[o], before); }
+    }
+    // the keys of every wavefront by owner (the order of a wavefront's LDS accesses is the program's)
+    for (int i = w0 + lane; i - lane < w1; i += 256) {
+        if (i - lane > w0) part_load(key, uq, i, w1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool on = i + 64 * j < w1;
+            const uint32_t o = part_owner(key[j], (uint32_t)n_owners, magic);
+            const uint64_t m = part_peers(o, on, bits);
+            if (on && (m & ((1ull << lane) - 1ull)) == 0) s_cur[wv][o] += __popcll(m);
+        }
+    }
+    __syncthreads();
+    const int mine = lane < n_owners ? s_all[lane] : 0;    // lane o: owner o
+    int inc = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += t;
+    }
+    if (blockIdx.x == 0 && wv == 0) {
+        if (lane < n_owners) offsets[lane] = inc - mine;
+        if (lane == 0) offsets[n_owners] = U;
+    }
+    int cur = lane < n_owners ? inc - mine + s_before[lane] : 0;
+    for (int w = 0; w < wv; ++w) cur += s_cur[w][lane];
+    __syncthreads();                                       // (the counts are replaced by places)
+    s_cur[wv][lane] = cur;
+    for (int i = w0 + lane; i - lane < w1; i += 256) {
+        if (quarter > 256) part_load(key, uq, i, w1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool on = i + 64 * j < w1;
+            const uint32_t o = part_owner(key[j], (uint32_t)n_owners, magic);
+            const uint64_t m = part_peers(o, on, bits), below = m & ((1ull << lane) - 1ull);
+            const int at = s_cur[wv][o] + __popcll(below); // lanes are in key order
             if (on) {
-                part_keys[at] = key;
-                part_index[at] = i;
+                part_keys[at] = key[j];
+                part_index[at] = i + 64 * j;
+                if (below == 0) s_cur[wv][o] += __popcll(m);
             }
-            cur += add;
         }
     }
 }

@@ -651,7 +651,7 @@ size_t pk_partition_scratch_bytes(const pk_plan* plan, int64_t nnz, int32_t n_ow
         set_error("pk_partition_scratch_bytes: plan is NULL, nnz negative or n_owners outside 1..64");
         return 0;
     }
-    return (size_t)(nnz / kPartChunk + 2) * (size_t)n_owners * 4;
+    return (size_t)std::min<int64_t>(nnz / kPartStep + 2, kPartChunks + 1) * (size_t)n_owners * 4;
 }
 
 pk_status pk_partition_unique(const pk_plan* plan, const void* workspace, size_t ws_bytes, int32_t B, int64_t nnz,
@@ -674,12 +674,14 @@ pk_status pk_partition_unique(const pk_plan* plan, const void* workspace, size_t
     const PackState* st = reinterpret_cast<const PackState*>(wsb + L.state);
     const uint32_t* unique = reinterpret_cast<const uint32_t*>(wsb + L.unique);
     int32_t* counts = static_cast<int32_t*>(scratch);
-    const unsigned grid = blocks_for(nnz / kPartChunk + 1, 1, 4096);
-    PK_LAUNCH("pk_partition_count", pk_partition_count_kernel, dim3(grid), dim3(NT), 0, st, p, unique, n_owners, counts);
-    PK_LAUNCH("pk_partition_scan", pk_partition_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, p, n_owners, counts,
-              part_offsets);
-    PK_LAUNCH("pk_partition_place", pk_partition_place_kernel, dim3(grid), dim3(64), 0, st, p, unique, n_owners, counts,
-              part_keys, part_index);
+    // (at most nnz distinct keys; blocks without a chunk leave at once)
+    const unsigned grid = (unsigned)std::min<int64_t>(nnz / kPartStep + 1, kPartChunks);
+    int bits = 0;
+    while ((1 << bits) < n_owners) ++bits;
+    const uint32_t magic = 0xFFFFFFFFu / (uint32_t)n_owners;
+    PK_LAUNCH("pk_partition_count", pk_partition_count_kernel, dim3(grid), dim3(NT), 0, st, p, unique, n_owners, bits, magic, counts);
+    PK_LAUNCH("pk_partition_place", pk_partition_place_kernel, dim3(grid), dim3(NT), 0, st, p, unique, n_owners, bits, magic, counts,
+              part_keys, part_index, part_offsets);
     return PK_OK;
 }
 
