@@ -989,7 +989,9 @@ pk_partition_place_kernel(const PackState* __restrict__ st, int p, const uint32_
         }
         if (all) { atomicAdd(&s_all[o], all); atomicAdd(&s_before[o], before); }
     }
-    // the keys of every wavefront by owner (the order of a wavefront's LDS accesses is the program's)
+    // the keys of every wavefront by owner (a lane's count is read by others in the next step: the compiler is kept
+    // from moving LDS accesses across the steps, the hardware does a wavefront's in order)
+    auto wave_order = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); };
     for (int i = w0 + lane; i - lane < w1; i += 256) {
         if (i - lane > w0) part_load(key, uq, i, w1);
 #pragma unroll
@@ -998,6 +1000,7 @@ pk_partition_place_kernel(const PackState* __restrict__ st, int p, const uint32_
             const uint32_t o = part_owner(key[j], (uint32_t)n_owners, magic);
             const uint64_t m = part_peers(o, on, bits);
             if (on && (m & ((1ull << lane) - 1ull)) == 0) s_cur[wv][o] += __popcll(m);
+            wave_order();
         }
     }
     __syncthreads();
@@ -1016,6 +1019,7 @@ pk_partition_place_kernel(const PackState* __restrict__ st, int p, const uint32_
     for (int w = 0; w < wv; ++w) cur += s_cur[w][lane];
     __syncthreads();                                       // (the counts are replaced by places)
     s_cur[wv][lane] = cur;
+    wave_order();
     for (int i = w0 + lane; i - lane < w1; i += 256) {
         if (quarter > 256) part_load(key, uq, i, w1);
 #pragma unroll
@@ -1024,11 +1028,13 @@ pk_partition_place_kernel(const PackState* __restrict__ st, int p, const uint32_
             const uint32_t o = part_owner(key[j], (uint32_t)n_owners, magic);
             const uint64_t m = part_peers(o, on, bits), below = m & ((1ull << lane) - 1ull);
             const int at = s_cur[wv][o] + __popcll(below); // lanes are in key order
+            wave_order();
             if (on) {
                 part_keys[at] = key[j];
                 part_index[at] = i + 64 * j;
                 if (below == 0) s_cur[wv][o] += __popcll(m);
             }
+            wave_order();
         }
     }
 }
