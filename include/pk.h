@@ -150,8 +150,10 @@ pk_status pk_forward(const pk_plan* plan, void* const* W,
  * every GPU it runs on until the process ends; neither this call nor anything it
  * runs calls hipMalloc, hipFree or another allocating routine (no internal streams
  * or events either: every kernel runs on hip_stream).  Arguments as for pk_forward,
- * without the workspace.  PK_EWORKSPACE when the plan's metadata plus
- * pk_workspace_bytes(plan, B, nnz) exceed the 32 MiB.  All calls on one GPU share
+ * without the workspace.  PK_EWORKSPACE when the plan's metadata plus the
+ * workspace exceed the 32 MiB (the workspace is pk_workspace_bytes(plan, B, nnz),
+ * less the counts that large batches keep to save time: near the limit they are
+ * left out).  All calls on one GPU share
  * that array: calls that overlap on one GPU race, and the dedup context of a call
  * (there is no pointer to hand to pk_backward_update) lasts until the next call. */
 pk_status pk_forward_static(const pk_plan* plan, void* const* W,

@@ -51,6 +51,7 @@ struct MetaImage {
     std::vector<SlotMeta> slm;
     std::vector<int2> sli;
     size_t o_desc, o_done, o_fm, o_pm, o_slot, o_sli, o_ss[kSmallCuts], o_tfi, o_tab, o_tf, o_slm, total;
+    size_t cuts;                 // bytes of the slice lists
 };
 
 void build_meta_image(const pk_plan* plan, MetaImage* mi)
@@ -102,6 +103,7 @@ void build_meta_image(const pk_plan* plan, MetaImage* mi)
     mi->o_slot = take(F * 4);
     mi->o_sli  = take(F * sizeof(int2));
     for (int c = 0; c < kSmallCuts; ++c) mi->o_ss[c] = take(plan->small_slices[c].size() * sizeof(SmallSlice));
+    mi->cuts   = off - mi->o_ss[0];
     mi->o_tfi  = take(mi->tfi.size() * sizeof(TableField));
     mi->o_tab  = take(plan->sort_tables.size() * sizeof(TableMeta));
     mi->o_tf   = take(plan->table_fields.size() * 4);
@@ -251,7 +253,8 @@ struct Ws {
     template <typename T> T* at(size_t off) const { return reinterpret_cast<T*>(base + off); }
 };
 
-pk_status check_common(const pk_plan* plan, int32_t B, int64_t nnz, const void* ws, size_t ws_bytes, const char* who)
+pk_status check_common(const pk_plan* plan, int32_t B, int64_t nnz, const void* ws, size_t ws_bytes, const char* who,
+                       size_t room = ~(size_t)0)
 {
     if (!plan) return fail(PK_EINVAL, std::string(who) + ": plan is NULL");
     if (B <= 0) return fail(PK_ESHAPE, std::string(who) + ": B must be positive");
@@ -263,7 +266,7 @@ pk_status check_common(const pk_plan* plan, int32_t B, int64_t nnz, const void* 
     if ((int64_t)B * (int64_t)plan->fields.size() >= ((int64_t)1 << 31)) return fail(PK_EOVERFLOW, std::string(who) + ": n_fields * B must be below 2^31");
     if (!ws) return fail(PK_EINVAL, std::string(who) + ": workspace is NULL");
     if (reinterpret_cast<uintptr_t>(ws) % kAlign) return fail(PK_EWORKSPACE, std::string(who) + ": workspace must be 256-byte aligned");
-    if (ws_bytes < make_layout(plan, B, nnz).total) return fail(PK_EWORKSPACE, std::string(who) + ": workspace is smaller than pk_workspace_bytes");
+    if (ws_bytes < make_layout(plan, B, nnz, room).total) return fail(PK_EWORKSPACE, std::string(who) + ": workspace is smaller than pk_workspace_bytes");
     return PK_OK;
 }
 

@@ -38,7 +38,8 @@ using namespace pk;
 // The scratch of pk_forward_static: workspace, plan metadata and look-back descriptors of callers that
 // cannot allocate.  Every GPU the library runs on holds its own copy until the process ends.
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+constexpr size_t kStaticCutBytes = kSmallCuts * ((size_t)kSmallSlicesMax * sizeof(SmallSlice) + 256);   // and the lists of slices
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticCutBytes];
 
 // One translation unit; the kernels and their launch helpers are kept in section files:
 //   dev_common.h   block scans, folding hash, look-back prefix sums, tile order
@@ -101,7 +102,8 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
                               int64_t out_row_stride, void* workspace, size_t ws_bytes, void* hip_stream)
 {
     const bool do_dedup = stages & kDedup, do_pool = stages & kPool;
-    pk_status rc = check_common(plan, B, nnz, workspace, ws_bytes, who);
+    const size_t room = ds_given ? ws_bytes : ~(size_t)0;        // the static scratch cannot be made larger
+    pk_status rc = check_common(plan, B, nnz, workspace, ws_bytes, who, room);
     if (rc != PK_OK) return rc;
     if (do_dedup && (!offsets || (!ids && nnz > 0))) return fail(PK_EINVAL, std::string(who) + ": NULL argument");
     if (do_pool && (!W || !out)) return fail(PK_EINVAL, std::string(who) + ": NULL argument");
@@ -116,7 +118,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
         if (rc != PK_OK) return rc;
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    Ws ws{static_cast<char*>(workspace), make_layout(plan, B, nnz)};
+    Ws ws{static_cast<char*>(workspace), make_layout(plan, B, nnz, room)};
     const Layout& L = ws.L;
 
     PackState* st = ws.at<PackState>(L.state);
@@ -347,9 +349,11 @@ pk_status pk_forward_static(const pk_plan* plan, void* const* W, const int64_t* 
     }
     MetaImage mi;
     build_meta_image(plan, &mi);
-    const Layout L = make_layout(plan, B, nnz);
-    if (mi.total + L.total > kStaticScratchBytes)
-        return fail(PK_EWORKSPACE, "pk_forward_static: this plan, B and nnz need " + std::to_string(mi.total + L.total) +
+    const size_t meta = mi.total - mi.cuts;      // what counts against the limit of the plan's metadata
+    const size_t room = kStaticScratchBytes - std::min(meta, kStaticScratchBytes);
+    const Layout L = make_layout(plan, B, nnz, room);
+    if (L.total > room)
+        return fail(PK_EWORKSPACE, "pk_forward_static: this plan, B and nnz need " + std::to_string(meta + L.total) +
                                    " bytes of scratch; the static scratch holds " + std::to_string(kStaticScratchBytes));
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (sd.plan_serial != plan->serial) {        // another plan's metadata (or none) is there: put this plan's
@@ -368,7 +372,7 @@ pk_status pk_forward_static(const pk_plan* plan, void* const* W, const int64_t* 
     }
     point_into(&sd.ds, reinterpret_cast<char*>(sd.ptr), mi);
     return forward_impl(plan, &sd.ds, kDedup | kPool, "pk_forward_static", W, nullptr, ids, offsets, B, nnz, out, out_row_stride,
-                        sd.ptr + mi.total, kStaticScratchBytes - mi.total, hip_stream);
+                        sd.ptr + mi.total, room, hip_stream);
 }
 
 static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const* A, const HotView* hot,

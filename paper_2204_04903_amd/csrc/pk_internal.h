@@ -230,6 +230,7 @@ struct pk_plan {
     std::vector<pk::TableMeta> sort_tables;   // tables with fields, in (pack, first key) order
     std::vector<int32_t> table_fields;        // per entry of sort_tables: the fields that read it
     std::vector<pk::SmallSlice> small_slices[pk::kSmallCuts];   // the cuts the one-launch forward pass chooses from
+    int64_t small_count[pk::kSmallCuts] = {};                   // their slices (above kSmallSlicesMax the list is not made)
     int64_t out_dim = 0;
     bool any_mean = false;
     int64_t bitmap_words = 0;             // all tables' bitmaps with their rank samples
@@ -242,6 +243,7 @@ struct pk_plan {
 namespace pk {
 void set_error(const std::string& msg);
 pk_status fail(pk_status s, const std::string& msg);
-Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz);
+// `room`: bytes that the workspace must fit, where the caller cannot give more (what is only kept to save time is left out)
+Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz, size_t room = ~(size_t)0);
 void destroy_device_state(pk_plan* plan);   // defined in pk_device.hip
 }  // namespace pk

@@ -44,13 +44,13 @@ static void count_slices(const pk_plan* plan, int64_t nnz, int32_t log_max, int6
     *total = std::min<int64_t>(each, coarse + nnz / kSliceOccLarge + (int64_t)plan->sort_tables.size());
 }
 
-Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz)
+Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz, size_t room)
 {
     const size_t F = plan->fields.size(), P = plan->packs.size();
     const size_t n = (size_t)std::max<int64_t>(nnz, 1);
     Layout L{};
     L.small_cut = small_cut(nnz, (int64_t)plan->sort_tables.size());
-    int64_t slices = (int64_t)plan->small_slices[L.small_cut].size();
+    int64_t slices = plan->small_count[L.small_cut];
     int32_t most = 0;
     L.small = nnz < kSmallNnz && slices <= kSmallSlicesMax && !(plan->opts.debug & 2);
     L.log_max = kSliceLogMax;
@@ -84,11 +84,6 @@ Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz)
     int32_t bt = avg_len >= 48 ? 32 : avg_len >= 32 ? 128 : avg_len >= 12 ? 256 : 1024;
     while (bt > 32 && (int64_t)F * ((B + bt - 1) / bt) < kTilesMin) bt /= 2;
     L.bags_per_tile  = bt;
-    // the keys kernel's counts per (tile, slice of the tile's table), so that the scatter kernel need not count
-    // again; only while that table stays small
-    const int64_t n_tiles = (int64_t)F * ((B + L.bags_per_tile - 1) / L.bags_per_tile);
-    L.tile_hist_stride = (!L.small && n_tiles * (int64_t)most <= ((int64_t)8 << 20)) ? most : 0;
-    L.tile_hist      = take((size_t)n_tiles * (size_t)L.tile_hist_stride * 4);
     L.packed_offsets = take((F * (size_t)B + P) * 4);
     L.keys           = take(n * 4 + 32);                 // keys are read eight at a time: room for the last reading past the end
     L.inverse        = take(n * 4);
@@ -103,6 +98,12 @@ Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz)
     L.ticket         = take(pieces * 4);
     L.rec            = take(L.small ? 0 : n * 8);
     L.bitmap         = take(L.small ? 0 : (size_t)plan->bitmap_words * 4);
+    // the keys kernel's counts per (tile, slice of the tile's table), so that the scatter kernel need not count
+    // again; only while that table stays small, and last, so that it can be left out where `room` ends
+    const int64_t n_tiles = (int64_t)F * ((B + L.bags_per_tile - 1) / L.bags_per_tile);
+    L.tile_hist_stride = (!L.small && n_tiles * (int64_t)most <= ((int64_t)8 << 20)) ? most : 0;
+    if (off + align_up((size_t)n_tiles * (size_t)L.tile_hist_stride * 4) > room) L.tile_hist_stride = 0;
+    L.tile_hist      = take((size_t)n_tiles * (size_t)L.tile_hist_stride * 4);
     L.total = off;
     return L;
 }
@@ -271,6 +272,8 @@ pk_status pk_plan_create(const pk_table_desc* tables, int32_t n_tables, const pk
     for (int cut = 0; cut < kSmallCuts; ++cut) {
         std::vector<SmallSlice>& list = pl->small_slices[cut];
         if (cut > 0 && ((int64_t)pl->sort_tables.size() << cut) > kSmallBlocks) continue;      // small_cut does not choose it
+        for (const TableMeta& tm : pl->sort_tables) pl->small_count[cut] += slice_geom_small(tm.rows, 1 << cut).n;
+        if (pl->small_count[cut] > kSmallSlicesMax) continue;                                  // (the batch is then partitioned)
         for (size_t p = 0; p < pl->packs.size(); ++p) {
             const Pack& k = pl->packs[p];
             const int32_t pack_first = (int32_t)list.size();

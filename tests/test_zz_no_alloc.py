@@ -60,3 +60,24 @@ def test_static_forward_refuses_what_the_static_array_cannot_hold():
         assert e.value.status == pk.PK_EWORKSPACE
     finally:
         layer.close()
+
+
+def test_static_forward_near_the_limit_leaves_the_stored_counts_out():
+    from paper_2204_04903_amd import binding as pk
+    from paper_2204_04903_amd.layer import PackedEmbedding
+    tables, fields = [(1_000_000, 8, 0)], [(0, 0)]
+    layer = PackedEmbedding(tables, fields)
+    try:
+        lo, hi = 1 << 19, 1 << 21                     # the smallest one-hot batch whose workspace exceeds the array
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if pk.pk_workspace_bytes(layer.plan, mid, mid) <= (32 << 20) else (lo, mid)
+        B = hi
+        rng = np.random.default_rng(902)
+        layer.load_table(0, rng.standard_normal((1_000_000, 8)).astype(np.float32))
+        pr = dict(ids=rng.integers(0, 1_000_000, size=B).astype(np.int64), offsets=np.arange(B + 1, dtype=np.int32))
+        print(f"[static] near the limit: B={B}", flush=True)
+        ref, got = _run_pair(layer, pr, B)
+        assert np.array_equal(ref.view(np.uint32), got.view(np.uint32))
+    finally:
+        layer.close()
