@@ -167,7 +167,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
         PoolJob pj{};
         int nb = 0;
         if (fuse_pool) {
-            fill_pool_job(plan, ds, order, W, nullptr, B, &pj);
+            fill_pool_job(plan, ds, order, W, nullptr, B, nnz, &pj);
             pj.coop_waves = coop_waves; pj.out = out; pj.out_stride = out_row_stride;
             pj.ids = ids; pj.offsets = offsets; pj.nnz = nnz;
             nb = (int)blocks_for((int64_t)pj.n_items + coop_waves, kSliceThreads / 64, 1 << 30);
@@ -213,10 +213,15 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
                   L.tile_hist_stride ? ws.at<int32_t>(L.tile_hist) : nullptr, L.tile_hist_stride);
     }
 
-    // Pooling needs the keys only.  Interleaving groups (Sec. III-C, K-Interleaving), when asked for: pack p belongs to
-    // group p mod G, every group pools on a stream of its own beside the rest of the dedup chain.
+    // Pooling needs the keys only, so in large calls it runs on an internal stream beside the rest of the dedup chain,
+    // whose kernels leave the memory system idle between them (1000 fields of 11 M IDs 939 -> 887 us a step, 200 of
+    // 21 M 1485 -> 1442, of 5 M 279 -> 264 forward alone).  Below kSidePoolNnz the two events cost what it gives (ragged
+    // layer of 1 M IDs: 6 to 11 us each).  Interleaving groups (Sec. III-C, K-Interleaving), when asked for: pack p
+    // belongs to group p mod G, every group pools on a stream of its own.
+    constexpr int64_t kSidePoolNnz = (int64_t)4 << 20;
     const int G = plan->opts.interleave_groups;
-    const int n_side = ds->overlap && !ds->prof_on && !L.small && do_pool && G >= 2 ? std::min<int>(P, G) : 0;
+    const bool beside = do_dedup && nnz >= kSidePoolNnz;
+    const int n_side = !ds->overlap || ds->prof_on || L.small || !do_pool ? 0 : G >= 2 ? std::min<int>(P, G) : beside && G == 0 ? 1 : 0;
     if (n_side) { rc = fork_streams(ds, stream, n_side); if (rc != PK_OK) return rc; }
     if (do_pool) {
         hipStream_t main_stream = stream;
@@ -227,7 +232,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
             if (n_side) stream = ds->side[grp];
             for (size_t i = 0; i < mine.size(); i += kPoolPacks) {
                 PoolJob pj{};
-                fill_pool_job(plan, ds, std::vector<int>(mine.begin() + i, mine.begin() + std::min(mine.size(), i + kPoolPacks)), W, hot, B, &pj);
+                fill_pool_job(plan, ds, std::vector<int>(mine.begin() + i, mine.begin() + std::min(mine.size(), i + kPoolPacks)), W, hot, B, nnz, &pj);
                 pj.coop_waves = coop_waves; pj.out = out; pj.out_stride = out_row_stride;
                 pj.keys = keys; pj.po = packed_offsets; pj.st = st;
                 // (the cooperating wavefronts follow the tiles in the same blocks)
