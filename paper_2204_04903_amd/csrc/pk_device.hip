@@ -214,8 +214,8 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     }
 
     // Pooling needs the keys only, so in large calls it runs on an internal stream beside the rest of the dedup chain,
-    // whose kernels leave the memory system idle between them (1000 fields of 11 M IDs 939 -> 887 us a step, 200 of
-    // 21 M 1485 -> 1442, of 5 M 279 -> 264 forward alone).  Below kSidePoolNnz the two events cost what it gives (ragged
+    // whose kernels leave the memory system idle between them (1000 fields of 11 M IDs 939 -> 918 us a step, 200 of
+    // 21 M 1485 -> 1470, of 5 M 279 -> 265 forward alone).  Below kSidePoolNnz the two events cost what it gives (ragged
     // layer of 1 M IDs: 6 to 11 us each).  Interleaving groups (Sec. III-C, K-Interleaving), when asked for: pack p
     // belongs to group p mod G, every group pools on a stream of its own.
     constexpr int64_t kSidePoolNnz = (int64_t)4 << 20;
