@@ -13,6 +13,8 @@
 // only the unevenness of whole runs.  The next round's keys are asked for before this round's rows are used.
 // A field of sequences (kSeqAvg IDs per bag or more on average) is left to the cooperating wavefronts at the
 // end of the grid: there all groups of a wavefront share a bag.
+// Sums are kept in double and rounded once, when the bag is written: one fp32 accumulator loses a bit of every
+// addition (bags of 25 normal weights: 1.4 times the error of adding four rows pairwise first, of 500: twice).
 // ---------------------------------------------------------------------------
 constexpr int kSeqAvg = 64;      // IDs per bag from which a field's bags take a whole wavefront each
 constexpr int kRunMax = 8;       // most bags in a lane group's run
@@ -119,15 +121,16 @@ __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k,
     int q = s_off[cb], c0 = q, ce = s_off[cb + 1];         // ... its first position and its end
     const int qe = s_off[last];
     float* o = as_global(job.out) + (size_t)(b0 + cb) * (size_t)job.out_stride + m.col + d0;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
     auto flush = [&]() {
         const int len = ce - c0;
         const float scale = m.pool == PK_MEAN && len > 0 ? 1.0f / (float)len : 1.0f;
+        float y[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] *= scale;
-        store_f32x4<NARROW>(o, k.D, acc);
+        for (int v = 0; v < 4; ++v) y[v] = (float)acc[v] * scale;
+        store_f32x4<NARROW>(o, k.D, y);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] = 0.f;
+        for (int v = 0; v < 4; ++v) acc[v] = 0.0;
         o += job.out_stride;
         c0 = ce;
         ce = ++cb < last ? s_off[cb + 1] : -1;
@@ -148,7 +151,7 @@ __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k,
 #pragma unroll
         for (int i = 0; i < R; ++i) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] += x[i][v];
+            for (int v = 0; v < 4; ++v) acc[v] += (double)x[i][v];
             while (ce == q + i + 1) flush();               // its bag is complete (and the empty ones after it)
         }
     }
@@ -173,7 +176,7 @@ __device__ __forceinline__ int pool_coop(const PoolJob& job, const PoolPack& k, 
             const KeySrc<IDS, R> src(job, k, m);
             for (; idx < B; idx += job.coop_waves) {
                 const int q0 = min(max(offs[idx], 0), src.n), q1 = min(max(offs[idx + 1], q0), src.n);
-                float acc[4] = {0.f, 0.f, 0.f, 0.f};
+                double acc[4] = {0.0, 0.0, 0.0, 0.0};
                 int q = q0 + g * R;
                 uint32_t kv[IDS ? 2 * R : R];
                 if (q < q1) src.raw(q, kv);
@@ -186,10 +189,18 @@ __device__ __forceinline__ int pool_coop(const PoolJob& job, const PoolPack& k, 
                         load_w4<BF16, NARROW>(pool_row<BF16, HYB>(k, row, d0), k.D, x[i]);
                     }
                     src.raw(min(q + R * gpw, q1 - 1), kv);
+                    // (the round's rows are added up as a tree in fp32 first: eight conversions to double would cost
+                    // the launch 2.5 % on bf16 sequences, and three roundings do not grow with the bag)
 #pragma unroll
-                    for (int i = 0; i < R; ++i)
+                    for (int v = 0; v < 4; ++v) {
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[v] += i == 0 || q + i < q1 ? x[i][v] : 0.f;
+                        for (int i = 1; i < R; ++i) x[i][v] = q + i < q1 ? x[i][v] : 0.f;
+#pragma unroll
+                        for (int d = 1; d < R; d *= 2)
+#pragma unroll
+                            for (int i = 0; i + d < R; i += 2 * d) x[i][v] += x[i + d][v];
+                        acc[v] += (double)x[0][v];
+                    }
                 }
 #pragma nounroll
                 for (int s = lpr; s < 64; s <<= 1)
@@ -197,9 +208,10 @@ __device__ __forceinline__ int pool_coop(const PoolJob& job, const PoolPack& k, 
                     for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], s, 64);
                 if (g == 0 && 4 * li < k.D) {
                     const float scale = m.pool == PK_MEAN && q1 > q0 ? 1.0f / (float)(q1 - q0) : 1.0f;
+                    float y[4];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[v] *= scale;
-                    store_f32x4<NARROW>(as_global(job.out) + (size_t)idx * (size_t)job.out_stride + m.col + d0, k.D, acc);
+                    for (int v = 0; v < 4; ++v) y[v] = (float)acc[v] * scale;
+                    store_f32x4<NARROW>(as_global(job.out) + (size_t)idx * (size_t)job.out_stride + m.col + d0, k.D, y);
                 }
             }
             idx -= B;
