@@ -310,18 +310,18 @@ pk_slice_scan_kernel(const TableCut* __restrict__ cut, int T,
 
 // Large batches: one record per occurrence, (key inside its slice, place of its bag's gradient chunk), written to
 // the slice's place.  A tile counts its occurrences per slice in LDS, reserves room in every
-// touched slice with one global add, and then places its records from block-local cursors.
+// touched slice with one global add, and then places its records from block-local cursors: one LDS word per slice
+// of the tile's table, first its count, then its cursor (a table has up to kTableSlicesMax).
 __global__ void __launch_bounds__(NT)
 pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int64_t nnz, int log_max,
                   const FieldMeta* __restrict__ fmeta, const TableCut* __restrict__ cut,
                   const PackState* __restrict__ st, const uint32_t* __restrict__ keys, int32_t* slice_cursor,
-                  uint2* __restrict__ rec, int hist_words, int64_t out_dim, const int32_t* __restrict__ fscan,
+                  uint2* __restrict__ rec, int64_t out_dim, const int32_t* __restrict__ fscan,
                   const int32_t* __restrict__ tile_hist, int tile_hist_stride)
 {
-    extern __shared__ int32_t s_dyn[];                     // the tile's bag offsets | counts | places, per slice of its table
+    extern __shared__ int32_t s_dyn[];                     // the tile's bag offsets | per slice of its table: count, then place
     int32_t* s_po = s_dyn;
     int32_t* s_hist = s_po + BT + 1;
-    int32_t* s_place = s_hist + hist_words;
     const int tid = threadIdx.x;
     if (fscan[3 * F + 2]) return;
     const int32_t* delta = fscan + (F + 1);
@@ -368,8 +368,7 @@ pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int
         const int slice0 = tc.first;
         for (int s = tid; s < g.n; s += NT) {
             const int c = s_hist[s];
-            s_place[s] = c ? atomicAdd(&slice_cursor[slice0 + s], c) : 0;
-            s_hist[s] = 0;
+            s_hist[s] = c ? atomicAdd(&slice_cursor[slice0 + s], c) : 0;
         }
         __syncthreads();
         // Every wavefront takes a contiguous quarter of the tile's positions, 64 at a time, so that a lane's
@@ -398,11 +397,10 @@ pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int
                     if (stepped) { while (t + 1 < tl.nb && s_po[t + 1] <= i) ++t; }
                     else if (valid) t = upper_bound_i32(s_po, tl.nb + 1, i) - 1;
                 }
-                int at_local = 0;
-                if (g.n <= kFewCounters) at_local = lds_inc_few<true>(s_hist, s, valid, g.n);   // (all lanes of the wavefront are here)
-                else if (valid) at_local = atomicAdd(&s_hist[s], 1);
+                int at = 0;
+                if (g.n <= kFewCounters) at = lds_inc_few<true>(s_hist, s, valid, g.n);   // (all lanes of the wavefront are here)
+                else if (valid) at = atomicAdd(&s_hist[s], 1);
                 if (!valid) continue;
-                const int64_t at = (int64_t)s_place[s] + at_local;
                 // the record: key inside the slice, the gradient's scale (bag length for mean pooling, 1 for sum;
                 // 0 = too long for its bits, to be looked up) above it, and the place of the bag's gradient chunk
                 uint32_t len = 1u;
@@ -410,7 +408,7 @@ pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int
                     const uint32_t L = (uint32_t)max(s_po[t + 1] - s_po[t], 1);
                     len = (L >> (32 - log_max)) ? 0u : L;
                 }
-                if ((uint64_t)at < (uint64_t)nnz)
+                if ((uint64_t)(int64_t)at < (uint64_t)nnz)
                     rec[at] = make_uint2((kk - (s << g.log_keys)) | (len << log_max),
                                          (uint32_t)((int64_t)(tl.b0 + t) * out_dim + m.col));
             }

@@ -188,9 +188,9 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     const int64_t n_tiles = (int64_t)F * ((B + bt - 1) / bt);
     const size_t scan_words = field_scan_words(F) + 2 * (size_t)T + 1;
     if (do_dedup && !L.small &&
-        std::max({scan_words, (size_t)bt + 1 + 2 * (size_t)L.max_table_slices, field_scan_words(F) + 4 * (size_t)F}) * 4 > 64 * 1024)
-        return fail(PK_EOVERFLOW, std::string(who) + ": fields, tables and slices per table together exceed what the "
-                                  "dedup kernels stage in LDS");
+        std::max(scan_words, field_scan_words(F) + 4 * (size_t)F) * 4 > 64 * 1024)
+        return fail(PK_EOVERFLOW, std::string(who) + ": fields and tables together exceed what the dedup kernels stage in LDS");
+    static_assert((1024 + 1 + kTableSlicesMax) * 4 <= 64 * 1024, "a tile's bag offsets and a longest table's slices fit LDS");
     if (do_dedup && !L.small) {
         sa.target = kSliceOccLarge; sa.log_max = L.log_max;
         sa.desc = nullptr; sa.gdesc = nullptr; sa.done = nullptr;
@@ -251,10 +251,10 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
                   dim3(kScanThreads), (size_t)(T + 1) * 4,
                   ws.at<TableCut>(L.tgeom), T, slice_total, slice_cursor, ws.at<SliceInfo>(L.slice_info),
                   L.n_slices, L.log_max == kSliceLogFine ? kBigSliceCount : 0x7FFFFFFF, big_list + kBigSlicesMax, big_list);
-        const size_t sc_lds = ((size_t)bt + 1 + 2 * (size_t)L.max_table_slices) * 4;
+        const size_t tile_lds = ((size_t)bt + 1 + (size_t)L.max_table_slices) * 4;
         const dim3 tile_grid(blocks_for(n_tiles, 1, 256 * 8));
-        PK_LAUNCH("pk_scatter", pk_scatter_kernel, tile_grid, dim3(NT), sc_lds, offsets, B, F, bt, nnz, sa.log_max, ds->fmeta,
-                  ws.at<TableCut>(L.tgeom), st, keys, slice_cursor, ws.at<uint2>(L.rec), L.max_table_slices, plan->out_dim,
+        PK_LAUNCH("pk_scatter", pk_scatter_kernel, tile_grid, dim3(NT), tile_lds, offsets, B, F, bt, nnz, sa.log_max, ds->fmeta,
+                  ws.at<TableCut>(L.tgeom), st, keys, slice_cursor, ws.at<uint2>(L.rec), plan->out_dim,
                   ws.at<int32_t>(L.fscan), L.tile_hist_stride ? ws.at<int32_t>(L.tile_hist) : nullptr, L.tile_hist_stride);
         const size_t tf_lds = (size_t)std::max(1, plan->max_table_fields) * kSliceTfWords * 4;
         if (L.n_slices > 0) {
