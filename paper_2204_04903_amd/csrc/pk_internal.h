@@ -33,6 +33,10 @@ constexpr int kSliceLogFine = 15;          // 32 K keys: 1024 bitmap words
 constexpr int kSliceWordsMax = 1 << (kSliceLogMax - 5);
 constexpr int kSliceOccLarge = 2048;       // occurrences per slice aimed at when the occurrences are partitioned
 constexpr int64_t kTilesMin = 1024;         // tiles that a launch of the keys and scatter kernels should have at least
+// Counts per (tile, slice) kept from the keys to the scatter kernel: room for one per occurrence and kCountRoomMin
+// more (a launch cut to kTilesMin tiles has up to twice as many, each with nnz / kSliceOccLarge + 1 slices), no more
+// than kCountRoomMax.
+constexpr int64_t kCountRoomMin = 2 * kTilesMin, kCountRoomMax = (int64_t)8 << 20;
 constexpr int64_t kSmallNnz = 1 << 19;     // below this many occurrences the forward pass is one launch
 constexpr int kSmallSlicesMax = 4096;      // ... if it has no more slices than this (descriptors the library owns)
 constexpr int kTableSlicesMax = 8192;      // slices per table (their counters are staged in LDS): rows <= 2^30

@@ -98,13 +98,17 @@ Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz, size_t room)
     L.ticket         = take(pieces * 4);
     L.rec            = take(L.small ? 0 : n * 8);
     L.bitmap         = take(L.small ? 0 : (size_t)plan->bitmap_words * 4);
-    // the keys kernel's counts per (tile, slice of the tile's table), so that the scatter kernel need not count
-    // again; only while that table stays small, and last, so that it can be left out where `room` ends
+    // The keys kernel's counts per (tile, slice of the tile's table), so that the scatter kernel need not count again.
+    // How many there are goes up and down with the tiles' size, and what a smaller call needs must fit a larger call's
+    // workspace, so the room for them depends on nnz alone: about one count per occurrence.  Where there are more (a
+    // tile then has fewer keys to count again than counts to read) they are not kept.  Last, so that they can be left
+    // out where `room` ends.
     const int64_t n_tiles = (int64_t)F * ((B + L.bags_per_tile - 1) / L.bags_per_tile);
-    L.tile_hist_stride = (!L.small && n_tiles * (int64_t)most <= ((int64_t)8 << 20)) ? most : 0;
-    if (off + align_up((size_t)n_tiles * (size_t)L.tile_hist_stride * 4) > room) L.tile_hist_stride = 0;
-    L.tile_hist      = take((size_t)n_tiles * (size_t)L.tile_hist_stride * 4);
-    L.total = off;
+    const int64_t count_room = L.small ? 0 : std::min<int64_t>((int64_t)n + kCountRoomMin, kCountRoomMax);
+    const int64_t counts = n_tiles * (int64_t)most;
+    L.tile_hist_stride = counts <= count_room && off + (size_t)counts * 4 <= room ? most : 0;
+    L.tile_hist      = off;
+    L.total          = std::min(align_up(off + (size_t)count_room * 4), std::max(off, room));
     return L;
 }
 

@@ -202,6 +202,36 @@ def test_micro_batch_size_follows_eq2():
         pk.pk_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("tables,n_fields,per_bag", [
+    ([(1_000_000, 16, 0)] * 26, 26, 13),
+    ([(1_000_000, 8, 0)], 1, 1),
+    ([(400_000, 8, 0), (30_000, 16, 0)] * 500, 1000, 5),
+    ([(500_000, 64, 1)] * 6, 6, 300),
+    ([(140_000_000, 4, 0)] * 2, 4, 2),
+])
+def test_a_smaller_call_fits_a_larger_calls_workspace(tables, n_fields, per_bag):
+    # callers size a workspace once, for their largest batch (MicroBatchPipeline does): wherever the tiles' size changes,
+    # fewer bags or fewer IDs need no more room, and the size that Eq. 2 gives fits its bound after it is evened out
+    plan = pk.pk_plan_create(tables, [(f % len(tables), f % 2) for f in range(n_fields)])
+    try:
+        B0 = -(-(1 << 19) // (n_fields * per_bag))                        # about where batches become large ones
+        sizes = sorted({b for t in (32, 64, 128, 256, 512, 1024) for k in (1, 2, 3, 5, 40, 1023 // n_fields, 1024 // n_fields)
+                        for b in (t * k - 1, t * k, t * k + 1) if b > 0} | {B0 - 1, B0, B0 + 1, 2 * B0, 3 * B0 + 1})
+        nnzs = sorted({n_fields * b * per_bag // part for b in (B0, 3 * B0) for part in (1, 2, 7)} | {(1 << 19) - 1, 1 << 19})
+        ws = np.array([[pk.pk_workspace_bytes(plan, b, n) for n in nnzs] for b in sizes], np.float64)
+        assert (np.diff(ws, axis=0) >= 0).all() and (np.diff(ws, axis=1) >= 0).all()
+        along = [pk.pk_workspace_bytes(plan, b, n_fields * b * per_bag) for b in sizes]
+        assert along == sorted(along)
+        for B in (B0 + 1, 2 * B0 + 1, 4 * B0 - 1):
+            nnz = n_fields * B * per_bag
+            for part in (1.5, 2, 2.3, 3, 4.1):
+                bound = int(pk.pk_workspace_bytes(plan, B, nnz) / part)
+                bs = pk.pk_micro_batch_size(plan, B, nnz, bound, 0)
+                assert bs == 0 or pk.pk_workspace_bytes(plan, bs, -(-nnz * bs // B)) <= bound
+    finally:
+        pk.pk_plan_destroy(plan)
+
+
 def test_forward_stages_reject_bad_arguments_before_touching_the_gpu():
     plan = pk.pk_plan_create([(100, 8, 0)], [(0, 0)])
     try:
