@@ -205,6 +205,13 @@ __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     acc[v] = v < k.D ? __hip_atomic_load(prow + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+                // ... and leaves them as the forward pass did, so that a context serves any number of backward passes
+                // (after all lanes' loads: the last two may hold the same columns)
+                asm volatile("s_waitcnt vmcnt(0)" ::"v"(acc[0]), "v"(acc[1]), "v"(acc[2]), "v"(acc[3]) : "memory");
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (v < k.D) __hip_atomic_store(prow + v, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (li == 0) __hip_atomic_store(as_global(job.ticket) + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 load_w4<BF16, NARROW>(r.w, k.D, w);
                 load_f32x4<NARROW>(r.a, k.D, ac);
             }
