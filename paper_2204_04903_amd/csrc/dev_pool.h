@@ -106,7 +106,7 @@ __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k,
     const int f = as_global(k.slot_field)[j];
     const FieldMeta m = as_global(job.fmeta)[f];
     const int32_t* offs = pool_offsets(job, k, IDS, j, f);
-    if (pool_is_seq(offs, B)) return;
+    if (job.coop_waves && pool_is_seq(offs, B)) return;    // (without them only rejected offsets look like a sequence field's)
     const KeySrc<IDS, R> src(job, k, m);
     const int b0 = (item - j * k.tiles) * ((64 >> k.sh) * k.run);
     const int nb = min((64 >> k.sh) * k.run, B - b0);
@@ -155,6 +155,7 @@ __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k,
             while (ce == q + i + 1) flush();               // its bag is complete (and the empty ones after it)
         }
     }
+    while (cb < last) flush();                             // (only after rejected offsets: every bag is written, whatever they hold)
 }
 
 // Sequence fields: a wavefront per bag, R positions per group and round.
