@@ -21,8 +21,8 @@
  *     of distinct keys) stay in device memory.
  *   - All functions return a pk_status (0 = success) and never throw;
  *     pk_last_error() gives a thread-local message for the last failure.
- *   - Limits: total rows of a pack < 2^32, of a table <= 2^30; dim <= 256; nnz < 2^31;
- *     B * out_dim < 2^32; at most 4096 fields and 4096 tables.
+ *   - Limits: total rows of a pack < 2^32, of a table <= 2^30; dim <= 256;
+ *     nnz <= 2^31 - 8192; B * out_dim < 2^32; at most 4096 fields and 4096 tables.
  */
 #ifndef PK_H
 #define PK_H

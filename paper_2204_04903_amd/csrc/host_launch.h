@@ -259,7 +259,7 @@ pk_status check_common(const pk_plan* plan, int32_t B, int64_t nnz, const void* 
     if (!plan) return fail(PK_EINVAL, std::string(who) + ": plan is NULL");
     if (B <= 0) return fail(PK_ESHAPE, std::string(who) + ": B must be positive");
     if (nnz < 0) return fail(PK_ESHAPE, std::string(who) + ": nnz must be non-negative");
-    if (nnz >= ((int64_t)1 << 31)) return fail(PK_EOVERFLOW, std::string(who) + ": nnz must be below 2^31");
+    if (nnz > kNnzMax) return fail(PK_EOVERFLOW, std::string(who) + ": nnz must be at most 2^31 - 8192");
     if (plan->opts.max_batch > 0 && B > plan->opts.max_batch) return fail(PK_ESHAPE, std::string(who) + ": B exceeds the plan's max_batch");
     if (plan->opts.max_nnz > 0 && nnz > plan->opts.max_nnz) return fail(PK_ESHAPE, std::string(who) + ": nnz exceeds the plan's max_nnz");
     if ((int64_t)B * plan->out_dim >= ((int64_t)1 << 32)) return fail(PK_EOVERFLOW, std::string(who) + ": B * out_dim must be below 2^32");

@@ -232,6 +232,23 @@ def test_a_smaller_call_fits_a_larger_calls_workspace(tables, n_fields, per_bag)
         pk.pk_plan_destroy(plan)
 
 
+def test_calls_whose_positions_would_not_fit_32_bits_are_refused():
+    # a kernel's last round counts up to 8192 positions past the last one
+    plan = pk.pk_plan_create([(100, 8, 0)], [(0, 0)])
+    try:
+        for nnz in (2 ** 31 - 8191, 2 ** 31 - 1):
+            need, fake = pk.pk_workspace_bytes(plan, 1, nnz), 0x10000
+            for call in (lambda: pk.pk_forward(plan, [fake], fake, fake, 1, nnz, fake, 8, fake, need),
+                         lambda: pk.pk_forward_dedup(plan, fake, fake, 1, nnz, fake, need, 0),
+                         lambda: pk.pk_forward_pool(plan, [fake], 1, nnz, fake, 8, fake, need, 0),
+                         lambda: pk.pk_backward_update(plan, [fake], [fake], fake, 8, 1, nnz, 0.01, 1e-8, fake, need)):
+                with pytest.raises(pk.PkError) as e:
+                    call()
+                assert e.value.status == pk.PK_EOVERFLOW
+    finally:
+        pk.pk_plan_destroy(plan)
+
+
 def test_forward_stages_reject_bad_arguments_before_touching_the_gpu():
     plan = pk.pk_plan_create([(100, 8, 0)], [(0, 0)])
     try:
