@@ -8,7 +8,8 @@
 //
 // The ID distribution is heavily skewed (Sec. II-B), so keys are handled by how many occurrences they have:
 //   up to kColdMax:   one lane group per key (a group is as many lanes as the row has 16-byte chunks);
-//   up to kLongMin:   the wavefront that met the key among its own, its groups stride over the occurrences;
+//   up to kLongMin:   the wavefront that met the key among its own, its groups stride over the occurrences; of
+//                     narrow rows, several such keys side by side;
 //   longer:           a block of its own, which the launch starts first, in pieces of kPiece occurrences; the
 //                     pieces of a key with several add into a row of partial sums, the last one to arrive
 //                     takes the step.
@@ -115,11 +116,11 @@ __device__ __forceinline__ void row_step(const RowPtr& r, int D, const double (&
     store_w4<BF16, NARROW>(r.w, D, w);
 }
 
-// sum over the lane groups of a wavefront (butterfly); every lane ends with the total
-__device__ __forceinline__ void wave_group_sum(double (&acc)[4], int lpr)
+// sum over the lane groups of `lanes` neighbouring lanes (butterfly); every lane ends with the total
+__device__ __forceinline__ void wave_group_sum(double (&acc)[4], int lpr, int lanes)
 {
 #pragma nounroll
-    for (int o = lpr; o < 64; o <<= 1)
+    for (int o = lpr; o < lanes; o <<= 1)
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], o, 64);
 }
@@ -129,7 +130,7 @@ __device__ __forceinline__ void wave_group_sum(double (&acc)[4], int lpr)
 constexpr int kMarksPerBlock = 4;      // (16: the mixed layer 16 % slower, a block then has several pieces one after the other)
 constexpr int kLongBlocks = 768;
 
-template <bool BF16, bool MEAN, bool NARROW, bool HYB>
+template <bool BF16, bool MEAN, bool NARROW, bool HYB, bool TEAMS>
 __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, double (*s_red)[64][4])
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -172,7 +173,7 @@ __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
             if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(a + (wv * gpw + g) * 4), (uint32_t)b, (uint32_t)(4 * gpw * (NT / 64)));
             if (fin && kn == 1) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }
-            wave_group_sum(acc, lpr);
+            wave_group_sum(acc, lpr, 64);
             __syncthreads();                           // the previous piece's sums are consumed
             if (g == 0) {
 #pragma unroll
@@ -221,9 +222,11 @@ __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k
     return idx - n_mine;
 }
 
+constexpr int kTeam = 4;               // lane groups that share a key of more than kColdMax occurrences at least
+
 // The other keys of a pack.  XCD x takes the x-th eighth of the keys (neighbouring keys share gradient
 // columns: one L2 then holds them), its wavefronts take consecutive handfuls.
-template <bool BF16, bool MEAN, bool NARROW, bool HYB>
+template <bool BF16, bool MEAN, bool NARROW, bool HYB, bool TEAMS>
 __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride)
 {
     const int lane = threadIdx.x & 63;
@@ -262,18 +265,48 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
             accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
             row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
         }
+        uint64_t todo = __ballot(li == 0 && len > kColdMax && len <= kLongMin);
+        if (todo == 0) continue;
+        if constexpr (!TEAMS) {                            // one key after the other
 #pragma nounroll
-        for (uint64_t todo = __ballot(li == 0 && len > kColdMax && len <= kLongMin); todo; todo &= todo - 1) {
-            const int lead = __ffsll((unsigned long long)todo) - 1;
-            const int wa = __builtin_amdgcn_readlane(a, lead), wb = __builtin_amdgcn_readlane(b, lead);
-            const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, (uint32_t)__builtin_amdgcn_readlane((int)r0, lead), k.D, d0);
-            const bool fin = g == 0 && act;
-            float w[4], ac[4];
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(wa + 4 * g), (uint32_t)wb, (uint32_t)(4 * gpw));
-            if (fin) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }    // (on their way while the groups are added up)
-            wave_group_sum(acc, lpr);
-            if (fin) row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
+            for (; todo; todo &= todo - 1) {
+                const int lead = __ffsll((unsigned long long)todo) - 1;
+                const int wa = __builtin_amdgcn_readlane(a, lead), wb = __builtin_amdgcn_readlane(b, lead);
+                const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, (uint32_t)__builtin_amdgcn_readlane((int)r0, lead), k.D, d0);
+                const bool fin = g == 0 && act;
+                float w[4], ac[4];
+                double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(wa + 4 * g), (uint32_t)wb, (uint32_t)(4 * gpw));
+                if (fin) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }    // (on their way while the groups are added up)
+                wave_group_sum(acc, lpr, 64);
+                if (fin) row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
+            }
+        } else {
+            // The keys met are dealt to teams of `team` lane groups: all groups for a key alone, several keys side by side.
+            const int n = __popcll(todo);
+            int team = gpw;
+            while (team > kTeam && gpw < team * n) team >>= 1;
+            const int in_team = g & (team - 1);
+            const uint64_t below = (1ull << lane) - 1ull;
+            const int rank = todo >> lane & 1 ? __popcll(todo & below) : n + __popcll(~todo & below);
+            const int nth = __builtin_amdgcn_ds_permute(rank * 4, lane);       // lane k: the first lane of the k-th key met
+#pragma nounroll
+            for (int k0 = 0; k0 < n; k0 += gpw / team) {
+                const int kk = k0 + g / team;
+                const int src = __shfl(nth, min(kk, n - 1), 64);
+                const int wa = __shfl(a, src, 64), sb = __shfl(b, src, 64), wb = kk < n ? sb : wa;
+                const uint32_t row_k = (uint32_t)__shfl((int)r0, src, 64);
+                double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
+                wave_group_sum(acc, lpr, lpr * team);
+                if (in_team == 0 && act && kk < n) {       // (asked for earlier, the row would not fit the registers)
+                    const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, row_k, k.D, d0);
+                    float w[4], ac[4];
+                    load_w4<BF16, NARROW>(r.w, k.D, w);
+                    load_f32x4<NARROW>(r.a, k.D, ac);
+                    row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
+                }
+            }
         }
     }
     return idx - n_mine;
@@ -282,17 +315,23 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
 // the code for a pack's kind
 #define PK_ADA_KINDS(FN, ...)                                                                   \
     switch (k.kind) {                                                                           \
-        case 0: idx = FN<false, false, false, HYB>(__VA_ARGS__); break;                         \
-        case 1: idx = FN<true, false, false, HYB>(__VA_ARGS__); break;                          \
-        case 2: idx = FN<false, true, false, HYB>(__VA_ARGS__); break;                          \
-        case 3: idx = FN<true, true, false, HYB>(__VA_ARGS__); break;                           \
-        case 4: idx = FN<false, false, true, HYB>(__VA_ARGS__); break;                          \
-        case 5: idx = FN<true, false, true, HYB>(__VA_ARGS__); break;                           \
-        case 6: idx = FN<false, true, true, HYB>(__VA_ARGS__); break;                           \
-        case 7: idx = FN<true, true, true, HYB>(__VA_ARGS__); break;                            \
+        case 0: idx = FN<false, false, false, HYB, TEAMS>(__VA_ARGS__); break;                  \
+        case 1: idx = FN<true, false, false, HYB, TEAMS>(__VA_ARGS__); break;                   \
+        case 2: idx = FN<false, true, false, HYB, TEAMS>(__VA_ARGS__); break;                   \
+        case 3: idx = FN<true, true, false, HYB, TEAMS>(__VA_ARGS__); break;                    \
+        case 4: if constexpr (TEAMS) idx = FN<false, false, true, HYB, TEAMS>(__VA_ARGS__); break;  \
+        case 5: if constexpr (TEAMS) idx = FN<true, false, true, HYB, TEAMS>(__VA_ARGS__); break;   \
+        case 6: if constexpr (TEAMS) idx = FN<false, true, true, HYB, TEAMS>(__VA_ARGS__); break;   \
+        case 7: if constexpr (TEAMS) idx = FN<true, true, true, HYB, TEAMS>(__VA_ARGS__); break;    \
     }
 
-template <bool HYB>
+// TEAMS: for launches with rows of kTeamDim columns and fewer, where a wavefront's handful has 16 to 64 keys: where
+// frequent IDs are neighbours, all of them can have more than kColdMax occurrences, and one after the other they take
+// longer than everything else (16 tables of 82 K occurrences, dimension 3: 238 us, in teams 79; dimension 8: 79,
+// 57).  Wider rows have few keys to a handful and keep the registers (26 one-hot fields of 32 columns, a
+// step: 52 us, 54 with the teams' code).
+constexpr int kTeamDim = 16;
+template <bool HYB, bool TEAMS>
 __global__ void __launch_bounds__(NT, 6)
 pk_adagrad_kernel(AdaJob job)
 {

@@ -42,7 +42,8 @@ __device__ __forceinline__ void load_f32x4(const float* p, int D, float (&v)[4])
         const f32x4 x = *reinterpret_cast<const f32x4*>(p);
         v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
     } else {
-        v[0] = p[0]; v[1] = D > 1 ? p[1] : 0.f; v[2] = D > 2 ? p[2] : 0.f; v[3] = 0.f;
+        v[0] = p[0]; v[1] = v[2] = v[3] = 0.f;
+        if (D > 1) { v[1] = p[1]; v[2] = p[D - 1]; }       // (of two columns the last one twice: a branch for the third would be waited for)
     }
 }
 
@@ -71,7 +72,8 @@ __device__ __forceinline__ void load_w4(const char* p, int D, float (&v)[4])
         v[2] = bf16_to_f32(x.y & 0xFFFFu); v[3] = bf16_to_f32(x.y >> 16);
     } else {
         const uint16_t* h = reinterpret_cast<const uint16_t*>(p);
-        v[0] = bf16_to_f32(h[0]); v[1] = D > 1 ? bf16_to_f32(h[1]) : 0.f; v[2] = D > 2 ? bf16_to_f32(h[2]) : 0.f; v[3] = 0.f;
+        v[0] = bf16_to_f32(h[0]); v[1] = v[2] = v[3] = 0.f;
+        if (D > 1) { v[1] = bf16_to_f32(h[1]); v[2] = bf16_to_f32(h[D - 1]); }
     }
 }
 

@@ -425,8 +425,11 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
                 job.hot_blocks = nnz <= kLongMin ? 0 : (int)((blocks_for(nnz, kMarkStep * kMarksPerBlock, kLongBlocks) + job.n_packs + 7u) & ~7u);
                 job.key_blocks = (int)((blocks_for(nnz + (int64_t)job.n_packs * (64 >> sh), (64 >> sh) * (NT / 64), 256 * 16) + 7u) & ~7u);
                 const dim3 grid(job.hot_blocks + job.key_blocks);
-                if (hot) PK_LAUNCH("pk_adagrad", pk_adagrad_kernel<true>, grid, dim3(NT), 0, job);
-                else PK_LAUNCH("pk_adagrad", pk_adagrad_kernel<false>, grid, dim3(NT), 0, job);
+                bool teams = false;
+                for (int q = 0; q < job.n_packs; ++q) teams |= job.pack[q].D <= kTeamDim;
+                const auto kernel = hot ? (teams ? pk_adagrad_kernel<true, true> : pk_adagrad_kernel<true, false>)
+                                        : (teams ? pk_adagrad_kernel<false, true> : pk_adagrad_kernel<false, false>);
+                PK_LAUNCH("pk_adagrad", kernel, grid, dim3(NT), 0, job);
                 job.n_packs = 0;
             }
             if (i == order.size()) break;
