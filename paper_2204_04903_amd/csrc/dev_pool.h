@@ -267,7 +267,9 @@ pk_pool_kernel(PoolJob job)
 // WAVES: wavefronts per SIMD the kernel is compiled for.  8 lets two blocks share a compute unit, which a
 // launch with more blocks than compute units needs; 4 gives a block twice the registers (nothing is then
 // kept in scratch memory), which is faster when every block has a compute unit to itself.
-template <int WAVES>
+// MANY: for plans with a table that several fields read (a slice block then looks for its occurrences in all of
+// them; without that code the other plans' launch keeps more in registers: 26 one-hot fields 52 us a step, 56 with it).
+template <int WAVES, bool MANY>
 __global__ void __launch_bounds__(kSliceThreads, WAVES)
 pk_fused_kernel(SliceArgs a, PoolJob pj, int slice_blocks, int meta_blocks)
 {
@@ -277,7 +279,7 @@ pk_fused_kernel(SliceArgs a, PoolJob pj, int slice_blocks, int meta_blocks)
     static_assert(kSmallLdsWords >= 3 * 4096 + 2, "the field scan must fit the block's LDS");
     if ((int)blockIdx.x < slice_blocks) {
         // (the kernel's arguments where they stand: `a` is the first of them)
-        small_slice_body<(WAVES > 4)>((SliceArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x, s_main, s_dyn);
+        small_slice_body<(WAVES > 4), MANY>((SliceArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x, s_main, s_dyn);
         return;
     }
     PK_PT(a, blockIdx.x, 0);

@@ -12,6 +12,10 @@
 //   - an occurrence's place inside its key comes from the counting pass, kept in a register.
 // Before (every field scanned in every block, a two-level look-back after the counting): 8 one-hot fields 15.5 us,
 // 26 fields of 8192 29.8 us, 26 fields of 64 17 us a launch.
+// A table that several fields read is one run of occurrences, numbered over its fields (field after field, each step
+// waited for: 26 fields of 64 on two tables 55 us a launch, 15.5 this way).  Slices of frequent keys, with more
+// occurrences than are kept, have the counters of all of them in one round where there is room (26 one-hot fields of
+// 16384, low IDs frequent: 90 us a launch with 4096 counters, 60 with 8192).
 
 // LDS words: bitmap | popcount prefix | counters | kept occurrences: key, position | bag offsets (or every 2^k-th of them)
 constexpr int kSmallWords = 1 << (kSliceLogMax - 5);
@@ -19,6 +23,8 @@ constexpr int kSmallRanks = 4096;
 constexpr int kSmallCache = 2 * kSliceThreads;
 constexpr int kSmallOffs = 2048;
 constexpr int kSmallLdsWords = 2 * kSmallWords + kSmallRanks + 2 * kSmallCache + kSmallOffs;
+constexpr uint32_t kSmallKeyMask = (1u << kSliceLogMax) - 1u;      // of a kept occurrence's first word: its key; above, its field of the table
+static_assert(kSliceLogMax + 12 <= 32, "a table has up to 4096 fields");
 constexpr int kDescGroup = 16;           // slices whose distinct keys also add up in one word
 
 __device__ __forceinline__ uint64_t small_load(const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -126,7 +132,29 @@ __device__ __forceinline__ int small_bag(const int32_t* __restrict__ offs, int B
     return b;
 }
 
-template <bool LEAN>
+// where the occurrences of a table of several fields stand: field, position of the v-th one, from where the last
+// lookup ended
+struct SmallField {
+    int j = 0, next = -1, shift = 0;                       // the field; first occurrence after it; position minus number
+    __device__ __forceinline__ int position(const int32_t* s_tf, int nf, int n_table, int v)
+    {
+        if (v >= next) {
+            int hi = nf;                                   // the last field with no more than v occurrences before it
+            while (hi - j > 1) {
+                const int mid = (j + hi) >> 1;
+                if (s_tf[kSliceTfWords * mid + 1] <= v) j = mid; else hi = mid;
+            }
+            next = j + 1 < nf ? s_tf[kSliceTfWords * (j + 1) + 1] : n_table;
+            shift = s_tf[kSliceTfWords * j] - s_tf[kSliceTfWords * j + 1];
+        }
+        return v + shift;
+    }
+};
+
+template <bool V> struct BoolTag { static constexpr bool value = V; };
+
+// MANY: some table of the plan has several fields
+template <bool LEAN, bool MANY>
 __device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int32_t* s_main, int32_t* s_tf)
 {
     constexpr int NTH = kSliceThreads, NW = NTH / 64;
@@ -146,7 +174,7 @@ __device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int3
     const int64_t* __restrict__ ids = as_global(a->ids);
     PK_PT(*a, slice, 0);
     SmallSlicePtr ss = slice_at(a, slice);
-    const int lg = ss->log_keys, nf = ss->n_fields;        // (fields of the table)
+    const int lg = ss->log_keys, nf = MANY ? ss->n_fields : 1;       // (fields of the table)
     const uint32_t lo = (uint32_t)ss->idx << lg;           // first key of the slice inside its table
     const int words = 1 << (lg - 5);
 
@@ -176,6 +204,7 @@ __device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int3
     // ---- sizes: occurrences of the packs before, of the tables before, of the pack, of the slots before ----
     int4 sum = make_int4(0, 0, 0, 0);
     int bad = 0, viol = 0;
+    const int len0 = o1 - o0;
     for (int i = tid; i < F; i += NTH) {
         if (i >= NTH) {
             sf = as_global(a->slot_info)[i];
@@ -192,10 +221,6 @@ __device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int3
     for (int b = b_lo + tid; b < b_hi; b += NTH) {
         if (b >= b_lo + NTH) { share0 = offs0[b]; share1 = offs0[b + 1]; }
         viol |= share0 > share1 || share0 < fb0 || share1 > fe0;
-    }
-    for (int j = 1; j < nf; ++j) {
-        const int32_t* offs = offsets + (int64_t)as_global(a->tfields)[ss->field_begin + j].field * B;
-        for (int b = b_lo + tid; b < b_hi; b += NTH) viol |= offs[b] > offs[b + 1] || offs[b] < offs[0] || offs[b + 1] > offs[B];
     }
     const int step_log = small_step(B), n_offs = ((B + (1 << step_log) - 1) >> step_log) + 1;
     if (nf == 1 && !onehot)
@@ -220,62 +245,104 @@ __device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int3
     }
     if (tid == 0) { s_ctx.pstart = sum.x; s_ctx.nnz_p = sum.z; s_ctx.rec_before = sum.y - sum.x; s_ctx.q0 = q0; }
     PK_PT(*a, slice, 1);
-    // the table's fields: where they begin and end, packed position minus position, column, pooling | field
+    // the table's fields: where they begin, the table's occurrences before them, packed position minus position, column,
+    // pooling | field
+    int n_table = q1 - q0;                                 // occurrences of the table
     if (nf == 1) {
-        if (tid == 0) { s_tf[0] = q0; s_tf[1] = q1; s_tf[2] = sum.w - fb0; s_tf[3] = ss->col0; s_tf[4] = ss->pool0 | (ss->field0 << 1); }
+        if (tid == 0) { s_tf[0] = q0; s_tf[1] = 0; s_tf[2] = sum.w - fb0; s_tf[3] = ss->col0; s_tf[4] = ss->pool0 | (ss->field0 << 1); }
     } else {
-        // (several fields: their packed positions from the sizes of the slots before each)
-        for (int j = 0; j < nf; ++j) {
-            const TableField tf = as_global(a->tfields)[ss->field_begin + j];
-            int before = 0;
-            for (int i = tid; i < ss->first_slot + tf.slot; i += NTH) {
+        // (several fields: the slots' packed positions from one scan of their sizes, where the kept occurrences go later)
+        int32_t* s_slotpos = s_cnt + kSmallRanks;
+        int carry = 0;
+        for (int i = tid; i - tid < F; i += NTH) {
+            int len = len0;
+            if (i >= NTH && i < F) {
                 const int f = as_global(a->slot_info)[i].x;
-                before += offsets[(int64_t)(f + 1) * B] - offsets[(int64_t)f * B];
+                len = offsets[(int64_t)(f + 1) * B] - offsets[(int64_t)f * B];
             }
             int tot;
-            (void)block_excl_scan<NTH>(before, &tot);
-            if (tid == 0) {
-                const int fb = offsets[(int64_t)tf.field * B];
-                s_tf[kSliceTfWords * j] = fb; s_tf[kSliceTfWords * j + 1] = offsets[(int64_t)(tf.field + 1) * B];
-                s_tf[kSliceTfWords * j + 2] = tot - fb; s_tf[kSliceTfWords * j + 3] = tf.col; s_tf[kSliceTfWords * j + 4] = tf.pool | (tf.field << 1);
-            }
+            const int ex = block_excl_scan<NTH>(i < F ? len : 0, &tot);
+            if (i < F) s_slotpos[i] = carry + ex;
+            carry += tot;
         }
         __syncthreads();
+        n_table = 0;
+        for (int j = tid; j - tid < nf; j += NTH) {
+            int len = 0;
+            int32_t* tf = s_tf + kSliceTfWords * j;
+            if (j < nf) {
+                const TableField x = as_global(a->tfields)[ss->field_begin + j];
+                tf[0] = offsets[(int64_t)x.field * B];
+                len = offsets[(int64_t)(x.field + 1) * B] - tf[0];
+                tf[2] = s_slotpos[ss->first_slot + x.slot] - tf[0]; tf[3] = x.col; tf[4] = x.pool | (x.field << 1);
+            }
+            int tot;
+            const int ex = block_excl_scan<NTH>(len, &tot);
+            if (j < nf) tf[1] = n_table + ex;
+            n_table += tot;
+        }
+        __syncthreads();
+        // the bags of this slice's share of the other fields
+        const unsigned share = (unsigned)(b_hi - b_lo);
+        for (unsigned x = tid; x < share * (unsigned)(nf - 1); x += NTH) {
+            const int j = 1 + (int)(x / share), b = b_lo + (int)(x % share);
+            const int32_t* tf = s_tf + kSliceTfWords * j;
+            const int32_t* offs = offsets + (int64_t)(tf[4] >> 1) * B;
+            viol |= offs[b] > offs[b + 1] || offs[b] < tf[0] || offs[b + 1] > offs[B];
+        }
     }
 
     // ---- which keys occur; the slice's occurrences are kept while they are at hand ----
     const uint32_t rows = ss->rows;
     const uint64_t magic = ss->magic;
     int before = 0;                                        // per wavefront: occurrences of the table in earlier slices
-    for (int j = 0; j < nf; ++j) {
-        const int j0 = nf == 1 ? q0 : s_tf[kSliceTfWords * j], j1 = nf == 1 ? q1 : s_tf[kSliceTfWords * j + 1];
-        for (int base = j0; base < j1; base += 4 * NTH) {
-            if (nf > 1 || base > j0) fetch(base, j1);
-            uint32_t kk[4];
-            uint64_t m[4];
-            int n = 0;
+    uint32_t kk[4];
+    auto find = [&](auto&& field, auto&& pos) {            // of the four occurrences per lane (rows kk): those of this slice
+        uint64_t m[4];
+        int n = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            before += __popcll(__ballot(kk[u] < lo));
+            m[u] = __ballot((kk[u] >> lg) == (uint32_t)ss->idx);
+            n += __popcll(m[u]);
+        }
+        if (n == 0) return;
+        int at = 0;                                        // room for the wavefront's finds in one add
+        if (lane == 0) at = atomicAdd(&s_n, n);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (m[u] >> lane & 1) {
+                const uint32_t kl = kk[u] - lo, bit = 1u << (kl & 31);
+                if (!(s_bits[kl >> 5] & bit)) atomicOr(&s_bits[kl >> 5], bit);
+                const int x = at + __popcll(m[u] & ((1ull << lane) - 1ull));
+                if (x < kSmallCache) { s_ckey[x] = kl | ((uint32_t)field(u) << kSliceLogMax); s_cpos[x] = pos(u); }
+            }
+            at += __popcll(m[u]);
+        }
+    };
+    if (nf == 1) {
+        for (int base = q0; base < q1; base += 4 * NTH) {
+            if (base > q0) fetch(base, q1);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                kk[u] = base + tid + u * NTH < q1 ? fold_id(idv[u], rows, magic) : 0xFFFFFFFFu;      // (no row: rows <= 2^30)
+            find([](int) { return 0; }, [&](int u) { return base + tid + u * NTH; });
+        }
+    } else {
+        SmallField at;
+        for (int base = 0; base < n_table; base += 4 * NTH) {
+            int fj[4], q[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                kk[u] = base + tid + u * NTH < j1 ? fold_id(idv[u], rows, magic) : 0xFFFFFFFFu;      // (no row: rows <= 2^30)
-                before += __popcll(__ballot(kk[u] < lo));
-                m[u] = __ballot((kk[u] >> lg) == (uint32_t)ss->idx);
-                n += __popcll(m[u]);
+                q[u] = at.position(s_tf, nf, n_table, min(base + tid + u * NTH, n_table - 1));
+                fj[u] = at.j;
+                idv[u] = ids[q[u]];
             }
-            if (n) {                                       // room for the wavefront's finds in one add
-                int at = 0;
-                if (lane == 0) at = atomicAdd(&s_n, n);
-                at = __builtin_amdgcn_readfirstlane(at);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (m[u] >> lane & 1) {
-                        const uint32_t kl = kk[u] - lo, bit = 1u << (kl & 31);
-                        if (!(s_bits[kl >> 5] & bit)) atomicOr(&s_bits[kl >> 5], bit);
-                        const int x = at + __popcll(m[u] & ((1ull << lane) - 1ull));
-                        if (x < kSmallCache) { s_ckey[x] = kl; s_cpos[x] = base + tid + u * NTH; }
-                    }
-                    at += __popcll(m[u]);
-                }
-            }
+            for (int u = 0; u < 4; ++u)
+                kk[u] = base + tid + u * NTH < n_table ? fold_id(idv[u], rows, magic) : 0xFFFFFFFFu;
+            find([&](int u) { return fj[u]; }, [&](int u) { return q[u]; });
         }
     }
     if (lane == 0 && before) atomicAdd(&s_before, before);
@@ -383,21 +450,23 @@ __device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int3
         return true;
     };
 
-    if (nf == 1 && n_rec <= kSmallCache && n_u <= kSmallRanks) {
-        // ---- occurrences per distinct key; every kept occurrence keeps its key's rank and its place among them ----
+    // ---- occurrences per distinct key; every kept occurrence keeps its key's rank and its place among them ----
+    const bool guessed = nf > 1 || onehot;                 // the bag is looked for first where it is if all hold one
+    if (n_rec <= kSmallCache && n_u <= kSmallRanks) {
         constexpr int PER = kSmallCache / NTH;
-        const int q0 = s_ctx.q0;
-        const int32_t* __restrict__ offs = as_global(a->offsets) + (int64_t)ss->field0 * B;
         int q[PER], ra[PER], g0[PER], g1[PER];             // ra: rank | place << 16
 #pragma unroll
         for (int e = 0; e < PER; ++e) {
             const int i = tid + e * NTH;
             const bool on = i < n_rec;
+            const uint32_t ck = on ? s_ckey[i] : 0u;
             q[e] = on ? s_cpos[i] : 0;
-            const int guess = min(max(q[e] - q0, 0), B - 1);
-            g0[e] = onehot ? offs[guess] : 0;              // the bag it is in if all hold one
-            g1[e] = onehot ? offs[guess + 1] : 0;
-            const int rk = small_rank(s_bits, s_pre, on ? s_ckey[i] : 0u);
+            const int32_t* tf = s_tf + (MANY ? kSliceTfWords * (int)(ck >> kSliceLogMax) : 0);
+            const int guess = min(max(q[e] - (MANY ? tf[0] : s_ctx.q0), 0), B - 1);
+            const int32_t* offs = as_global(a->offsets) + (int64_t)(MANY ? tf[4] >> 1 : ss->field0) * B;
+            g0[e] = guessed ? offs[guess] : 0;             // the bag it is in if all hold one
+            g1[e] = guessed ? offs[guess + 1] : 0;
+            const int rk = small_rank(s_bits, s_pre, ck & kSmallKeyMask);
             ra[e] = rk;
             if (wv * 64 + e * NTH < n_rec) ra[e] |= lds_inc_grouped(s_cnt, (uint32_t)rk, on) << 16;
         }
@@ -420,67 +489,88 @@ __device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int3
 #pragma unroll
             for (int e = 0; e < PER; ++e)
                 if (tid + e * NTH < n_rec) {
-                    int L = g1[e] - g0[e], b = q[e] - q0;
-                    if (!onehot || q[e] < g0[e] || q[e] >= g1[e]) b = small_bag(offs, B, s_offs, !onehot, q[e] - q0, q[e], &L);
+                    const uint32_t ck = s_ckey[tid + e * NTH];
+                    const int32_t* tf = s_tf + (MANY ? kSliceTfWords * (int)(ck >> kSliceLogMax) : 0);
+                    const int first = MANY ? tf[0] : s_ctx.q0;
+                    int L = g1[e] - g0[e], b = min(max(q[e] - first, 0), B - 1);
+                    if (!guessed || q[e] < g0[e] || q[e] >= g1[e])
+                        b = small_bag(as_global(a->offsets) + (int64_t)(MANY ? tf[4] >> 1 : ss->field0) * B, B, s_offs, !guessed, -1, q[e], &L);
                     const int rk = ra[e] & 0xFFFF;
-                    small_place(a, ss, s_tf, pstart, nnz_p, base_u, s_ckey[tid + e * NTH], q[e], rk, s_cnt[rk] + (ra[e] >> 16), b, L);
+                    small_place(a, ss, tf, pstart, nnz_p, base_u, ck & kSmallKeyMask, q[e], rk, s_cnt[rk] + (ra[e] >> 16), b, L);
                 }
         }
     } else {
-        // ---- more occurrences than are kept, or several fields: from the IDs again, kSmallRanks keys a round ----
-        if (wv == 0) finish_wait();
+        // ---- more occurrences than are kept: from the IDs again, in rounds of as many keys as there is room for
+        //      counters (that of the kept occurrences with it: slices of frequent keys have more than kSmallRanks, and a
+        //      second round reads the IDs twice more) ----
+        constexpr int RANKS = kSmallRanks + 2 * kSmallCache;
+        for (int i = kSmallRanks + tid; i < min(RANKS, n_u); i += NTH) s_cnt[i] = 0;
         __syncthreads();
-        bool ok = after_wait();
-        a = forget<LEAN>(a);
-        ss = slice_at(a, slice);
-        auto for_ids = [&](auto&& fn) {                    // fn(field of the table, key in slice, position, on): all lanes make every trip
-            for (int j = 0; j < nf; ++j) {
-                const int j0 = s_tf[kSliceTfWords * j], j1 = s_tf[kSliceTfWords * j + 1];
-                for (int base = j0; base < j1; base += 2 * NTH) {
-                    int64_t v[2];
+        // fn(field of the table, key in slice, position, on, bounds of the bag it is in if all hold one): all lanes make every trip
+        auto for_ids = [&](auto bags, auto&& fn) {
+            constexpr int UN = decltype(bags)::value ? 2 : 4;
+            SmallField at;
+            for (int base = 0; base < n_table; base += UN * NTH) {
+                int64_t v[UN];
+                int fj[UN], q[UN], g0[UN], g1[UN];
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int i = base + tid + u * NTH;
-                        v[u] = i < j1 ? as_global(a->ids)[i] : 0;
+                for (int u = 0; u < UN; ++u) {
+                    const int i = min(base + tid + u * NTH, n_table - 1);
+                    q[u] = MANY ? at.position(s_tf, nf, n_table, i) : s_ctx.q0 + i;
+                    fj[u] = MANY ? at.j : 0;
+                    v[u] = as_global(a->ids)[q[u]];
+                    g0[u] = g1[u] = 0;
+                    if (decltype(bags)::value && guessed) {
+                        const int32_t* tf = s_tf + kSliceTfWords * fj[u];
+                        const int32_t* offs = as_global(a->offsets) + (int64_t)(tf[4] >> 1) * B + min(max(q[u] - tf[0], 0), B - 1);
+                        g0[u] = offs[0]; g1[u] = offs[1];
                     }
+                }
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int i = base + tid + u * NTH;
-                        const uint32_t kk = i < j1 ? fold_id(v[u], ss->rows, ss->magic) : 0xFFFFFFFFu;
-                        const bool on = (kk >> lg) == (uint32_t)ss->idx;
-                        fn(j, on ? kk - lo : 0u, i, on);
-                    }
+                for (int u = 0; u < UN; ++u) {
+                    const uint32_t kk = base + tid + u * NTH < n_table ? fold_id(v[u], ss->rows, ss->magic) : 0xFFFFFFFFu;
+                    const bool on = (kk >> lg) == (uint32_t)ss->idx;
+                    fn(fj[u], on ? kk - lo : 0u, q[u], on, g0[u], g1[u]);
                 }
             }
         };
         int placed = 0;
-        for (int r0 = 0; ok && r0 < n_u; r0 += kSmallRanks) {
-            const int width = min(kSmallRanks, n_u - r0);
-            __syncthreads();
+        bool ok = true;
+        for (int r0 = 0; ok && r0 < n_u; r0 += RANKS) {
+            const int width = min(RANKS, n_u - r0);
             if (r0) {
+                __syncthreads();
                 for (int i = tid; i < width; i += NTH) s_cnt[i] = 0;
                 __syncthreads();
             }
-            for_ids([&](int, uint32_t kl, int, bool on) {
+            for_ids(BoolTag<false>{}, [&](int, uint32_t kl, int, bool on, int, int) {
                 const uint32_t rr = (uint32_t)(small_rank(s_bits, s_pre, kl) - r0);
                 (void)lds_inc_grouped(s_cnt, rr, on && rr < (uint32_t)width);
             });
             __syncthreads();
             const int per = (width + NTH - 1) / NTH;
+            const int s = small_sum(s_cnt, width, per);
+            if (r0 == 0 && wv == 0) finish_wait();
             int tot;
-            const int ex = block_excl_scan<NTH>(small_sum(s_cnt, width, per), &tot);
+            const int ex = block_excl_scan<NTH>(s, &tot);
+            if (r0 == 0) {
+                ok = after_wait();
+                a = forget<LEAN>(a);
+                ss = slice_at(a, slice);
+            }
+            if (!ok) break;
             small_starts(a, ss, s_cnt, s_ctx.pstart, s_base, r0, width, s_ctx.rec_before + placed + ex, per);
             __syncthreads();
-            for_ids([&](int j, uint32_t kl, int i, bool on) {
+            for_ids(BoolTag<true>{}, [&](int j, uint32_t kl, int q, bool on, int g0, int g1) {
                 const int rk = small_rank(s_bits, s_pre, kl);
                 const uint32_t rr = (uint32_t)(rk - r0);
                 on = on && rr < (uint32_t)width;
                 const int pos = lds_inc_grouped(s_cnt, rr, on);
                 if (on) {
                     const int32_t* tf = s_tf + kSliceTfWords * j;
-                    int L;
-                    const int b = small_bag(as_global(a->offsets) + (int64_t)(tf[4] >> 1) * B, B, s_offs, nf == 1 && !onehot, i - tf[0], i, &L);
-                    small_place(a, ss, tf, s_ctx.pstart, s_ctx.nnz_p, s_base, kl, i, rk, pos, b, L);
+                    int L = g1 - g0, b = min(max(q - tf[0], 0), B - 1);
+                    if (!guessed || q < g0 || q >= g1) b = small_bag(as_global(a->offsets) + (int64_t)(tf[4] >> 1) * B, B, s_offs, !guessed, -1, q, &L);
+                    small_place(a, ss, tf, s_ctx.pstart, s_ctx.nnz_p, s_base, kl, q, rk, pos, b, L);
                 }
             });
             placed += tot;

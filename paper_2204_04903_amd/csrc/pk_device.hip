@@ -175,10 +175,9 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
         const int meta_blocks = (int)blocks_for(n_bags, kSliceThreads * 4, 64);
         const size_t dyn = (size_t)std::max(1, plan->max_table_fields) * kSliceTfWords * 4;
         const unsigned fused_blocks = (unsigned)(L.n_slices + meta_blocks + nb);
-        if ((int)fused_blocks <= ds->n_cus)
-            PK_LAUNCH("pk_fused", pk_fused_kernel<4>, dim3(fused_blocks), dim3(kSliceThreads), dyn, sa, pj, L.n_slices, meta_blocks);
-        else
-            PK_LAUNCH("pk_fused", pk_fused_kernel<8>, dim3(fused_blocks), dim3(kSliceThreads), dyn, sa, pj, L.n_slices, meta_blocks);
+        const auto fused = plan->max_table_fields > 1 ? ((int)fused_blocks <= ds->n_cus ? pk_fused_kernel<4, true> : pk_fused_kernel<8, true>)
+                                                      : ((int)fused_blocks <= ds->n_cus ? pk_fused_kernel<4, false> : pk_fused_kernel<8, false>);
+        PK_LAUNCH("pk_fused", fused, dim3(fused_blocks), dim3(kSliceThreads), dyn, sa, pj, L.n_slices, meta_blocks);
         if (!do_pool || fuse_pool) return PK_OK;
     }
 
