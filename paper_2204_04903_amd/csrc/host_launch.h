@@ -303,7 +303,7 @@ void fill_pool_job(const pk_plan* plan, const DeviceState* ds, const std::vector
         q.item_begin = (int32_t)items; q.p = p;
         items += (int64_t)q.n_fields * q.tiles;
     }
-    job->B = B; job->fmeta = ds->fmeta; job->n_items = (int32_t)items;
+    job->B = B; job->n_fields = (int32_t)plan->fields.size(); job->fmeta = ds->fmeta; job->n_items = (int32_t)items;
 }
 
 template <typename WT>

@@ -1,0 +1,50 @@
+"""Pooling of layers of many fields (the sequence fields among them are looked for by groups of neighbours): against
+the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from helpers import small_problem
+from test_gpu_parity import run_dense_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("debug", [0, 2])            # the one-launch forward pass, and the large-batch kernels
+@pytest.mark.parametrize("n_fields,seq", [(64, [63]), (65, []), (65, [64]), (72, [7, 8]), (520, [0, 511, 519]), (600, [503, 504, 512])])
+def test_sequence_fields_among_many(n_fields, seq, debug):
+    rng = np.random.default_rng(9000 + n_fields + len(seq))
+    B, dim = 5, 4
+    tables, fields = [(200, dim, 0), (90, dim, 0)], [(f % 2, f % 2) for f in range(n_fields)]
+    lens = rng.integers(0, 3, size=(n_fields, B))
+    for f in seq:
+        lens[f] = rng.integers(0, 129, size=B)
+        lens[f, 0] += max(0, 64 * B - int(lens[f].sum()))          # 64 a bag at least: the field's bags are pooled cooperatively
+    offsets = np.zeros(lens.size + 1, np.int32)
+    offsets[1:] = np.cumsum(lens.reshape(-1))
+    ids = rng.integers(0, 200, size=int(offsets[-1])).astype(np.int64)
+    step = dict(tables=tables, fields=fields, B=B, ids=ids, offsets=offsets, D_out=dim * n_fields,
+                Wt=[(rng.standard_normal((r, dim)) * 0.1).astype(np.float32) for r, _, _ in tables],
+                grad=rng.standard_normal((B, dim * n_fields)).astype(np.float32))
+    run_dense_case(f"many fields {n_fields} {seq} {debug}", tables, fields, [step], lr=0.01, debug=debug)
+
+
+@pytest.mark.parametrize("debug", [0, 2])
+@pytest.mark.parametrize("place,value", [(8 * 3, 10**9), (8 * 6, -1), (8 * 10, 0), (8 * 70 + 3, 10**9)])
+def test_many_fields_with_rejected_offsets_write_every_output(place, value, debug):
+    from paper_2204_04903_amd.layer import PackedEmbedding
+    tables, fields, B = [(50, 4, 0)], [(0, f % 2) for f in range(80)], 8
+    pr = small_problem(97, B=B, tables=tables, fields=fields, max_len=3, allow_empty=False)
+    bad = pr["offsets"].copy()
+    bad[place] = value
+    layer = PackedEmbedding(tables, fields, debug=debug)
+    try:
+        layer.load_table(0, pr["Wt"][0])
+        out = torch.full((B, layer.out_dim), float("nan"), dtype=torch.float32, device="cuda")
+        layer.forward(torch.from_numpy(pr["ids"]).cuda(), torch.from_numpy(bad).cuda(), B, out=out)
+        torch.cuda.synchronize()
+        assert layer.error_word() & 1
+        assert torch.isfinite(out).all()
+    finally:
+        layer.close()
