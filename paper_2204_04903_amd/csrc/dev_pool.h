@@ -62,6 +62,8 @@ struct KeySrc {
                     v[2 * i] = (uint32_t)id; v[2 * i + 1] = (uint32_t)(id >> 32);
                 }
             }
+        } else if constexpr (R == 1) {
+            v[0] = keys[q];
         } else {                                           // (the workspace has room past the last key)
 #pragma unroll
             for (int i = 0; i < R; i += 4) load_u32<4>(keys + q + i, v + i);
@@ -168,6 +170,9 @@ __device__ __forceinline__ void pool_tile_by(const PoolJob& job, const PoolPack&
     while (cb < last) flush();                             // (only after rejected offsets: every bag is written, whatever they hold)
 }
 
+// Rounds of R positions; of one where the field's runs hold about one (a round's idle places ask for a row again: 26
+// one-hot fields of 2048 bags, one bag a run, pooled in 7.4 us with rounds of eight, 6.0 with rounds of one; for runs of
+// three IDs on average rounds of four are slower than of eight, the longest run then takes two).
 template <bool BF16, bool NARROW, bool HYB, bool IDS, int R>
 __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k, int item, int32_t* s_off)
 {
@@ -176,6 +181,10 @@ __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k,
     const FieldMeta m = as_global(job.fmeta)[f];
     const int32_t* offs = pool_offsets(job, k, IDS, j, f);
     if (job.coop_waves && pool_is_seq(job, k, IDS, j, f)) return;       // (without them only rejected offsets look like a sequence field's)
+    if constexpr (R == 8) {
+        const int64_t per_run = ((int64_t)offs[job.B] - offs[0]) * k.run;      // times B
+        if (2 * per_run <= (int64_t)3 * job.B) return pool_tile_by<BF16, NARROW, HYB, IDS, 1>(job, k, item, j, m, offs, s_off);
+    }
     pool_tile_by<BF16, NARROW, HYB, IDS, R>(job, k, item, j, m, offs, s_off);
 }
 

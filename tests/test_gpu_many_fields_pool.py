@@ -1,5 +1,5 @@
-"""Pooling of layers of many fields (the sequence fields among them are looked for by groups of neighbours): against
-the oracle."""
+"""Pooling of layers of many fields (the sequence fields among them are looked for by groups of neighbours) and of runs
+of one ID: against the oracle."""
 import numpy as np
 import pytest
 
@@ -48,3 +48,19 @@ def test_many_fields_with_rejected_offsets_write_every_output(place, value, debu
         assert torch.isfinite(out).all()
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("dim,dtype", [(3, 0), (20, 1), (64, 0)])
+def test_one_hot_fields_beside_others(dim, dtype):
+    # the large-batch kernels: rounds of one position for fields of about one ID a bag, of eight for the others
+    rng = np.random.default_rng(9500 + dim)
+    tables, fields = [(70, dim, dtype), (90, dim, dtype)], [(0, 0), (1, 1), (0, 1)]
+    for B in (3, 190):
+        pr = small_problem(9500 + B, B=B, tables=tables, fields=fields, max_len=5)
+        lens = np.diff(pr["offsets"]).reshape(3, B)
+        lens[0] = 1
+        lens[2] = rng.permutation(np.arange(B) % 3)                # 0, 1, 2: one on average
+        offsets = np.zeros(3 * B + 1, np.int32)
+        offsets[1:] = np.cumsum(lens.reshape(-1))
+        pr.update(offsets=offsets, ids=rng.integers(0, 70, size=int(offsets[-1])).astype(np.int64))
+        run_dense_case(f"one-hot {dim} {B}", tables, fields, [pr], lr=0.01, debug=2)
