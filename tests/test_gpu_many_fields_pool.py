@@ -1,5 +1,5 @@
-"""Pooling of layers of many fields (the sequence fields among them are looked for by groups of neighbours) and of runs
-of one ID: against the oracle."""
+"""Pooling of layers of many fields (the sequence fields among them are looked for by groups of neighbours), of runs of
+one ID, and beside the dedup chain in calls of few wide rows: against the oracle, or the two stages one after the other."""
 import numpy as np
 import pytest
 
@@ -64,3 +64,22 @@ def test_one_hot_fields_beside_others(dim, dtype):
         offsets[1:] = np.cumsum(lens.reshape(-1))
         pr.update(offsets=offsets, ids=rng.integers(0, 70, size=int(offsets[-1])).astype(np.int64))
         run_dense_case(f"one-hot {dim} {B}", tables, fields, [pr], lr=0.01, debug=2)
+
+
+def test_few_wide_rows_pool_beside_the_dedup_chain():
+    # 540 K IDs of 256 fp32 columns: enough to gather for the pooling to run on a stream of its own
+    from paper_2204_04903_amd.layer import MicroBatchPipeline, PackedEmbedding
+    torch.manual_seed(3)
+    B, L = 540, 1000
+    layer = PackedEmbedding([(500, 256, 0)], [(0, 0)])
+    try:
+        layer.W[0].normal_()
+        ids = torch.randint(0, 500, (B * L,), device="cuda")
+        offsets = torch.arange(0, B * L + 1, L, dtype=torch.int32, device="cuda")
+        out = layer.forward(ids, offsets, B)
+        pipe = MicroBatchPipeline(layer, B, B * L)
+        stages = pipe.pool(pipe.submit(ids, offsets, B), torch.empty_like(out))
+        torch.cuda.synchronize()
+        assert layer.error_word() == 0 and torch.equal(out, stages)
+    finally:
+        layer.close()
