@@ -36,8 +36,6 @@ __device__ __forceinline__ int block_excl_scan(int v, int* total)
 // magic = floor((2^64 - 1) / rows): the upper half of ID * magic is the quotient or up to two below
 // it, so the remainder formed from it is put right by two conditional subtractions (rows <= 2^30:
 // nothing overflows).  A dozen integer operations instead of a 64-bit division.
-__device__ __forceinline__ uint64_t fold_magic(uint32_t rows) { return ~(uint64_t)0 / (uint64_t)rows; }
-
 __device__ __forceinline__ uint32_t fold_id(int64_t id, uint32_t rows, uint64_t magic)
 {
     const uint64_t u = (uint64_t)id;

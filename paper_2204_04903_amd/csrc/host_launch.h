@@ -1,4 +1,4 @@
-// Host side: per-plan device state, profiling brackets, launch helpers and the per-pack template dispatch.
+// Host side: per-plan device state, profiling brackets, launch helpers.
 // Part of pk_device.hip: included there, in this order, inside its anonymous namespace.
 
 // ---------------------------------------------------------------------------
@@ -17,9 +17,7 @@ struct DeviceState {
     int2* slot_info = nullptr;            // per slot (over all packs): its field, the field's table in the table list
     TableField* tfields = nullptr;        // the table field list with what the slice blocks need of a field
     TableMeta* sort_tables = nullptr;
-    int32_t* table_fields = nullptr;
     SlotMeta* slot_meta = nullptr;        // per (pack, slot): what the inverse kernel needs of the slot's table
-    std::mutex mu;
     // Side streams: packs (and the pooling of a pack vs the dedup chain) are independent
     // pieces of memory-bound work; running them side by side hides launch gaps and
     // latency tails (the interleaving of packed operations of Sec. III-C, on one GPU).
@@ -50,7 +48,7 @@ struct MetaImage {
     std::vector<TableField> tfi;
     std::vector<SlotMeta> slm;
     std::vector<int2> sli;
-    size_t o_desc, o_done, o_fm, o_pm, o_slot, o_sli, o_ss[kSmallCuts], o_tfi, o_tab, o_tf, o_slm, total;
+    size_t o_desc, o_done, o_fm, o_pm, o_slot, o_sli, o_ss[kSmallCuts], o_tfi, o_tab, o_slm, total;
     size_t cuts;                 // bytes of the slice lists
 };
 
@@ -106,7 +104,6 @@ void build_meta_image(const pk_plan* plan, MetaImage* mi)
     mi->cuts   = off - mi->o_ss[0];
     mi->o_tfi  = take(mi->tfi.size() * sizeof(TableField));
     mi->o_tab  = take(plan->sort_tables.size() * sizeof(TableMeta));
-    mi->o_tf   = take(plan->table_fields.size() * 4);
     mi->o_slm  = take(F * sizeof(SlotMeta));
     mi->total = off;
 }
@@ -122,7 +119,6 @@ void point_into(DeviceState* ds, char* base, const MetaImage& mi)
     for (int c = 0; c < kSmallCuts; ++c) ds->small_slices[c] = reinterpret_cast<SmallSlice*>(base + mi.o_ss[c]);
     ds->tfields = reinterpret_cast<TableField*>(base + mi.o_tfi);
     ds->sort_tables = reinterpret_cast<TableMeta*>(base + mi.o_tab);
-    ds->table_fields = reinterpret_cast<int32_t*>(base + mi.o_tf);
     ds->slot_meta = reinterpret_cast<SlotMeta*>(base + mi.o_slm);
 }
 
@@ -137,7 +133,6 @@ void for_meta_pieces(const pk_plan* plan, const MetaImage& mi, Fn&& fn)
     for (int c = 0; c < kSmallCuts; ++c) fn(mi.o_ss[c], plan->small_slices[c].data(), plan->small_slices[c].size() * sizeof(SmallSlice));
     fn(mi.o_tfi, mi.tfi.data(), mi.tfi.size() * sizeof(TableField));
     fn(mi.o_tab, plan->sort_tables.data(), plan->sort_tables.size() * sizeof(TableMeta));
-    fn(mi.o_tf, plan->table_fields.data(), plan->table_fields.size() * 4);
     fn(mi.o_slm, mi.slm.data(), mi.slm.size() * sizeof(SlotMeta));
 }
 
@@ -161,7 +156,7 @@ pk_status ensure_device_state(const pk_plan* cplan, DeviceState** out)
     if (e != hipSuccess) { delete ds; return fail(PK_EHIP, hip_msg("hipMalloc(plan metadata)", e)); }
     char* base = static_cast<char*>(ds->blob);
     point_into(ds, base, mi);
-    // one copy for everything (a copy of its own for each of the fifteen pieces made a plan's first pass 70 us
+    // one copy for everything (a copy of its own for each of the pieces made a plan's first pass 70 us
     // longer); the descriptors and their counter start at zero
     std::vector<char> image(mi.total, 0);
     for_meta_pieces(plan, mi, [&](size_t off, const void* src, size_t bytes) {
@@ -235,8 +230,6 @@ unsigned blocks_for(int64_t items, int64_t per_block, int64_t cap)
     if (b > cap) b = cap;
     return (unsigned)b;
 }
-
-int pow2_ceil(int v) { int p = 1; while (p < v) p <<= 1; return p; }
 
 // log2 of the lanes that hold a row, four columns each
 int lane_shift(int D) { int s = 0; while ((4 << s) < D) ++s; return s; }

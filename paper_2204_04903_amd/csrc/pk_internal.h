@@ -18,7 +18,6 @@ constexpr int kLongMin   = 256;    // up to this many: one wavefront per key; ab
 constexpr int kMarkStep  = 256;    // every kMarkStep-th position of the grouped occurrences names its key: how long keys are found
 constexpr int kPiece     = 1024;   // occurrences per piece of a long key (the last piece takes what is left, up to twice that)
 static_assert(kMarkStep <= kLongMin && kPiece > kLongMin, "every piece of a long key holds a marked position");
-constexpr int kRankWords = 3;      // in memory a rank sample follows every 3 bitmap words (96 keys): a lookup is one 16-byte read
 // Occurrences of a call.  Kernels walk positions in 32 bits and in rounds: the longest round (8192 positions: a listed
 // slice's records, a tile's keys touched ahead) must still be counted past the last position.
 constexpr int64_t kNnzMax = ((int64_t)1 << 31) - 8192;
