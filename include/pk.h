@@ -131,6 +131,11 @@ size_t    pk_workspace_bytes(const pk_plan* plan, int32_t B, int64_t nnz);
  * first or last offset of a field that is wrong); see pk_ctx_error.  Such a pack's
  * results are undefined, but no read or write leaves the caller's buffers and
  * all kernels still terminate.
+ * Calls of 2^22 occurrences and more, and large batches that gather 512 MiB of rows and more,
+ * run their pooling on a stream of the library's own that waits for hip_stream
+ * and that hip_stream waits for (events; interleave_groups = 1 or debug bit 0 keep all on
+ * hip_stream).  One host thread at a time enqueues such calls on one plan, and a
+ * caller that captures them in a graph finds both streams in it.
  * Small batches (nnz < 2^19) run as ONE launch whose blocks sum each other's
  * counts through descriptors in device memory that the library owns and that
  * are shared by all calls on a plan: such calls on one plan must follow one
@@ -146,8 +151,9 @@ pk_status pk_forward(const pk_plan* plan, void* const* W,
  * For callers that may not allocate device memory around the call: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  The same
  * kernels as pk_forward, with the workspace, the plan's device metadata and the
- * scan descriptors in a static device array of 32 MiB that the library holds on
- * every GPU it runs on until the process ends; neither this call nor anything it
+ * scan descriptors in a static device array that the library holds on every GPU it
+ * runs on until the process ends (32 MiB, and 2.4 MiB for the one-launch path's
+ * lists of slices, which do not count against the limit below); neither this call nor anything it
  * runs calls hipMalloc, hipFree or another allocating routine (no internal streams
  * or events either: every kernel runs on hip_stream).  Arguments as for pk_forward,
  * without the workspace.  PK_EWORKSPACE when the plan's metadata plus the

@@ -16,7 +16,8 @@
 // A wavefront takes as many consecutive keys as it has lane groups and waits for nobody: no LDS, no barrier.
 // Against tiles of occurrences decoded into LDS with a second launch for long keys (one launch per pack):
 // small layer 22.5 -> 18.4 us a step, mixed dtypes with dimensions that are no multiple of four 514 -> 315
-// (they ran one column per lane), bf16 sequences 725 -> 660.  What bounds it: HBM on one-hot batches (4.8 TB/s),
+// (they ran one column per lane), bf16 sequences 725 -> 660.  What bounds it: with one-hot fields of 8192 bags (26 fields,
+// 27 us) the chain of dependent loads, 2.9 TB/s of the bytes it needs;
 // else the gathered gradient chunks, which the L2s hold only while an XCD's wavefronts stay on neighbouring
 // tables: hence the eighths per XCD below, for long keys too, and no more than kLongBlocks blocks of those.
 // 80 registers, six wavefronts per SIMD: with 64 the compiler spills and everything is a quarter slower.
@@ -45,7 +46,9 @@ struct GradView {
     int D;
 };
 
-// 1 / L in double without a division: the hardware's fp32 reciprocal and two Newton steps (to the last ulp).
+// 1 / L in double without a division: the hardware's fp32 reciprocal (1 ulp, and L's own rounding above 2^24: 2^-22.4
+// together) and two Newton steps.  Correctly rounded, as the division: the second step's error is 2^-89 of the result, and
+// 1 / L for L below 2^31 is 2^-84 or more away from the middle between two doubles (unless L is a power of two: exact).
 __device__ __forceinline__ double recip_len(uint32_t L)
 {
     const double d = (double)max(L, 1u);

@@ -17,7 +17,7 @@
 //                   launch (dev_small.h);
 //   large batches   the occurrences are partitioned by slice first: the keys kernel counts them
 //                   per slice (block-local counts in LDS, one global add per touched slice), a
-//                   one-block scan turns the counts into places, a scatter kernel writes a
+//                   scan turns the counts into places, a scatter kernel writes a
 //                   (key in slice, bag) record per occurrence to its slice's place, and the slice
 //                   kernel reads its records; the inverse index is then looked up per occurrence
 //                   from the bitmap and rank samples the slice kernel leaves in memory.

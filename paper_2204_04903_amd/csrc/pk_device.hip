@@ -10,10 +10,10 @@
 //             slice of a table's key range and finds its occurrences in the IDs), blocks that write
 //             the packed bag offsets, and pooling blocks (H3-H5, keys formed from the IDs)
 //   large batches:
-//   clear     per-pack state, slice totals and look-back descriptors of this call
+//   setup     per-pack state, slice totals; field scan and every table's cut for this batch
 //   keys      H1: key = base_row + (uint64)id mod rows in packed order, packed bag offsets,
 //             occurrences per slice
-//   pool      H3-H5: per pack, gather rows by key, pool per bag, write concatenated
+//   pool      H3-H5: gather rows by key, pool per bag, write concatenated (all packs in one launch)
 //   scan      H2: places of the slices' records
 //   scatter   H2: one (key in slice, bag) record per occurrence, grouped by slice
 //   slices    H2: per slice, in LDS: mark (bitmap, number of distinct keys), a scan, then place: distinct
@@ -42,14 +42,14 @@ constexpr size_t kStaticCutBytes = kSmallCuts * ((size_t)kSmallSlicesMax * sizeo
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticCutBytes];
 
 // One translation unit; the kernels and their launch helpers are kept in section files:
-//   dev_common.h   block scans, folding hash, look-back prefix sums, tile order
+//   dev_common.h   block scans, folding hash, combined LDS counters, tile order
 //   dev_dedup.h    keys, slice scan, scatter, slices, inverse (H1, H2), large batches
 //   dev_small.h    H1 and H2 of small batches
 //   dev_rows.h     row access, plain or hybrid row addressing
 //   dev_pool.h     pooling (H3-H5) and the one launch of the forward pass for small batches
 //   dev_adagrad.h  gradient reduction + Adagrad (H6, H7)
 //   dev_hybrid.h   HybridHash bookkeeping kernels
-//   host_launch.h  device state of a plan, profiling brackets, launchers, template dispatch
+//   host_launch.h  device state of a plan, profiling brackets, launchers
 // and this file holds the entry points of the C ABI.
 namespace {
 
