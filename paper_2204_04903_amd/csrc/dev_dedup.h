@@ -19,7 +19,7 @@
 //                   per slice (block-local counts in LDS, one global add per touched slice), a
 //                   scan turns the counts into places, a scatter kernel writes a
 //                   (key in slice, bag) record per occurrence to its slice's place, and the slice
-//                   kernel reads its records; the inverse index is then looked up per occurrence
+//                   kernel reads its records (one launch for all slices); the inverse index is then looked up per occurrence
 //                   from the bitmap and rank samples the slice kernel leaves in memory.
 
 // ---------------------------------------------------------------------------
@@ -263,10 +263,6 @@ pk_keys_kernel(const int64_t* __restrict__ ids, const int32_t* __restrict__ offs
     }
 }
 
-constexpr int kBigSlicesMax = 256;         // listed slices with many records
-constexpr int kBigSliceFlag = 1 << 30;     // in SliceInfo::table: the slice is listed
-constexpr int kBigSliceCount = 6144;       // records from which a slice is listed
-
 // Large batches: the slices' totals become places.  A block takes 1024 slices; what lies before them
 // it adds up itself (there are some thousand slices: a block reads a few values per thread).  Every slice
 // gets its table, its index in the table, the place of its first record and the number of records; the
@@ -275,8 +271,7 @@ constexpr int kScanThreads = 1024;
 __global__ void __launch_bounds__(kScanThreads)
 pk_slice_scan_kernel(const TableCut* __restrict__ cut, int T,
                      const int32_t* __restrict__ slice_total, int32_t* __restrict__ slice_cursor,
-                     SliceInfo* __restrict__ slice_info, int n_slices, int big_count, int32_t* n_big,
-                     int32_t* __restrict__ big_list)
+                     SliceInfo* __restrict__ slice_info, int n_slices)
 {
     extern __shared__ int32_t s_first[];                   // [T+1]
     table_cut_load<kScanThreads>(cut, T, s_first, nullptr);
@@ -294,15 +289,6 @@ pk_slice_scan_kernel(const TableCut* __restrict__ cut, int T,
         SliceInfo si;
         si.table = t; si.idx = s - s_first[t]; si.start = carry + ex; si.count = c;
         if (s >= s_first[T]) { si.table = -1; si.idx = 0; si.count = 0; }      // room for slices this batch does not have
-        // A slice that holds a hot key has many times the records of the others: such slices are listed,
-        // and blocks of four times the threads take them, in launches that run beside the others'.
-        if (c > big_count && si.table >= 0) {
-            const int at = atomicAdd(n_big, 1);
-            if (at < kBigSlicesMax) {
-                big_list[at] = s;
-                si.table |= kBigSliceFlag;
-            }
-        }
         slice_info[s] = si;
         slice_cursor[s] = carry + ex;
     }
@@ -432,8 +418,8 @@ struct SliceArgs {
     const FieldMeta* fmeta;
     int32_t* packed_offsets;
     uint32_t* keys; int32_t* inverse;                           // written here for small batches only
-    uint32_t* bitmap; int32_t* slice_nu;                        // large batches only: bitmaps with rank samples, distinct keys per slice
-    const int32_t* big_list; const int32_t* n_big;              // ... and the listed slices with many records
+    uint32_t* bitmap;                                           // large batches only: bitmaps with rank samples
+    uint32_t* slice_nu; uint64_t* nu_group; int n_groups, sum_stride;   // ... distinct keys per slice, and their sums (SliceSums)
     uint32_t* unique; int32_t* seg_all; uint32_t* ent_all; int ent_mult;
     int32_t* marks; double* ghot; int32_t* ticket; int dmax;
     uint64_t* desc; uint64_t* gdesc; int32_t* done; int n_slices;   // small batches: descriptors the library owns, cleaned by the last block
@@ -448,74 +434,174 @@ struct SliceArgs {
 #define PK_PT(a, blk, k) do { } while (0)
 #endif
 
-// LDS words of a slice block: bitmap words | their popcount prefix | counters of a round of distinct keys
-constexpr int slice_lds_words(int log_max, int ranks) { return 2 * (1 << (log_max - 5)) + ranks; }
+// The kernel's arguments, and what the host or an earlier launch has written, through pointers that the compiler loses
+// track of between the phases of a block: held from the start, all that a slice block needs is forty scalar registers
+// more than there are.
+typedef const __attribute__((address_space(4))) SliceArgs* SliceArgsPtr;
+template <bool LEAN, typename P>
+__device__ __forceinline__ P forget(P p)
+{
+    if (LEAN) asm volatile("" : "+s"(p));
+    return p;
+}
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* as_constant(const T* p) { return (const __attribute__((address_space(4))) T*)p; }
+
+// ---------------------------------------------------------------------------
+// Large batches, one launch for all slices: a block owns a slice.  It reads the slice's records once, keeps them in
+// registers (kSliceKeep per thread), and
+//   marks the bitmap -> popcount prefix of its words, number of distinct keys, which is published;
+//   counts the occurrences per key (a record's rank and place go into a register) -> the keys' first places;
+//   places every record's entry: that needs the records before the slice only, and their number is known;
+//   adds up the distinct keys of the pack's slices before its own (SliceSums), published long ago by then;
+//   writes what needs that sum: distinct keys, segment offsets, marks, the bitmap with its rank samples.
+// A slice of more records (a frequent key's) reads them again for each of these passes.
+// What bounds it is the chain of these steps, 13 us a block, so four blocks of 512 threads share a CU.  (Five launches,
+// mark, scan, place, and mark and place for the slices with many records in blocks of four times the threads, wrote the
+// bitmaps, read them back and read the records three times.  Launches of the step's dedup together, us, before and
+// after: 200 fields of 21 M IDs 290 -> 185 without pooling beside; 26 one-hot fields of 65536 65 -> 29; 1 M IDs of
+// unequal tables 71 -> 37.)  256 threads: 20 % slower, more for slices of frequent keys; 1024: the same alone, but they
+// find no room beside the pooling (200 fields, forward alone 235 -> 265).
+// ---------------------------------------------------------------------------
 constexpr int kSliceTfWords = 5;           // dynamic LDS words per field of a table
+constexpr int kFineThreads = 512, kFineRanks = 4096;
+constexpr int kSliceThreads = 1024, kSliceRanks = 8192;
+constexpr int kSliceKeep = 8;              // records per thread kept in registers
+
+// LDS words of a slice block: bitmap words with their popcount prefix | counters of a round of distinct keys
+constexpr int slice_lds_words(int log_max, int ranks) { return 2 * (1 << (log_max - 5)) + ranks; }
 
 // one occurrence of a slice: key minus the slice's first key, the place of its gradient chunk, the chunk's scale
 struct SliceRec { uint32_t kl, ref, L; };
 
-// MODE: what the block does with its slice of a large batch
-//   kSliceMark   first half: which keys occur -> the slice's bitmap and its number of distinct keys
-//   kSlicePlace  second half (after a scan of those numbers): everything else
-// (With thousands of slices in flight a look-back makes every block wait for the slowest slice before it;
-// two launches with a scan between them let every block run without waiting.)
-enum { kSliceMark = 1, kSlicePlace = 2 };
+// Distinct keys before a slice.  Every slice publishes its number and adds it to its group of kSumFan slices; the first
+// slice of a group adds up the groups before and publishes that; the others take what was published for the group
+// before theirs (long there, usually), that group, and the slices of their own before them.  (Every block looking at all
+// groups itself: a thousand blocks then poll the same few lines, and a round trip takes 20 us instead of 3.)  Groups are counted from the pack's first slice, so a pack's sums never mix
+// with another's.  The words carry their own validity (a flag, or how many have been added): relaxed accesses do,
+// and nothing is returned to the publishing block.  A block waits for blocks before it only.
+constexpr int kSumFan = 64;
+constexpr uint32_t kNuReady = 0x80000000u;
+struct SliceSums {
+    uint32_t* nu; uint64_t* group; uint64_t* prefix;     // per slice; per group: count << 32 | sum; kSumFan << 32 | sum before it
+    int i, stride;                                       // the slice, counted from the pack's first; words between groups
+    __device__ __forceinline__ SliceSums(SliceArgsPtr a, int slice, int pack_first, int p)
+    {
+        i = slice - pack_first;
+        nu = as_global(a->slice_nu) + pack_first;
+        stride = a->sum_stride;
+        group = as_global(a->nu_group) + (size_t)(pack_first / kSumFan + p) * stride;
+        prefix = group + (size_t)a->n_groups * stride;
+    }
+    __device__ __forceinline__ void publish(int n_u) const                     // one thread
+    {
+        __hip_atomic_store(nu + i, kNuReady | (uint32_t)n_u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        (void)__hip_atomic_fetch_add(group + i / kSumFan * stride, (uint64_t)1 << 32 | (uint32_t)n_u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // One wavefront, all lanes.  `ask` sends the loads out, `before` waits for them, and for the numbers themselves: the
+    // distinct keys of the pack's slices before this one; -1 after waiting too long.
+    struct Seen { uint32_t n; uint64_t g; };
+    __device__ __forceinline__ Seen ask() const
+    {
+        // lanes 0 .. : the slices of the group before this one; the last two: the group before, and what is before that
+        const int lane = threadIdx.x & 63, g = i / kSumFan, in = i % kSumFan;
+        Seen s{kNuReady, (uint64_t)kSumFan << 32};
+        if (lane < in) s.n = __hip_atomic_load(nu + (i - in) + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (in != 0 && lane >= kSumFan - 2 && g > kSumFan - 1 - lane)
+            s.g = __hip_atomic_load((lane == kSumFan - 2 ? prefix : group) + (g - 1) * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return s;
+    }
+    __device__ __forceinline__ int before(Seen s) const
+    {
+        const int lane = threadIdx.x & 63, g = i / kSumFan;
+        for (int spin = 0; spin < kSpinLimit; ++spin) {
+            bool ok = (s.n & kNuReady) && (s.g >> 32) == kSumFan;
+            int sum = (int)((s.n & ~kNuReady) + (uint32_t)s.g);
+            if (i % kSumFan == 0)
+                for (int k = lane; k < g; k += 64) {
+                    const uint64_t z = __hip_atomic_load(group + k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    ok = ok && (z >> 32) == kSumFan;
+                    sum += (int)(uint32_t)z;
+                }
+            if (!__all(ok)) {
+                __builtin_amdgcn_s_sleep(8);
+                s = ask();
+                continue;
+            }
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+            if (i % kSumFan == 0 && lane == 0)
+                __hip_atomic_store(prefix + g * stride, (uint64_t)kSumFan << 32 | (uint32_t)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return sum;
+        }
+        return -1;
+    }
+};
 
-template <int MODE, int NTH, int LOGMAX, int RANKS, bool BIG = false>
-__device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_t* s_main, int32_t* s_tf)
+template <int N> struct InFlight { static constexpr int value = N; };
+
+// KEPT: the slice's records fit the threads' registers
+template <int NTH, int LOGMAX, int RANKS, bool KEPT>
+__device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s_main, int32_t* s_tf, int32_t* s_base)
 {
-    constexpr bool GROUPED = BIG || NTH > 256;             // lanes that share a key combine their counter updates
-    constexpr int WMAX = 1 << (LOGMAX - 5);
-    constexpr int KEEP = NTH > 256 ? 0 : 12;               // records per thread whose rank and place stay in a register
+    constexpr int WMAX = 1 << (LOGMAX - 5), WPT = WMAX / NTH;       // bitmap words, of them per thread
+    constexpr int KEEP = kSliceKeep;
+    static_assert(WPT == 4 && KEEP * NTH <= 0xFFFF && KEEP * NTH <= RANKS, "a thread's words are two 16-byte reads; ranks and places of kept records fit 16 bits");
     const int tid = threadIdx.x;
-    uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_main);
-    uint32_t* s_pre = s_bits + WMAX;
+    uint2* s_bp = reinterpret_cast<uint2*>(s_main);        // a word of the bitmap, set bits before it
     int32_t* s_cnt = s_main + 2 * WMAX;
-    const int B = a.B;
-    const int64_t out_dim = a.out_dim;
 
-    // ---- which slice, of which table; where the pack's arrays start ----
-    const SliceInfo si = a.slice_info[slice];
-    if (si.table < 0) return;                              // room for a slice this batch does not have
-    if (BIG != ((si.table & kBigSliceFlag) != 0)) return;  // listed slices belong to the launch that takes the list
-    const int t = si.table & ~kBigSliceFlag, idx = si.idx, rec_start = si.start, n_rec = si.count;
-    const TableMeta tm = a.tmeta[t];
-    const int p = tm.pack, nf = tm.field_end - tm.field_begin;
-    const uint32_t key_lo = tm.key_lo, rows = tm.rows;
-    const TableCut tc = a.cut[t];
-    const int lg = tc.log_keys;
-    const PackMeta k = a.pm[p];
-    const int pstart = a.st[p].start, nnz_p = a.st[p].nnz, pack_first = a.st[p].first_slice;
-    const bool is_last = t == k.first_stable + k.n_stables - 1 && idx + 1 == tc.n;     // last slice of the pack's last table
-    if (a.st[p].error) return;                             // offsets of this pack were rejected
-    if (MODE == kSlicePlace)
+    // ---- which slice, of which table; its records ----
+    const auto* si = as_constant(a->slice_info) + slice;
+    const int t = si->table, rec_start = si->start, n_rec = si->count;
+    const uint2* __restrict__ rec = as_global(a->rec) + rec_start;
+    // (loads without a condition: under one, the compiler waits for each before the next; places without a record ask
+    // for the last one again)
+    auto load_record = [&](int base, int i) {              // record base + i, base the same for the block: a 32-bit offset from a scalar address
+        const char* at = reinterpret_cast<const char*>(rec + base);
+        return *reinterpret_cast<const uint2*>(at + (uint32_t)min(i, max(n_rec - 1 - base, 0)) * (uint32_t)sizeof(uint2));
+    };
+    uint2 kept[KEEP];
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u) kept[u] = KEPT ? load_record(0, tid + u * NTH) : make_uint2(0, 0);
+    const auto* tm = as_constant(a->tmeta) + t;
+    const int p = tm->pack;
+    const PackState* st = as_global(a->st) + p;
+    const int pstart = st->start, nnz_p = st->nnz;
+    if (st->error & 1) return;                             // offsets of this pack were rejected (so all its slices return here)
+    const int lg = as_constant(a->cut)[t].log_keys;
+    const bool wide = as_constant(a->pm)[p].has_mean != 0; // the pack's entries carry the bag length
+    const int nf = tm->field_end - tm->field_begin;
+    if (wide)
         for (int j = tid; j < nf; j += NTH) {
-            const TableField tf = a.tfields[tm.field_begin + j];
+            const TableField tf = as_global(a->tfields)[tm->field_begin + j];
             s_tf[kSliceTfWords * j] = tf.slot;
             s_tf[kSliceTfWords * j + 3] = tf.col;
         }
-    const uint32_t lo = (uint32_t)idx << lg;               // first key of the slice inside its table
-    const uint32_t nkeys = min((uint32_t)1 << lg, rows - lo);
+    const uint32_t nkeys = min((uint32_t)1 << lg, tm->rows - ((uint32_t)si->idx << lg));
     const int words = 1 << (lg - 5);
+    const bool mine = tid * WPT < words;                   // thread i owns words [i * WPT, (i + 1) * WPT)
+    if (mine) {
+#pragma unroll
+        for (int j = 0; j < WPT; ++j) s_bp[tid * WPT + j] = make_uint2(0, 0);
+    }
+    for (int i = tid; i < min(RANKS, n_rec); i += NTH) s_cnt[i] = 0;
+    __syncthreads();
 
-    // all records of the slice: fn(SliceRec, on).  Every lane makes the same trips and calls fn every time, with
-    // on = false where it has none, so that fn may combine lanes.
-    const uint2* __restrict__ rec = a.rec + rec_start;
     auto unpack = [&](uint2 r, bool valid, bool* on) {
         const uint32_t kl = r.x & ((1u << LOGMAX) - 1u);
         *on = valid && kl < nkeys;
         return SliceRec{*on ? kl : 0u, r.y, r.x >> LOGMAX};
     };
-    auto for_records = [&](auto&& fn) {
-        constexpr int UN = BIG ? 8 : 4;                    // records per thread in flight: a listed slice is long
+    // all records, where they are not kept: fn(SliceRec, on).  Every lane makes the same trips and calls fn every time, with
+    // on = false where it has none, so that fn may combine lanes.
+    auto for_records = [&](auto in_flight, auto&& fn) {    // (a record's first word alone, where fn uses no more)
+        constexpr int UN = decltype(in_flight)::value;     // records per thread in flight
+#pragma nounroll
         for (int base = 0; base < n_rec; base += UN * NTH) {
             uint2 r[UN];
 #pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int i = base + tid + u * NTH;
-                r[u] = i < n_rec ? rec[i] : make_uint2(0, 0);
-            }
+            for (int u = 0; u < UN; ++u) r[u] = load_record(base, tid + u * NTH);
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 bool on;
@@ -526,99 +612,71 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
     };
 
     // ---- which keys occur ----
-    // The slice's bitmap in memory: word w of the table's bitmap stands at w + w / 3 of the table's
-    // region, so that every 16 bytes hold three words and, in the fourth, the rank of their first key.
-    uint32_t* bmw = a.bitmap + tm.word_base;
-    const uint32_t tw0 = (uint32_t)idx * (uint32_t)words;
-    if (MODE == kSliceMark) {
-        for (int w = tid; w < words; w += NTH) s_bits[w] = 0;
-        __syncthreads();
-        for_records([&](const SliceRec& r, bool on) {
-            if (on) {
-                const uint32_t bit = 1u << (r.kl & 31);
-                if (!(s_bits[r.kl >> 5] & bit)) atomicOr(&s_bits[r.kl >> 5], bit);
-            }
-        });
-        __syncthreads();
-        int c = 0;
-        for (int w = tid; w < words; w += NTH) {
-            const uint32_t x = s_bits[w];
-            bmw[tw0 + w + (tw0 + w) / 3u] = x;             // the bitmap and the count go to memory; the rest follows the scan
-            c += __popc(x);
+    auto mark = [&](const SliceRec& r, bool on) {
+        if (on) {
+            const uint32_t bit = 1u << (r.kl & 31);
+            if (!(s_bp[r.kl >> 5].x & bit)) atomicOr(&s_bp[r.kl >> 5].x, bit);
         }
-        int n_u;
-        (void)block_excl_scan<NTH>(c, &n_u);
-        if (tid == 0) a.slice_nu[slice] = n_u;
-        return;
+    };
+    if constexpr (KEPT) {
+#pragma unroll
+        for (int u = 0; u < KEEP; ++u) {
+            if (u * NTH >= n_rec) break;
+            bool on;
+            const SliceRec x = unpack(kept[u], tid + u * NTH < n_rec, &on);
+            mark(x, on);
+        }
+    } else {
+        for_records(InFlight<16>{}, mark);
     }
-    for (int w = tid; w < words; w += NTH) s_bits[w] = bmw[tw0 + w + (tw0 + w) / 3u];
-    for (int i = tid; i < RANKS; i += NTH) s_cnt[i] = 0;
-    const int base_u = a.slice_nu[slice] - a.slice_nu[pack_first];     // scanned: distinct keys of the pack's slices before
-    const int rec_before = rec_start - pstart;
     __syncthreads();
-    // popcount prefix of the words: thread i owns words [i * wpt, (i + 1) * wpt)
-    const int wpt = max(1, words / NTH);
-    int c = 0;
-    if (tid * wpt < words)
-        for (int j = 0; j < wpt; ++j) c += __popc(s_bits[tid * wpt + j]);
+    // popcount prefix of the words, number of distinct keys
     int n_u;
-    const int ex = block_excl_scan<NTH>(c, &n_u);
-    // whatever the sums hold, no write below leaves the pack's arrays
-    if (base_u < 0 || rec_before < 0 || (int64_t)base_u + n_u > (int64_t)nnz_p || (int64_t)rec_before + n_rec > (int64_t)nnz_p) {
-        if (tid == 0) atomicOr(&a.st[p].error, 2);
-        return;
-    }
-    uint32_t* __restrict__ uq = a.unique + pstart;
-    int32_t* __restrict__ seg = a.seg_all + pstart + p;
-    if (tid * wpt < words) {                               // prefix, and the slice's distinct keys (ascending) in their place
-        int run = ex;
-        for (int j = 0; j < wpt; ++j) {
-            const int w = tid * wpt + j;
-            s_pre[w] = (uint32_t)run;
-            uint32_t x = s_bits[w];
-            const uint32_t key0 = key_lo + lo + (uint32_t)w * 32u;
-            while (x) {
-                const int bit = __ffs(x) - 1;
-                x &= x - 1;
-                uq[base_u + run++] = key0 + bit;
+    {
+        uint32_t x[WPT];
+        int c = 0;
+#pragma unroll
+        for (int j = 0; j < WPT; ++j) {
+            x[j] = mine ? s_bp[tid * WPT + j].x : 0u;
+            c += __popc(x[j]);
+        }
+        int run = block_excl_scan<NTH>(c, &n_u);
+        if (tid == 0) SliceSums(a, slice, st->first_slice, p).publish(n_u);
+        if (mine) {
+#pragma unroll
+            for (int j = 0; j < WPT; ++j) {
+                s_bp[tid * WPT + j].y = (uint32_t)run;
+                run += __popc(x[j]);
             }
         }
     }
-    if (is_last && tid == 0) {
-        a.st[p].n_unique = base_u + n_u;
-        seg[base_u + n_u] = nnz_p;
-    }
     __syncthreads();
-    for (uint32_t u = (tw0 + 2u) / 3u + tid; 3u * u < tw0 + (uint32_t)words; u += NTH)     // rank samples beside the bitmap, for the inverse kernel
-        bmw[4u * u + 3u] = (uint32_t)(base_u + (int)s_pre[3u * u - tw0]);
-    if (n_u == 0) return;
 
-    // ---- occurrences per distinct key, segment offsets, marks for the backward pass, and every
-    //      occurrence's gradient place at its key's next free position; a round handles RANKS keys ----
-    const int dim = k.dim;
-    const bool wide = k.has_mean != 0;                     // the pack's entries carry the bag length
-    uint32_t* __restrict__ ent = a.ent_all + (size_t)pstart * a.ent_mult;
-    int32_t* __restrict__ marks = a.marks + (pstart / kMarkStep + p);
-    const int32_t* __restrict__ po = a.packed_offsets + (int64_t)k.first_slot * B + p;
+    // ---- occurrences per distinct key, and every occurrence's gradient place at its key's next free position ----
+    const int rec_before = rec_start - pstart;
+    a = forget<true>(a);
+    uint32_t* __restrict__ ent = as_global(a->ent_all) + (size_t)pstart * a->ent_mult;
     auto rank_of = [&](uint32_t kl) {
-        return (int)(s_pre[kl >> 5] + __popc(s_bits[kl >> 5] & ((1u << (kl & 31)) - 1u)));
+        const uint2 w = s_bp[kl >> 5];
+        return (int)(w.y + __popc(w.x & ((1u << (kl & 31)) - 1u)));
     };
     auto put = [&](const SliceRec& r, int pos) {
         if ((unsigned)pos >= (unsigned)nnz_p) return;
         if (!wide) { ent[pos] = r.ref; return; }
         uint32_t len = r.L;
         if (len == 0) {                                    // a bag too long for the record's bits: its length from the bag
-            const uint32_t b = r.ref / (uint32_t)out_dim, col = r.ref - b * (uint32_t)out_dim;
+            const uint32_t out_dim = (uint32_t)a->out_dim;
+            const uint32_t b = r.ref / out_dim, col = r.ref - b * out_dim;
             int j = 0;
             while (j + 1 < nf && (uint32_t)s_tf[kSliceTfWords * j + 3] != col) ++j;
-            const uint32_t g = (uint32_t)s_tf[kSliceTfWords * j] * (uint32_t)B + b;
+            const uint32_t g = (uint32_t)s_tf[kSliceTfWords * j] * (uint32_t)a->B + b;
+            const int32_t* po = as_global(a->packed_offsets) + (int64_t)as_constant(a->pm)[p].first_slot * a->B + p;
             len = (uint32_t)max(po[g + 1] - po[g], 1);
         }
         reinterpret_cast<uint2*>(ent)[pos] = make_uint2(r.ref, len);
     };
-    // counters of keys [r0, r0 + width) become the keys' first places; segment offsets and marks go out
-    int placed = 0;                                        // occurrences of the keys of earlier rounds
-    auto starts = [&](int r0, int width) {
+    // the counters of `width` keys become the keys' first places, after `placed` occurrences of the slice
+    auto starts = [&](int width, int placed) {
         const int per = (width + NTH - 1) / NTH;           // consecutive counters per thread
         int sum = 0;
         for (int j = 0; j < per; ++j) {
@@ -626,145 +684,207 @@ __device__ __forceinline__ void slice_body(const SliceArgs& a, int slice, int32_
             sum += i < width ? s_cnt[i] : 0;
         }
         int tot;
-        const int ex_occ = block_excl_scan<NTH>(sum, &tot);
-        int s0 = rec_before + placed + ex_occ;
+        int s0 = block_excl_scan<NTH>(sum, &tot) + rec_before + placed;
         for (int j = 0; j < per; ++j) {
             const int i = tid * per + j;
             if (i < width) {
                 const int len = s_cnt[i];
-                const int u = base_u + r0 + i;
-                seg[u] = s0;
                 s_cnt[i] = s0;
-                // every kMarkStep-th position names its key: how the backward pass finds the long ones
-                for (int m = (s0 + kMarkStep - 1) / kMarkStep; (int64_t)m * kMarkStep < (int64_t)s0 + len; ++m) marks[m] = u;
-                if (len >= 2 * kPiece) {                   // the key is reduced in pieces: its partial sums start at zero
-                    const size_t slot = (size_t)(pstart / kPiece + p) + (size_t)(s0 / kPiece);    // (no two such keys share one)
-                    double* gh = a.ghot + slot * a.dmax;
-                    for (int d = 0; d < dim; ++d) gh[d] = 0.0;
-                    a.ticket[slot] = 0;
-                }
                 s0 += len;
             }
         }
-        placed += tot;
+        __syncthreads();
+        return tot;
     };
-    if (KEEP && n_rec <= KEEP * NTH && n_u <= RANKS) {
+    // what the backward pass needs of key u with the places [s0, s1): its segment, the marks by which a long one is
+    // found, and, where it is reduced in pieces, partial sums that start at zero
+    auto segments = [&](int first, int width, int end) {
+        a = forget<true>(a);
+        int32_t* __restrict__ seg = as_global(a->seg_all) + pstart + p;
+        int32_t* __restrict__ marks = as_global(a->marks) + (pstart / kMarkStep + p);
+        for (int i = tid; i < width; i += NTH) {
+            const int u = first + i, s0 = s_cnt[i], s1 = i + 1 < width ? s_cnt[i + 1] : end;
+            seg[u] = s0;
+            for (int m = (s0 + kMarkStep - 1) / kMarkStep; (int64_t)m * kMarkStep < (int64_t)s1; ++m) marks[m] = u;
+            if (s1 - s0 >= 2 * kPiece) {
+                const size_t slot = (size_t)(pstart / kPiece + p) + (size_t)(s0 / kPiece);    // (no two such keys share one)
+                double* gh = as_global(a->ghot) + slot * a->dmax;
+                const int dim = as_constant(a->pm)[p].dim;
+                for (int d = 0; d < dim; ++d) gh[d] = 0.0;
+                as_global(a->ticket)[slot] = 0;
+            }
+        }
+    };
+    // the sum before this slice; false (for the whole block) where it cannot be had, or where what it and the records'
+    // place say would leave the pack's arrays
+    auto ask = [&]() { return tid < 64 ? SliceSums(a, slice, st->first_slice, p).ask() : SliceSums::Seen{0, 0}; };
+    auto get_base = [&](SliceSums::Seen seen) {
+        if (tid < 64) {
+            const int b = SliceSums(a, slice, st->first_slice, p).before(seen);
+            if (tid == 0) *s_base = b;
+        }
+        __syncthreads();
+        const int base = *s_base;
+        if (base >= 0 && rec_before >= 0 && (int64_t)base + n_u <= (int64_t)nnz_p && (int64_t)rec_before + n_rec <= (int64_t)nnz_p) return true;
+        if (tid == 0) atomicOr(&as_global(a->st)[p].error, 2);
+        return false;
+    };
+    if constexpr (KEPT) {
         // The counting pass gives every record its key's rank and its place among the key's occurrences: both fit a
         // register, and the placing pass needs no counter.
-        uint32_t rp[KEEP ? KEEP : 1];
+        uint32_t rp[KEEP];
 #pragma unroll
-        for (int u0 = 0; u0 < KEEP; u0 += 4) {
-            if (u0 * NTH >= n_rec) break;
-            uint2 r[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = tid + (u0 + u) * NTH;
-                r[u] = i < n_rec ? rec[i] : make_uint2(0, 0);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                bool on;
-                const SliceRec x = unpack(r[u], tid + (u0 + u) * NTH < n_rec, &on);
-                const uint32_t rk = (uint32_t)rank_of(x.kl);
-                rp[u0 + u] = on ? rk | ((uint32_t)atomicAdd(&s_cnt[rk], 1) << 16) : 0xFFFFFFFFu;
-            }
+        for (int u = 0; u < KEEP; ++u) {
+            if (u * NTH >= n_rec) break;
+            bool on;
+            const SliceRec r = unpack(kept[u], tid + u * NTH < n_rec, &on);
+            const uint32_t rk = (uint32_t)rank_of(r.kl);
+            rp[u] = on ? rk | ((uint32_t)atomicAdd(&s_cnt[rk], 1) << 16) : 0xFFFFFFFFu;
         }
         __syncthreads();
-        starts(0, n_u);
-        __syncthreads();
+        const int tot = starts(n_u, 0);
+        const SliceSums::Seen seen = ask();                // (on its way while the records are placed)
 #pragma unroll
-        for (int u0 = 0; u0 < KEEP; u0 += 4) {
-            if (u0 * NTH >= n_rec) break;
-            uint2 r[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = tid + (u0 + u) * NTH;
-                r[u] = i < n_rec ? rec[i] : make_uint2(0, 0);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                bool on;
-                const SliceRec x = unpack(r[u], tid + (u0 + u) * NTH < n_rec, &on);
-                if (on) put(x, s_cnt[rp[u0 + u] & 0xFFFFu] + (int)(rp[u0 + u] >> 16));
-            }
+        for (int u = 0; u < KEEP; ++u) {
+            if (u * NTH >= n_rec) break;
+            bool on;
+            const SliceRec r = unpack(kept[u], tid + u * NTH < n_rec, &on);
+            if (on) put(r, s_cnt[rp[u] & 0xFFFFu] + (int)(rp[u] >> 16));
         }
-        return;
+        if (!get_base(seen)) return;
+        segments(*s_base, n_u, rec_before + tot);
+    } else {
+        // Most of a slice with many records is one frequent key's: the one that most of the first 64 records have is
+        // counted and placed by ballots, a whole wavefront's at once; the others have one LDS atomic each.  (Lanes that
+        // share a key combined for any key, 64 records are a chain of 1100 cycles: 52 K records 100 us.)
+        if (tid < 64) {
+            const uint32_t kl = load_record(0, tid).x & ((1u << LOGMAX) - 1u);
+            int best = 0;
+            uint32_t hot = 0;
+            for (int l = 0; l < 64; l += 8) {
+                const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)kl, l);
+                const int n = __popcll(__ballot(kl == v));
+                if (n > best) { best = n; hot = v; }
+            }
+            if (tid == 0) *s_base = (int)hot;
+        }
+        __syncthreads();
+        const uint32_t hot = (uint32_t)*s_base;
+        const int hot_rank = rank_of(hot);
+        __syncthreads();
+        const int lane = tid & 63;
+        const uint64_t below = (1ull << lane) - 1ull;
+        if (!get_base(ask())) return;
+        const int base_u = *s_base;
+        int placed = 0;                                    // occurrences of the keys of earlier rounds
+        for (int r0 = 0; r0 < n_u; r0 += RANKS) {          // a round handles RANKS keys
+            const int width = min(RANKS, n_u - r0);
+            const bool hot_now = (unsigned)(hot_rank - r0) < (unsigned)width;
+            if (r0) {
+                __syncthreads();
+                for (int i = tid; i < width; i += NTH) s_cnt[i] = 0;
+                __syncthreads();
+            }
+            int n_hot = 0;
+            for_records(InFlight<16>{}, [&](const SliceRec& r, bool on) {
+                const bool is_hot = on && r.kl == hot;
+                n_hot += __popcll(__ballot(is_hot));
+                const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
+                if (on && !is_hot && rr < (uint32_t)width) atomicAdd(&s_cnt[rr], 1);
+            });
+            if (hot_now && lane == 0 && n_hot) atomicAdd(&s_cnt[hot_rank - r0], n_hot);
+            __syncthreads();
+            const int tot = starts(width, placed);
+            placed += tot;
+            segments(base_u + r0, width, rec_before + placed);
+            __syncthreads();                               // (the placing pass moves the places on)
+            // every wavefront takes room for all its records of the frequent key at once
+            int at_hot = 0;
+            if (hot_now && lane == 0) at_hot = atomicAdd(&s_cnt[hot_rank - r0], n_hot);
+            at_hot = __builtin_amdgcn_readfirstlane(at_hot);
+            for_records(InFlight<8>{}, [&](const SliceRec& r, bool on) {
+                const bool is_hot = on && r.kl == hot;
+                const uint64_t m = __ballot(is_hot);
+                const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
+                if (is_hot) {
+                    if (hot_now) put(r, at_hot + __popcll(m & below));
+                } else if (on && rr < (uint32_t)width) {
+                    put(r, atomicAdd(&s_cnt[rr], 1));
+                }
+                at_hot += __popcll(m);
+            });
+        }
     }
-    for (int r0 = 0; r0 < n_u; r0 += RANKS) {
-        const int width = min(RANKS, n_u - r0);
-        if (r0) {
-            __syncthreads();
-            for (int i = tid; i < width; i += NTH) s_cnt[i] = 0;
-            __syncthreads();
+
+    // ---- the slice's distinct keys (ascending) ----
+    a = forget<true>(a);
+    si = as_constant(a->slice_info) + slice;
+    tm = as_constant(a->tmeta) + t;
+    const int base_u = *s_base, idx = si->idx;
+    uint32_t* __restrict__ uq = as_global(a->unique) + pstart + base_u;
+    if (mine) {
+        const uint32_t key0 = tm->key_lo + ((uint32_t)idx << lg) + (uint32_t)(tid * WPT) * 32u;
+#pragma nounroll
+        for (int j = 0; j < WPT; ++j) {
+            const uint2 w = s_bp[tid * WPT + j];
+            uint32_t y = w.x;
+            int run = (int)w.y;
+            while (y) {
+                const int bit = __ffs(y) - 1;
+                y &= y - 1;
+                uq[run++] = key0 + 32u * (uint32_t)j + bit;
+            }
         }
-        for_records([&](const SliceRec& r, bool on) {
-            const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
-            if (GROUPED) (void)lds_inc_grouped(s_cnt, rr, on && rr < (uint32_t)width);
-            else if (on && rr < (uint32_t)width) atomicAdd(&s_cnt[rr], 1);
-        });
-        __syncthreads();
-        starts(r0, width);
-        __syncthreads();
-        for_records([&](const SliceRec& r, bool on) {
-            const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
-            on = on && rr < (uint32_t)width;
-            int pos = 0;
-            if (GROUPED) pos = lds_inc_grouped(s_cnt, rr, on);
-            else if (on) pos = atomicAdd(&s_cnt[rr], 1);
-            if (on) put(r, pos);
-        });
+    }
+    if (tid == 0) {
+        const auto* k = as_constant(a->pm) + p;
+        if (t == k->first_stable + k->n_stables - 1 && idx + 1 == as_constant(a->cut)[t].n) {     // last slice of the pack's last table
+            as_global(a->st)[p].n_unique = base_u + n_u;
+            as_global(a->seg_all)[pstart + p + base_u + n_u] = nnz_p;
+        }
+    }
+    // ---- the bitmap for the inverse kernel: every 16 bytes hold three words and the rank of their first key.  Sixteen
+    //      bytes without a key are not asked for, unless the slice shares them with a neighbour ----
+    uint32_t* bmw = as_global(a->bitmap) + tm->word_base;
+    const uint32_t tw0 = (uint32_t)idx * (uint32_t)words, tw1 = tw0 + (uint32_t)words;
+    const uint32_t q0 = (tw0 + 2u) / 3u, q1 = tw1 / 3u;    // the 16 bytes that are the slice's alone
+    for (uint32_t q = q0 + tid; q < q1; q += NTH) {
+        const uint2* w = s_bp + (3u * q - tw0);
+        if (w[0].x | w[1].x | w[2].x) reinterpret_cast<uint4*>(bmw)[q] = make_uint4(w[0].x, w[1].x, w[2].x, (uint32_t)base_u + w[0].y);
+    }
+    if (tid < 4) {
+        const uint32_t w = tid < 2 ? tw0 + tid : 3u * q1 + (tid - 2);          // words before q0's and from q1's on
+        if (tid < 2 ? w < min(3u * q0, tw1) : w < tw1 && w >= 3u * q0) {
+            bmw[w + w / 3u] = s_bp[w - tw0].x;
+            if (w % 3u == 0) bmw[4u * (w / 3u) + 3u] = (uint32_t)base_u + s_bp[w - tw0].y;
+        }
     }
 }
 
-// Large batches: one block per slice, in two launches with a scan between them.
-constexpr int kFineThreads = 256, kFineRanks = 2048;
-constexpr int kSliceThreads = 1024, kSliceRanks = 8192;
+template <int NTH, int LOGMAX, int RANKS>
+__device__ __forceinline__ void slice_block(SliceArgsPtr a, int32_t* s_tf)
+{
+    __shared__ __align__(16) int32_t s_main[slice_lds_words(LOGMAX, RANKS)];
+    __shared__ int32_t s_base;
+    const auto* si = as_constant(a->slice_info) + blockIdx.x;
+    if (si->table < 0) return;                             // room for a slice this batch does not have
+    if (si->count <= kSliceKeep * NTH) slice_body<NTH, LOGMAX, RANKS, true>(a, blockIdx.x, s_main, s_tf, &s_base);
+    else slice_body<NTH, LOGMAX, RANKS, false>(a, blockIdx.x, s_main, s_tf, &s_base);
+}
 
-template <int MODE>
 __global__ void __launch_bounds__(kFineThreads, 8)
 pk_slices_kernel(SliceArgs a)
 {
     extern __shared__ int32_t s_dyn[];
-    __shared__ int32_t s_main[slice_lds_words(kSliceLogFine, kFineRanks)];
-    slice_body<MODE, kFineThreads, kSliceLogFine, kFineRanks>(a, blockIdx.x, s_main, s_dyn);
+    slice_block<kFineThreads, kSliceLogFine, kFineRanks>((SliceArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), s_dyn);
 }
 
-// ... the listed slices with many records: four times the threads, same cut
-template <int MODE>
-__global__ void __launch_bounds__(kSliceThreads)
-pk_slices_big_kernel(SliceArgs a)
-{
-    extern __shared__ int32_t s_dyn[];
-    __shared__ int32_t s_main[slice_lds_words(kSliceLogFine, kSliceRanks)];
-    if ((int)blockIdx.x >= min(*a.n_big, kBigSlicesMax)) return;
-    slice_body<MODE, kSliceThreads, kSliceLogFine, kSliceRanks, true>(a, a.big_list[blockIdx.x], s_main, s_dyn);
-}
-
-// ... and the shape for calls with a table too long for slices of 32 K keys
-template <int MODE>
-__global__ void __launch_bounds__(kSliceThreads)
+// ... the shape for calls with a table too long for slices of 64 K keys
+__global__ void __launch_bounds__(kSliceThreads, 8)
 pk_slices_wide_kernel(SliceArgs a)
 {
     extern __shared__ int32_t s_dyn[];
-    __shared__ int32_t s_main[slice_lds_words(kSliceLogMax, kSliceRanks)];
-    slice_body<MODE, kSliceThreads, kSliceLogMax, kSliceRanks>(a, blockIdx.x, s_main, s_dyn);
-}
-
-// Large batches: the slices' numbers of distinct keys become running sums, in place (exclusive, over all
-// packs; a slice takes the difference to its pack's first slice).  Blocks as in the scan of the records.
-__global__ void __launch_bounds__(kScanThreads)
-pk_unique_scan_kernel(int32_t* __restrict__ slice_nu, int n_slices, int32_t* __restrict__ sums)
-{
-    const int base = blockIdx.x * kScanThreads;
-    int before = 0;
-    for (int i = threadIdx.x; i < base; i += kScanThreads) before += slice_nu[i];
-    int carry;
-    (void)block_excl_scan<kScanThreads>(before, &carry);
-    const int s = base + (int)threadIdx.x;
-    const int c = s < n_slices ? slice_nu[s] : 0;
-    int tot;
-    const int ex = block_excl_scan<kScanThreads>(c, &tot);
-    if (s < n_slices) sums[s] = carry + ex;
+    slice_block<kSliceThreads, kSliceLogMax, kSliceRanks>((SliceArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), s_dyn);
 }
 
 // Small batches: the blocks beside the slice blocks that write what is per bag and per pack:

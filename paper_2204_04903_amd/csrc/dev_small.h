@@ -33,14 +33,7 @@ __device__ __forceinline__ uint64_t small_load(const uint64_t* p) { return __hip
 // through pointers that the compiler loses track of between the phases: held from the start they are forty scalar
 // registers more than there are, and with the spills of those the 26-field launch is 5 us slower.  A block that has
 // its CU to itself has the registers and would only wait for the reads.
-typedef const __attribute__((address_space(4))) SliceArgs* SliceArgsPtr;
 typedef const __attribute__((address_space(4))) SmallSlice* SmallSlicePtr;
-template <bool LEAN>
-__device__ __forceinline__ SliceArgsPtr forget(SliceArgsPtr p)
-{
-    if (LEAN) asm volatile("" : "+s"(p));
-    return p;
-}
 __device__ __forceinline__ SmallSlicePtr slice_at(SliceArgsPtr a, int slice) { return (SmallSlicePtr)a->small_slices + slice; }
 
 // what the phases of a block hand on, in LDS

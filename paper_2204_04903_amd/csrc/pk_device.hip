@@ -16,8 +16,8 @@
 //   pool      H3-H5: gather rows by key, pool per bag, write concatenated (all packs in one launch)
 //   scan      H2: places of the slices' records
 //   scatter   H2: one (key in slice, bag) record per occurrence, grouped by slice
-//   slices    H2: per slice, in LDS: mark (bitmap, number of distinct keys), a scan, then place: distinct
-//             keys (ascending), occurrences grouped by key, segment offsets, marks for the backward pass
+//   slices    H2: per slice, in LDS: bitmap, occurrences per key, occurrences grouped by key; with the distinct keys
+//             of the slices before it: distinct keys (ascending), segment offsets, marks for the backward pass
 //   inverse   H2: inverse[q] = rank(key[q]) from the bitmap and rank samples of the slices
 //   adagrad   H6+H7: per distinct key: reduce gradients, update row in place (all packs in one launch)
 #include <hip/hip_runtime.h>
@@ -249,11 +249,10 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     if (do_dedup && !L.small) {
         int32_t* slice_total = ws.at<int32_t>(L.slice_total);
         int32_t* slice_cursor = ws.at<int32_t>(L.slice_cursor);
-        int32_t* big_list = ws.at<int32_t>(L.big_list);
         PK_LAUNCH("pk_slice_scan", pk_slice_scan_kernel, dim3(blocks_for(L.n_slices, kScanThreads, 1 << 20)),
                   dim3(kScanThreads), (size_t)(T + 1) * 4,
                   ws.at<TableCut>(L.tgeom), T, slice_total, slice_cursor, ws.at<SliceInfo>(L.slice_info),
-                  L.n_slices, L.log_max == kSliceLogFine ? kBigSliceCount : 0x7FFFFFFF, big_list + kBigSlicesMax, big_list);
+                  L.n_slices);
         const size_t tile_lds = ((size_t)bt + 1 + (size_t)L.max_table_slices) * 4;
         const dim3 tile_grid(blocks_for(n_tiles, 1, 256 * 8));
         PK_LAUNCH("pk_scatter", pk_scatter_kernel, tile_grid, dim3(NT), tile_lds, offsets, B, F, bt, nnz, sa.log_max, ds->fmeta,
@@ -261,27 +260,11 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
                   ws.at<int32_t>(L.fscan), L.tile_hist_stride ? ws.at<int32_t>(L.tile_hist) : nullptr, L.tile_hist_stride);
         const size_t tf_lds = (size_t)std::max(1, plan->max_table_fields) * kSliceTfWords * 4;
         if (L.n_slices > 0) {
-            SliceArgs sm = sa, sp = sa;
-            sm.slice_nu = ws.at<int32_t>(L.slice_nu);       // the mark launch writes the counts ...
-            sp.slice_nu = ws.at<int32_t>(L.slice_usum);     // ... the place launch reads their running sums
-            sm.big_list = sp.big_list = big_list;
-            sm.n_big = sp.n_big = big_list + kBigSlicesMax;
+            sa.slice_nu = ws.at<uint32_t>(L.slice_nu);
+            sa.nu_group = ws.at<uint64_t>(L.nu_group); sa.n_groups = L.n_groups; sa.sum_stride = L.sum_stride;
             const dim3 sgrid((unsigned)L.n_slices);
-            const bool fine = L.log_max == kSliceLogFine;
-            if (fine) {
-                PK_LAUNCH("pk_slices_mark_big", pk_slices_big_kernel<kSliceMark>, dim3(kBigSlicesMax), dim3(kSliceThreads), tf_lds, sm);
-                PK_LAUNCH("pk_slices_mark", pk_slices_kernel<kSliceMark>, sgrid, dim3(kFineThreads), tf_lds, sm);
-            } else {
-                PK_LAUNCH("pk_slices_mark", pk_slices_wide_kernel<kSliceMark>, sgrid, dim3(kSliceThreads), tf_lds, sm);
-            }
-            PK_LAUNCH("pk_unique_scan", pk_unique_scan_kernel, dim3(blocks_for(L.n_slices, kScanThreads, 1 << 20)),
-                      dim3(kScanThreads), 0, sm.slice_nu, L.n_slices, sp.slice_nu);
-            if (fine) {
-                PK_LAUNCH("pk_slices_place_big", pk_slices_big_kernel<kSlicePlace>, dim3(kBigSlicesMax), dim3(kSliceThreads), tf_lds, sp);
-                PK_LAUNCH("pk_slices_place", pk_slices_kernel<kSlicePlace>, sgrid, dim3(kFineThreads), tf_lds, sp);
-            } else {
-                PK_LAUNCH("pk_slices_place", pk_slices_wide_kernel<kSlicePlace>, sgrid, dim3(kSliceThreads), tf_lds, sp);
-            }
+            if (L.log_max == kSliceLogFine) PK_LAUNCH("pk_slices", pk_slices_kernel, sgrid, dim3(kFineThreads), tf_lds, sa);
+            else PK_LAUNCH("pk_slices", pk_slices_wide_kernel, sgrid, dim3(kSliceThreads), tf_lds, sa);
         }
         const size_t inv_lds = (field_scan_words(F) + 4 * (size_t)F) * 4;
         // (every block stages the field scan and the slots' metadata: with many fields fewer blocks take more tiles each)

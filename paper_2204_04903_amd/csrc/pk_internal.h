@@ -27,13 +27,14 @@ constexpr size_t kAlign = 256;
 // the slice's bitmap, its popcount prefix and the occurrence counters of its distinct keys in LDS.
 // Two shapes of slice block: 1024 threads for slices of up to 128 K keys (small batches, where a
 // block scans its table's IDs itself, and large batches with tables too long for the other shape),
-// and 256 threads for slices of up to 32 K keys (large batches: many small blocks hide the latency
+// and 512 threads for slices of up to 64 K keys (large batches: several blocks per compute unit hide the latency
 // of the few dependent memory accesses a slice makes).
 constexpr int kSliceLogMin = 10;           // 1 K keys
 constexpr int kSliceLogMax = 17;           // 128 K keys: 4096 bitmap words
-constexpr int kSliceLogFine = 15;          // 32 K keys: 1024 bitmap words
+constexpr int kSliceLogFine = 16;          // 64 K keys: 2048 bitmap words
 constexpr int kSliceWordsMax = 1 << (kSliceLogMax - 5);
-constexpr int kSliceOccLarge = 2048;       // occurrences per slice aimed at when the occurrences are partitioned
+constexpr int kSliceOccLarge = 3072;       // occurrences per slice aimed at when the occurrences are partitioned (slices have up to twice that: mostly what a block keeps in registers; 2048: bf16 sequences 597 us a step, 571)
+constexpr int32_t kSumStride = 16;         // 64-bit words of a cache line: the sums of the slices' distinct keys stand this far apart
 constexpr int64_t kTilesMin = 1024;         // tiles that a launch of the keys and scatter kernels should have at least
 // Counts per (tile, slice) kept from the keys to the scatter kernel: room for one per occurrence and kCountRoomMin
 // more (a launch cut to kTilesMin tiles has up to twice as many, each with nnz / kSliceOccLarge + 1 slices), no more
@@ -42,7 +43,7 @@ constexpr int64_t kCountRoomMin = 2 * kTilesMin, kCountRoomMax = (int64_t)8 << 2
 constexpr int64_t kSmallNnz = 1 << 19;     // below this many occurrences the forward pass is one launch
 constexpr int kSmallSlicesMax = 4096;      // ... if it has no more slices than this (descriptors the library owns)
 constexpr int kTableSlicesMax = 8192;      // slices per table (their counters are staged in LDS): rows <= 2^30
-constexpr int64_t kFineRowsMax = (int64_t)4096 << kSliceLogFine;   // longest table the 32 K-key shape is used with
+constexpr int64_t kFineRowsMax = (int64_t)4096 << kSliceLogFine;   // longest table the 64 K-key shape is used with
 
 #if defined(__HIPCC__)
 #define PK_HD __host__ __device__
@@ -208,9 +209,11 @@ struct Pack {
 // Byte offsets of the workspace's arrays for one (plan, B, nnz).
 struct Layout {
     size_t state, packed_offsets, keys, inverse, seg_ent, marks, unique, seg, ghot, ticket,
-           clear_begin, slice_total, slice_nu, big_list, slice_cursor, slice_usum, slice_info, tgeom, fscan, tile_hist, rec, bitmap, total;
+           clear_begin, slice_total, slice_nu, nu_group, slice_cursor, slice_info, tgeom, fscan, tile_hist, rec, bitmap, total;
     size_t clear_bytes;          // what the partitioned path clears before its first kernel: per-pack state,
                                  // slice totals and distinct-key counts, contiguous from `clear_begin`
+    int32_t n_groups;            // groups of 64 slices, with room for a started one per pack
+    int32_t sum_stride;          // 64-bit words from one group's sum to the next
     int32_t n_slices;            // slices of all tables for this call
     int32_t max_table_slices;    // most slices any table has
     int32_t log_max;             // partitioned path: largest slice (log2 of its keys) of this call

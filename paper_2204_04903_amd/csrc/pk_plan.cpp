@@ -44,7 +44,7 @@ static void count_slices(const pk_plan* plan, int64_t nnz, int32_t log_max, int6
     *total = std::min<int64_t>(each, coarse + nnz / kSliceOccLarge + (int64_t)plan->sort_tables.size());
 }
 
-Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz, size_t room)
+static Layout layout_with(const pk_plan* plan, int32_t B, int64_t nnz, size_t room, int32_t sum_stride)
 {
     const size_t F = plan->fields.size(), P = plan->packs.size();
     const size_t n = (size_t)std::max<int64_t>(nnz, 1);
@@ -68,10 +68,11 @@ Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz, size_t room)
     L.state          = take(P * sizeof(PackState));
     L.slice_total    = take(L.small ? 0 : (size_t)slices * 4);
     L.slice_nu       = take(L.small ? 0 : (size_t)slices * 4);
-    L.big_list       = take(L.small ? 0 : (size_t)(256 + 64) * 4);          // listed slices, then their count
+    L.n_groups       = (int32_t)(slices / 64 + (int64_t)P + 1);
+    L.sum_stride     = sum_stride;
+    L.nu_group       = take(L.small ? 0 : (size_t)L.n_groups * sum_stride * 16);       // sums of 64 slices' distinct keys, and what is before each
     L.clear_bytes    = off - L.clear_begin;
     L.slice_cursor   = take(L.small ? 0 : (size_t)slices * 4);
-    L.slice_usum     = take(L.small ? 0 : (size_t)slices * 4);
     L.slice_info     = take(L.small ? 0 : (size_t)slices * sizeof(SliceInfo));
     L.tgeom          = take(L.small ? 0 : plan->sort_tables.size() * sizeof(TableCut));
     L.fscan          = take(L.small ? 0 : (3 * F + 3) * 4);          // the field scan of the batch, with its verdict
@@ -110,6 +111,14 @@ Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz, size_t room)
     L.tile_hist      = off;
     L.total          = std::min(align_up(off + (size_t)count_room * 4), std::max(off, room));
     return L;
+}
+
+// Each of the slices' sums has a cache line of its own (polls and adds of a thousand blocks on shared lines make a round
+// trip 20 us instead of 3), except where the scratch ends.
+Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz, size_t room)
+{
+    const Layout L = layout_with(plan, B, nnz, room, kSumStride);
+    return L.total <= room ? L : layout_with(plan, B, nnz, room, 1);
 }
 
 }  // namespace pk
