@@ -236,19 +236,20 @@ pk_keys_kernel(const int64_t* __restrict__ ids, const int32_t* __restrict__ offs
         for (int t = tid; t < tl.nb; t += NT)
             packed_offsets[(int64_t)k.first_slot * B + m.pack + (int64_t)m.slot * B + tl.b0 + t] = s_po[t] + dl - pbase;
         const int q_lo = s_po[0], q_hi = s_po[tl.nb];
-        for (int base = q_lo; base < q_hi; base += 4 * NT) {       // the same trips for every lane: lanes combine their counts
-            int64_t idv[4];
+        constexpr int UK = 8;                              // IDs per thread in flight
+        for (int base = q_lo; base < q_hi; base += UK * NT) {      // the same trips for every lane: lanes combine their counts
+            const int64_t* id_at = ids + base;
+            uint32_t* key_at = keys + (base + dl);
+            const int left = q_hi - base;
+            int64_t idv[UK];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {                  // the loads of four rounds in flight together
-                const int i = base + tid + j * NT;
-                idv[j] = i < q_hi ? ids[i] : 0;
-            }
+            for (int j = 0; j < UK; ++j) idv[j] = id_at[min(tid + j * NT, left - 1)];      // (no condition: nothing is waited for in between)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = base + tid + j * NT;
-                const bool on = i < q_hi;
-                const uint32_t kk = on ? fold_id(idv[j], m.rows, m.magic) : 0u;
-                if (on) keys[i + dl] = m.base_row + kk;
+            for (int j = 0; j < UK; ++j) {
+                const int i = tid + j * NT;
+                const bool on = i < left;
+                const uint32_t kk = fold_id(idv[j], m.rows, m.magic);
+                if (on) key_at[i] = m.base_row + kk;
                 if (g.n <= kFewCounters) (void)lds_inc_few<false>(s_hist, kk >> g.log_keys, on, g.n);
                 else if (on) atomicAdd(&s_hist[kk >> g.log_keys], 1);
             }
@@ -297,7 +298,10 @@ pk_slice_scan_kernel(const TableCut* __restrict__ cut, int T,
 // Large batches: one record per occurrence, (key inside its slice, place of its bag's gradient chunk), written to
 // the slice's place.  A tile counts its occurrences per slice in LDS, reserves room in every
 // touched slice with one global add, and then places its records from block-local cursors: one LDS word per slice
-// of the tile's table, first its count, then its cursor (a table has up to kTableSlicesMax).
+// of the tile's table, first its count, then its cursor (a table has up to kTableSlicesMax).  Bound by the latency of
+// the keys and by its 8-byte stores, so a wavefront's keys are asked for eight at a time without a condition: under
+// one, each was waited for before the next (200 fields beside the pooling 361 -> 155 us, 26 one-hot fields of 65536
+// 23 -> 17, bf16 sequences 120 -> 68; touching the tile's keys ahead then gives nothing more).
 __global__ void __launch_bounds__(NT)
 pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int64_t nnz, int log_max,
                   const FieldMeta* __restrict__ fmeta, const TableCut* __restrict__ cut,
@@ -329,23 +333,14 @@ pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int
         for (int s = tid; s < g.n; s += NT) s_hist[s] = tile_hist ? tile_hist[tile * tile_hist_stride + s] : 0;
         __syncthreads();
         const int q_lo = s_po[0], q_hi = s_po[tl.nb];
-        if (tile_hist) {
-            // one word of every 128 bytes of the tile's keys, so that the placing pass finds them in the cache
-            uint32_t pf = 0;
-            for (int i = q_lo + tid * 32; i < q_hi; i += NT * 32) pf ^= keys[i + dl];
-            asm volatile("" ::"v"(pf));
-        }
         if (!tile_hist)                                    // (the keys kernel's counts of this tile were not kept)
         for (int base = q_lo; base < q_hi; base += 4 * NT) {      // four loads in flight
             uint32_t kv[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = base + tid + u * NT;
-                kv[u] = i < q_hi ? keys[i + dl] - m.base_row : 0xFFFFFFFFu;
-            }
+            for (int u = 0; u < 4; ++u) kv[u] = keys[min(base + tid + u * NT, q_hi - 1) + dl];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const uint32_t s = kv[u] >> g.log_keys;
+                const uint32_t s = base + tid + u * NT < q_hi ? (kv[u] - m.base_row) >> g.log_keys : 0xFFFFFFFFu;
                 if (g.n <= kFewCounters) (void)lds_inc_few<false>(s_hist, s, s < (uint32_t)g.n, g.n);
                 else if (s < (uint32_t)g.n) atomicAdd(&s_hist[s], 1);
             }
@@ -360,32 +355,36 @@ pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int
         // Every wavefront takes a contiguous quarter of the tile's positions, 64 at a time, so that a lane's
         // positions rise by 64 from one to the next: where bags are not short, the bag of a position is found
         // by stepping on from the bag of the lane's previous one (one search at the start).
-        const int lane = tid & 63;
+        const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int per_wave = ((q_hi - q_lo + NT - 1) / NT) * 64;
-        const int w_lo = q_lo + (tid >> 6) * per_wave, w_hi = min(w_lo + per_wave, q_hi);
+        const int w_lo = q_lo + wv * per_wave, w_hi = min(w_lo + per_wave, q_hi);
         const bool stepped = (int64_t)tl.nb * 64 <= (int64_t)6 * (q_hi - q_lo);     // (short bags: a search per position is shorter)
         int t = stepped && w_lo + lane < w_hi ? upper_bound_i32(s_po, tl.nb + 1, w_lo + lane) - 1 : 0;
         constexpr int UP = 8;                              // key loads in flight (they come from memory: nothing has read them since they were written)
         for (int base = w_lo; base < w_hi; base += UP * 64) {
+            const uint32_t* key_at = keys + (base + dl);
+            const int left = w_hi - base;
             uint32_t kv[UP];
 #pragma unroll
+            for (int u = 0; u < UP; ++u) kv[u] = key_at[min(u * 64 + lane, left - 1)];     // (no condition, and no arithmetic before the last is asked for)
+            uint32_t sl[UP];
+            int at[UP];
+#pragma unroll
             for (int u = 0; u < UP; ++u) {
-                const int i = base + u * 64 + lane;
-                kv[u] = i < w_hi ? keys[i + dl] - m.base_row : 0xFFFFFFFFu;
+                kv[u] -= m.base_row;
+                sl[u] = u * 64 + lane < left ? kv[u] >> g.log_keys : 0xFFFFFFFFu;
+                at[u] = 0;
+                if (g.n <= kFewCounters) at[u] = lds_inc_few<true>(s_hist, sl[u], sl[u] < (uint32_t)g.n, g.n);   // (all lanes of the wavefront are here)
+                else if (sl[u] < (uint32_t)g.n) at[u] = atomicAdd(&s_hist[sl[u]], 1);
             }
 #pragma unroll
             for (int u = 0; u < UP; ++u) {
                 const int i = base + u * 64 + lane;
-                const uint32_t kk = kv[u];
-                const uint32_t s = kk >> g.log_keys;
-                const bool valid = i < w_hi && s < (uint32_t)g.n;
+                const bool valid = sl[u] < (uint32_t)g.n;
                 if (i < w_hi) {
                     if (stepped) { while (t + 1 < tl.nb && s_po[t + 1] <= i) ++t; }
                     else if (valid) t = upper_bound_i32(s_po, tl.nb + 1, i) - 1;
                 }
-                int at = 0;
-                if (g.n <= kFewCounters) at = lds_inc_few<true>(s_hist, s, valid, g.n);   // (all lanes of the wavefront are here)
-                else if (valid) at = atomicAdd(&s_hist[s], 1);
                 if (!valid) continue;
                 // the record: key inside the slice, the gradient's scale (bag length for mean pooling, 1 for sum;
                 // 0 = too long for its bits, to be looked up) above it, and the place of the bag's gradient chunk
@@ -394,9 +393,9 @@ pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int
                     const uint32_t L = (uint32_t)max(s_po[t + 1] - s_po[t], 1);
                     len = (L >> (32 - log_max)) ? 0u : L;
                 }
-                if ((uint64_t)(int64_t)at < (uint64_t)nnz)
-                    rec[at] = make_uint2((kk - (s << g.log_keys)) | (len << log_max),
-                                         (uint32_t)((int64_t)(tl.b0 + t) * out_dim + m.col));
+                if ((uint64_t)(int64_t)at[u] < (uint64_t)nnz)
+                    rec[at[u]] = make_uint2((kv[u] - (sl[u] << g.log_keys)) | (len << log_max),
+                                            (uint32_t)((int64_t)(tl.b0 + t) * out_dim + m.col));
             }
         }
     }
@@ -953,31 +952,28 @@ pk_inverse_kernel(int F, const int32_t* __restrict__ fscan, const SlotMeta* __re
     const int n = s_slotpos[F];
     const int n_tiles = (n + KT - 1) / KT;
     for (XcdTiles it(n_tiles); it.valid(); it.next()) {
-        uint32_t key[KT / NT];
-#pragma unroll
-        for (int k = 0; k < KT / NT; ++k) {
-            const int q = it.tile * KT + k * NT + (int)threadIdx.x;
-            key[k] = q < n ? keys[q] : 0;
-        }
-        // the lookups of the tile's positions are all asked for before any is used
-        int j = -1;
+        // (every load without a condition, so that nothing is waited for in between)
+        const int q0 = it.tile * KT, left = n - q0;
+        const uint32_t* key_at = keys + q0;
         uint32_t kk[KT / NT];
-        uint4 x[KT / NT];
+#pragma unroll
+        for (int k = 0; k < KT / NT; ++k) kk[k] = key_at[min(k * NT + (int)threadIdx.x, left - 1)];
+        int j = -1;
+        uint32_t at[KT / NT];
         bool ok[KT / NT];
 #pragma unroll
         for (int k = 0; k < KT / NT; ++k) {
-            const int q = it.tile * KT + k * NT + (int)threadIdx.x;
-            ok[k] = q < n;
-            kk[k] = 0;
-            x[k] = make_uint4(0, 0, 0, 0);
-            if (ok[k]) {
-                if (j < 0 || q >= s_slotpos[j + 1]) j = upper_bound_i32(s_slotpos, F + 1, q) - 1;   // the slot of this position
-                kk[k] = key[k] - s_klo[j];
-                // no lookup for a pack with rejected offsets, nor for a key that is none of its table (only possible then)
-                ok[k] = s_pack[j] == 0 && kk[k] < s_rows[j];
-                if (ok[k]) x[k] = bitmap4[(size_t)s_wb[j] / 4 + (kk[k] >> 5) / 3u];
-            }
+            const int q = min(q0 + k * NT + (int)threadIdx.x, n - 1);
+            if (j < 0 || q >= s_slotpos[j + 1]) j = upper_bound_i32(s_slotpos, F + 1, q) - 1;   // the slot of this position
+            kk[k] -= s_klo[j];
+            // no lookup for a pack with rejected offsets, nor for a key that is none of its table (only possible then)
+            ok[k] = k * NT + (int)threadIdx.x < left && s_pack[j] == 0 && kk[k] < s_rows[j];
+            at[k] = s_wb[j] / 4 + (ok[k] ? (kk[k] >> 5) / 3u : 0u);
         }
+        // the lookups of the tile's positions are all asked for before any is used
+        uint4 x[KT / NT];
+#pragma unroll
+        for (int k = 0; k < KT / NT; ++k) x[k] = bitmap4[at[k]];
 #pragma unroll
         for (int k = 0; k < KT / NT; ++k) {
             const int q = it.tile * KT + k * NT + (int)threadIdx.x;
