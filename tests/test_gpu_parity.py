@@ -395,7 +395,7 @@ def test_config5_shrunk_long_sequences_bf16():
 
 @pytest.mark.timeout(600)
 def test_tables_above_the_fine_slice_limit():
-    """Two tables of 140 M rows: the large-batch dedup then cuts slices of 2^17 keys (the wide slice kernels)."""
+    """Two tables of 140 M rows: thousands of slices per table in the large-batch dedup."""
     free, _ = torch.cuda.mem_get_info()
     if free < 90 * 2**30:
         pytest.skip("needs 90 GiB of free device memory")
