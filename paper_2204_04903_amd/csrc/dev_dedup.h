@@ -237,6 +237,7 @@ pk_keys_kernel(const int64_t* __restrict__ ids, const int32_t* __restrict__ offs
             packed_offsets[(int64_t)k.first_slot * B + m.pack + (int64_t)m.slot * B + tl.b0 + t] = s_po[t] + dl - pbase;
         const int q_lo = s_po[0], q_hi = s_po[tl.nb];
         constexpr int UK = 8;                              // IDs per thread in flight
+        static_assert(UK * NT <= kRoundMax, "positions are counted in 32 bits");
         for (int base = q_lo; base < q_hi; base += UK * NT) {      // the same trips for every lane: lanes combine their counts
             const int64_t* id_at = ids + base;
             uint32_t* key_at = keys + (base + dl);
@@ -361,6 +362,7 @@ pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int
         const bool stepped = (int64_t)tl.nb * 64 <= (int64_t)6 * (q_hi - q_lo);     // (short bags: a search per position is shorter)
         int t = stepped && w_lo + lane < w_hi ? upper_bound_i32(s_po, tl.nb + 1, w_lo + lane) - 1 : 0;
         constexpr int UP = 8;                              // key loads in flight (they come from memory: nothing has read them since they were written)
+        static_assert(4 * NT <= kRoundMax && UP * NT <= kRoundMax, "positions are counted in 32 bits");
         for (int base = w_lo; base < w_hi; base += UP * 64) {
             const uint32_t* key_at = keys + (base + dl);
             const int left = w_hi - base;
@@ -556,13 +558,13 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
     const uint2* __restrict__ rec = as_global(a->rec) + rec_start;
     // (loads without a condition: under one, the compiler waits for each before the next; places without a record ask
     // for the last one again)
-    auto load_record = [&](int base, int i) {              // record base + i, base the same for the block: a 32-bit offset from a scalar address
+    auto load_record = [&](int base, int left, int i) {    // record base + i of `left` from base on, the same for the block: a 32-bit offset from a scalar address
         const char* at = reinterpret_cast<const char*>(rec + base);
-        return *reinterpret_cast<const uint2*>(at + (uint32_t)min(i, max(n_rec - 1 - base, 0)) * (uint32_t)sizeof(uint2));
+        return *reinterpret_cast<const uint2*>(at + (uint32_t)min(i, max(left - 1, 0)) * (uint32_t)sizeof(uint2));
     };
     uint2 kept[KEEP];
 #pragma unroll
-    for (int u = 0; u < KEEP; ++u) kept[u] = KEPT ? load_record(0, tid + u * NTH) : make_uint2(0, 0);
+    for (int u = 0; u < KEEP; ++u) kept[u] = KEPT ? load_record(0, n_rec, tid + u * NTH) : make_uint2(0, 0);
     const auto* tm = as_constant(a->tmeta) + t;
     const int p = tm->pack;
     const PackState* st = as_global(a->st) + p;
@@ -597,14 +599,14 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
     auto for_records = [&](auto in_flight, auto&& fn) {    // (a record's first word alone, where fn uses no more)
         constexpr int UN = decltype(in_flight)::value;     // records per thread in flight
 #pragma nounroll
-        for (int base = 0; base < n_rec; base += UN * NTH) {
+        for (Rounds<UN * NTH> at(n_rec); at.any(); at.next()) {
             uint2 r[UN];
 #pragma unroll
-            for (int u = 0; u < UN; ++u) r[u] = load_record(base, tid + u * NTH);
+            for (int u = 0; u < UN; ++u) r[u] = load_record(at.base, at.left, tid + u * NTH);
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 bool on;
-                const SliceRec x = unpack(r[u], base + tid + u * NTH < n_rec, &on);
+                const SliceRec x = unpack(r[u], tid + u * NTH < at.left, &on);
                 fn(x, on);
             }
         }
@@ -757,7 +759,7 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
         // counted and placed by ballots, a whole wavefront's at once; the others have one LDS atomic each.  (Lanes that
         // share a key combined for any key, 64 records are a chain of 1100 cycles: 52 K records 100 us.)
         if (tid < 64) {
-            const uint32_t kl = load_record(0, tid).x & ((1u << LOGMAX) - 1u);
+            const uint32_t kl = load_record(0, n_rec, tid).x & ((1u << LOGMAX) - 1u);
             int best = 0;
             uint32_t hot = 0;
             for (int l = 0; l < 64; l += 8) {
@@ -949,6 +951,7 @@ pk_inverse_kernel(int F, const int32_t* __restrict__ fscan, const SlotMeta* __re
         s_klo[j] = m.key_lo; s_wb[j] = m.word_base; s_rows[j] = m.rows; s_pack[j] = st[m.pack].error;   // (the error word, final by now)
     }
     if (field_scan_load<NT>(fscan, F, s_fb)) return;
+    static_assert(KT <= kRoundMax, "positions are counted in 32 bits");
     const int n = s_slotpos[F];
     const int n_tiles = (n + KT - 1) / KT;
     for (XcdTiles it(n_tiles); it.valid(); it.next()) {

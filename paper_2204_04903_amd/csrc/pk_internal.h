@@ -18,9 +18,10 @@ constexpr int kLongMin   = 256;    // up to this many: one wavefront per key; ab
 constexpr int kMarkStep  = 256;    // every kMarkStep-th position of the grouped occurrences names its key: how long keys are found
 constexpr int kPiece     = 1024;   // occurrences per piece of a long key (the last piece takes what is left, up to twice that)
 static_assert(kMarkStep <= kLongMin && kPiece > kLongMin, "every piece of a long key holds a marked position");
-// Occurrences of a call.  Kernels walk positions in 32 bits and in rounds: the longest round (8192 positions: a listed
-// slice's records, a tile's keys touched ahead) must still be counted past the last position.
-constexpr int64_t kNnzMax = ((int64_t)1 << 31) - 8192;
+// Occurrences of a call.  Kernels walk positions in 32 bits and in rounds: a round of up to kRoundMax positions can still
+// be counted past the last position.  Longer ones count what is left (Rounds).
+constexpr int kRoundMax = 8192;
+constexpr int64_t kNnzMax = ((int64_t)1 << 31) - kRoundMax;
 constexpr size_t kAlign = 256;
 
 // The dedup cuts every table's key range into slices of 2^k keys; one block owns a slice and keeps
@@ -50,6 +51,15 @@ constexpr int64_t kFineRowsMax = (int64_t)4096 << kSliceLogFine;   // longest ta
 #else
 #define PK_HD
 #endif
+
+// n positions in rounds of N, by what is left of them, which no round length takes out of 32 bits.
+template <int N>
+struct Rounds {
+    int base = 0, left;                  // the round's first position; positions from there on
+    PK_HD explicit Rounds(int n) : left(n) {}
+    PK_HD bool any() const { return left > 0; }
+    PK_HD void next() { base = (int)((unsigned)base + (unsigned)N); left -= N; }
+};
 
 // Slices of one table for a partitioned call: 2^log_keys keys each, n of them.  The aim is `target`
 // occurrences per slice, given how many occurrences the table's fields have in THIS batch (the
