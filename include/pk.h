@@ -69,7 +69,11 @@ typedef struct {
                                    on it.                                               */
     int32_t debug;              /* for tests and measurements; results do not depend on it.
                                    bit 0: no internal streams, every kernel on hip_stream;
-                                   bit 1: the partitioned dedup also for small batches      */
+                                   bit 1: the partitioned dedup also for small batches;
+                                   bit 2: its blocks count for themselves what they would
+                                   else wait for other blocks to publish;
+                                   bit 3 (this one raises error bit 1): every 64th slice
+                                   of a pack gives up waiting at once                      */
 } pk_plan_opts;
 
 typedef struct pk_plan pk_plan;   /* opaque, host memory, owned by the library */

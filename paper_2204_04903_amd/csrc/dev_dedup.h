@@ -420,7 +420,7 @@ struct SliceArgs {
     int32_t* packed_offsets;
     uint32_t* keys; int32_t* inverse;                           // written here for small batches only
     uint32_t* bitmap;                                           // large batches only: bitmaps with rank samples
-    uint32_t* slice_nu; uint64_t* nu_group; int n_groups, sum_stride;   // ... distinct keys per slice, and their sums (SliceSums)
+    uint32_t* slice_nu; uint64_t* nu_group; int n_groups, sum_stride, waits;   // ... distinct keys per slice, and their sums (SliceSums)
     uint32_t* unique; int32_t* seg_all; uint32_t* ent_all; int ent_mult;
     int32_t* marks; double* ghot; int32_t* ticket; int dmax;
     uint64_t* desc; uint64_t* gdesc; int32_t* done; int n_slices;   // small batches: descriptors the library owns, cleaned by the last block
@@ -478,13 +478,20 @@ struct SliceRec { uint32_t kl, ref, L; };
 // Distinct keys before a slice.  Every slice publishes its number and adds it to its group of kSumFan slices; the first
 // slice of a group adds up the groups before and publishes that; the others take what was published for the group
 // before theirs (long there, usually), that group, and the slices of their own before them.  (Every block looking at all
-// groups itself: a thousand blocks then poll the same few lines, and a round trip takes 20 us instead of 3.)  Groups are counted from the pack's first slice, so a pack's sums never mix
-// with another's.  The words carry their own validity (a flag, or how many have been added): relaxed accesses do,
-// and nothing is returned to the publishing block.  A block waits for blocks before it only.
+// groups itself: a thousand blocks then poll the same few lines, and a round trip takes 20 us instead of 3.)  Groups are
+// counted from the pack's first slice, so a pack's sums never mix with another's.  The words carry their own validity (a
+// flag, or how many have been added): relaxed accesses do, and nothing is returned to the publishing block.
+// A block that sees nothing for kPatience looks counts what it lacks itself (count_before in slice_body), so it waits for
+// no block that may not have started.
 constexpr int kSumFan = 64;
-constexpr uint32_t kNuReady = 0x80000000u;
+constexpr int kPatience = 1024;                          // looks of about 3 us
+constexpr int kNotSeen = -2;
+constexpr uint32_t kNuReady = 0x80000000u, kNuBegun = 0x40000000u;     // begun: a slice of more records than are kept, by its block
+constexpr uint32_t kNuMask = kNuBegun - 1u;
+enum { kWaitNever = 1, kWaitGivesUp = 2 };               // SliceArgs::waits, for tests
 struct SliceSums {
     uint32_t* nu; uint64_t* group; uint64_t* prefix;     // per slice; per group: count << 32 | sum; kSumFan << 32 | sum before it
+    const int32_t* error;                                // the pack's error word
     int i, stride;                                       // the slice, counted from the pack's first; words between groups
     __device__ __forceinline__ SliceSums(SliceArgsPtr a, int slice, int pack_first, int p)
     {
@@ -493,31 +500,47 @@ struct SliceSums {
         stride = a->sum_stride;
         group = as_global(a->nu_group) + (size_t)(pack_first / kSumFan + p) * stride;
         prefix = group + (size_t)a->n_groups * stride;
+        error = &as_global(a->st)[p].error;
+    }
+    __device__ __forceinline__ void begin() const                              // one thread, the one that publishes
+    {
+        __hip_atomic_store(nu + i, kNuBegun, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __device__ __forceinline__ void publish(int n_u) const                     // one thread
     {
         __hip_atomic_store(nu + i, kNuReady | (uint32_t)n_u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         (void)__hip_atomic_fetch_add(group + i / kSumFan * stride, (uint64_t)1 << 32 | (uint32_t)n_u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    __device__ __forceinline__ void publish_before(int sum) const              // one thread, a group's first slice
+    {
+        __hip_atomic_store(prefix + i / kSumFan * stride, (uint64_t)kSumFan << 32 | (uint32_t)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ uint32_t word(int j) const { return __hip_atomic_load(nu + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    // a slice of the pack gave up, or found sums that cannot be: its number may never come
+    __device__ __forceinline__ bool given_up() const { return __hip_atomic_load(error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0; }
     // One wavefront, all lanes.  `ask` sends the loads out, `before` waits for them, and for the numbers themselves: the
-    // distinct keys of the pack's slices before this one; -1 after waiting too long.
+    // distinct keys of the pack's slices before this one; kNotSeen where they have not come, -1 where they will not.
     struct Seen { uint32_t n; uint64_t g; };
     __device__ __forceinline__ Seen ask() const
     {
         // lanes 0 .. : the slices of the group before this one; the last two: the group before, and what is before that
         const int lane = threadIdx.x & 63, g = i / kSumFan, in = i % kSumFan;
         Seen s{kNuReady, (uint64_t)kSumFan << 32};
-        if (lane < in) s.n = __hip_atomic_load(nu + (i - in) + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane < in) s.n = word((i - in) + lane);
         if (in != 0 && lane >= kSumFan - 2 && g > kSumFan - 1 - lane)
             s.g = __hip_atomic_load((lane == kSumFan - 2 ? prefix : group) + (g - 1) * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return s;
     }
-    __device__ __forceinline__ int before(Seen s) const
+    __device__ __forceinline__ int before(Seen s, int waits) const
     {
         const int lane = threadIdx.x & 63, g = i / kSumFan;
-        for (int spin = 0; spin < kSpinLimit; ++spin) {
+        if (waits && i) {
+            if (waits & kWaitNever) return kNotSeen;
+            if (i % kSumFan == 0) return -1;
+        }
+        for (int spin = 0; spin < kPatience; ++spin) {
             bool ok = (s.n & kNuReady) && (s.g >> 32) == kSumFan;
-            int sum = (int)((s.n & ~kNuReady) + (uint32_t)s.g);
+            int sum = (int)((s.n & kNuMask) + (uint32_t)s.g);
             if (i % kSumFan == 0)
                 for (int k = lane; k < g; k += 64) {
                     const uint64_t z = __hip_atomic_load(group + k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -525,17 +548,28 @@ struct SliceSums {
                     sum += (int)(uint32_t)z;
                 }
             if (!__all(ok)) {
+                if (spin % 64 == 63 && __any(given_up())) return -1;
                 __builtin_amdgcn_s_sleep(8);
                 s = ask();
                 continue;
             }
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
-            if (i % kSumFan == 0 && lane == 0)
-                __hip_atomic_store(prefix + g * stride, (uint64_t)kSumFan << 32 | (uint32_t)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (i % kSumFan == 0 && lane == 0) publish_before(sum);
             return sum;
         }
-        return -1;
+        return kNotSeen;
+    }
+    // One thread: the number of a slice whose block has begun, which publishes before it waits for anything.
+    __device__ __forceinline__ uint32_t published(int j) const
+    {
+        for (int spin = 0; spin < kSpinLimit; ++spin) {
+            const uint32_t w = word(j);
+            if (w & kNuReady) return w & kNuMask;
+            if (given_up()) break;
+            __builtin_amdgcn_s_sleep(8);
+        }
+        return ~0u;
     }
 };
 
@@ -543,7 +577,7 @@ template <int N> struct InFlight { static constexpr int value = N; };
 
 // KEPT: the slice's records fit the threads' registers
 template <int NTH, int LOGMAX, int RANKS, bool KEPT>
-__device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s_main, int32_t* s_tf, int32_t* s_base)
+__device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s_main, int32_t* s_tf, int32_t* s_base)      // s_base: four words
 {
     constexpr int WMAX = 1 << (LOGMAX - 5), WPT = WMAX / NTH;       // bitmap words, of them per thread
     constexpr int KEEP = kSliceKeep;
@@ -569,7 +603,8 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
     const int p = tm->pack;
     const PackState* st = as_global(a->st) + p;
     const int pstart = st->start, nnz_p = st->nnz;
-    if (st->error & 1) return;                             // offsets of this pack were rejected (so all its slices return here)
+    if (st->error) return;                                 // offsets of this pack were rejected (so all its slices return here), or one gave up
+    if (!KEPT && tid == 0) SliceSums(a, slice, st->first_slice, p).begin();
     const int lg = as_constant(a->cut)[t].log_keys;
     const bool wide = as_constant(a->pm)[p].has_mean != 0; // the pack's entries carry the bag length
     const int nf = tm->field_end - tm->field_begin;
@@ -719,16 +754,99 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
     // the sum before this slice; false (for the whole block) where it cannot be had, or where what it and the records'
     // place say would leave the pack's arrays
     auto ask = [&]() { return tid < 64 ? SliceSums(a, slice, st->first_slice, p).ask() : SliceSums::Seen{0, 0}; };
-    auto get_base = [&](SliceSums::Seen seen) {
+    // Distinct keys of the pack's slices before this one where they have not come: a block before this one may not have
+    // started, and may not be able to while this one holds its place.  (Blocks start in index order on each XCD, but
+    // the XCDs take their shares of a launch at their own pace, and another launch's blocks may be waiting beside.)  So
+    // what is published is taken, what a running block will publish is waited for, and the keys of a slice whose block has not
+    // begun are counted here, from its records, in the bitmap's size of counters.  Only blocks of more records than they keep say
+    // that they have begun: the others' records are few and nobody changes them, so those are counted whether begun or not.
+    auto count_before = [&]() -> int {
+        __syncthreads();                                   // (*s_base has been read)
+        const SliceSums sums(a, slice, st->first_slice, p);
+        uint32_t* s_map = reinterpret_cast<uint32_t*>(s_cnt);
+        const int lane = tid & 63;
+        int sum = 0;
+        for (int j0 = 0; j0 < sums.i; j0 += 64) {
+            if (tid < 64) {
+                uint32_t w = j0 + lane < sums.i ? sums.word(j0 + lane) : kNuReady;
+                if (j0 + lane < sums.i && (a->waits & kWaitNever)) w = 0;
+                const uint64_t m = __ballot(!(w & kNuReady));
+                int n = w & kNuReady ? (int)(w & kNuMask) : 0;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o, 64);
+                if (tid == 0) { s_base[0] = n; s_base[1] = (int)(uint32_t)m; s_base[2] = (int)(uint32_t)(m >> 32); }
+            }
+            __syncthreads();
+            sum += s_base[0];
+            uint64_t todo = (uint64_t)(uint32_t)s_base[1] | (uint64_t)(uint32_t)s_base[2] << 32;
+            __syncthreads();
+            while (todo) {
+                const int j = j0 + __ffsll((unsigned long long)todo) - 1;
+                todo &= todo - 1;
+                const auto* sj = as_constant(a->slice_info) + (slice - sums.i + j);
+                const int n_j = sj->count, t_j = sj->table;
+                const uint2* __restrict__ rec_j = as_global(a->rec) + sj->start;
+                const bool few = n_j <= KEEP * NTH;
+                // number of the slice: ~0u = it will not come; its block has not begun: kNuBegun
+                auto look = [&]() {
+                    if (tid == 0) {
+                        const uint32_t w = few ? 0u : sums.word(j);
+                        s_base[3] = (int)(w == 0 ? kNuBegun : sums.published(j));
+                    }
+                    __syncthreads();
+                    const uint32_t w = (uint32_t)s_base[3];
+                    __syncthreads();
+                    return w;
+                };
+                uint32_t n = look();
+                if (n == kNuBegun) {
+                    const int lg_j = as_constant(a->cut)[t_j].log_keys;
+                    const uint32_t nkeys_j = min((uint32_t)1 << lg_j, as_constant(a->tmeta)[t_j].rows - ((uint32_t)sj->idx << lg_j));
+                    for (int w = tid; w < WMAX; w += NTH) s_map[w] = 0;
+                    __syncthreads();
+                    for (Rounds<4 * NTH> at(n_j); at.any(); at.next()) {
+                        uint32_t x[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) x[u] = rec_j[at.base + min(tid + u * NTH, at.left - 1)].x & ((1u << LOGMAX) - 1u);
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (x[u] < nkeys_j) atomicOr(&s_map[x[u] >> 5], 1u << (x[u] & 31));
+                    }
+                    __syncthreads();
+                    int c = 0, tot;
+                    for (int w = tid; w < WMAX; w += NTH) c += __popc(s_map[w]);
+                    (void)block_excl_scan<NTH>(c, &tot);
+                    n = (uint32_t)tot;
+                    if (!few) {                            // its block may have begun meanwhile: what was read may have been changed
+                        const uint32_t again = look();
+                        if (again != kNuBegun) n = again;
+                    }
+                }
+                if (n == ~0u) return -1;
+                sum += (int)n;
+            }
+        }
+        if (tid == 0 && sums.i % kSumFan == 0) sums.publish_before(sum);
+        return sum;
+    };
+    enum { kNone, kBase, kBaseOnly };                      // no sum; the sum; the sum, and the counters are overwritten
+    auto get_base = [&](SliceSums::Seen seen) -> int {
         if (tid < 64) {
-            const int b = SliceSums(a, slice, st->first_slice, p).before(seen);
+            const int b = SliceSums(a, slice, st->first_slice, p).before(seen, a->waits);
             if (tid == 0) *s_base = b;
         }
         __syncthreads();
-        const int base = *s_base;
-        if (base >= 0 && rec_before >= 0 && (int64_t)base + n_u <= (int64_t)nnz_p && (int64_t)rec_before + n_rec <= (int64_t)nnz_p) return true;
+        int base = *s_base;
+        const int got = base == kNotSeen ? kBaseOnly : kBase;
+        if (got == kBaseOnly) {
+            base = count_before();
+            __syncthreads();
+            if (tid == 0) *s_base = base;
+            __syncthreads();
+        }
+        if (base >= 0 && rec_before >= 0 && (int64_t)base + n_u <= (int64_t)nnz_p && (int64_t)rec_before + n_rec <= (int64_t)nnz_p) return got;
         if (tid == 0) atomicOr(&as_global(a->st)[p].error, 2);
-        return false;
+        return kNone;
     };
     if constexpr (KEPT) {
         // The counting pass gives every record its key's rank and its place among the key's occurrences: both fit a
@@ -752,7 +870,15 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
             const SliceRec r = unpack(kept[u], tid + u * NTH < n_rec, &on);
             if (on) put(r, s_cnt[rp[u] & 0xFFFFu] + (int)(rp[u] >> 16));
         }
-        if (!get_base(seen)) return;
+        const int got = get_base(seen);
+        if (got == kNone) return;
+        if (got == kBaseOnly) {                            // the keys' first places again
+            for (int i = tid; i < n_u; i += NTH) s_cnt[i] = 0;
+            __syncthreads();
+            for_records(InFlight<4>{}, [&](const SliceRec& r, bool on) { if (on) atomicAdd(&s_cnt[rank_of(r.kl)], 1); });
+            __syncthreads();
+            (void)starts(n_u, 0);
+        }
         segments(*s_base, n_u, rec_before + tot);
     } else {
         // Most of a slice with many records is one frequent key's: the one that most of the first 64 records have is
@@ -775,7 +901,12 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
         __syncthreads();
         const int lane = tid & 63;
         const uint64_t below = (1ull << lane) - 1ull;
-        if (!get_base(ask())) return;
+        const int got = get_base(ask());
+        if (got == kNone) return;
+        if (got == kBaseOnly) {
+            for (int i = tid; i < min(RANKS, n_rec); i += NTH) s_cnt[i] = 0;
+            __syncthreads();
+        }
         const int base_u = *s_base;
         int placed = 0;                                    // occurrences of the keys of earlier rounds
         for (int r0 = 0; r0 < n_u; r0 += RANKS) {          // a round handles RANKS keys
@@ -866,11 +997,11 @@ template <int NTH, int LOGMAX, int RANKS>
 __device__ __forceinline__ void slice_block(SliceArgsPtr a, int32_t* s_tf)
 {
     __shared__ __align__(16) int32_t s_main[slice_lds_words(LOGMAX, RANKS)];
-    __shared__ int32_t s_base;
+    __shared__ int32_t s_base[4];
     const auto* si = as_constant(a->slice_info) + blockIdx.x;
     if (si->table < 0) return;                             // room for a slice this batch does not have
-    if (si->count <= kSliceKeep * NTH) slice_body<NTH, LOGMAX, RANKS, true>(a, blockIdx.x, s_main, s_tf, &s_base);
-    else slice_body<NTH, LOGMAX, RANKS, false>(a, blockIdx.x, s_main, s_tf, &s_base);
+    if (si->count <= kSliceKeep * NTH) slice_body<NTH, LOGMAX, RANKS, true>(a, blockIdx.x, s_main, s_tf, s_base);
+    else slice_body<NTH, LOGMAX, RANKS, false>(a, blockIdx.x, s_main, s_tf, s_base);
 }
 
 __global__ void __launch_bounds__(kFineThreads, 8)

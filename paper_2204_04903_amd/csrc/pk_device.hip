@@ -262,6 +262,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
         if (L.n_slices > 0) {
             sa.slice_nu = ws.at<uint32_t>(L.slice_nu);
             sa.nu_group = ws.at<uint64_t>(L.nu_group); sa.n_groups = L.n_groups; sa.sum_stride = L.sum_stride;
+            sa.waits = plan->opts.debug >> 2;
             const dim3 sgrid((unsigned)L.n_slices);
             if (L.log_max == kSliceLogFine) PK_LAUNCH("pk_slices", pk_slices_kernel, sgrid, dim3(kFineThreads), tf_lds, sa);
             else PK_LAUNCH("pk_slices", pk_slices_wide_kernel, sgrid, dim3(kSliceThreads), tf_lds, sa);

@@ -159,7 +159,7 @@ pk_status pk_plan_create(const pk_table_desc* tables, int32_t n_tables, const pk
         return fail(PK_EINVAL, "pk_plan_create: negative option");
     if (opts && (opts->interleave_groups < 0 || opts->interleave_groups > 8))
         return fail(PK_EINVAL, "pk_plan_create: interleave_groups must be 0 (automatic) to 8");
-    if (opts && (opts->debug < 0 || opts->debug > 3))
+    if (opts && (opts->debug < 0 || opts->debug > 15))
         return fail(PK_EINVAL, "pk_plan_create: unknown debug bits");
     if (opts && opts->field_volume)
         for (int32_t f = 0; f < n_fields; ++f)
