@@ -7,15 +7,18 @@ constexpr int NT = 256;   // threads per block of the streaming kernels
 template <typename T>
 __device__ __forceinline__ T* as_global(T* p) { return (T*)(__attribute__((address_space(1))) T*)p; }
 
-template <int NTHREADS>
+// FRESH: the shuffles' addresses are formed again, where a scan stands in a loop that has no registers to keep them in.
+template <int NTHREADS, bool FRESH = false>
 __device__ __forceinline__ int block_excl_scan(int v, int* total)
 {
     __shared__ int wsum[NTHREADS / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6;
+    if (FRESH) asm volatile("" : "+v"(lane));
     int inc = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(inc, o, 64);
+        const int t = FRESH ? __builtin_amdgcn_ds_bpermute((lane - o) << 2, inc) : __shfl_up(inc, o, 64);
         if (lane >= o) inc += t;
     }
     __syncthreads();   // readers of the previous call are done with wsum

@@ -273,7 +273,7 @@ constexpr int kScanThreads = 1024;
 __global__ void __launch_bounds__(kScanThreads)
 pk_slice_scan_kernel(const TableCut* __restrict__ cut, int T,
                      const int32_t* __restrict__ slice_total, int32_t* __restrict__ slice_cursor,
-                     SliceInfo* __restrict__ slice_info, int n_slices)
+                     SliceInfo* __restrict__ slice_info, int n_slices, int32_t* __restrict__ long_list, int n_long_max)
 {
     extern __shared__ int32_t s_first[];                   // [T+1]
     table_cut_load<kScanThreads>(cut, T, s_first, nullptr);
@@ -291,6 +291,17 @@ pk_slice_scan_kernel(const TableCut* __restrict__ cut, int T,
         SliceInfo si;
         si.table = t; si.idx = s - s_first[t]; si.start = carry + ex; si.count = c;
         if (s >= s_first[T]) { si.table = -1; si.idx = 0; si.count = 0; }      // room for slices this batch does not have
+        // Slices of many records are listed, and the slice kernel's first blocks take them: each is one block's work, so
+        // the launch ends with the one that started last, and by their place in the pack they could all fall to one XCD
+        // (every table's first slice, where low IDs are the frequent ones: the dedup of 200 fields of 21 M IDs 860 us,
+        // 540 with the list; of 26 one-hot fields of 65536 248 and 154).
+        if (c >= kLongSlice) {
+            const int at = atomicAdd(long_list, 1);
+            if (at < n_long_max) {
+                long_list[1 + at] = s;
+                si.table |= kListedFlag;
+            }
+        }
         slice_info[s] = si;
         slice_cursor[s] = carry + ex;
     }
@@ -414,12 +425,13 @@ struct SliceArgs {
     const PackMeta* pm; const int32_t* slot_field; PackState* st; int P;
     int F, B; int64_t nnz; int target, log_max;
     const int64_t* ids; const int32_t* offsets; const SmallSlice* small_slices; const int2* slot_info;   // small batches: the block finds its occurrences itself
-    const SliceInfo* slice_info; const uint2* rec;              // large batches: the slice's records
+    const SliceInfo* slice_info; uint2* rec;                    // large batches: the slice's records
     const TableCut* cut;                                        // ... and the tables' cuts for this batch
     const FieldMeta* fmeta;
     int32_t* packed_offsets;
     uint32_t* keys; int32_t* inverse;                           // written here for small batches only
     uint32_t* bitmap;                                           // large batches only: bitmaps with rank samples
+    const int32_t* long_list; int n_long_max;                   // ... slices of many records: how many, which
     uint32_t* slice_nu; uint64_t* nu_group; int n_groups, sum_stride, waits;   // ... distinct keys per slice, and their sums (SliceSums)
     uint32_t* unique; int32_t* seg_all; uint32_t* ent_all; int ent_mult;
     int32_t* marks; double* ghot; int32_t* ticket; int dmax;
@@ -456,7 +468,10 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* as_constan
 //   places every record's entry: that needs the records before the slice only, and their number is known;
 //   adds up the distinct keys of the pack's slices before its own (SliceSums), published long ago by then;
 //   writes what needs that sum: distinct keys, segment offsets, marks, the bitmap with its rank samples.
-// A slice of more records (a frequent key's) reads them again for each of these passes.
+// A slice of more records reads them again for each of these passes, the next ones on their way while some are worked on,
+// and counts up to RANKS keys a round, after which the records of later rounds' keys alone are left.  (All records read
+// in every round, none ahead, and such slices not listed first: 26 one-hot fields of 65536, low IDs frequent, dedup 357 us,
+// 154 now; 200 fields of 21 M IDs 1068 and 540; 2 M IDs of tables of ten rows 1298 and 943.)
 // What bounds it is the chain of these steps, 13 us a block, so four blocks of 512 threads share a CU.  (Five launches,
 // mark, scan, place, and mark and place for the slices with many records in blocks of four times the threads, wrote the
 // bitmaps, read them back and read the records three times.  Launches of the step's dedup together, us, before and
@@ -481,10 +496,17 @@ struct SliceRec { uint32_t kl, ref, L; };
 // groups itself: a thousand blocks then poll the same few lines, and a round trip takes 20 us instead of 3.)  Groups are
 // counted from the pack's first slice, so a pack's sums never mix with another's.  The words carry their own validity (a
 // flag, or how many have been added): relaxed accesses do, and nothing is returned to the publishing block.
-// A block that sees nothing for kPatience looks counts what it lacks itself (count_before in slice_body), so it waits for
-// no block that may not have started.
+// A block that has waited for long while no slice of the launch published counts what it lacks itself (count_before in
+// slice_body), so it waits for no block that may not have started.
+// (a loop: unrolled, the six shuffles' addresses are kept from one use to the next, in registers that there are not)
+__device__ __forceinline__ int wave_sum(int v)
+{
+#pragma nounroll
+    for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
 constexpr int kSumFan = 64;
-constexpr int kPatience = 1024;                          // looks of about 3 us
+constexpr int kLooks = 64, kPatience = 16;               // 16 times 64 looks of about 3 us
 constexpr int kNotSeen = -2;
 constexpr uint32_t kNuReady = 0x80000000u, kNuBegun = 0x40000000u;     // begun: a slice of more records than are kept, by its block
 constexpr uint32_t kNuMask = kNuBegun - 1u;
@@ -531,14 +553,16 @@ struct SliceSums {
             s.g = __hip_atomic_load((lane == kSumFan - 2 ? prefix : group) + (g - 1) * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return s;
     }
-    __device__ __forceinline__ int before(Seen s, int waits) const
+    __device__ __forceinline__ int before(Seen s, SliceArgsPtr a) const
     {
         const int lane = threadIdx.x & 63, g = i / kSumFan;
-        if (waits && i) {
-            if (waits & kWaitNever) return kNotSeen;
+        if (a->waits && i) {
+            if (a->waits & kWaitNever) return kNotSeen;
             if (i % kSumFan == 0) return -1;
         }
-        for (int spin = 0; spin < kPatience; ++spin) {
+        uint32_t seen = 0;
+        int quiet = 0;
+        for (int spin = 0; spin < kSpinLimit; ++spin) {
             bool ok = (s.n & kNuReady) && (s.g >> 32) == kSumFan;
             int sum = (int)((s.n & kNuMask) + (uint32_t)s.g);
             if (i % kSumFan == 0)
@@ -547,16 +571,23 @@ struct SliceSums {
                     ok = ok && (z >> 32) == kSumFan;
                     sum += (int)(uint32_t)z;
                 }
-            if (!__all(ok)) {
-                if (spin % 64 == 63 && __any(given_up())) return -1;
-                __builtin_amdgcn_s_sleep(8);
-                s = ask();
-                continue;
+            if (__all(ok)) {
+                sum = wave_sum(sum);
+                if (i % kSumFan == 0 && lane == 0) publish_before(sum);
+                return sum;
             }
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
-            if (i % kSumFan == 0 && lane == 0) publish_before(sum);
-            return sum;
+            if (spin % kLooks == kLooks - 1) {             // has any slice of the launch published since?
+                if (__any(given_up())) return -1;
+                uint32_t n = 0;
+                for (int k = lane; k < a->n_groups; k += 64)
+                    n += (uint32_t)(__hip_atomic_load(as_global(a->nu_group) + (size_t)k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
+                n = (uint32_t)wave_sum((int)n);
+                quiet = n == seen ? quiet + 1 : 0;
+                seen = n;
+                if (quiet == kPatience) return kNotSeen;
+            }
+            __builtin_amdgcn_s_sleep(8);
+            s = ask();
         }
         return kNotSeen;
     }
@@ -588,8 +619,8 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
 
     // ---- which slice, of which table; its records ----
     const auto* si = as_constant(a->slice_info) + slice;
-    const int t = si->table, rec_start = si->start, n_rec = si->count;
-    const uint2* __restrict__ rec = as_global(a->rec) + rec_start;
+    const int t = si->table & ~kListedFlag, rec_start = si->start, n_rec = si->count;
+    uint2* rec = as_global(a->rec) + rec_start;
     // (loads without a condition: under one, the compiler waits for each before the next; places without a record ask
     // for the last one again)
     auto load_record = [&](int base, int left, int i) {    // record base + i of `left` from base on, the same for the block: a 32-bit offset from a scalar address
@@ -629,30 +660,37 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
         *on = valid && kl < nkeys;
         return SliceRec{*on ? kl : 0u, r.y, r.x >> LOGMAX};
     };
-    // all records, where they are not kept: fn(SliceRec, on).  Every lane makes the same trips and calls fn every time, with
-    // on = false where it has none, so that fn may combine lanes.
-    auto for_records = [&](auto in_flight, auto&& fn) {    // (a record's first word alone, where fn uses no more)
-        constexpr int UN = decltype(in_flight)::value;     // records per thread in flight
+    // Records where they are not kept, UN per lane in flight: a wavefront takes a contiguous share of the slice's, of which
+    // the first `n` are gone through, and every lane makes the same trips, so that fn(records, number left from the
+    // lane's first on) may combine lanes.
+    const int lane = tid & 63;
+    const int share = (n_rec + NTH - 1) / NTH * 64, share_lo = min(__builtin_amdgcn_readfirstlane(tid >> 6) * share, n_rec);
+    const int n_share = min(share, n_rec - share_lo);
+    auto for_records = [&](auto in_flight, int n, auto&& fn) {
+        constexpr int UN = decltype(in_flight)::value;
+        int first = lane;                                  // (what follows from it is not kept over the rounds of keys)
+        asm volatile("" : "+v"(first));
+        uint2 r[UN], next[UN];
+        if (n > 0) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) next[u] = load_record(share_lo, n, first + u * 64);
+        }
 #pragma nounroll
-        for (Rounds<UN * NTH> at(n_rec); at.any(); at.next()) {
-            uint2 r[UN];
+        for (Rounds<UN * 64> at(n); at.any(); at.next()) {
+            const bool last = at.left <= UN * 64;
 #pragma unroll
-            for (int u = 0; u < UN; ++u) r[u] = load_record(at.base, at.left, tid + u * NTH);
+            for (int u = 0; u < UN; ++u) r[u] = next[u];
 #pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                bool on;
-                const SliceRec x = unpack(r[u], tid + u * NTH < at.left, &on);
-                fn(x, on);
-            }
+            for (int u = 0; u < UN; ++u)                   // (on their way while these are worked on; after the last, the last again)
+                next[u] = load_record(share_lo + at.base + (last ? 0 : UN * 64), last ? at.left : at.left - UN * 64, first + u * 64);
+            fn(r, at.left - first);
         }
     };
 
     // ---- which keys occur ----
-    auto mark = [&](const SliceRec& r, bool on) {
-        if (on) {
-            const uint32_t bit = 1u << (r.kl & 31);
-            if (!(s_bp[r.kl >> 5].x & bit)) atomicOr(&s_bp[r.kl >> 5].x, bit);
-        }
+    auto mark = [&](uint32_t kl, uint32_t seen, bool on) {
+        const uint32_t bit = 1u << (kl & 31);
+        if (on && !(seen & bit)) atomicOr(&s_bp[kl >> 5].x, bit);
     };
     if constexpr (KEPT) {
 #pragma unroll
@@ -660,10 +698,20 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
             if (u * NTH >= n_rec) break;
             bool on;
             const SliceRec x = unpack(kept[u], tid + u * NTH < n_rec, &on);
-            mark(x, on);
+            mark(x.kl, on ? s_bp[x.kl >> 5].x : 0u, on);
         }
     } else {
-        for_records(InFlight<16>{}, mark);
+        for_records(InFlight<8>{}, n_share, [&](const uint2 (&r)[8], int left) {
+            uint32_t seen[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) seen[u] = s_bp[(r[u].x & ((1u << LOGMAX) - 1u)) >> 5].x;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                bool on;
+                const SliceRec x = unpack(r[u], u * 64 < left, &on);
+                mark(x.kl, seen[u], on);
+            }
+        });
     }
     __syncthreads();
     // popcount prefix of the words, number of distinct keys
@@ -720,7 +768,7 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
             sum += i < width ? s_cnt[i] : 0;
         }
         int tot;
-        int s0 = block_excl_scan<NTH>(sum, &tot) + rec_before + placed;
+        int s0 = block_excl_scan<NTH, !KEPT>(sum, &tot) + rec_before + placed;
         for (int j = 0; j < per; ++j) {
             const int i = tid * per + j;
             if (i < width) {
@@ -733,13 +781,15 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
         return tot;
     };
     // what the backward pass needs of key u with the places [s0, s1): its segment, the marks by which a long one is
-    // found, and, where it is reduced in pieces, partial sums that start at zero
-    auto segments = [&](int first, int width, int end) {
+    // found, and, where it is reduced in pieces, partial sums that start at zero.  From the keys' first places, or, where
+    // the placing pass has moved them on, from where they end.
+    auto segments = [&](int first, int width, int begin, int end) {
         a = forget<true>(a);
         int32_t* __restrict__ seg = as_global(a->seg_all) + pstart + p;
         int32_t* __restrict__ marks = as_global(a->marks) + (pstart / kMarkStep + p);
         for (int i = tid; i < width; i += NTH) {
-            const int u = first + i, s0 = s_cnt[i], s1 = i + 1 < width ? s_cnt[i + 1] : end;
+            const int u = first + i;
+            const int s0 = KEPT ? s_cnt[i] : i ? s_cnt[i - 1] : begin, s1 = !KEPT ? s_cnt[i] : i + 1 < width ? s_cnt[i + 1] : end;
             seg[u] = s0;
             for (int m = (s0 + kMarkStep - 1) / kMarkStep; (int64_t)m * kMarkStep < (int64_t)s1; ++m) marks[m] = u;
             if (s1 - s0 >= 2 * kPiece) {
@@ -764,16 +814,13 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
         __syncthreads();                                   // (*s_base has been read)
         const SliceSums sums(a, slice, st->first_slice, p);
         uint32_t* s_map = reinterpret_cast<uint32_t*>(s_cnt);
-        const int lane = tid & 63;
         int sum = 0;
         for (int j0 = 0; j0 < sums.i; j0 += 64) {
             if (tid < 64) {
                 uint32_t w = j0 + lane < sums.i ? sums.word(j0 + lane) : kNuReady;
                 if (j0 + lane < sums.i && (a->waits & kWaitNever)) w = 0;
                 const uint64_t m = __ballot(!(w & kNuReady));
-                int n = w & kNuReady ? (int)(w & kNuMask) : 0;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o, 64);
+                const int n = wave_sum(w & kNuReady ? (int)(w & kNuMask) : 0);
                 if (tid == 0) { s_base[0] = n; s_base[1] = (int)(uint32_t)m; s_base[2] = (int)(uint32_t)(m >> 32); }
             }
             __syncthreads();
@@ -784,7 +831,7 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
                 const int j = j0 + __ffsll((unsigned long long)todo) - 1;
                 todo &= todo - 1;
                 const auto* sj = as_constant(a->slice_info) + (slice - sums.i + j);
-                const int n_j = sj->count, t_j = sj->table;
+                const int n_j = sj->count, t_j = sj->table & ~kListedFlag;
                 const uint2* __restrict__ rec_j = as_global(a->rec) + sj->start;
                 const bool few = n_j <= KEEP * NTH;
                 // number of the slice: ~0u = it will not come; its block has not begun: kNuBegun
@@ -813,10 +860,15 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
                             if (x[u] < nkeys_j) atomicOr(&s_map[x[u] >> 5], 1u << (x[u] & 31));
                     }
                     __syncthreads();
-                    int c = 0, tot;
+                    int c = 0;
                     for (int w = tid; w < WMAX; w += NTH) c += __popc(s_map[w]);
-                    (void)block_excl_scan<NTH>(c, &tot);
-                    n = (uint32_t)tot;
+                    c = wave_sum(c);
+                    if (tid == 0) s_base[3] = 0;
+                    __syncthreads();
+                    if (lane == 0) atomicAdd(&s_base[3], c);
+                    __syncthreads();
+                    n = (uint32_t)s_base[3];
+                    __syncthreads();
                     if (!few) {                            // its block may have begun meanwhile: what was read may have been changed
                         const uint32_t again = look();
                         if (again != kNuBegun) n = again;
@@ -829,24 +881,28 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
         if (tid == 0 && sums.i % kSumFan == 0) sums.publish_before(sum);
         return sum;
     };
-    enum { kNone, kBase, kBaseOnly };                      // no sum; the sum; the sum, and the counters are overwritten
-    auto get_base = [&](SliceSums::Seen seen) -> int {
+    auto get_base = [&](SliceSums::Seen seen) -> bool {
         if (tid < 64) {
-            const int b = SliceSums(a, slice, st->first_slice, p).before(seen, a->waits);
+            const int b = SliceSums(a, slice, st->first_slice, p).before(seen, a);
             if (tid == 0) *s_base = b;
         }
         __syncthreads();
         int base = *s_base;
-        const int got = base == kNotSeen ? kBaseOnly : kBase;
-        if (got == kBaseOnly) {
+        bool ok = rec_before >= 0 && (int64_t)rec_before + n_rec <= (int64_t)nnz_p;
+        if (ok && base == kNotSeen) {
+            // (the counters meanwhile in the slice's share of the inverse index, which is written after this launch)
+            int32_t* save = as_global(a->inverse) + rec_start;
+            const int n = min(min(RANKS, n_u), n_rec);
+            for (int i = tid; i < n; i += NTH) save[i] = s_cnt[i];
             base = count_before();
             __syncthreads();
+            for (int i = tid; i < n; i += NTH) s_cnt[i] = save[i];
             if (tid == 0) *s_base = base;
             __syncthreads();
         }
-        if (base >= 0 && rec_before >= 0 && (int64_t)base + n_u <= (int64_t)nnz_p && (int64_t)rec_before + n_rec <= (int64_t)nnz_p) return got;
-        if (tid == 0) atomicOr(&as_global(a->st)[p].error, 2);
-        return kNone;
+        ok = ok && base >= 0 && (int64_t)base + n_u <= (int64_t)nnz_p;
+        if (!ok && tid == 0) atomicOr(&as_global(a->st)[p].error, 2);
+        return ok;
     };
     if constexpr (KEPT) {
         // The counting pass gives every record its key's rank and its place among the key's occurrences: both fit a
@@ -870,22 +926,14 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
             const SliceRec r = unpack(kept[u], tid + u * NTH < n_rec, &on);
             if (on) put(r, s_cnt[rp[u] & 0xFFFFu] + (int)(rp[u] >> 16));
         }
-        const int got = get_base(seen);
-        if (got == kNone) return;
-        if (got == kBaseOnly) {                            // the keys' first places again
-            for (int i = tid; i < n_u; i += NTH) s_cnt[i] = 0;
-            __syncthreads();
-            for_records(InFlight<4>{}, [&](const SliceRec& r, bool on) { if (on) atomicAdd(&s_cnt[rank_of(r.kl)], 1); });
-            __syncthreads();
-            (void)starts(n_u, 0);
-        }
-        segments(*s_base, n_u, rec_before + tot);
+        if (!get_base(seen)) return;
+        segments(*s_base, n_u, 0, rec_before + tot);
     } else {
-        // Most of a slice with many records is one frequent key's: the one that most of the first 64 records have is
-        // counted and placed by ballots, a whole wavefront's at once; the others have one LDS atomic each.  (Lanes that
-        // share a key combined for any key, 64 records are a chain of 1100 cycles: 52 K records 100 us.)
+        // Where IDs are scattered over the rows, most of a slice with many records is one frequent key's: the one that most
+        // of the first 64 records have is counted and placed by ballots, a whole wavefront's at once; the others have one LDS
+        // atomic each.  (Lanes that share a key combined for any key, 64 records are a chain of 1100 cycles: 52 K records 100 us.)
         if (tid < 64) {
-            const uint32_t kl = load_record(0, n_rec, tid).x & ((1u << LOGMAX) - 1u);
+            const uint32_t kl = min(load_record(0, n_rec, tid).x & ((1u << LOGMAX) - 1u), nkeys - 1u);
             int best = 0;
             uint32_t hot = 0;
             for (int l = 0; l < 64; l += 8) {
@@ -899,52 +947,77 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
         const uint32_t hot = (uint32_t)*s_base;
         const int hot_rank = rank_of(hot);
         __syncthreads();
-        const int lane = tid & 63;
-        const uint64_t below = (1ull << lane) - 1ull;
-        const int got = get_base(ask());
-        if (got == kNone) return;
-        if (got == kBaseOnly) {
-            for (int i = tid; i < min(RANKS, n_rec); i += NTH) s_cnt[i] = 0;
-            __syncthreads();
-        }
-        const int base_u = *s_base;
+        auto below = [](uint64_t m) { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)); };
         int placed = 0;                                    // occurrences of the keys of earlier rounds
+        int n_mine = n_share;                              // records of the wavefront that are still to be placed
         for (int r0 = 0; r0 < n_u; r0 += RANKS) {          // a round handles RANKS keys
             const int width = min(RANKS, n_u - r0);
             const bool hot_now = (unsigned)(hot_rank - r0) < (unsigned)width;
+            const uint32_t hot_at = hot_now ? (uint32_t)(hot_rank - r0) : 0x80000000u;
             if (r0) {
                 __syncthreads();
                 for (int i = tid; i < width; i += NTH) s_cnt[i] = 0;
                 __syncthreads();
             }
+            // ranks in the round (above it: a later round's, or no record's), all asked for before any is used
+            auto ranks = [&](auto& rr, const auto& r, int left) {
+#pragma unroll
+                for (int u = 0; u < (int)(sizeof(r) / sizeof(uint2)); ++u) {
+                    bool on;
+                    const SliceRec x = unpack(r[u], u * 64 < left, &on);
+                    const uint32_t k = (uint32_t)(rank_of(x.kl) - r0);
+                    rr[u] = on ? k : ~0u;
+                }
+            };
             int n_hot = 0;
-            for_records(InFlight<16>{}, [&](const SliceRec& r, bool on) {
-                const bool is_hot = on && r.kl == hot;
-                n_hot += __popcll(__ballot(is_hot));
-                const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
-                if (on && !is_hot && rr < (uint32_t)width) atomicAdd(&s_cnt[rr], 1);
+            for_records(InFlight<8>{}, n_mine, [&](const uint2 (&r)[8], int left) {
+                uint32_t rr[8];
+                ranks(rr, r, left);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    n_hot += __popcll(__ballot(rr[u] == hot_at));
+                    if (rr[u] != hot_at && rr[u] < (uint32_t)width) atomicAdd(&s_cnt[rr[u]], 1);
+                }
             });
-            if (hot_now && lane == 0 && n_hot) atomicAdd(&s_cnt[hot_rank - r0], n_hot);
+            if (lane == 0 && n_hot) atomicAdd(&s_cnt[hot_at], n_hot);
             __syncthreads();
             const int tot = starts(width, placed);
-            placed += tot;
-            segments(base_u + r0, width, rec_before + placed);
-            __syncthreads();                               // (the placing pass moves the places on)
             // every wavefront takes room for all its records of the frequent key at once
             int at_hot = 0;
-            if (hot_now && lane == 0) at_hot = atomicAdd(&s_cnt[hot_rank - r0], n_hot);
+            if (lane == 0 && n_hot) at_hot = atomicAdd(&s_cnt[hot_at], n_hot);
             at_hot = __builtin_amdgcn_readfirstlane(at_hot);
-            for_records(InFlight<8>{}, [&](const SliceRec& r, bool on) {
-                const bool is_hot = on && r.kl == hot;
-                const uint64_t m = __ballot(is_hot);
-                const uint32_t rr = (uint32_t)(rank_of(r.kl) - r0);
-                if (is_hot) {
-                    if (hot_now) put(r, at_hot + __popcll(m & below));
-                } else if (on && rr < (uint32_t)width) {
-                    put(r, atomicAdd(&s_cnt[rr], 1));
+            const bool more = r0 + width < n_u;
+            int n_later = 0;                               // ... and moves those of later rounds' keys to the front of its share
+            for_records(InFlight<4>{}, n_mine, [&](const uint2 (&r)[4], int left) {
+                uint32_t rr[4];
+                int at[4];
+                ranks(rr, r, left);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint64_t m = __ballot(rr[u] == hot_at);
+                    at[u] = at_hot + below(m);
+                    at_hot += __popcll(m);
+                    if (rr[u] != hot_at && rr[u] < (uint32_t)width) at[u] = atomicAdd(&s_cnt[rr[u]], 1);
                 }
-                at_hot += __popcll(m);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (rr[u] < (uint32_t)width) put(SliceRec{0u, r[u].y, r[u].x >> LOGMAX}, at[u]);
+                }
+                if (more) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const bool later = rr[u] >= (uint32_t)width && rr[u] != ~0u;
+                        const uint64_t m = __ballot(later);
+                        if (later) rec[share_lo + n_later + below(m)] = r[u];
+                        n_later += __popcll(m);
+                    }
+                }
             });
+            n_mine = n_later;
+            __syncthreads();                               // (the places have been moved on)
+            if (r0 == 0 && !get_base(ask())) return;
+            segments(*s_base + r0, width, rec_before + placed, 0);
+            placed += tot;
         }
     }
 
@@ -998,10 +1071,17 @@ __device__ __forceinline__ void slice_block(SliceArgsPtr a, int32_t* s_tf)
 {
     __shared__ __align__(16) int32_t s_main[slice_lds_words(LOGMAX, RANKS)];
     __shared__ int32_t s_base[4];
-    const auto* si = as_constant(a->slice_info) + blockIdx.x;
+    // the first blocks have the listed slices, the others all that are not listed
+    const int n_long_max = a->n_long_max;
+    const bool listed = (int)blockIdx.x < n_long_max;
+    const auto* list = as_constant(a->long_list);
+    if (listed && (int)blockIdx.x >= list[0]) return;
+    const int slice = listed ? list[1 + blockIdx.x] : (int)blockIdx.x - n_long_max;
+    const auto* si = as_constant(a->slice_info) + slice;
     if (si->table < 0) return;                             // room for a slice this batch does not have
-    if (si->count <= kSliceKeep * NTH) slice_body<NTH, LOGMAX, RANKS, true>(a, blockIdx.x, s_main, s_tf, s_base);
-    else slice_body<NTH, LOGMAX, RANKS, false>(a, blockIdx.x, s_main, s_tf, s_base);
+    if (!listed && (si->table & kListedFlag)) return;
+    if (si->count <= kSliceKeep * NTH) slice_body<NTH, LOGMAX, RANKS, true>(a, slice, s_main, s_tf, s_base);
+    else slice_body<NTH, LOGMAX, RANKS, false>(a, slice, s_main, s_tf, s_base);
 }
 
 __global__ void __launch_bounds__(kFineThreads, 8)

@@ -252,7 +252,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
         PK_LAUNCH("pk_slice_scan", pk_slice_scan_kernel, dim3(blocks_for(L.n_slices, kScanThreads, 1 << 20)),
                   dim3(kScanThreads), (size_t)(T + 1) * 4,
                   ws.at<TableCut>(L.tgeom), T, slice_total, slice_cursor, ws.at<SliceInfo>(L.slice_info),
-                  L.n_slices);
+                  L.n_slices, ws.at<int32_t>(L.long_list), L.n_long_max);
         const size_t tile_lds = ((size_t)bt + 1 + (size_t)L.max_table_slices) * 4;
         const dim3 tile_grid(blocks_for(n_tiles, 1, 256 * 8));
         PK_LAUNCH("pk_scatter", pk_scatter_kernel, tile_grid, dim3(NT), tile_lds, offsets, B, F, bt, nnz, sa.log_max, ds->fmeta,
@@ -263,7 +263,8 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
             sa.slice_nu = ws.at<uint32_t>(L.slice_nu);
             sa.nu_group = ws.at<uint64_t>(L.nu_group); sa.n_groups = L.n_groups; sa.sum_stride = L.sum_stride;
             sa.waits = plan->opts.debug >> 2;
-            const dim3 sgrid((unsigned)L.n_slices);
+            sa.long_list = ws.at<int32_t>(L.long_list); sa.n_long_max = L.n_long_max;
+            const dim3 sgrid((unsigned)(L.n_slices + L.n_long_max));
             if (L.log_max == kSliceLogFine) PK_LAUNCH("pk_slices", pk_slices_kernel, sgrid, dim3(kFineThreads), tf_lds, sa);
             else PK_LAUNCH("pk_slices", pk_slices_wide_kernel, sgrid, dim3(kSliceThreads), tf_lds, sa);
         }

@@ -35,6 +35,9 @@ constexpr int kSliceLogMax = 17;           // 128 K keys: 4096 bitmap words
 constexpr int kSliceLogFine = 16;          // 64 K keys: 2048 bitmap words
 constexpr int kSliceWordsMax = 1 << (kSliceLogMax - 5);
 constexpr int kSliceOccLarge = 3072;       // occurrences per slice aimed at when the occurrences are partitioned (slices have up to twice that: mostly what a block keeps in registers; 2048: bf16 sequences 597 us a step, 571)
+constexpr int kLongSlice = 16384;          // records from which a slice is listed, up to kLongSlicesMax of them (8192: the same, but a block more per 8192 records)
+constexpr int kLongSlicesMax = 256;
+constexpr int32_t kListedFlag = 1 << 30;   // in SliceInfo::table
 constexpr int32_t kSumStride = 16;         // 64-bit words of a cache line: the sums of the slices' distinct keys stand this far apart
 constexpr int64_t kTilesMin = 1024;         // tiles that a launch of the keys and scatter kernels should have at least
 // Counts per (tile, slice) kept from the keys to the scatter kernel: room for one per occurrence and kCountRoomMin
@@ -219,9 +222,10 @@ struct Pack {
 // Byte offsets of the workspace's arrays for one (plan, B, nnz).
 struct Layout {
     size_t state, packed_offsets, keys, inverse, seg_ent, marks, unique, seg, ghot, ticket,
-           clear_begin, slice_total, slice_nu, nu_group, slice_cursor, slice_info, tgeom, fscan, tile_hist, rec, bitmap, total;
+           clear_begin, slice_total, slice_nu, nu_group, long_list, slice_cursor, slice_info, tgeom, fscan, tile_hist, rec, bitmap, total;
     size_t clear_bytes;          // what the partitioned path clears before its first kernel: per-pack state,
                                  // slice totals and distinct-key counts, contiguous from `clear_begin`
+    int32_t n_long_max;          // slices of many records that can be listed
     int32_t n_groups;            // groups of 64 slices, with room for a started one per pack
     int32_t sum_stride;          // 64-bit words from one group's sum to the next
     int32_t n_slices;            // slices of all tables for this call

@@ -71,6 +71,8 @@ static Layout layout_with(const pk_plan* plan, int32_t B, int64_t nnz, size_t ro
     L.n_groups       = (int32_t)(slices / 64 + (int64_t)P + 1);
     L.sum_stride     = sum_stride;
     L.nu_group       = take(L.small ? 0 : (size_t)L.n_groups * sum_stride * 16);       // sums of 64 slices' distinct keys, and what is before each
+    L.n_long_max     = L.small ? 0 : (int32_t)std::min<int64_t>(std::min<int64_t>(nnz / kLongSlice, slices), kLongSlicesMax);
+    L.long_list      = take(L.small ? 0 : (size_t)(1 + L.n_long_max) * 4);             // how many, then which
     L.clear_bytes    = off - L.clear_begin;
     L.slice_cursor   = take(L.small ? 0 : (size_t)slices * 4);
     L.slice_info     = take(L.small ? 0 : (size_t)slices * sizeof(SliceInfo));
