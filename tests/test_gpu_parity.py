@@ -394,12 +394,14 @@ def test_config5_shrunk_long_sequences_bf16():
 
 
 @pytest.mark.timeout(600)
-def test_tables_above_the_fine_slice_limit():
-    """Two tables of 140 M rows: thousands of slices per table in the large-batch dedup."""
+@pytest.mark.parametrize("n_fields,row_scale", [(2, 140.0), (1, 280.0)])
+def test_tables_of_many_slices(n_fields, row_scale):
+    """Two tables of 140 M rows (thousands of slices of 64 K keys in the large-batch dedup), and one of 280 M rows (slices
+    of 128 K keys: the shape for tables above 2^28 rows)."""
     free, _ = torch.cuda.mem_get_info()
     if free < 90 * 2**30:
         pytest.skip("needs 90 GiB of free device memory")
-    run_config(2, n_fields=2, row_scale=140.0, plan_opts=dict(debug=2))
+    run_config(2, n_fields=n_fields, row_scale=row_scale, plan_opts=dict(debug=2))
 
 
 def test_config2_full_size():
