@@ -73,7 +73,9 @@ typedef struct {
                                    bit 2: its blocks count for themselves what they would
                                    else wait for other blocks to publish;
                                    bit 3 (this one raises error bit 1): every 64th slice
-                                   of a pack gives up waiting at once                      */
+                                   of a pack gives up waiting at once;
+                                   bit 4: the sums its blocks publish stand side by side,
+                                   as where pk_forward_static's scratch ends               */
 } pk_plan_opts;
 
 typedef struct pk_plan pk_plan;   /* opaque, host memory, owned by the library */

@@ -505,7 +505,7 @@ __device__ __forceinline__ int wave_sum(int v)
     for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-constexpr int kSumFan = 64;
+static_assert(kSumFan == 64, "a wavefront's lanes look at the slices of a group, the last two at the groups");
 constexpr int kLooks = 64, kPatience = 16;               // 16 times 64 looks of about 3 us
 constexpr int kNotSeen = -2;
 constexpr uint32_t kNuReady = 0x80000000u, kNuBegun = 0x40000000u;     // begun: a slice of more records than are kept, by its block

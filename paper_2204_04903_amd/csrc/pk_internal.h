@@ -38,6 +38,7 @@ constexpr int kSliceOccLarge = 3072;       // occurrences per slice aimed at whe
 constexpr int kLongSlice = 16384;          // records from which a slice is listed, up to kLongSlicesMax of them (8192: the same, but a block more per 8192 records)
 constexpr int kLongSlicesMax = 256;
 constexpr int32_t kListedFlag = 1 << 30;   // in SliceInfo::table
+constexpr int kSumFan = 64;                // slices whose distinct keys add up in one word (SliceSums)
 constexpr int32_t kSumStride = 16;         // 64-bit words of a cache line: the sums of the slices' distinct keys stand this far apart
 constexpr int64_t kTilesMin = 1024;         // tiles that a launch of the keys and scatter kernels should have at least
 // Counts per (tile, slice) kept from the keys to the scatter kernel: room for one per occurrence and kCountRoomMin
@@ -226,7 +227,7 @@ struct Layout {
     size_t clear_bytes;          // what the partitioned path clears before its first kernel: per-pack state,
                                  // slice totals and distinct-key counts, contiguous from `clear_begin`
     int32_t n_long_max;          // slices of many records that can be listed
-    int32_t n_groups;            // groups of 64 slices, with room for a started one per pack
+    int32_t n_groups;            // groups of kSumFan slices, with room for a started one per pack
     int32_t sum_stride;          // 64-bit words from one group's sum to the next
     int32_t n_slices;            // slices of all tables for this call
     int32_t max_table_slices;    // most slices any table has

@@ -68,9 +68,9 @@ static Layout layout_with(const pk_plan* plan, int32_t B, int64_t nnz, size_t ro
     L.state          = take(P * sizeof(PackState));
     L.slice_total    = take(L.small ? 0 : (size_t)slices * 4);
     L.slice_nu       = take(L.small ? 0 : (size_t)slices * 4);
-    L.n_groups       = (int32_t)(slices / 64 + (int64_t)P + 1);
+    L.n_groups       = (int32_t)(slices / kSumFan + (int64_t)P + 1);
     L.sum_stride     = sum_stride;
-    L.nu_group       = take(L.small ? 0 : (size_t)L.n_groups * sum_stride * 16);       // sums of 64 slices' distinct keys, and what is before each
+    L.nu_group       = take(L.small ? 0 : (size_t)L.n_groups * sum_stride * 16);       // sums of kSumFan slices' distinct keys, and what is before each
     L.n_long_max     = L.small ? 0 : (int32_t)std::min<int64_t>(std::min<int64_t>(nnz / kLongSlice, slices), kLongSlicesMax);
     L.long_list      = take(L.small ? 0 : (size_t)(1 + L.n_long_max) * 4);             // how many, then which
     L.clear_bytes    = off - L.clear_begin;
@@ -120,7 +120,7 @@ static Layout layout_with(const pk_plan* plan, int32_t B, int64_t nnz, size_t ro
 Layout make_layout(const pk_plan* plan, int32_t B, int64_t nnz, size_t room)
 {
     const Layout L = layout_with(plan, B, nnz, room, kSumStride);
-    return L.total <= room ? L : layout_with(plan, B, nnz, room, 1);
+    return L.total <= room && !(plan->opts.debug & 16) ? L : layout_with(plan, B, nnz, room, 1);
 }
 
 }  // namespace pk
@@ -161,7 +161,7 @@ pk_status pk_plan_create(const pk_table_desc* tables, int32_t n_tables, const pk
         return fail(PK_EINVAL, "pk_plan_create: negative option");
     if (opts && (opts->interleave_groups < 0 || opts->interleave_groups > 8))
         return fail(PK_EINVAL, "pk_plan_create: interleave_groups must be 0 (automatic) to 8");
-    if (opts && (opts->debug < 0 || opts->debug > 15))
+    if (opts && (opts->debug < 0 || opts->debug > 31))
         return fail(PK_EINVAL, "pk_plan_create: unknown debug bits");
     if (opts && opts->field_volume)
         for (int32_t f = 0; f < n_fields; ++f)

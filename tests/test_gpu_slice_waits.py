@@ -1,5 +1,6 @@
 """The large-batch dedup where blocks cannot wait for the blocks before them: their numbers counted from the records give
-the same results bit for bit, and a block that gives up ends the pack's others at once and leaves the tables alone."""
+the same results bit for bit, and a block that gives up ends the pack's others at once and leaves the tables alone.  And the
+published sums side by side, as where the scratch of calls that cannot allocate ends."""
 import time
 
 import numpy as np
@@ -38,7 +39,7 @@ def test_numbers_counted_from_the_records(name):
     ids, d_ids, d_off = _inputs(case, B, np.random.default_rng(sum(map(ord, name))))
     tables, fields = [(c[0], c[2], c[3]) for c in case], [(t, c[4]) for t, c in enumerate(case)]
     got = []
-    for debug in (2, 2 | 4):
+    for debug in (2, 2 | 4, 2 | 16):
         layer = PackedEmbedding(tables, fields, debug=debug)
         try:
             for W in layer.W:
@@ -58,10 +59,11 @@ def test_numbers_counted_from_the_records(name):
             got.append(([d["unique"] for d in ctx], [A.cpu() for A in layer.A]))
         finally:
             layer.close()
-    for u0, u1 in zip(got[0][0], got[1][0]):
-        assert np.array_equal(u0, u1)
-    for a0, a1 in zip(got[0][1], got[1][1]):              # (sums in fp64, in another order)
-        assert torch.allclose(a0, a1, rtol=1e-6, atol=0.0)
+    for other in got[1:]:
+        for u0, u1 in zip(got[0][0], other[0]):
+            assert np.array_equal(u0, u1)
+        for a0, a1 in zip(got[0][1], other[1]):           # (sums in fp64, in another order)
+            assert torch.allclose(a0, a1, rtol=1e-6, atol=0.0)
 
 
 @pytest.mark.parametrize("rows", [400 << 16, (4096 << 16) + 5])

@@ -81,3 +81,37 @@ def test_static_forward_near_the_limit_leaves_the_stored_counts_out():
         assert np.array_equal(ref.view(np.uint32), got.view(np.uint32))
     finally:
         layer.close()
+
+
+def test_static_forward_at_the_largest_call_it_takes():
+    # there the stored counts are left out and the slices' sums stand side by side (tests/test_layout.py)
+    from paper_2204_04903_amd import binding as pk
+    from paper_2204_04903_amd.layer import PackedEmbedding
+    tables, fields = [(6_000_000, 4, 0), (900, 8, 0)], [(0, 0), (1, 1)]
+    layer = PackedEmbedding(tables, fields)
+    try:
+        lo, hi = 1 << 18, 1 << 20
+        rng = np.random.default_rng(903)
+        layer.load_table(0, rng.standard_normal((6_000_000, 4)).astype(np.float32))
+        layer.load_table(1, rng.standard_normal((900, 8)).astype(np.float32))
+        ids = torch.from_numpy(np.concatenate([rng.integers(0, 6_000_000, size=hi), rng.integers(0, 900, size=hi)])).cuda()
+        out = torch.empty((hi, layer.out_dim), device="cuda")
+        stream = torch.cuda.current_stream().cuda_stream
+        while hi - lo > 1:
+            B = (lo + hi) // 2
+            offsets = torch.arange(2 * B + 1, dtype=torch.int32, device="cuda")
+            try:
+                pk.pk_forward_static(layer.plan, layer.W, ids, offsets, B, 2 * B, out, out.stride(0), stream)
+                lo = B
+            except pk.PkError as e:
+                assert e.status == pk.PK_EWORKSPACE
+                hi = B
+        torch.cuda.synchronize()
+        assert (1 << 18) < lo < (1 << 20) - 1
+        pr = dict(ids=np.concatenate([rng.integers(0, 6_000_000, size=lo), rng.integers(0, 900, size=lo)]).astype(np.int64),
+                  offsets=np.arange(2 * lo + 1, dtype=np.int32))
+        print(f"[static] the largest: B={lo}", flush=True)
+        ref, got = _run_pair(layer, pr, lo)
+        assert np.array_equal(ref.view(np.uint32), got.view(np.uint32))
+    finally:
+        layer.close()
