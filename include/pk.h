@@ -158,8 +158,9 @@ pk_status pk_forward(const pk_plan* plan, void* const* W,
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  The same
  * kernels as pk_forward, with the workspace, the plan's device metadata and the
  * scan descriptors in a static device array that the library holds on every GPU it
- * runs on until the process ends (32 MiB, and 2.4 MiB for the one-launch path's
- * lists of slices, which do not count against the limit below); neither this call nor anything it
+ * runs on until the process ends (32 MiB, and 2.5 MiB for the one-launch path's
+ * lists of slices and the sums of large batches' slices, which do not count against
+ * the limit below); neither this call nor anything it
  * runs calls hipMalloc, hipFree or another allocating routine (no internal streams
  * or events either: every kernel runs on hip_stream).  Arguments as for pk_forward,
  * without the workspace.  PK_EWORKSPACE when the plan's metadata plus the

@@ -39,7 +39,8 @@ using namespace pk;
 // cannot allocate.  Every GPU the library runs on holds its own copy until the process ends.
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
 constexpr size_t kStaticCutBytes = kSmallCuts * ((size_t)kSmallSlicesMax * sizeof(SmallSlice) + 256);   // and the lists of slices
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticCutBytes];
+constexpr size_t kStaticSumsBytes = (size_t)80 << 10;      // and up to that much of the slices' sums, a word or two per pack
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticSumsBytes + kStaticCutBytes];
 
 // One translation unit; the kernels and their launch helpers are kept in section files:
 //   dev_common.h   block scans, folding hash, combined LDS counters, tile order
@@ -343,7 +344,10 @@ pk_status pk_forward_static(const pk_plan* plan, void* const* W, const int64_t* 
     MetaImage mi;
     build_meta_image(plan, &mi);
     const size_t meta = mi.total - mi.cuts;      // what counts against the limit of the plan's metadata
-    const size_t room = kStaticScratchBytes - std::min(meta, kStaticScratchBytes);
+    // (the slices' sums do not count against it: a plan of hundreds of packs has more of them than the running sums that
+    // calls at the limit had room for)
+    const size_t sums = std::min(make_layout(plan, B, nnz, 0).sums_least, kStaticSumsBytes);
+    const size_t room = kStaticScratchBytes - std::min(meta, kStaticScratchBytes) + sums;
     const Layout L = make_layout(plan, B, nnz, room);
     if (L.total > room)
         return fail(PK_EWORKSPACE, "pk_forward_static: this plan, B and nnz need " + std::to_string(meta + L.total) +

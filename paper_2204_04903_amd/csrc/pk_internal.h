@@ -229,6 +229,7 @@ struct Layout {
     int32_t n_long_max;          // slices of many records that can be listed
     int32_t n_groups;            // groups of kSumFan slices, with room for a started one per pack
     int32_t sum_stride;          // 64-bit words from one group's sum to the next
+    size_t sums_least;           // bytes of the sums side by side
     int32_t n_slices;            // slices of all tables for this call
     int32_t max_table_slices;    // most slices any table has
     int32_t log_max;             // partitioned path: largest slice (log2 of its keys) of this call

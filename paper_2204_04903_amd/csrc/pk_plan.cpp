@@ -70,6 +70,7 @@ static Layout layout_with(const pk_plan* plan, int32_t B, int64_t nnz, size_t ro
     L.slice_nu       = take(L.small ? 0 : (size_t)slices * 4);
     L.n_groups       = (int32_t)(slices / kSumFan + (int64_t)P + 1);
     L.sum_stride     = sum_stride;
+    L.sums_least     = L.small ? 0 : align_up((size_t)L.n_groups * 16);
     L.nu_group       = take(L.small ? 0 : (size_t)L.n_groups * sum_stride * 16);       // sums of kSumFan slices' distinct keys, and what is before each
     L.n_long_max     = L.small ? 0 : (int32_t)std::min<int64_t>(std::min<int64_t>(nnz / kLongSlice, slices), kLongSlicesMax);
     L.long_list      = take(L.small ? 0 : (size_t)(1 + L.n_long_max) * 4);             // how many, then which

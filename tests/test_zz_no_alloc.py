@@ -115,3 +115,22 @@ def test_static_forward_at_the_largest_call_it_takes():
         assert np.array_equal(ref.view(np.uint32), got.view(np.uint32))
     finally:
         layer.close()
+
+
+def test_static_forward_of_many_packs_at_the_limit():
+    # 250 packs: the sums of the slices' distinct keys, 16 bytes and more a pack, do not count against the scratch's limit,
+    # which is a call of 807 935 occurrences from what such a plan needs otherwise
+    from paper_2204_04903_amd.layer import PackedEmbedding
+    T, B, nnz = 250, 3231, 807_935
+    layer = PackedEmbedding([(50, 1 + t, 0) for t in range(T)], [(t, 0) for t in range(T)])
+    try:
+        rng = np.random.default_rng(904)
+        for W in layer.W:
+            W.uniform_(-1.0, 1.0)
+        offsets = np.arange(T * B + 1, dtype=np.int32)
+        offsets[-1] = nnz                             # (one-hot but for the last bag)
+        print(f"[static] many packs: B={B} nnz={nnz}", flush=True)
+        ref, got = _run_pair(layer, dict(ids=rng.integers(0, 50, size=nnz).astype(np.int64), offsets=offsets), B)
+        assert np.array_equal(ref.view(np.uint32), got.view(np.uint32))
+    finally:
+        layer.close()
