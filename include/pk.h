@@ -70,10 +70,10 @@ typedef struct {
     int32_t debug;              /* for tests and measurements; results do not depend on it.
                                    bit 0: no internal streams, every kernel on hip_stream;
                                    bit 1: the partitioned dedup also for small batches;
-                                   bit 2: its blocks count for themselves what they would
-                                   else wait for other blocks to publish;
+                                   bit 2: the dedup's blocks count for themselves what they
+                                   would else wait for other blocks to publish;
                                    bit 3 (this one raises error bit 1): every 64th slice
-                                   of a pack gives up waiting at once;
+                                   of a pack gives up waiting at once (partitioned dedup);
                                    bit 4: the sums its blocks publish stand side by side,
                                    as where pk_forward_static's scratch ends               */
 } pk_plan_opts;
@@ -146,8 +146,10 @@ size_t    pk_workspace_bytes(const pk_plan* plan, int32_t B, int64_t nnz);
  * counts through descriptors in device memory that the library owns and that
  * are shared by all calls on a plan: such calls on one plan must follow one
  * another (one stream, or streams ordered by events as for the two stages
- * below).  A block's wait for another block is bounded; giving up raises bit 1
- * of the error word. */
+ * below).  In these and in larger calls blocks take numbers that other blocks
+ * publish, but wait for none that may not have started: calls on other plans, and
+ * anything else, may run beside them.  A wait for a running block is bounded;
+ * giving up raises bit 1 of the error word. */
 pk_status pk_forward(const pk_plan* plan, void* const* W,
                      const int64_t* ids, const int32_t* offsets, int32_t B, int64_t nnz,
                      float* out, int64_t out_row_stride,

@@ -63,12 +63,13 @@ __device__ __forceinline__ int upper_bound_i32(P a, int n, int x)
 }
 
 // ---------------------------------------------------------------------------
-// Blocks that need numbers from the blocks before them (the one-launch forward pass): block i takes item i and
-// nothing else, and an item waits only for lower items: the hardware starts the blocks of a launch in index
-// order, so whatever a block waits for belongs to a block that has started (or finished), however many blocks
-// the chip holds at once and whatever else runs beside the launch.  The wait is bounded all the same: running
-// out of patience raises bit 1 of the packs' error words; the kernels after it skip their work and the tables
-// stay as they are.
+// Blocks that need numbers from the blocks before them (the one-launch forward pass, the slices of large batches).  A block
+// publishes its own number before it waits, and waits for lower ones only.  A lower block may not have started all the same:
+// workgroups go to the eight XCDs in turn and each XCD starts its share in index order but at its own pace, and a second
+// launch whose blocks wait may hold the places that the first one's need.  So patience is short, and a block that has run
+// out of it counts what it lacks itself (count_before, small_count_before): it ends whatever else runs.  Only a block
+// that says it has begun is waited for longer, bounded all the same: giving up raises bit 1 of the pack's error word, the
+// pack's other waiting blocks see it and end too, and the kernels after it skip their work: the tables stay as they are.
 // ---------------------------------------------------------------------------
 constexpr int kSpinLimit = 1 << 22;
 

@@ -152,6 +152,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     sa.marks = marks; sa.ghot = ghot; sa.ticket = ws.at<int32_t>(L.ticket); sa.dmax = L.dmax;
     sa.n_slices = L.n_slices;
     sa.out_dim = plan->out_dim;
+    sa.waits = plan->opts.debug >> 2 & 3;
 #ifdef PK_PHASE_TIMES
     static long long* g_pt = nullptr;
     if (!g_pt) { (void)hipMalloc(&g_pt, (size_t)16 * 65536 * 8); }
@@ -263,7 +264,6 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
         if (L.n_slices > 0) {
             sa.slice_nu = ws.at<uint32_t>(L.slice_nu);
             sa.nu_group = ws.at<uint64_t>(L.nu_group); sa.n_groups = L.n_groups; sa.sum_stride = L.sum_stride;
-            sa.waits = plan->opts.debug >> 2 & 3;
             sa.long_list = ws.at<int32_t>(L.long_list); sa.n_long_max = L.n_long_max;
             const dim3 sgrid((unsigned)(L.n_slices + L.n_long_max));
             if (L.log_max == kSliceLogFine) PK_LAUNCH("pk_slices", pk_slices_kernel, sgrid, dim3(kFineThreads), tf_lds, sa);
