@@ -423,7 +423,8 @@ struct TableField { int32_t field, slot, col, pool; };
 struct SliceArgs {
     const TableMeta* tmeta; const TableField* tfields; int T;
     const PackMeta* pm; const int32_t* slot_field; PackState* st; int P;
-    int F, B; int64_t nnz; int target, log_max;
+    int F, B; int64_t nnz; int log_max;
+    int patience;                                               // small batches: looks at what other blocks publish (beside what is read first)
     const int64_t* ids; const int32_t* offsets; const SmallSlice* small_slices; const int2* slot_info;   // small batches: the block finds its occurrences itself
     const SliceInfo* slice_info; uint2* rec;                    // large batches: the slice's records
     const TableCut* cut;                                        // ... and the tables' cuts for this batch

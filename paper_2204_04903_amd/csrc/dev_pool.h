@@ -329,12 +329,7 @@ pk_fused_kernel(SliceArgs a, PoolJob pj, int slice_blocks, int meta_blocks)
     static_assert(kSmallLdsWords >= 3 * 4096 + 2, "the field scan must fit the block's LDS");
     if ((int)blockIdx.x < slice_blocks) {
         // (the kernel's arguments where they stand: `a` is the first of them)
-        SliceArgsPtr args = (SliceArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-        if (!__builtin_amdgcn_readfirstlane(small_slice_body<(WAVES > 4), MANY>(args, blockIdx.x, s_main, s_dyn, SmallBefore{kNotSeen, 0}))) {
-            args = forget<true>(args);
-            const SmallBefore before = small_count_before<MANY>(args, blockIdx.x, s_main);
-            small_slice_body<true, MANY>(forget<true>(args), blockIdx.x, s_main, s_dyn, before);
-        }
+        small_slice_body<(WAVES > 4), MANY>((SliceArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x, s_main, s_dyn);
         return;
     }
     PK_PT(a, blockIdx.x, 0);

@@ -148,69 +148,63 @@ template <bool V> struct BoolTag { static constexpr bool value = V; };
 
 // Distinct keys of the pack's slices before `slice`, and whether one of them has found bad offsets, for a block that
 // has waited long: a block before it may not have started, and may not be able to while this one holds its place (as
-// count_before of the large batches).  What is published is taken, the rest counted from the IDs.  The block then begins its
-// slice again with that number, in code of its own: with the counting inside the first attempt, or the attempts in a loop,
-// what is kept across it costs registers (26 fields of 64 a launch: 10.78 us without this, 10.95 with, 11.5 inside).
+// count_before of the large batches).  What is published is taken, the rest counted from the IDs, 64 K keys at a time.  One
+// wavefront; s_map: kSmallOffs words.  (Its registers cost the launch some of what waiting alone takes: 26 fields of 64
+// 10.9 -> 11.2 us, 889 tables of 70 samples 60 -> 62 a step, 26 fields of 8192 none.  The block begun again in code of its
+// own, with nothing kept meanwhile: 11.0, 63 to 66 and 3 % for launches of many blocks.)
 constexpr int kSmallPatience = 2048;                       // looks of about 2.5 us
-struct SmallBefore { int n; uint32_t flags; };             // n: kNotSeen, or the number
 template <bool MANY>
-__device__ __forceinline__ SmallBefore small_count_before(SliceArgsPtr a, int slice, int32_t* s_main)
+__device__ __forceinline__ void small_count_before(SliceArgsPtr a, int slice, uint32_t* s_map, uint32_t* before, uint32_t* flags)
 {
-    constexpr int NTH = kSliceThreads;
-    const int tid = threadIdx.x, B = a->B, n_all = (int)a->nnz;
-    uint32_t* s_map = reinterpret_cast<uint32_t*>(s_main);
-    uint32_t* s_out = s_map + kSmallWords;                 // published word (two halves), number counted
-    SmallBefore before{0, 0};
+    const int lane = threadIdx.x & 63, B = a->B, n_all = (int)a->nnz;
+    uint32_t sum = 0, bad = 0;
 #pragma nounroll
     for (int j = slice_at(a, slice)->pack_first; j < slice; ++j) {
-        __syncthreads();                                   // the block's LDS is consumed
-        if (tid == 0) {
-            const uint64_t d = a->waits & kWaitNever ? 0 : small_load(as_global(a->desc) + j);
-            s_out[0] = (uint32_t)d; s_out[1] = (uint32_t)(d >> 32); s_out[2] = 0;
-        }
-        for (int w = tid; w < kSmallWords; w += NTH) s_map[w] = 0;
-        __syncthreads();
-        const int d_lo = __builtin_amdgcn_readfirstlane((int)s_out[0]);
-        const uint32_t d_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_out[1]);
-        if (d_hi >> 16) {
-            before.n += d_lo;
-            before.flags |= d_hi >> 8 & 1u;
+        const uint64_t d = small_load(as_global(a->desc) + j);
+        if (a->patience >= 0 && __all((d >> 48) != 0)) {
+            sum += (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)d);
+            bad |= (uint32_t)(d >> 40) & 1u;
             continue;
         }
         const SmallSlicePtr sj = slice_at(a, j);
         const int lg = sj->log_keys, nf = MANY ? sj->n_fields : 1;
         const int b_lo = (int)((int64_t)B * sj->idx / sj->n_table_slices), b_hi = (int)((int64_t)B * (sj->idx + 1) / sj->n_table_slices);
-        int viol = 0;
-        for (int f = 0; f < nf; ++f) {
-            const int field = MANY ? as_global(a->tfields)[sj->field_begin + f].field : sj->field0;
-            const int32_t* offs = as_global(a->offsets) + (int64_t)field * B;
-            const int fb = offs[0], fe = offs[B], q0 = min(max(fb, 0), n_all), q1 = min(max(fe, q0), n_all);
-            for (int b = b_lo + tid; b < b_hi; b += NTH) viol |= offs[b] > offs[b + 1] || offs[b] < fb || offs[b + 1] > fe;
-            for (int q = q0 + tid; q < q1; q += NTH) {
-                const uint32_t k = fold_id(as_global(a->ids)[q], sj->rows, sj->magic), kl = k & ((1u << lg) - 1u);
-                if ((k >> lg) == (uint32_t)sj->idx) atomicOr(&s_map[kl >> 5], 1u << (kl & 31));
-            }
-        }
-        before.flags |= __builtin_amdgcn_readfirstlane(__syncthreads_or(viol)) ? 1u : 0u;
         int c = 0;
-        for (int w = tid; w < kSmallWords; w += NTH) c += __popc(s_map[w]);
-        c = wave_sum(c);
-        if ((tid & 63) == 0 && c) atomicAdd(&s_out[2], (uint32_t)c);
-        __syncthreads();
-        before.n += __builtin_amdgcn_readfirstlane((int)s_out[2]);
+#pragma nounroll
+        for (uint32_t w0 = 0; w0 < 1u << lg; w0 += 32u * kSmallOffs) {
+#pragma nounroll
+            for (int i = lane; i < kSmallOffs; i += 64) s_map[i] = 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma nounroll
+            for (int f = 0; f < nf; ++f) {
+                const int field = MANY ? as_global(a->tfields)[sj->field_begin + f].field : sj->field0;
+                const int32_t* offs = as_global(a->offsets) + (int64_t)field * B;
+                const int fb = offs[0], fe = offs[B], q0 = min(max(fb, 0), n_all), q1 = min(max(fe, q0), n_all);
+#pragma nounroll
+                for (int b = b_lo + lane; b < b_hi; b += 64) bad |= offs[b] > offs[b + 1] || offs[b] < fb || offs[b + 1] > fe;
+#pragma nounroll
+                for (int q = q0 + lane; q < q1; q += 64) {
+                    const uint32_t k = fold_id(as_global(a->ids)[q], sj->rows, sj->magic), kl = (k & ((1u << lg) - 1u)) - w0;
+                    if ((k >> lg) == (uint32_t)sj->idx && kl < 32u * kSmallOffs) atomicOr(&s_map[kl >> 5], 1u << (kl & 31));
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma nounroll
+            for (int i = lane; i < kSmallOffs; i += 64) c += __popc(s_map[i]);
+        }
+        sum += (uint32_t)wave_sum(c);
     }
-    __syncthreads();
-    return before;
+    *before = sum;
+    *flags = __any(bad) ? 1u : 0u;
 }
 
-// MANY: some table of the plan has several fields.  Returns false, with the slice's number published but nothing written,
-// where the numbers of the slices before did not come; it is called again then, with them.
+// MANY: some table of the plan has several fields
 template <bool LEAN, bool MANY>
-__device__ __forceinline__ bool small_slice_body(SliceArgsPtr a, int slice, int32_t* s_main, int32_t* s_tf, SmallBefore known)
+__device__ __forceinline__ void small_slice_body(SliceArgsPtr a, int slice, int32_t* s_main, int32_t* s_tf)
 {
     constexpr int NTH = kSliceThreads, NW = NTH / 64;
     int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));                         // (nothing that follows from it is kept for a second call)
+    asm volatile("" : "+v"(tid));                          // (what shuffles and scans derive from the index is formed where it is used: 5 to 8 registers spilled, not 13)
     const int lane = tid & 63, wv = tid >> 6;
     uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_main);
     uint32_t* s_pre = s_bits + kSmallWords;
@@ -222,7 +216,7 @@ __device__ __forceinline__ bool small_slice_body(SliceArgsPtr a, int slice, int3
     __shared__ int s_n, s_before, s_flag, s_base;
     __shared__ SmallCtx s_ctx;
     const int F = a->F, B = a->B;
-    const int patience = a->waits & kWaitNever ? 0 : kSmallPatience;       // (read here, where a wait for it costs nothing)
+    const int patience = a->patience;                      // (read here, with what is waited for anyway)
     const int64_t nnz = a->nnz;
     const int32_t* __restrict__ offsets = as_global(a->offsets);
     const int64_t* __restrict__ ids = as_global(a->ids);
@@ -290,12 +284,12 @@ __device__ __forceinline__ bool small_slice_body(SliceArgsPtr a, int slice, int3
         }
         if (lane == 0) s_red[wv] = sum;
     }
-    bad = __builtin_amdgcn_readfirstlane(__syncthreads_or(bad));
+    bad = __syncthreads_or(bad);
     sum = make_int4(0, 0, 0, 0);
     for (int w = 0; w < NW && w * 64 < F; ++w) { const int4 x = s_red[w]; sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w; }
     if (bad) {                                             // every block sees the same boundaries: nobody publishes, nobody waits
         if (ss->is_last && tid == 0) { as_global(a->st)[ss->pack].n_unique = 0; as_global(a->st)[ss->pack].error = 1; }
-        return true;
+        return;
     }
     if (tid == 0) { s_ctx.pstart = sum.x; s_ctx.nnz_p = sum.z; s_ctx.rec_before = sum.y - sum.x; s_ctx.q0 = q0; }
     PK_PT(*a, slice, 1);
@@ -423,7 +417,7 @@ __device__ __forceinline__ bool small_slice_body(SliceArgsPtr a, int slice, int3
     if (wv == 0) {
         uint64_t* desc = as_global(a->desc) + slice;
         uint64_t* gd = as_global(a->gdesc) + (ss->pack_first / kDescGroup + ss->pack);     // the pack's groups (packs never share one)
-        if (lane == 0 && known.n < 0) {
+        if (lane == 0) {
             const uint64_t v = ((uint64_t)1 << 48) | ((uint64_t)own_flags << 40) | (uint32_t)n_u;     // count of slices | flags | distinct keys
             ack0 = atomicExch((unsigned long long*)desc, (unsigned long long)v);
             ack1 = atomicAdd((unsigned long long*)gd + g, (unsigned long long)v);
@@ -446,28 +440,37 @@ __device__ __forceinline__ bool small_slice_body(SliceArgsPtr a, int slice, int3
     auto finish_wait = [&]() {                             // wavefront 0: distinct keys of the slices before
         uint64_t* desc = as_global(a->desc) + slice;
         uint64_t* gd = as_global(a->gdesc) + (ss->pack_first / kDescGroup + ss->pack);
-        int left = known.n >= 0 ? 0 : patience;
-        auto waits = [&](bool missing) {                   // another look, if something is missing and there is patience left
-            if (!__any(missing) || left <= 0) return false;
-            --left;
+        bool gave_up = patience < 0;
+        int spins = 0;
+        while (__any(lane < r && (d_own >> 48) == 0)) {
+            if (++spins > patience) { gave_up = true; break; }
             __builtin_amdgcn_s_sleep(1);
-            return true;
-        };
-        while (waits(lane < r && (d_own >> 48) == 0))
             if (lane < r && (d_own >> 48) == 0) d_own = small_load(desc - 1 - lane);
+        }
         uint32_t u = lane < r ? (uint32_t)d_own : 0u, fl = lane < r ? (uint32_t)(d_own >> 40) & 1u : 0u;
         for (int k0 = 0; k0 < g; k0 += 64) {               // a group is complete when all its slices have added themselves
             const bool mine = k0 + lane < g;
             if (k0 && mine) d_grp = small_load(gd + k0 + lane);
-            while (waits(mine && (d_grp >> 48) != kDescGroup))
+            while (__any(mine && (d_grp >> 48) != kDescGroup)) {
+                if (++spins > patience) { gave_up = true; break; }
+                __builtin_amdgcn_s_sleep(1);
                 if (mine && (d_grp >> 48) != kDescGroup) d_grp = small_load(gd + k0 + lane);
+            }
             if (mine) { u += (uint32_t)d_grp; fl |= ((uint32_t)(d_grp >> 40) & 0xFFu) ? 1u : 0u; }
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) { u += __shfl_xor(u, o, 64); fl |= __shfl_xor(fl, o, 64); }
+        if (__builtin_expect(gave_up, 0)) {
+            small_count_before<MANY>(a, slice, reinterpret_cast<uint32_t*>(s_offs), &u, &fl);
+            if (nf == 1 && !onehot) {                      // (the offsets' place was used)
+                const int k = small_step(B);
+#pragma nounroll
+                for (int i = lane; i < ((B + (1 << k) - 1) >> k) + 1; i += 64) s_offs[i] = as_global(a->offsets)[(int64_t)ss->field0 * B + min(i << k, B)];
+            }
+        }
         if (lane == 0) {
-            s_base = known.n >= 0 ? known.n : left <= 0 ? kNotSeen : (int)u;
-            s_flag = (int)((known.n >= 0 ? known.flags : fl) | own_flags);
+            s_base = (int)u;
+            s_flag = (int)(fl | own_flags);
         }
     };
     // The slice's distinct keys (ascending) in their place, the pack's totals.  Returns false when the sums cannot be
@@ -530,7 +533,6 @@ __device__ __forceinline__ bool small_slice_body(SliceArgsPtr a, int slice, int3
         int tot;
         const int ex = block_excl_scan<NTH, true>(s, &tot);      // (its barriers also publish what wavefront 0 found)
         PK_PT(*a, slice, 4);
-        if (__builtin_amdgcn_readfirstlane(s_base) == kNotSeen) return false;
         const bool ok = after_wait();
         if (ok) small_starts(a, ss, s_cnt, s_ctx.pstart, s_base, 0, n_u, s_ctx.rec_before + ex, per);
         __syncthreads();
@@ -607,8 +609,7 @@ __device__ __forceinline__ bool small_slice_body(SliceArgsPtr a, int slice, int3
             int tot;
             const int ex = block_excl_scan<NTH, true>(s, &tot);
             if (r0 == 0) {
-                if (__builtin_amdgcn_readfirstlane(s_base) == kNotSeen) return false;
-                ok = after_wait();
+                        ok = after_wait();
                 a = forget<LEAN>(a);
                 ss = slice_at(a, slice);
             }
@@ -650,5 +651,4 @@ __device__ __forceinline__ bool small_slice_body(SliceArgsPtr a, int slice, int3
             }
         }
     }
-    return true;
 }

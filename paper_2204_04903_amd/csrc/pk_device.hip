@@ -164,7 +164,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
     // ---- small batches: dedup (and pooling) in one launch ----
     if (L.small && do_dedup) {
         const bool fuse_pool = do_pool && !hot && (int)order.size() <= kPoolPacks;
-        sa.target = 0; sa.log_max = kSliceLogMax;
+        sa.patience = sa.waits & kWaitNever ? -1 : kSmallPatience; sa.log_max = kSliceLogMax;
         sa.desc = ds->small_desc; sa.gdesc = ds->small_desc + kSmallSlicesMax; sa.done = ds->small_done;
         PoolJob pj{};
         int nb = 0;
@@ -193,7 +193,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
         return fail(PK_EOVERFLOW, std::string(who) + ": fields and tables together exceed what the dedup kernels stage in LDS");
     static_assert((1024 + 1 + kTableSlicesMax) * 4 <= 64 * 1024, "a tile's bag offsets and a longest table's slices fit LDS");
     if (do_dedup && !L.small) {
-        sa.target = kSliceOccLarge; sa.log_max = L.log_max;
+        sa.log_max = L.log_max;
         sa.desc = nullptr; sa.gdesc = nullptr; sa.done = nullptr;
         sa.slice_info = ws.at<SliceInfo>(L.slice_info); sa.rec = ws.at<uint2>(L.rec);
         sa.cut = ws.at<TableCut>(L.tgeom);
@@ -204,7 +204,7 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
         const int64_t n_clear4 = (int64_t)((L.clear_bytes - state_bytes) / 16);
         const size_t setup_lds = scan_words * 4;
         PK_LAUNCH("pk_setup", pk_setup_kernel, dim3(blocks_for(n_clear4, kSetupThreads, 256)), dim3(kSetupThreads), setup_lds,
-                  ws.at<uint4>(L.slice_total), n_clear4, offsets, B, F, P, T, nnz, sa.target, sa.log_max, ds->fmeta, ds->pmeta,
+                  ws.at<uint4>(L.slice_total), n_clear4, offsets, B, F, P, T, nnz, kSliceOccLarge, sa.log_max, ds->fmeta, ds->pmeta,
                   ds->sort_tables, ds->slot_field, st, packed_offsets, seg, ws.at<TableCut>(L.tgeom), L.n_slices,
                   ws.at<int32_t>(L.fscan));
         const dim3 key_grid(blocks_for(n_tiles, 1, 256 * 8));
