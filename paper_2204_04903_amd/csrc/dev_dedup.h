@@ -312,8 +312,8 @@ pk_slice_scan_kernel(const TableCut* __restrict__ cut, int T,
 // touched slice with one global add, and then places its records from block-local cursors: one LDS word per slice
 // of the tile's table, first its count, then its cursor (a table has up to kTableSlicesMax).  Bound by the latency of
 // the keys and by its 8-byte stores, so a wavefront's keys are asked for eight at a time without a condition: under
-// one, each was waited for before the next (200 fields beside the pooling 361 -> 155 us, 26 one-hot fields of 65536
-// 23 -> 17, bf16 sequences 120 -> 68; touching the tile's keys ahead then gives nothing more).
+// one, each was waited for before the next (averages beside the pooling: 200 fields 269 -> 149 us, bf16 sequences 118 ->
+// 64; 26 one-hot fields of 65536 23 -> 17; touching the tile's keys ahead then gives nothing more).
 __global__ void __launch_bounds__(NT)
 pk_scatter_kernel(const int32_t* __restrict__ offsets, int B, int F, int BT, int64_t nnz, int log_max,
                   const FieldMeta* __restrict__ fmeta, const TableCut* __restrict__ cut,
