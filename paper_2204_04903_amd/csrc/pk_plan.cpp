@@ -72,7 +72,10 @@ static Layout layout_with(const pk_plan* plan, int32_t B, int64_t nnz, size_t ro
     L.sum_stride     = sum_stride;
     L.sums_least     = L.small ? 0 : align_up((size_t)L.n_groups * 16);
     L.nu_group       = take(L.small ? 0 : (size_t)L.n_groups * sum_stride * 16);       // sums of kSumFan slices' distinct keys, and what is before each
-    L.n_long_max     = L.small ? 0 : (int32_t)std::min<int64_t>(std::min<int64_t>(nnz / kLongSlice, slices), kLongSlicesMax);
+    // (room for the list is a block each in the slices' launch, which waits for a place beside the pooling: 1 % of a
+    // thousand-table step.  Where a table has fewer occurrences than a listed slice, few slices are that long)
+    L.n_long_max     = L.small || nnz < kLongSlice * (int64_t)plan->sort_tables.size() ? 0
+                       : (int32_t)std::min<int64_t>(std::min<int64_t>(nnz / kLongSlice, slices), kLongSlicesMax);
     L.long_list      = take(L.small ? 0 : (size_t)(1 + L.n_long_max) * 4);             // how many, then which
     L.clear_bytes    = off - L.clear_begin;
     L.slice_cursor   = take(L.small ? 0 : (size_t)slices * 4);
