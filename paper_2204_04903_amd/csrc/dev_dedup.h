@@ -614,6 +614,7 @@ __device__ __forceinline__ void slice_body(SliceArgsPtr a, int slice, int32_t* s
     constexpr int WMAX = 1 << (LOGMAX - 5), WPT = WMAX / NTH;       // bitmap words, of them per thread
     constexpr int KEEP = kSliceKeep;
     static_assert(WPT == 4 && KEEP * NTH <= 0xFFFF && KEEP * NTH <= RANKS, "a thread's words are two 16-byte reads; ranks and places of kept records fit 16 bits");
+    static_assert(WMAX <= RANKS, "the counters' room holds another slice's bitmap");
     const int tid = threadIdx.x;
     uint2* s_bp = reinterpret_cast<uint2*>(s_main);        // a word of the bitmap, set bits before it
     int32_t* s_cnt = s_main + 2 * WMAX;
