@@ -170,6 +170,76 @@ __device__ __forceinline__ void pool_tile_by(const PoolJob& job, const PoolPack&
     while (cb < last) flush();                             // (only after rejected offsets: every bag is written, whatever they hold)
 }
 
+// A tile of two bags to a group, for fields of several IDs a bag.  A group takes the g-th longest bag of the tile and the
+// g-th shortest, so that all groups have about as many positions, and a bag begins with a round: bags end at the ends of
+// rounds only.  (In a walk across bags the groups' bags end at different positions of a round, and the forty instructions
+// that write a bag are gone through at nearly every one of them where 32 groups have bags of 25 IDs.)  What is left is the
+// rate of row requests: 200 fields of 25 IDs, batch 4096, beside the dedup chain 427 us a launch, 401 this way, 1024 bags
+// alone 63 and 59.  Fields of kPairAvg IDs a bag and more: 1000 fields of 5.5 lose more to rounds that are not full than
+// they gain (242 us, 254).
+constexpr int kPairAvg = 10;
+template <bool BF16, int R>
+__device__ __forceinline__ void pool_tile_pairs(const PoolJob& job, const PoolPack& k, int item, int j, const FieldMeta& m, const int32_t* offs,
+                                                int32_t* s_off)
+{
+    const int lane = threadIdx.x & 63, B = job.B;
+    const KeySrc<false, R> src(job, k, m);
+    const int b0 = (item - j * k.tiles) * (128 >> k.sh), nb = min(128 >> k.sh, B - b0);     // (at most 64)
+    for (int i = lane; i <= nb; i += 64) s_off[i] = min(max(offs[b0 + i], 0), src.n);   // whatever the offsets hold, no read leaves the keys
+    auto wave_order = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); };
+    wave_order();
+    int32_t* s_order = s_off + 128;                        // the bags, longest first
+    {
+        const int len = lane < nb ? min(max(s_off[lane + 1] - s_off[lane], 0), 1 << 24) : 0, key = len << 6 | lane;
+        int rank = 0;
+        for (int i = 0; i < nb; ++i) rank += __builtin_amdgcn_readlane(key, i) > key;
+        if (lane < nb) s_order[rank] = lane;
+    }
+    wave_order();
+    const int li = lane & ((1 << k.sh) - 1), g = lane >> k.sh;
+    if (g >= nb || 4 * li >= k.D) return;
+    const int d0 = lane_col(li, k.D);
+    const int i2 = (128 >> k.sh) - 1 - g;                  // (the tile's last half may be missing)
+    const int other = i2 < nb ? s_order[i2] : -1;
+    const int q2 = s_off[max(other, 0)], e2 = s_off[max(other, 0) + 1];
+    int bag = s_order[g], q = s_off[bag], c0 = q, ce = s_off[bag + 1];
+    bool more = other >= 0;
+    float* out = as_global(job.out) + (size_t)b0 * (size_t)job.out_stride + m.col + d0;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    uint32_t kv[R];
+    src.raw(q, kv);                                        // (an empty bag: keys of its neighbour or the room past the last, not used)
+#pragma nounroll
+    for (;;) {
+        float x[R][4];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const uint32_t row = i == 0 || q + i < ce ? src.key(kv, i) : src.key(kv, 0);     // past the bag: a row that is there anyway, not used
+            load_w4<BF16, false>(pool_row<BF16, false>(k, row, d0), k.D, x[i]);
+        }
+        const bool end = q + R >= ce;
+        src.raw(end ? (more ? q2 : q) : q + R, kv);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if (q + i < ce) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[v] += (double)x[i][v];
+            }
+        }
+        q += R;
+        if (end) {
+            const int len = ce - c0;
+            const float scale = m.pool == PK_MEAN && len > 0 ? 1.0f / (float)len : 1.0f;
+            float y[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) { y[v] = (float)acc[v] * scale; acc[v] = 0.0; }
+            store_f32x4<false>(out + (size_t)bag * (size_t)job.out_stride, k.D, y);
+            if (!more) break;
+            more = false;
+            bag = other; q = c0 = q2; ce = e2;
+        }
+    }
+}
+
 // Rounds of R positions; of one where the field's runs hold about one (a round's idle places ask for a row again: 26
 // one-hot fields of 2048 bags, one bag a run, pooled in 7.4 us with rounds of eight, 6.0 with rounds of one; for runs of
 // three IDs on average rounds of four are slower than of eight, the longest run then takes two).
@@ -184,6 +254,9 @@ __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k,
     if constexpr (R == 8) {
         const int64_t per_run = ((int64_t)offs[job.B] - offs[0]) * k.run;      // times B
         if (2 * per_run <= (int64_t)3 * job.B) return pool_tile_by<BF16, NARROW, HYB, IDS, 1>(job, k, item, j, m, offs, s_off);
+        if constexpr (!IDS && !HYB && !NARROW) {           // (rows of four columns and fewer have more bags to a tile than lanes)
+            if (k.run == 2 && k.sh >= 1 && per_run >= (int64_t)2 * kPairAvg * job.B) return pool_tile_pairs<BF16, R>(job, k, item, j, m, offs, s_off);
+        }
     }
     pool_tile_by<BF16, NARROW, HYB, IDS, R>(job, k, item, j, m, offs, s_off);
 }
