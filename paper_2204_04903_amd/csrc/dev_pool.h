@@ -243,7 +243,7 @@ __device__ __forceinline__ void pool_tile_pairs(const PoolJob& job, const PoolPa
 // Rounds of R positions; of one where the field's runs hold about one (a round's idle places ask for a row again: 26
 // one-hot fields of 2048 bags, one bag a run, pooled in 7.4 us with rounds of eight, 6.0 with rounds of one; for runs of
 // three IDs on average rounds of four are slower than of eight, the longest run then takes two).
-template <bool BF16, bool NARROW, bool HYB, bool IDS, int R>
+template <bool BF16, bool NARROW, bool HYB, bool IDS, bool PAIRS, int R>
 __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k, int item, int32_t* s_off)
 {
     const int j = item / k.tiles;
@@ -254,7 +254,7 @@ __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k,
     if constexpr (R == 8) {
         const int64_t per_run = ((int64_t)offs[job.B] - offs[0]) * k.run;      // times B
         if (2 * per_run <= (int64_t)3 * job.B) return pool_tile_by<BF16, NARROW, HYB, IDS, 1>(job, k, item, j, m, offs, s_off);
-        if constexpr (!IDS && !HYB && !NARROW) {           // (rows of four columns and fewer have more bags to a tile than lanes)
+        if constexpr (PAIRS && !NARROW) {           // (rows of four columns and fewer have more bags to a tile than lanes)
             if (k.run == 2 && k.sh >= 1 && per_run >= (int64_t)2 * kPairAvg * job.B) return pool_tile_pairs<BF16, R>(job, k, item, j, m, offs, s_off);
         }
     }
@@ -278,7 +278,7 @@ __device__ __forceinline__ bool pool_seq_likely(const int32_t* offs, int n, int 
 }
 
 // Sequence fields: a wavefront per bag, R positions per group and round.
-template <bool BF16, bool NARROW, bool HYB, bool IDS, int R>
+template <bool BF16, bool NARROW, bool HYB, bool IDS, bool PAIRS, int R>
 __device__ __forceinline__ int pool_coop(const PoolJob& job, const PoolPack& k, int idx)
 {
     const int lane = threadIdx.x & 63, B = job.B;
@@ -344,14 +344,14 @@ __device__ __forceinline__ int pool_coop(const PoolJob& job, const PoolPack& k, 
 // the code for a pack's kind
 #define PK_POOL_KINDS(FN, RES, ...)                                                             \
     switch (k.kind) {                                                                           \
-        case 0: RES FN<false, false, HYB, IDS, R>(__VA_ARGS__); break;                          \
-        case 1: RES FN<true, false, HYB, IDS, R>(__VA_ARGS__); break;                           \
-        case 2: RES FN<false, true, HYB, IDS, R>(__VA_ARGS__); break;                           \
-        case 3: RES FN<true, true, HYB, IDS, R>(__VA_ARGS__); break;                            \
+        case 0: RES FN<false, false, HYB, IDS, PAIRS, R>(__VA_ARGS__); break;                   \
+        case 1: RES FN<true, false, HYB, IDS, PAIRS, R>(__VA_ARGS__); break;                    \
+        case 2: RES FN<false, true, HYB, IDS, PAIRS, R>(__VA_ARGS__); break;                    \
+        case 3: RES FN<true, true, HYB, IDS, PAIRS, R>(__VA_ARGS__); break;                     \
     }
 
 // one wavefront's share of a launch's pooling: `wave` counts its wavefronts
-template <bool HYB, bool IDS, int R>
+template <bool HYB, bool IDS, bool PAIRS, int R>
 __device__ __forceinline__ void pool_wave(const PoolJob& job, int wave, int32_t* s_off)
 {
     if (wave < job.n_items) {
@@ -373,13 +373,15 @@ __device__ __forceinline__ void pool_wave(const PoolJob& job, int wave, int32_t*
     }
 }
 
-template <bool HYB>
+// PAIRS: for launches where two bags of a group hold eight IDs or more on average (without that code the others' loop is
+// 1 % faster: 26 one-hot fields of 65536 74.2 us, 75.2 with it)
+template <bool HYB, bool PAIRS>
 __global__ void __launch_bounds__(NT, 6)
 pk_pool_kernel(PoolJob job)
 {
     __shared__ int32_t s_off[NT / 64][64 * kRunMax + 1];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    pool_wave<HYB, false, 8>(job, (int)blockIdx.x * (NT / 64) + wv, s_off[wv]);
+    pool_wave<HYB, false, PAIRS, 8>(job, (int)blockIdx.x * (NT / 64) + wv, s_off[wv]);
 }
 
 // Small batches: the whole forward pass is ONE launch.  The first blocks are the slices of the
@@ -412,7 +414,7 @@ pk_fused_kernel(SliceArgs a, PoolJob pj, int slice_blocks, int meta_blocks)
         return;
     }
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    pool_wave<false, true, 4>(pj, ((int)blockIdx.x - slice_blocks - meta_blocks) * (kSliceThreads / 64) + wv,
+    pool_wave<false, true, false, 4>(pj, ((int)blockIdx.x - slice_blocks - meta_blocks) * (kSliceThreads / 64) + wv,
                               s_main + wv * (64 * kRunMax + 1));
     PK_PT(a, blockIdx.x, 8);
 }

@@ -242,8 +242,8 @@ static pk_status forward_impl(const pk_plan* plan, DeviceState* ds_given, int st
                 pj.keys = keys; pj.po = packed_offsets; pj.st = st;
                 // (the cooperating wavefronts follow the tiles in the same blocks)
                 const dim3 grid(blocks_for((int64_t)pj.n_items + coop_waves, NT / 64, 1 << 30));
-                if (hot) PK_LAUNCH("pk_pool", pk_pool_kernel<true>, grid, dim3(NT), 0, pj);
-                else PK_LAUNCH("pk_pool", pk_pool_kernel<false>, grid, dim3(NT), 0, pj);
+                const auto kernel = hot ? pk_pool_kernel<true, false> : pj.pack[0].run == 2 && nnz >= 4 * n_bags ? pk_pool_kernel<false, true> : pk_pool_kernel<false, false>;
+                PK_LAUNCH("pk_pool", kernel, grid, dim3(NT), 0, pj);
             }
         }
         stream = main_stream;
