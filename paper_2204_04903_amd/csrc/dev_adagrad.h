@@ -26,6 +26,7 @@ struct AdaPack {
     void* W; float* A; HotView hv;
     uint32_t addr_max;           // largest element offset into grad_out at which a chunk of the pack can start
     int32_t D, sh, p;            // dimension, log2 of the lanes per row, pack
+    int32_t batch;               // log2 of the keys that a wavefront takes at once (pk_adagrad_batch_kernel)
     int32_t kind;                // 1: bf16, 2: mean pooling (entries carry bag lengths), 4: dimension below four
 };
 constexpr int kAdaPacks = 16;    // packs of one launch
@@ -42,6 +43,7 @@ struct AdaJob {
 struct GradView {
     const float* grad;           // + the lane's first column
     const uint32_t* ent;
+    const double* recip;         // 1 / L of bag lengths below kRecips, in LDS
     uint32_t gstride, out_dim, addr_max;
     int D;
 };
@@ -57,49 +59,96 @@ __device__ __forceinline__ double recip_len(uint32_t L)
     return fma(r, fma(-d, r, 1.0), r);
 }
 
-// acc += sum over the entries [s, s+UN), [s+step, s+step+UN), ... below s_end of scale * gradient chunk.
+// where entries' chunks stand: inside grad_out, whatever the list holds
+template <int N>
+__device__ __forceinline__ void grad_places(const GradView& g, uint32_t (&at)[N])
+{
+    if (g.gstride != g.out_dim) {                          // padded gradient rows
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const uint32_t b = at[k] / g.out_dim;
+            at[k] = b * g.gstride + (at[k] - b * g.out_dim);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) at[k] = min(at[k], g.addr_max);
+}
+
+// Bag lengths whose reciprocals a block keeps in LDS (mean pooling): one read where the two Newton steps and their
+// conversions are nine instructions, in every lane, for every entry.
+constexpr uint32_t kRecips = 512;
+
+// a round's entries: the chunks' offsets and their bags' lengths (read past the range's end up to 3 entries far)
+template <bool MEAN> struct Entries { uint32_t v[MEAN ? 8 : 4]; };
+template <bool MEAN>
+__device__ __forceinline__ Entries<MEAN> load_entries(const GradView& g, uint32_t s)
+{
+    Entries<MEAN> e;
+    load_u32<4>(g.ent + (MEAN ? 2 : 1) * (size_t)s, e.v);
+    if constexpr (MEAN) load_u32<4>(g.ent + 2 * (size_t)s + 4, e.v + 4);
+    return e;
+}
+
+// acc += sum of scale * gradient chunk over the entries e of positions s to s + 3, of which those below s_end count (ALL:
+// every one).
 // The 1/L of mean pooling is formed and applied in double: the first Adagrad step of a row moves a weight by
 // lr*g/(|g|+eps), so where the gradients of a key cancel (|g| near eps) an error of 1e-8 in g is an error of
 // lr in the weight, and a float 1/L alone is off by 6e-8 of every term.
 // The chunks of a round are asked for without branches between them (the compiler would wait for each before
 // the next one's branch): where the range ends inside a round, its first chunk again, counted as zero.
-template <bool MEAN, bool NARROW, int UN>
+template <bool MEAN, bool NARROW, bool ALL, typename Fn>
+__device__ __forceinline__ void accum_round(double (&acc)[4], const GradView& g, const Entries<MEAN>& e, uint32_t s, uint32_t s_end, Fn&& meanwhile)
+{
+    uint32_t at[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) at[k] = e.v[MEAN ? 2 * k : k];
+    grad_places(g, at);
+    float x[4][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) load_f32x4<NARROW>(g.grad + (ALL || s + k < s_end ? at[k] : at[0]), g.D, x[k]);
+    double c[4] = {1.0, 1.0, 1.0, 1.0};
+    if constexpr (MEAN) {
+        if (max(max(e.v[1], e.v[3]), max(e.v[5], e.v[7])) < kRecips) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[k] = g.recip[e.v[2 * k + 1]];
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[k] = recip_len(e.v[2 * k + 1]);
+        }
+    }
+    meanwhile();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool on = ALL || k == 0 || s + k < s_end;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const double d = (double)(on ? x[k][v] : 0.f);
+            acc[v] = MEAN ? fma(c[k], d, acc[v]) : acc[v] + d;
+        }
+    }
+}
+
+// acc += the entries [s, s+4), [s+step, s+step+4), ... below s_end
+template <bool MEAN, bool NARROW>
 __device__ __forceinline__ void accum_range(double (&acc)[4], const GradView& g, uint32_t s, uint32_t s_end, uint32_t step)
 {
 #pragma nounroll
-    for (; s < s_end; s += step) {
-        uint32_t at[UN], L[UN];
-        if (MEAN) {                                        // (offset, bag length) pairs; read past the end up to 3 entries far
-            uint32_t e[2 * UN];
-            load_u32<UN>(g.ent + 2 * (size_t)s, e);
-            load_u32<UN>(g.ent + 2 * (size_t)s + UN, e + UN);
-#pragma unroll
-            for (int k = 0; k < UN; ++k) { at[k] = e[2 * k]; L[k] = e[2 * k + 1]; }
-        } else {
-            load_u32<UN>(g.ent + s, at);
-        }
-        if (g.gstride != g.out_dim) {                      // padded gradient rows
-#pragma unroll
-            for (int k = 0; k < UN; ++k) {
-                const uint32_t b = at[k] / g.out_dim;
-                at[k] = b * g.gstride + (at[k] - b * g.out_dim);
-            }
-        }
-        const uint32_t first = min(at[0], g.addr_max);     // never leave grad_out, whatever the list holds
-        float x[UN][4];
-#pragma unroll
-        for (int k = 0; k < UN; ++k) load_f32x4<NARROW>(g.grad + (s + k < s_end ? min(at[k], g.addr_max) : first), g.D, x[k]);
-#pragma unroll
-        for (int k = 0; k < UN; ++k) {
-            const bool on = k == 0 || s + k < s_end;
-            const double c = MEAN ? recip_len(L[k]) : 1.0;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const double d = (double)(on ? x[k][v] : 0.f);
-                acc[v] = MEAN ? fma(c, d, acc[v]) : acc[v] + d;
-            }
-        }
+    for (; s < s_end; s += step) accum_round<MEAN, NARROW, false>(acc, g, load_entries<MEAN>(g, s), s, s_end, [] {});
+}
+
+// The same for a long key's piece: nearly all its rounds are whole ones, and the next one's entries are on their way while
+// the chunks of this one are.
+template <bool MEAN, bool NARROW>
+__device__ __forceinline__ void accum_piece(double (&acc)[4], const GradView& g, uint32_t s, uint32_t s_end, uint32_t step)
+{
+    Entries<MEAN> e = load_entries<MEAN>(g, min(s, s_end - 1));
+#pragma nounroll
+    for (; s + 4 <= s_end; s += step) {
+        Entries<MEAN> next;
+        accum_round<MEAN, NARROW, true>(acc, g, e, s, s_end, [&] { next = load_entries<MEAN>(g, min(s + step, s_end - 1)); });
+        e = next;
     }
+    if (s < s_end) accum_round<MEAN, NARROW, false>(acc, g, e, s, s_end, [] {});
 }
 
 // one Adagrad step of the lane's columns of a row: a += g^2 ; w -= lr * g / (sqrt(a) + eps)
@@ -134,7 +183,7 @@ constexpr int kMarksPerBlock = 4;      // (16: the mixed layer 16 % slower, a bl
 constexpr int kLongBlocks = 768;
 
 template <bool BF16, bool MEAN, bool NARROW, bool HYB, bool TEAMS>
-__device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, double (*s_red)[64][4])
+__device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, const double* recip, double (*s_red)[64][4])
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const PackState* st = as_global(job.st) + k.p;
@@ -150,7 +199,7 @@ __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k
     const int lpr = 1 << k.sh, gpw = 64 >> k.sh, li = lane & (lpr - 1), g = lane >> k.sh;
     const int d0 = NARROW ? 0 : lane_col(li, k.D);
     const bool act = 4 * li < k.D;
-    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, (uint32_t)job.gstride,
+    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, recip, (uint32_t)job.gstride,
                       (uint32_t)job.out_dim, k.addr_max, k.D};
     for (; idx < n_mine; idx += stride) {
         const int m0 = (x * per + idx) * kMarksPerBlock + lane;
@@ -174,7 +223,7 @@ __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k
             const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, as_global(job.unique)[start + ku], k.D, d0);
             float w[4], ac[4];
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(a + (wv * gpw + g) * 4), (uint32_t)b, (uint32_t)(4 * gpw * (NT / 64)));
+            if (act) accum_piece<MEAN, NARROW>(acc, gv, (uint32_t)(a + (wv * gpw + g) * 4), (uint32_t)b, (uint32_t)(4 * gpw * (NT / 64)));
             if (fin && kn == 1) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }
             wave_group_sum(acc, lpr, 64);
             __syncthreads();                           // the previous piece's sums are consumed
@@ -230,7 +279,7 @@ constexpr int kTeam = 4;               // lane groups that share a key of more t
 // The other keys of a pack.  XCD x takes the x-th eighth of the keys (neighbouring keys share gradient
 // columns: one L2 then holds them), its wavefronts take consecutive handfuls.
 template <bool BF16, bool MEAN, bool NARROW, bool HYB, bool TEAMS>
-__device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride)
+__device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, const double* recip)
 {
     const int lane = threadIdx.x & 63;
     const PackState* st = as_global(job.st) + k.p;
@@ -244,7 +293,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
     const int u_end = U - (x * per) * gpw;
     const int d0 = NARROW ? 0 : lane_col(li, k.D);
     const bool act = 4 * li < k.D;
-    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, (uint32_t)job.gstride,
+    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, recip, (uint32_t)job.gstride,
                       (uint32_t)job.out_dim, k.addr_max, k.D};
     int s0 = 0, s1 = 0;
     uint32_t row = 0;
@@ -265,7 +314,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
             load_w4<BF16, NARROW>(r.w, k.D, w);
             load_f32x4<NARROW>(r.a, k.D, ac);
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
+            accum_range<MEAN, NARROW>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
             row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
         }
         uint64_t todo = __ballot(li == 0 && len > kColdMax && len <= kLongMin);
@@ -279,7 +328,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
                 const bool fin = g == 0 && act;
                 float w[4], ac[4];
                 double acc[4] = {0.0, 0.0, 0.0, 0.0};
-                if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(wa + 4 * g), (uint32_t)wb, (uint32_t)(4 * gpw));
+                if (act) accum_range<MEAN, NARROW>(acc, gv, (uint32_t)(wa + 4 * g), (uint32_t)wb, (uint32_t)(4 * gpw));
                 if (fin) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }    // (on their way while the groups are added up)
                 wave_group_sum(acc, lpr, 64);
                 if (fin) row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
@@ -300,7 +349,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
                 const int wa = __shfl(a, src, 64), sb = __shfl(b, src, 64), wb = kk < n ? sb : wa;
                 const uint32_t row_k = (uint32_t)__shfl((int)r0, src, 64);
                 double acc[4] = {0.0, 0.0, 0.0, 0.0};
-                if (act) accum_range<MEAN, NARROW, 4>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
+                if (act) accum_range<MEAN, NARROW>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
                 wave_group_sum(acc, lpr, lpr * team);
                 if (in_team == 0 && act && kk < n) {       // (asked for earlier, the row would not fit the registers)
                     const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, row_k, k.D, d0);
@@ -316,7 +365,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
 }
 
 // the code for a pack's kind
-#define PK_ADA_KINDS(FN, ...)                                                                   \
+#define PK_ADA_KINDS(FN, HYB, TEAMS, ...)                                                                   \
     switch (k.kind) {                                                                           \
         case 0: idx = FN<false, false, false, HYB, TEAMS>(__VA_ARGS__); break;                  \
         case 1: idx = FN<true, false, false, HYB, TEAMS>(__VA_ARGS__); break;                   \
@@ -334,16 +383,28 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
 // 57).  Wider rows have few keys to a handful and keep the registers (26 one-hot fields of 32 columns, a
 // step: 52 us, 54 with the teams' code).
 constexpr int kTeamDim = 16;
+
+// reciprocals of bag lengths, where some pack of the launch pools by the mean
+__device__ __forceinline__ void ada_recips(const AdaJob& job, double* s_recip)
+{
+    if (job.ent_mult == 2) {
+        for (uint32_t i = threadIdx.x; i < kRecips; i += NT) s_recip[i] = recip_len(i);
+        __syncthreads();
+    }
+}
+
 template <bool HYB, bool TEAMS>
 __global__ void __launch_bounds__(NT, 6)
 pk_adagrad_kernel(AdaJob job)
 {
     __shared__ double s_red[NT / 64][64][4];               // per-wavefront sums of a long key's piece
+    __shared__ double s_recip[kRecips];
+    ada_recips(job, s_recip);
     if ((int)blockIdx.x < job.hot_blocks) {
         int idx = blockIdx.x >> 3;
         for (int i = 0; i < job.n_packs; ++i) {
             const AdaPack& k = job.pack[i];
-            PK_ADA_KINDS(ada_long_keys, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_red)
+            PK_ADA_KINDS(ada_long_keys, HYB, TEAMS, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip, s_red)
         }
         return;
     }
@@ -352,6 +413,165 @@ pk_adagrad_kernel(AdaJob job)
     int idx = (kb >> 3) * (NT / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (int i = 0; i < job.n_packs; ++i) {
         const AdaPack& k = job.pack[i];
-        PK_ADA_KINDS(ada_keys, job, k, idx, kb & 7, stride)
+        PK_ADA_KINDS(ada_keys, HYB, TEAMS, job, k, idx, kb & 7, stride, s_recip)
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Large batches.  A wavefront takes batches of 2^k.batch consecutive keys, a lane per key at first: its segment, its row,
+// its first entry, the next batches' on their way.  Then the keys are taken by their number of occurrences, one, few, more, a
+// lane group each (or a team of groups), so that a wavefront's groups do about the same.  Two thirds of the keys have one
+// occurrence: their entries are there, so row and gradient chunk are asked for at once.  Against handfuls of
+// consecutive keys, each taking rounds of four entries: 150 M vector instructions for 200 fields of 21 M IDs, 86 M now.  What is
+// left is the rate of line requests (26 M reads, of them 7 M for rows, and 11 M writes): with more wavefronts or
+// fewer, or more rows in flight in each, the times are the same.  200 fields 650 us a launch, 590; 1000 fields of 8 and 16
+// columns 418, 399; bf16 sequences 253, 212; the mixed layer of 1 M IDs 83, 70; 26 one-hot fields of 65536 126, 128.  A small batch
+// (26 one-hot fields of 8192) is a chain of loads, one longer here: 20 us, 23.
+// ---------------------------------------------------------------------------
+// batches of the XCD's eighth of U keys
+__device__ __forceinline__ int ada_batches(int U, int batch, int x, int* per)
+{
+    const int n = (U + (1 << batch) - 1) >> batch;
+    *per = (n + 7) >> 3;
+    return max(0, min(*per, n - x * *per));
+}
+
+template <bool BF16, bool MEAN, bool NARROW, bool HYB, bool TEAMS>
+__device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, const double* recip)
+{
+    const int lane = threadIdx.x & 63;
+    const PackState* st = as_global(job.st) + k.p;
+    const int U = st->error ? 0 : st->n_unique, start = st->start;
+    int per;
+    const int n_mine = ada_batches(U, k.batch, x, &per), u0 = (x * per) << k.batch;
+    if (idx >= n_mine) return idx - n_mine;
+    const int lpr = 1 << k.sh, gpw = 64 >> k.sh, li = lane & (lpr - 1), g = lane >> k.sh;
+    const int32_t* seg = as_global(job.seg) + start + k.p + u0;
+    const uint32_t* uq = as_global(job.unique) + start + u0;
+    const int u_end = U - u0;
+    const int d0 = NARROW ? 0 : lane_col(li, k.D);
+    const bool act = 4 * li < k.D;
+    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, recip, (uint32_t)job.gstride,
+                      (uint32_t)job.out_dim, k.addr_max, k.D};
+    struct Key { int a, b; uint32_t row; };                // a lane's key: its segment, its row
+    struct First { uint32_t at, L; };                      // its first entry
+    auto fetch = [&](int c) {
+        const int u = (c << k.batch) + lane, v = min(u, u_end - 1);      // (past the end: some key, not used)
+        Key q{seg[v], seg[v + 1], uq[v]};
+        if (u >= u_end || lane >> k.batch) q.b = q.a;
+        return q;
+    };
+    auto fetch_first = [&](const Key& q) {
+        First f{0, 1};
+        if constexpr (MEAN) { uint32_t e[2]; load_u32<2>(gv.ent + 2 * (size_t)q.a, e); f.at = e[0]; f.L = e[1]; }
+        else f.at = gv.ent[q.a];
+        return f;
+    };
+    Key cur = fetch(idx), next = fetch(min(idx + stride, n_mine - 1));
+    First first = fetch_first(cur);
+#pragma nounroll
+    for (; idx < n_mine; idx += stride) {
+        const Key q = cur;
+        const First f = first;
+        cur = next;
+        first = fetch_first(cur);
+        next = fetch(min(idx + 2 * stride, n_mine - 1));
+        // the batch in the order of the keys' occurrences: one | up to 4 | up to kColdMax | up to kLongMin | others
+        const int len = q.b - q.a;
+        const uint64_t m1 = __ballot(len == 1), m4 = __ballot(len >= 2 && len <= 4), m8 = __ballot(len > 4 && len <= kColdMax);
+        const uint64_t mt = __ballot(len > kColdMax && len <= kLongMin), mo = ~(m1 | m4 | m8 | mt);
+        const int n1 = __popcll(m1), n4 = n1 + __popcll(m4), n8 = n4 + __popcll(m8), nt = n8 + __popcll(mt);
+        const bool none = len < 1 || len > kLongMin;
+        const uint64_t mm = none ? mo : len == 1 ? m1 : len <= 4 ? m4 : len <= kColdMax ? m8 : mt;
+        const int base = none ? nt : len == 1 ? 0 : len <= 4 ? n1 : len <= kColdMax ? n4 : n8;
+        const int to = (base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u))) * 4;
+        const uint32_t p_row = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)q.row);
+        if (n1) {
+            const uint32_t p_at = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)f.at);
+            const uint32_t p_L = MEAN ? (uint32_t)__builtin_amdgcn_ds_permute(to, (int)f.L) : 1u;
+#pragma nounroll
+            for (int h = 0; h < n1; h += gpw) {
+                const int i = h + g, src = min(i, n1 - 1);
+                const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, (uint32_t)__shfl((int)p_row, src, 64), k.D, d0);
+                const uint32_t L = MEAN ? (uint32_t)__shfl((int)p_L, src, 64) : 1u;
+                uint32_t at[1] = {(uint32_t)__shfl((int)p_at, src, 64)};
+                grad_places(gv, at);
+                float xg[4], w[4], a[4];
+                load_f32x4<NARROW>(gv.grad + at[0], k.D, xg);
+                load_w4<BF16, NARROW>(r.w, k.D, w);
+                load_f32x4<NARROW>(r.a, k.D, a);
+                if (i < n1 && act) {
+                    double acc[4];
+                    const double c = MEAN ? (L < kRecips ? recip[L] : recip_len(L)) : 1.0;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[v] = MEAN ? fma(c, (double)xg[v], 0.0) : 0.0 + (double)xg[v];
+                    row_step<BF16, NARROW>(r, k.D, acc, w, a, job.lr, job.eps);
+                }
+            }
+        }
+        if (n1 == nt) continue;
+        const int p_a = __builtin_amdgcn_ds_permute(to, q.a), p_b = __builtin_amdgcn_ds_permute(to, q.b);
+#pragma nounroll
+        for (int h = n1; h < n8; h += gpw) {
+            const int i = h + g, src = min(i, n8 - 1);
+            const int a = __shfl(p_a, src, 64), b = __shfl(p_b, src, 64);
+            const uint32_t row = (uint32_t)__shfl((int)p_row, src, 64);
+            if (i < n8 && act) {
+                const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, row, k.D, d0);
+                float w[4], ac[4];
+                load_w4<BF16, NARROW>(r.w, k.D, w);
+                load_f32x4<NARROW>(r.a, k.D, ac);
+                double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                accum_range<MEAN, NARROW>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
+                row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
+            }
+        }
+        // the keys of more occurrences, dealt to teams of `team` lane groups: all groups for a key alone, several keys side by side
+        const int n = nt - n8;
+        int team = gpw;
+        while (team > kTeam && gpw < team * n) team >>= 1;
+        const int in_team = g & (team - 1);
+#pragma nounroll
+        for (int k0 = 0; k0 < n; k0 += gpw / team) {
+            const int kk = k0 + g / team, src = n8 + min(kk, n - 1);
+            const int wa = __shfl(p_a, src, 64), sb = __shfl(p_b, src, 64), wb = kk < n ? sb : wa;
+            const uint32_t row = (uint32_t)__shfl((int)p_row, src, 64);
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            if (act) accum_range<MEAN, NARROW>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
+            wave_group_sum(acc, lpr, lpr * team);
+            if (in_team == 0 && act && kk < n) {           // (asked for earlier, the row would not fit the registers)
+                const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, row, k.D, d0);
+                float w[4], ac[4];
+                load_w4<BF16, NARROW>(r.w, k.D, w);
+                load_f32x4<NARROW>(r.a, k.D, ac);
+                row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
+            }
+        }
+    }
+    return idx - n_mine;
+}
+
+constexpr int64_t kBatchNnz = 3 << 20;  // occurrences, or
+constexpr int kBatchDim = 48;          // columns of the launch's widest rows, from which this kernel is taken
+__global__ void __launch_bounds__(NT, 6)
+pk_adagrad_batch_kernel(AdaJob job)
+{
+    __shared__ double s_red[NT / 64][64][4];               // per-wavefront sums of a long key's piece
+    __shared__ double s_recip[kRecips];
+    ada_recips(job, s_recip);
+    if ((int)blockIdx.x < job.hot_blocks) {
+        int idx = blockIdx.x >> 3;
+        for (int i = 0; i < job.n_packs; ++i) {
+            const AdaPack& k = job.pack[i];
+            PK_ADA_KINDS(ada_long_keys, false, true, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip, s_red)
+        }
+        return;
+    }
+    const int kb = (int)blockIdx.x - job.hot_blocks;       // (hot_blocks is a multiple of 8)
+    const int stride = (job.key_blocks >> 3) * (NT / 64);
+    int idx = (kb >> 3) * (NT / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (int i = 0; i < job.n_packs; ++i) {
+        const AdaPack& k = job.pack[i];
+        PK_ADA_KINDS(ada_batch_keys, false, true, job, k, idx, kb & 7, stride, s_recip)
     }
 }

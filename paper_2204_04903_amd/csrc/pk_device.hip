@@ -416,11 +416,24 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
                 // long keys: none in a batch that has no more occurrences than a key needs to be long
                 job.hot_blocks = nnz <= kLongMin ? 0 : (int)((blocks_for(nnz, kMarkStep * kMarksPerBlock, kLongBlocks) + job.n_packs + 7u) & ~7u);
                 job.key_blocks = (int)((blocks_for(nnz + (int64_t)job.n_packs * (64 >> sh), (64 >> sh) * (NT / 64), 256 * 16) + 7u) & ~7u);
+                // Large batches of many IDs or wide rows: the keys in batches by their occurrences.  (Fewer and narrower: the
+                // same or 1 % slower; 26 one-hot fields of 65536, 32 columns, 126 us and 128, four micro-batches of 2.8 M IDs, 8 and
+                // 16 columns, 1255 and 1273.  A Hot-storage's rows: not tried, the host's memory bounds those.)  Blocks for a third as
+                // many keys as there are occurrences, the others in a second round: a block without keys costs 2.5 ns (the
+                // mixed layer of 1 M IDs 75 us with blocks for half as many, 96 for all of them).
+                int widest = 0;
+                for (int q = 0; q < job.n_packs; ++q) widest = std::max(widest, job.pack[q].D);
+                const bool batches = !L.small && !hot && (nnz >= kBatchNnz || widest >= kBatchDim);
+                if (batches) {
+                    int log = 6;
+                    for (int q = 0; q < job.n_packs; ++q) log = std::min(log, job.pack[q].batch);
+                    job.key_blocks = (int)((blocks_for(nnz / 3 + ((int64_t)8 * job.n_packs << log), (int64_t)(NT / 64) << log, 256 * 32) + 7u) & ~7u);
+                }
                 const dim3 grid(job.hot_blocks + job.key_blocks);
                 bool teams = false;
                 for (int q = 0; q < job.n_packs; ++q) teams |= job.pack[q].D <= kTeamDim;
-                const auto kernel = hot ? (teams ? pk_adagrad_kernel<true, true> : pk_adagrad_kernel<true, false>)
-                                        : (teams ? pk_adagrad_kernel<false, true> : pk_adagrad_kernel<false, false>);
+                const auto kernel = batches ? pk_adagrad_batch_kernel : hot ? (teams ? pk_adagrad_kernel<true, true> : pk_adagrad_kernel<true, false>)
+                                            : (teams ? pk_adagrad_kernel<false, true> : pk_adagrad_kernel<false, false>);
                 PK_LAUNCH("pk_adagrad", kernel, grid, dim3(NT), 0, job);
                 job.n_packs = 0;
             }
@@ -430,7 +443,7 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
             const Pack& k = plan->packs[p];
             job.pack[job.n_packs++] = AdaPack{W[p], A[p], hot ? hot[p] : HotView{nullptr, nullptr, nullptr},
                                               (uint32_t)((int64_t)(B - 1) * grad_row_stride + plan->out_dim - k.dim), k.dim,
-                                              lane_shift(k.dim), p,
+                                              lane_shift(k.dim), p, ada_batch_log(nnz, k.dim),
                                               (k.dtype == PK_BF16 ? 1 : 0) | (k.has_mean ? 2 : 0) | (k.dim < 4 ? 4 : 0)};
         }
     }
