@@ -13,7 +13,7 @@
 //   longer:           a block of its own, which the launch starts first, in pieces of kPiece occurrences; the
 //                     pieces of a key with several add into a row of partial sums, the last one to arrive
 //                     takes the step.
-// A wavefront takes as many consecutive keys as it has lane groups and waits for nobody: no LDS, no barrier.
+// A wavefront takes as many consecutive keys as it has lane groups (in large batches more, ada_batch_keys) and waits for nobody.
 // Against tiles of occurrences decoded into LDS with a second launch for long keys (one launch per pack):
 // small layer 22.5 -> 18.4 us a step, mixed dtypes with dimensions that are no multiple of four 514 -> 315
 // (they ran one column per lane), bf16 sequences 725 -> 660.  What bounds it: with one-hot fields of 8192 bags (26 fields,
@@ -26,7 +26,7 @@ struct AdaPack {
     void* W; float* A; HotView hv;
     uint32_t addr_max;           // largest element offset into grad_out at which a chunk of the pack can start
     int32_t D, sh, p;            // dimension, log2 of the lanes per row, pack
-    int32_t batch;               // log2 of the keys that a wavefront takes at once (pk_adagrad_batch_kernel)
+    int32_t batch;               // log2 of the keys that a wavefront takes at once (ada_batch_keys)
     int32_t kind;                // 1: bf16, 2: mean pooling (entries carry bag lengths), 4: dimension below four
 };
 constexpr int kAdaPacks = 16;    // packs of one launch
@@ -377,46 +377,6 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
         case 7: if constexpr (TEAMS) idx = FN<true, true, true, HYB, TEAMS>(__VA_ARGS__); break;    \
     }
 
-// TEAMS: for launches with rows of kTeamDim columns and fewer, where a wavefront's handful has 16 to 64 keys: where
-// frequent IDs are neighbours, all of them can have more than kColdMax occurrences, and one after the other they take
-// longer than everything else (16 tables of 82 K occurrences, dimension 3: 238 us, in teams 79; dimension 8: 79,
-// 57).  Wider rows have few keys to a handful and keep the registers (26 one-hot fields of 32 columns, a
-// step: 52 us, 54 with the teams' code).
-constexpr int kTeamDim = 16;
-
-// reciprocals of bag lengths, where some pack of the launch pools by the mean
-__device__ __forceinline__ void ada_recips(const AdaJob& job, double* s_recip)
-{
-    if (job.ent_mult == 2) {
-        for (uint32_t i = threadIdx.x; i < kRecips; i += NT) s_recip[i] = recip_len(i);
-        __syncthreads();
-    }
-}
-
-template <bool HYB, bool TEAMS>
-__global__ void __launch_bounds__(NT, 6)
-pk_adagrad_kernel(AdaJob job)
-{
-    __shared__ double s_red[NT / 64][64][4];               // per-wavefront sums of a long key's piece
-    __shared__ double s_recip[kRecips];
-    ada_recips(job, s_recip);
-    if ((int)blockIdx.x < job.hot_blocks) {
-        int idx = blockIdx.x >> 3;
-        for (int i = 0; i < job.n_packs; ++i) {
-            const AdaPack& k = job.pack[i];
-            PK_ADA_KINDS(ada_long_keys, HYB, TEAMS, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip, s_red)
-        }
-        return;
-    }
-    const int kb = (int)blockIdx.x - job.hot_blocks;       // (hot_blocks is a multiple of 8)
-    const int stride = (job.key_blocks >> 3) * (NT / 64);
-    int idx = (kb >> 3) * (NT / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    for (int i = 0; i < job.n_packs; ++i) {
-        const AdaPack& k = job.pack[i];
-        PK_ADA_KINDS(ada_keys, HYB, TEAMS, job, k, idx, kb & 7, stride, s_recip)
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Large batches.  A wavefront takes batches of 2^k.batch consecutive keys, a lane per key at first: its segment, its row,
 // its first entry, the next batches' on their way.  Then the keys are taken by their number of occurrences, one, few, more, a
@@ -551,10 +511,28 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
     return idx - n_mine;
 }
 
-constexpr int64_t kBatchNnz = 3 << 20;  // occurrences, or
-constexpr int kBatchDim = 48;          // columns of the launch's widest rows, from which this kernel is taken
+// TEAMS: for launches with rows of kTeamDim columns and fewer, where a wavefront's handful has 16 to 64 keys: where
+// frequent IDs are neighbours, all of them can have more than kColdMax occurrences, and one after the other they take
+// longer than everything else (16 tables of 82 K occurrences, dimension 3: 238 us, in teams 79; dimension 8: 79,
+// 57).  Wider rows have few keys to a handful and keep the registers (26 one-hot fields of 32 columns, a
+// step: 52 us, 54 with the teams' code).
+constexpr int kTeamDim = 16;
+
+// reciprocals of bag lengths, where some pack of the launch pools by the mean
+__device__ __forceinline__ void ada_recips(const AdaJob& job, double* s_recip)
+{
+    if (job.ent_mult == 2) {
+        for (uint32_t i = threadIdx.x; i < kRecips; i += NT) s_recip[i] = recip_len(i);
+        __syncthreads();
+    }
+}
+
+// BATCH: the keys in batches, by ada_batch_keys; for launches of kBatchNnz occurrences, or of rows of kBatchDim columns, and more.
+constexpr int64_t kBatchNnz = 3 << 20;
+constexpr int kBatchDim = 48;
+template <bool HYB, bool TEAMS, bool BATCH>
 __global__ void __launch_bounds__(NT, 6)
-pk_adagrad_batch_kernel(AdaJob job)
+pk_adagrad_kernel(AdaJob job)
 {
     __shared__ double s_red[NT / 64][64][4];               // per-wavefront sums of a long key's piece
     __shared__ double s_recip[kRecips];
@@ -563,7 +541,7 @@ pk_adagrad_batch_kernel(AdaJob job)
         int idx = blockIdx.x >> 3;
         for (int i = 0; i < job.n_packs; ++i) {
             const AdaPack& k = job.pack[i];
-            PK_ADA_KINDS(ada_long_keys, false, true, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip, s_red)
+            PK_ADA_KINDS(ada_long_keys, HYB, TEAMS, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip, s_red)
         }
         return;
     }
@@ -572,6 +550,7 @@ pk_adagrad_batch_kernel(AdaJob job)
     int idx = (kb >> 3) * (NT / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (int i = 0; i < job.n_packs; ++i) {
         const AdaPack& k = job.pack[i];
-        PK_ADA_KINDS(ada_batch_keys, false, true, job, k, idx, kb & 7, stride, s_recip)
+        if constexpr (BATCH) { PK_ADA_KINDS(ada_batch_keys, HYB, TEAMS, job, k, idx, kb & 7, stride, s_recip) }
+        else { PK_ADA_KINDS(ada_keys, HYB, TEAMS, job, k, idx, kb & 7, stride, s_recip) }
     }
 }

@@ -422,7 +422,8 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
                 // many keys as there are occurrences, the others in a second round: a block without keys costs 2.5 ns (the
                 // mixed layer of 1 M IDs 75 us with blocks for half as many, 96 for all of them).
                 int widest = 0;
-                for (int q = 0; q < job.n_packs; ++q) widest = std::max(widest, job.pack[q].D);
+                bool teams = false;
+                for (int q = 0; q < job.n_packs; ++q) { widest = std::max(widest, job.pack[q].D); teams |= job.pack[q].D <= kTeamDim; }
                 const bool batches = !L.small && !hot && (nnz >= kBatchNnz || widest >= kBatchDim);
                 if (batches) {
                     int log = 6;
@@ -430,10 +431,9 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
                     job.key_blocks = (int)((blocks_for(nnz / 3 + ((int64_t)8 * job.n_packs << log), (int64_t)(NT / 64) << log, 256 * 32) + 7u) & ~7u);
                 }
                 const dim3 grid(job.hot_blocks + job.key_blocks);
-                bool teams = false;
-                for (int q = 0; q < job.n_packs; ++q) teams |= job.pack[q].D <= kTeamDim;
-                const auto kernel = batches ? pk_adagrad_batch_kernel : hot ? (teams ? pk_adagrad_kernel<true, true> : pk_adagrad_kernel<true, false>)
-                                            : (teams ? pk_adagrad_kernel<false, true> : pk_adagrad_kernel<false, false>);
+                const auto kernel = batches ? pk_adagrad_kernel<false, true, true>
+                                    : hot   ? (teams ? pk_adagrad_kernel<true, true, false> : pk_adagrad_kernel<true, false, false>)
+                                            : (teams ? pk_adagrad_kernel<false, true, false> : pk_adagrad_kernel<false, false, false>);
                 PK_LAUNCH("pk_adagrad", kernel, grid, dim3(NT), 0, job);
                 job.n_packs = 0;
             }
