@@ -13,7 +13,8 @@
 //   longer:           a block of its own, which the launch starts first, in pieces of kPiece occurrences; the
 //                     pieces of a key with several add into a row of partial sums, the last one to arrive
 //                     takes the step.
-// A wavefront takes as many consecutive keys as it has lane groups (in large batches more, ada_batch_keys) and waits for nobody.
+// A wavefront takes as many consecutive keys as it has lane groups (in large batches more, ada_batch_keys) and waits for
+// nobody; only the blocks of large batches whose plan pools by the mean fill a table first (ada_recips).
 // Against tiles of occurrences decoded into LDS with a second launch for long keys (one launch per pack):
 // small layer 22.5 -> 18.4 us a step, mixed dtypes with dimensions that are no multiple of four 514 -> 315
 // (they ran one column per lane), bf16 sequences 725 -> 660.  What bounds it: with one-hot fields of 8192 bags (26 fields,
@@ -26,8 +27,8 @@ struct AdaPack {
     void* W; float* A; HotView hv;
     uint32_t addr_max;           // largest element offset into grad_out at which a chunk of the pack can start
     int32_t D, sh, p;            // dimension, log2 of the lanes per row, pack
-    int32_t batch;               // log2 of the keys that a wavefront takes at once (ada_batch_keys)
     int32_t kind;                // 1: bf16, 2: mean pooling (entries carry bag lengths), 4: dimension below four
+    int32_t batch;               // log2 of the keys that a wavefront takes at once (ada_batch_keys)
 };
 constexpr int kAdaPacks = 16;    // packs of one launch
 struct AdaJob {
@@ -43,7 +44,7 @@ struct AdaJob {
 struct GradView {
     const float* grad;           // + the lane's first column
     const uint32_t* ent;
-    const double* recip;         // 1 / L of bag lengths below kRecips, in LDS
+    const double* recip;         // 1 / L of bag lengths below kRecips, in LDS (large batches' launches)
     uint32_t gstride, out_dim, addr_max;
     int D;
 };
@@ -74,9 +75,12 @@ __device__ __forceinline__ void grad_places(const GradView& g, uint32_t (&at)[N]
     for (int k = 0; k < N; ++k) at[k] = min(at[k], g.addr_max);
 }
 
-// Bag lengths whose reciprocals a block keeps in LDS (mean pooling): one read where the two Newton steps and their
-// conversions are nine instructions, in every lane, for every entry.
+// Bag lengths whose reciprocals a block of a large batch keeps in LDS (mean pooling; TABLE below): one read where the two
+// Newton steps and their conversions are nine instructions, in every lane, for every entry.  The other launches form
+// them: filling the table and the barrier after it would stand before the first load of a block that has little to do.
 constexpr uint32_t kRecips = 512;
+template <bool TABLE>
+__device__ __forceinline__ double recip_of(const GradView& g, uint32_t L) { return TABLE && L < kRecips ? g.recip[L] : recip_len(L); }
 
 // a round's entries: the chunks' offsets and their bags' lengths (read past the range's end up to 3 entries far)
 template <bool MEAN> struct Entries { uint32_t v[MEAN ? 8 : 4]; };
@@ -96,7 +100,7 @@ __device__ __forceinline__ Entries<MEAN> load_entries(const GradView& g, uint32_
 // lr in the weight, and a float 1/L alone is off by 6e-8 of every term.
 // The chunks of a round are asked for without branches between them (the compiler would wait for each before
 // the next one's branch): where the range ends inside a round, its first chunk again, counted as zero.
-template <bool MEAN, bool NARROW, bool ALL, typename Fn>
+template <bool MEAN, bool NARROW, bool ALL, bool TABLE, typename Fn>
 __device__ __forceinline__ void accum_round(double (&acc)[4], const GradView& g, const Entries<MEAN>& e, uint32_t s, uint32_t s_end, Fn&& meanwhile)
 {
     uint32_t at[4];
@@ -107,7 +111,7 @@ __device__ __forceinline__ void accum_round(double (&acc)[4], const GradView& g,
 #pragma unroll
     for (int k = 0; k < 4; ++k) load_f32x4<NARROW>(g.grad + (ALL || s + k < s_end ? at[k] : at[0]), g.D, x[k]);
     double c[4] = {1.0, 1.0, 1.0, 1.0};
-    if constexpr (MEAN) {
+    if constexpr (MEAN && TABLE) {
         if (max(max(e.v[1], e.v[3]), max(e.v[5], e.v[7])) < kRecips) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) c[k] = g.recip[e.v[2 * k + 1]];
@@ -120,6 +124,7 @@ __device__ __forceinline__ void accum_round(double (&acc)[4], const GradView& g,
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const bool on = ALL || k == 0 || s + k < s_end;
+        if constexpr (MEAN && !TABLE) c[k] = recip_len(e.v[2 * k + 1]);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const double d = (double)(on ? x[k][v] : 0.f);
@@ -129,15 +134,15 @@ __device__ __forceinline__ void accum_round(double (&acc)[4], const GradView& g,
 }
 
 // acc += the entries [s, s+4), [s+step, s+step+4), ... below s_end
-template <bool MEAN, bool NARROW>
+template <bool MEAN, bool NARROW, bool TABLE>
 __device__ __forceinline__ void accum_range(double (&acc)[4], const GradView& g, uint32_t s, uint32_t s_end, uint32_t step)
 {
 #pragma nounroll
-    for (; s < s_end; s += step) accum_round<MEAN, NARROW, false>(acc, g, load_entries<MEAN>(g, s), s, s_end, [] {});
+    for (; s < s_end; s += step) accum_round<MEAN, NARROW, false, TABLE>(acc, g, load_entries<MEAN>(g, s), s, s_end, [] {});
 }
 
-// The same for a long key's piece: nearly all its rounds are whole ones, and the next one's entries are on their way while
-// the chunks of this one are.
+// The same for a long key's piece in a large batch: nearly all its rounds are whole ones, and the next one's entries are on
+// their way while the chunks of this one are.
 template <bool MEAN, bool NARROW>
 __device__ __forceinline__ void accum_piece(double (&acc)[4], const GradView& g, uint32_t s, uint32_t s_end, uint32_t step)
 {
@@ -145,10 +150,10 @@ __device__ __forceinline__ void accum_piece(double (&acc)[4], const GradView& g,
 #pragma nounroll
     for (; s + 4 <= s_end; s += step) {
         Entries<MEAN> next;
-        accum_round<MEAN, NARROW, true>(acc, g, e, s, s_end, [&] { next = load_entries<MEAN>(g, min(s + step, s_end - 1)); });
+        accum_round<MEAN, NARROW, true, true>(acc, g, e, s, s_end, [&] { next = load_entries<MEAN>(g, min(s + step, s_end - 1)); });
         e = next;
     }
-    if (s < s_end) accum_round<MEAN, NARROW, false>(acc, g, e, s, s_end, [] {});
+    if (s < s_end) accum_round<MEAN, NARROW, false, true>(acc, g, e, s, s_end, [] {});
 }
 
 // one Adagrad step of the lane's columns of a row: a += g^2 ; w -= lr * g / (sqrt(a) + eps)
@@ -182,7 +187,11 @@ __device__ __forceinline__ void wave_group_sum(double (&acc)[4], int lpr, int la
 constexpr int kMarksPerBlock = 4;      // (16: the mixed layer 16 % slower, a block then has several pieces one after the other)
 constexpr int kLongBlocks = 768;
 
-template <bool BF16, bool MEAN, bool NARROW, bool HYB, bool TEAMS>
+// How a launch takes the keys of up to kLongMin occurrences: handfuls, a key of more than kColdMax at a time, or several in
+// teams of lane groups (ada_keys); batches by the number of occurrences (ada_batch_keys).
+constexpr int kHandfuls = 0, kTeams = 1, kBatches = 2;
+
+template <bool BF16, bool MEAN, bool NARROW, bool HYB, int KEYS>
 __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, const double* recip, double (*s_red)[64][4])
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -223,7 +232,11 @@ __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k
             const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, as_global(job.unique)[start + ku], k.D, d0);
             float w[4], ac[4];
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            if (act) accum_piece<MEAN, NARROW>(acc, gv, (uint32_t)(a + (wv * gpw + g) * 4), (uint32_t)b, (uint32_t)(4 * gpw * (NT / 64)));
+            if (act) {
+                const uint32_t s = (uint32_t)(a + (wv * gpw + g) * 4), step = (uint32_t)(4 * gpw * (NT / 64));
+                if constexpr (KEYS == kBatches) accum_piece<MEAN, NARROW>(acc, gv, s, (uint32_t)b, step);
+                else accum_range<MEAN, NARROW, false>(acc, gv, s, (uint32_t)b, step);
+            }
             if (fin && kn == 1) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }
             wave_group_sum(acc, lpr, 64);
             __syncthreads();                           // the previous piece's sums are consumed
@@ -278,8 +291,8 @@ constexpr int kTeam = 4;               // lane groups that share a key of more t
 
 // The other keys of a pack.  XCD x takes the x-th eighth of the keys (neighbouring keys share gradient
 // columns: one L2 then holds them), its wavefronts take consecutive handfuls.
-template <bool BF16, bool MEAN, bool NARROW, bool HYB, bool TEAMS>
-__device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, const double* recip)
+template <bool BF16, bool MEAN, bool NARROW, bool HYB, int KEYS>
+__device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride)
 {
     const int lane = threadIdx.x & 63;
     const PackState* st = as_global(job.st) + k.p;
@@ -293,7 +306,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
     const int u_end = U - (x * per) * gpw;
     const int d0 = NARROW ? 0 : lane_col(li, k.D);
     const bool act = 4 * li < k.D;
-    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, recip, (uint32_t)job.gstride,
+    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, nullptr, (uint32_t)job.gstride,
                       (uint32_t)job.out_dim, k.addr_max, k.D};
     int s0 = 0, s1 = 0;
     uint32_t row = 0;
@@ -314,12 +327,12 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
             load_w4<BF16, NARROW>(r.w, k.D, w);
             load_f32x4<NARROW>(r.a, k.D, ac);
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            accum_range<MEAN, NARROW>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
+            accum_range<MEAN, NARROW, false>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
             row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
         }
         uint64_t todo = __ballot(li == 0 && len > kColdMax && len <= kLongMin);
         if (todo == 0) continue;
-        if constexpr (!TEAMS) {                            // one key after the other
+        if constexpr (KEYS != kTeams) {                            // one key after the other
 #pragma nounroll
             for (; todo; todo &= todo - 1) {
                 const int lead = __ffsll((unsigned long long)todo) - 1;
@@ -328,7 +341,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
                 const bool fin = g == 0 && act;
                 float w[4], ac[4];
                 double acc[4] = {0.0, 0.0, 0.0, 0.0};
-                if (act) accum_range<MEAN, NARROW>(acc, gv, (uint32_t)(wa + 4 * g), (uint32_t)wb, (uint32_t)(4 * gpw));
+                if (act) accum_range<MEAN, NARROW, false>(acc, gv, (uint32_t)(wa + 4 * g), (uint32_t)wb, (uint32_t)(4 * gpw));
                 if (fin) { load_w4<BF16, NARROW>(r.w, k.D, w); load_f32x4<NARROW>(r.a, k.D, ac); }    // (on their way while the groups are added up)
                 wave_group_sum(acc, lpr, 64);
                 if (fin) row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
@@ -349,7 +362,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
                 const int wa = __shfl(a, src, 64), sb = __shfl(b, src, 64), wb = kk < n ? sb : wa;
                 const uint32_t row_k = (uint32_t)__shfl((int)r0, src, 64);
                 double acc[4] = {0.0, 0.0, 0.0, 0.0};
-                if (act) accum_range<MEAN, NARROW>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
+                if (act) accum_range<MEAN, NARROW, false>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
                 wave_group_sum(acc, lpr, lpr * team);
                 if (in_team == 0 && act && kk < n) {       // (asked for earlier, the row would not fit the registers)
                     const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, row_k, k.D, d0);
@@ -365,16 +378,16 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
 }
 
 // the code for a pack's kind
-#define PK_ADA_KINDS(FN, HYB, TEAMS, ...)                                                                   \
+#define PK_ADA_KINDS(FN, ...)                                                                   \
     switch (k.kind) {                                                                           \
-        case 0: idx = FN<false, false, false, HYB, TEAMS>(__VA_ARGS__); break;                  \
-        case 1: idx = FN<true, false, false, HYB, TEAMS>(__VA_ARGS__); break;                   \
-        case 2: idx = FN<false, true, false, HYB, TEAMS>(__VA_ARGS__); break;                   \
-        case 3: idx = FN<true, true, false, HYB, TEAMS>(__VA_ARGS__); break;                    \
-        case 4: if constexpr (TEAMS) idx = FN<false, false, true, HYB, TEAMS>(__VA_ARGS__); break;  \
-        case 5: if constexpr (TEAMS) idx = FN<true, false, true, HYB, TEAMS>(__VA_ARGS__); break;   \
-        case 6: if constexpr (TEAMS) idx = FN<false, true, true, HYB, TEAMS>(__VA_ARGS__); break;   \
-        case 7: if constexpr (TEAMS) idx = FN<true, true, true, HYB, TEAMS>(__VA_ARGS__); break;    \
+        case 0: idx = FN<false, false, false, HYB, KEYS>(__VA_ARGS__); break;                   \
+        case 1: idx = FN<true, false, false, HYB, KEYS>(__VA_ARGS__); break;                    \
+        case 2: idx = FN<false, true, false, HYB, KEYS>(__VA_ARGS__); break;                    \
+        case 3: idx = FN<true, true, false, HYB, KEYS>(__VA_ARGS__); break;                     \
+        case 4: if constexpr (KEYS != kHandfuls) idx = FN<false, false, true, HYB, KEYS>(__VA_ARGS__); break;  \
+        case 5: if constexpr (KEYS != kHandfuls) idx = FN<true, false, true, HYB, KEYS>(__VA_ARGS__); break;   \
+        case 6: if constexpr (KEYS != kHandfuls) idx = FN<false, true, true, HYB, KEYS>(__VA_ARGS__); break;   \
+        case 7: if constexpr (KEYS != kHandfuls) idx = FN<true, true, true, HYB, KEYS>(__VA_ARGS__); break;    \
     }
 
 // ---------------------------------------------------------------------------
@@ -396,7 +409,7 @@ __device__ __forceinline__ int ada_batches(int U, int batch, int x, int* per)
     return max(0, min(*per, n - x * *per));
 }
 
-template <bool BF16, bool MEAN, bool NARROW, bool HYB, bool TEAMS>
+template <bool BF16, bool MEAN, bool NARROW, bool HYB, int KEYS>
 __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, const double* recip)
 {
     const int lane = threadIdx.x & 63;
@@ -462,7 +475,7 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
                 load_f32x4<NARROW>(r.a, k.D, a);
                 if (i < n1 && act) {
                     double acc[4];
-                    const double c = MEAN ? (L < kRecips ? recip[L] : recip_len(L)) : 1.0;
+                    const double c = MEAN ? recip_of<true>(gv, L) : 1.0;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) acc[v] = MEAN ? fma(c, (double)xg[v], 0.0) : 0.0 + (double)xg[v];
                     row_step<BF16, NARROW>(r, k.D, acc, w, a, job.lr, job.eps);
@@ -482,7 +495,7 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
                 load_w4<BF16, NARROW>(r.w, k.D, w);
                 load_f32x4<NARROW>(r.a, k.D, ac);
                 double acc[4] = {0.0, 0.0, 0.0, 0.0};
-                accum_range<MEAN, NARROW>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
+                accum_range<MEAN, NARROW, true>(acc, gv, (uint32_t)a, (uint32_t)b, 4);
                 row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
             }
         }
@@ -497,7 +510,7 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
             const int wa = __shfl(p_a, src, 64), sb = __shfl(p_b, src, 64), wb = kk < n ? sb : wa;
             const uint32_t row = (uint32_t)__shfl((int)p_row, src, 64);
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            if (act) accum_range<MEAN, NARROW>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
+            if (act) accum_range<MEAN, NARROW, true>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
             wave_group_sum(acc, lpr, lpr * team);
             if (in_team == 0 && act && kk < n) {           // (asked for earlier, the row would not fit the registers)
                 const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, row, k.D, d0);
@@ -511,7 +524,7 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
     return idx - n_mine;
 }
 
-// TEAMS: for launches with rows of kTeamDim columns and fewer, where a wavefront's handful has 16 to 64 keys: where
+// kTeams: for launches with rows of kTeamDim columns and fewer, where a wavefront's handful has 16 to 64 keys: where
 // frequent IDs are neighbours, all of them can have more than kColdMax occurrences, and one after the other they take
 // longer than everything else (16 tables of 82 K occurrences, dimension 3: 238 us, in teams 79; dimension 8: 79,
 // 57).  Wider rows have few keys to a handful and keep the registers (26 one-hot fields of 32 columns, a
@@ -527,30 +540,30 @@ __device__ __forceinline__ void ada_recips(const AdaJob& job, double* s_recip)
     }
 }
 
-// BATCH: the keys in batches, by ada_batch_keys; for launches of kBatchNnz occurrences, or of rows of kBatchDim columns, and more.
+// kBatches: for launches of kBatchNnz occurrences, or of rows of kBatchDim columns, and more.
 constexpr int64_t kBatchNnz = 3 << 20;
 constexpr int kBatchDim = 48;
-template <bool HYB, bool TEAMS, bool BATCH>
+template <bool HYB, int KEYS>
 __global__ void __launch_bounds__(NT, 6)
 pk_adagrad_kernel(AdaJob job)
 {
     __shared__ double s_red[NT / 64][64][4];               // per-wavefront sums of a long key's piece
-    __shared__ double s_recip[kRecips];
-    ada_recips(job, s_recip);
+    __shared__ double s_recip[KEYS == kBatches ? kRecips : 1];
+    if constexpr (KEYS == kBatches) ada_recips(job, s_recip);
     if ((int)blockIdx.x < job.hot_blocks) {
         int idx = blockIdx.x >> 3;
         for (int i = 0; i < job.n_packs; ++i) {
             const AdaPack& k = job.pack[i];
-            PK_ADA_KINDS(ada_long_keys, HYB, TEAMS, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip, s_red)
+            PK_ADA_KINDS(ada_long_keys, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip, s_red)
         }
         return;
     }
-    const int kb = (int)blockIdx.x - job.hot_blocks;       // (hot_blocks is a multiple of 8)
-    const int stride = (job.key_blocks >> 3) * (NT / 64);
+    const int kb = (int)blockIdx.x - job.hot_blocks, stride = (job.key_blocks >> 3) * (NT / 64);
+    // (the same in all lanes, so that a pack's work and the choice of its code are found on the scalar unit)
     int idx = (kb >> 3) * (NT / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (int i = 0; i < job.n_packs; ++i) {
         const AdaPack& k = job.pack[i];
-        if constexpr (BATCH) { PK_ADA_KINDS(ada_batch_keys, HYB, TEAMS, job, k, idx, kb & 7, stride, s_recip) }
-        else { PK_ADA_KINDS(ada_keys, HYB, TEAMS, job, k, idx, kb & 7, stride, s_recip) }
+        if constexpr (KEYS == kBatches) { PK_ADA_KINDS(ada_batch_keys, job, k, idx, kb & 7, stride, s_recip) }
+        else { PK_ADA_KINDS(ada_keys, job, k, idx, kb & 7, stride) }
     }
 }

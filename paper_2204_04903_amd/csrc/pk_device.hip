@@ -431,9 +431,9 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
                     job.key_blocks = (int)((blocks_for(nnz / 3 + ((int64_t)8 * job.n_packs << log), (int64_t)(NT / 64) << log, 256 * 32) + 7u) & ~7u);
                 }
                 const dim3 grid(job.hot_blocks + job.key_blocks);
-                const auto kernel = batches ? pk_adagrad_kernel<false, true, true>
-                                    : hot   ? (teams ? pk_adagrad_kernel<true, true, false> : pk_adagrad_kernel<true, false, false>)
-                                            : (teams ? pk_adagrad_kernel<false, true, false> : pk_adagrad_kernel<false, false, false>);
+                const auto kernel = batches ? pk_adagrad_kernel<false, kBatches>
+                                    : hot   ? (teams ? pk_adagrad_kernel<true, kTeams> : pk_adagrad_kernel<true, kHandfuls>)
+                                            : (teams ? pk_adagrad_kernel<false, kTeams> : pk_adagrad_kernel<false, kHandfuls>);
                 PK_LAUNCH("pk_adagrad", kernel, grid, dim3(NT), 0, job);
                 job.n_packs = 0;
             }
@@ -443,8 +443,9 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
             const Pack& k = plan->packs[p];
             job.pack[job.n_packs++] = AdaPack{W[p], A[p], hot ? hot[p] : HotView{nullptr, nullptr, nullptr},
                                               (uint32_t)((int64_t)(B - 1) * grad_row_stride + plan->out_dim - k.dim), k.dim,
-                                              lane_shift(k.dim), p, ada_batch_log(nnz, k.dim),
-                                              (k.dtype == PK_BF16 ? 1 : 0) | (k.has_mean ? 2 : 0) | (k.dim < 4 ? 4 : 0)};
+                                              lane_shift(k.dim), p,
+                                              (k.dtype == PK_BF16 ? 1 : 0) | (k.has_mean ? 2 : 0) | (k.dim < 4 ? 4 : 0),
+                                              ada_batch_log(nnz, k.dim)};
         }
     }
     stream = main_stream;
