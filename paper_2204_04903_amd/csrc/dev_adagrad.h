@@ -28,7 +28,7 @@ struct AdaPack {
     uint32_t addr_max;           // largest element offset into grad_out at which a chunk of the pack can start
     int32_t D, sh, p;            // dimension, log2 of the lanes per row, pack
     int32_t kind;                // 1: bf16, 2: mean pooling (entries carry bag lengths), 4: dimension below four
-    int32_t batch;               // log2 of the keys that a wavefront takes at once (ada_batch_keys)
+    uint32_t batch;              // how many keys a wavefront takes at once (ada_batch_keys), as key_batch_word
 };
 constexpr int kAdaPacks = 16;    // packs of one launch
 struct AdaJob {
@@ -391,7 +391,7 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
     }
 
 // ---------------------------------------------------------------------------
-// Large batches.  A wavefront takes batches of 2^k.batch consecutive keys, a lane per key at first: its segment, its row,
+// Large batches.  A wavefront takes batches of up to 64 consecutive keys, a lane per key at first: its segment, its row,
 // its first entry, the next batches' on their way.  Then the keys are taken by their number of occurrences, one, few, more, a
 // lane group each (or a team of groups), so that a wavefront's groups do about the same.  Two thirds of the keys have one
 // occurrence: their entries are there, so row and gradient chunk are asked for at once.  Against handfuls of
@@ -401,10 +401,11 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
 // columns 418, 399; bf16 sequences 253, 212; the mixed layer of 1 M IDs 83, 70; 26 one-hot fields of 65536 126, 128.  A small batch
 // (26 one-hot fields of 8192) is a chain of loads, one longer here: 20 us, 23.
 // ---------------------------------------------------------------------------
-// batches of the XCD's eighth of U keys
-__device__ __forceinline__ int ada_batches(int U, int batch, int x, int* per)
+// batches of the XCD's eighth of U keys (a division here stands in every wavefront's way once per pack: the mixed layer of
+// eight packs 72.0 us, 70.1 with the product)
+__device__ __forceinline__ int ada_batches(int U, const AdaPack& k, int x, int* per)
 {
-    const int n = (U + (1 << batch) - 1) >> batch;
+    const int n = key_batches(U, k.batch);
     *per = (n + 7) >> 3;
     return max(0, min(*per, n - x * *per));
 }
@@ -416,7 +417,7 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
     const PackState* st = as_global(job.st) + k.p;
     const int U = st->error ? 0 : st->n_unique, start = st->start;
     int per;
-    const int n_mine = ada_batches(U, k.batch, x, &per), u0 = (x * per) << k.batch;
+    const int n_mine = ada_batches(U, k, x, &per), K = key_batch_size(k.batch), u0 = x * per * K;
     if (idx >= n_mine) return idx - n_mine;
     const int lpr = 1 << k.sh, gpw = 64 >> k.sh, li = lane & (lpr - 1), g = lane >> k.sh;
     const int32_t* seg = as_global(job.seg) + start + k.p + u0;
@@ -429,9 +430,9 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
     struct Key { int a, b; uint32_t row; };                // a lane's key: its segment, its row
     struct First { uint32_t at, L; };                      // its first entry
     auto fetch = [&](int c) {
-        const int u = (c << k.batch) + lane, v = min(u, u_end - 1);      // (past the end: some key, not used)
+        const int u = c * K + lane, v = min(u, u_end - 1);      // (past the end: some key, not used)
         Key q{seg[v], seg[v + 1], uq[v]};
-        if (u >= u_end || lane >> k.batch) q.b = q.a;
+        if (u >= min(u_end, (c + 1) * K)) q.b = q.a;
         return q;
     };
     auto fetch_first = [&](const Key& q) {
@@ -540,9 +541,7 @@ __device__ __forceinline__ void ada_recips(const AdaJob& job, double* s_recip)
     }
 }
 
-// kBatches: for launches of kBatchNnz occurrences, or of rows of kBatchDim columns, and more.
-constexpr int64_t kBatchNnz = 3 << 20;
-constexpr int kBatchDim = 48;
+// (kBatches: for launches that keys_in_batches chooses)
 template <bool HYB, int KEYS>
 __global__ void __launch_bounds__(NT, 6)
 pk_adagrad_kernel(AdaJob job)

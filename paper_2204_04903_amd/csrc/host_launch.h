@@ -234,19 +234,6 @@ unsigned blocks_for(int64_t items, int64_t per_block, int64_t cap)
 // log2 of the lanes that hold a row, four columns each
 int lane_shift(int D) { int s = 0; while ((4 << s) < D) ++s; return s; }
 
-// log2 of the keys that a wavefront of a large backward pass takes at once: as many as leave it fewer than kAdaBatches batches of
-// occurrences (half of a layer's are other occurrences of few keys, and 6144 wavefronts run at a time; the mixed layer
-// of 1 M IDs 69 us with 16 keys, 83 with 32), and up to eight of its handfuls (750 K IDs of 256 columns, a key to a handful: 121 us,
-// 142 with 16 handfuls; bf16 sequences 212 and 209)
-constexpr int64_t kAdaBatches = 73728;
-int ada_batch_log(int64_t nnz, int D)
-{
-    const int handful = 6 - lane_shift(D);
-    int b = handful;
-    while (b < std::min(6, handful + 3) && (nnz >> b) >= kAdaBatches) ++b;
-    return b;
-}
-
 // pack p's packed_offsets start (entries): the packs before it hold k*B+1 each
 int64_t po_off(const pk_plan* plan, int p, int32_t B)
 {

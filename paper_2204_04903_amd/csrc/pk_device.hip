@@ -409,6 +409,7 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
         job.ent = ws.at<uint32_t>(L.seg_ent); job.ghot = ws.at<double>(L.ghot); job.ticket = ws.at<int32_t>(L.ticket);
         job.dmax = L.dmax; job.grad = grad_out; job.gstride = grad_row_stride; job.out_dim = plan->out_dim;
         job.lr = lr; job.eps = eps;
+        KeyShare share;                                      // of the launch's packs
         for (size_t i = 0; i <= order.size(); ++i) {
             if (job.n_packs == kAdaPacks || (i == order.size() && job.n_packs)) {
                 int sh = 0;
@@ -416,19 +417,20 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
                 // long keys: none in a batch that has no more occurrences than a key needs to be long
                 job.hot_blocks = nnz <= kLongMin ? 0 : (int)((blocks_for(nnz, kMarkStep * kMarksPerBlock, kLongBlocks) + job.n_packs + 7u) & ~7u);
                 job.key_blocks = (int)((blocks_for(nnz + (int64_t)job.n_packs * (64 >> sh), (64 >> sh) * (NT / 64), 256 * 16) + 7u) & ~7u);
-                // Large batches of many IDs or wide rows: the keys in batches by their occurrences.  (Fewer and narrower: the
-                // same or 1 % slower; 26 one-hot fields of 65536, 32 columns, 126 us and 128, four micro-batches of 2.8 M IDs, 8 and
-                // 16 columns, 1255 and 1273.  A Hot-storage's rows: not tried, the host's memory bounds those.)  Blocks for a third as
-                // many keys as there are occurrences, the others in a second round: a block without keys costs 2.5 ns (the
-                // mixed layer of 1 M IDs 75 us with blocks for half as many, 96 for all of them).
-                int widest = 0;
                 bool teams = false;
-                for (int q = 0; q < job.n_packs; ++q) { widest = std::max(widest, job.pack[q].D); teams |= job.pack[q].D <= kTeamDim; }
-                const bool batches = !L.small && !hot && (nnz >= kBatchNnz || widest >= kBatchDim);
+                for (int q = 0; q < job.n_packs; ++q) teams |= job.pack[q].D <= kTeamDim;
+                // (A Hot-storage's rows in batches: not tried, the host's memory bounds those.)
+                const bool batches = !L.small && !hot && keys_in_batches(share);
                 if (batches) {
-                    int log = 6;
-                    for (int q = 0; q < job.n_packs; ++q) log = std::min(log, job.pack[q].batch);
-                    job.key_blocks = (int)((blocks_for(nnz / 3 + ((int64_t)8 * job.n_packs << log), (int64_t)(NT / 64) << log, 256 * 32) + 7u) & ~7u);
+                    // Blocks for a third as many keys as there are occurrences, the others in a second round: a block
+                    // without keys costs 2.5 ns (the mixed layer of 1 M IDs 75 us with blocks for half as many, 96 for all).
+                    int least = 64;
+                    for (int q = 0; q < job.n_packs; ++q) {
+                        const int size = keys_per_batch(share.distinct, 64 >> job.pack[q].sh);
+                        job.pack[q].batch = key_batch_word(size);
+                        least = std::min(least, size);
+                    }
+                    job.key_blocks = (int)((blocks_for(nnz / 3 + (int64_t)8 * job.n_packs * least, (int64_t)(NT / 64) * least, 256 * 32) + 7u) & ~7u);
                 }
                 const dim3 grid(job.hot_blocks + job.key_blocks);
                 const auto kernel = batches ? pk_adagrad_kernel<false, kBatches>
@@ -436,6 +438,7 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
                                             : (teams ? pk_adagrad_kernel<false, kTeams> : pk_adagrad_kernel<false, kHandfuls>);
                 PK_LAUNCH("pk_adagrad", kernel, grid, dim3(NT), 0, job);
                 job.n_packs = 0;
+                share = KeyShare{};
             }
             if (i == order.size()) break;
             const int p = order[i];
@@ -444,8 +447,13 @@ static pk_status backward_impl(const pk_plan* plan, void* const* W, float* const
             job.pack[job.n_packs++] = AdaPack{W[p], A[p], hot ? hot[p] : HotView{nullptr, nullptr, nullptr},
                                               (uint32_t)((int64_t)(B - 1) * grad_row_stride + plan->out_dim - k.dim), k.dim,
                                               lane_shift(k.dim), p,
-                                              (k.dtype == PK_BF16 ? 1 : 0) | (k.has_mean ? 2 : 0) | (k.dim < 4 ? 4 : 0),
-                                              ada_batch_log(nnz, k.dim)};
+                                              (k.dtype == PK_BF16 ? 1 : 0) | (k.has_mean ? 2 : 0) | (k.dim < 4 ? 4 : 0), 0};
+            if (L.small || hot) continue;
+            for (int t = k.first_stable; t < k.first_stable + k.n_stables; ++t) {
+                const TableMeta& tm = plan->sort_tables[t];
+                const int64_t n_fields = tm.field_end - tm.field_begin;
+                share.add(k.dim, tm.rows, n_fields, nnz * n_fields / (int64_t)plan->fields.size());
+            }
         }
     }
     stream = main_stream;

@@ -124,6 +124,51 @@ inline int small_cut(int64_t nnz, int64_t n_tables)
     return cut;
 }
 
+// How a backward launch takes its keys, by what its packs hold when every field has the batch's average of IDs: keys one
+// handful a wavefront, or (large batches) batches of more that are sorted by their number of occurrences first.
+// kernel times in us, handfuls then batches, 1.05-Zipf IDs of one-hot fields or 1.1-Zipf of bags of 10:
+//   rows of 48 columns and more in a quarter of the fields: 60 48-column fields of 0.7 M IDs 62, 56; 64 columns, 1.3 M 126, 117; 26
+//     one-hot fields of 64 columns 246, 242; of 0.2 M the same, of 0.1 M 23, 28 (hence kBatchNnz); a third of the fields
+//     84, 80 (1.5 M); an eighth 62, 65 (the narrow rows' loss)
+//   of 32 and more in half: 1.6 M 68, 70; 2.4 M 109, 105; 3.4 M 144, 135; one-hot 3.4 M 230, 226
+//   of 16 and more in half: 3.4 M 108, 107 and one-hot 176, 183; 5.5 M 155, 151 and 271, 274; 8.6 M 238, 230; 21 M 505, 485; 1000
+//     fields of 8 and 16 columns, 5.5 M 229, 226, 11 M 423, 408
+//   of 8: 3.4 M 98, 106; 8.6 M 198, 203; 21 M 421, 427; of 4: 83, 90 and 373, 386: a handful is 32 or 64 keys there anyway
+// Where tables have few rows for their IDs, keys have many occurrences each and there is little to sort (37 ragged fields of
+// 3.0 M IDs, 46 % of them distinct at most: 201, 193; of 3.5 M, 43 %: 221, 237).
+struct KeyShare {
+    int64_t fields = 0, wide16 = 0, wide32 = 0, wide48 = 0;    // fields; those with rows of 16, 32, 48 columns and more
+    int64_t ids = 0, distinct = 0;                             // IDs; rows that they can be, at most
+    void add(int dim, uint32_t rows, int64_t n_fields, int64_t n)      // a table, its fields, their IDs
+    {
+        fields += n_fields; ids += n; distinct += std::min<int64_t>(rows, n);
+        wide16 += dim >= 16 ? n_fields : 0; wide32 += dim >= 32 ? n_fields : 0; wide48 += dim >= 48 ? n_fields : 0;
+    }
+};
+constexpr int64_t kBatchNnz = 5 << 16, kBatchNnz32 = 3 << 20, kBatchNnz16 = 5 << 20;
+inline bool keys_in_batches(const KeyShare& s)
+{
+    if (16 * s.distinct < 7 * s.ids) return false;
+    return (4 * s.wide48 >= s.fields && s.ids >= kBatchNnz) || (2 * s.wide32 >= s.fields && s.ids >= kBatchNnz32) ||
+           (2 * s.wide16 >= s.fields && s.ids >= kBatchNnz16);
+}
+// Keys in a batch: whole handfuls, as many as leave the launch kKeyBatches batches (6144 wavefronts run at a time, and there
+// are fewer distinct rows than can be: 37 ragged fields of 1.05 M IDs, 0.67 M rows at most, in batches of 16, 24, 32, 64: 76.6, 75.1,
+// 78.2, 80.7 us; of 2.3 M, 1.2 M 156, 153, 150, 162; of 3.0 M, 1.4 M 195, 193, 195, 216), 16 at least (of 0.5 M 50.1, in
+// batches of 8 55.7), eight handfuls or 64 at most.
+constexpr int64_t kKeyBatches = 36864;
+inline int keys_per_batch(int64_t distinct, int handful)
+{
+    const int most = std::min(64, 8 * handful), least = std::min(most, std::max(handful, 16));
+    const int64_t n = (distinct / kKeyBatches + handful / 2) / handful * handful;
+    return (int)std::min<int64_t>(most, std::max<int64_t>(least, n));
+}
+// A batch's size (8 and more), and what takes the place of the division by it: floor(2^24 / size) + 1.  Where U is large, the
+// batches of U keys are up to U / 2^24 + 1 too many, which have no keys; none for U = 0.
+inline uint32_t key_batch_word(int size) { return (uint32_t)size | (((uint32_t)1 << 24) / (uint32_t)size + 1) << 8; }
+PK_HD inline int key_batch_size(uint32_t word) { return (int)(word & 255); }
+PK_HD inline int key_batches(int U, uint32_t word) { return (int)(((uint64_t)((uint32_t)U + (word & 255) - 1) * (word >> 8)) >> 24); }
+
 // One slice of the small-batch cut, with all that its block needs of the plan; static, device side, in
 // (pack, table, slice) order.
 struct SmallSlice {
