@@ -175,9 +175,11 @@ __device__ __forceinline__ void pool_tile_by(const PoolJob& job, const PoolPack&
 // rounds only.  (In a walk across bags the groups' bags end at different positions of a round, and the forty instructions
 // that write a bag are gone through at nearly every one of them where 32 groups have bags of 25 IDs.)  What is left is the
 // rate of row requests: 200 fields of 25 IDs, batch 4096, beside the dedup chain 427 us a launch, 401 this way, 1024 bags
-// alone 63 and 59.  Fields of kPairAvg IDs a bag and more: 1000 fields of 5.5 lose more to rounds that are not full than
-// they gain (242 us, 254).
-constexpr int kPairAvg = 10;
+// alone 63 and 59.  Fields of kPairAvg IDs a bag and more, where a bag fills a round: with fewer, more is lost to rounds that
+// are not full than is gained.  us a launch, walk and pairs, of 6, 7, 8, 10, 12 IDs a bag: 100 fields of 16 columns, batch 8192,
+// 82.5 81.6, 90.9 87.4, 101 95.0, 116 110, 127 117; 600 of 8 and 16, 2048, 127 129, 146 145, 152 152, 186 184, 217 214; 60 of 64,
+// 4096, 57.2 57.9, 63.5 63.0, 69.9 68.2, 82.7 81.2, 94.6 89.8; 1000 of 8 and 16 with 5.5 IDs 242 254, the ragged layer's 9.5 34.2 32.8.
+constexpr int kPairAvg = 8;
 template <bool BF16, int R>
 __device__ __forceinline__ void pool_tile_pairs(const PoolJob& job, const PoolPack& k, int item, int j, const FieldMeta& m, const int32_t* offs,
                                                 int32_t* s_off)
@@ -278,7 +280,7 @@ __device__ __forceinline__ bool pool_seq_likely(const int32_t* offs, int n, int 
 }
 
 // Sequence fields: a wavefront per bag, R positions per group and round.
-template <bool BF16, bool NARROW, bool HYB, bool IDS, bool PAIRS, int R>
+template <bool BF16, bool NARROW, bool HYB, bool IDS, int R>
 __device__ __forceinline__ int pool_coop(const PoolJob& job, const PoolPack& k, int idx)
 {
     const int lane = threadIdx.x & 63, B = job.B;
@@ -344,11 +346,13 @@ __device__ __forceinline__ int pool_coop(const PoolJob& job, const PoolPack& k, 
 // the code for a pack's kind
 #define PK_POOL_KINDS(FN, RES, ...)                                                             \
     switch (k.kind) {                                                                           \
-        case 0: RES FN<false, false, HYB, IDS, PAIRS, R>(__VA_ARGS__); break;                   \
-        case 1: RES FN<true, false, HYB, IDS, PAIRS, R>(__VA_ARGS__); break;                    \
-        case 2: RES FN<false, true, HYB, IDS, PAIRS, R>(__VA_ARGS__); break;                    \
-        case 3: RES FN<true, true, HYB, IDS, PAIRS, R>(__VA_ARGS__); break;                     \
+        case 0: RES FN(false, false)(__VA_ARGS__); break;                                       \
+        case 1: RES FN(true, false)(__VA_ARGS__); break;                                        \
+        case 2: RES FN(false, true)(__VA_ARGS__); break;                                        \
+        case 3: RES FN(true, true)(__VA_ARGS__); break;                                         \
     }
+#define PK_POOL_TILE(BF16, NARROW) pool_tile<BF16, NARROW, HYB, IDS, PAIRS, R>
+#define PK_POOL_COOP(BF16, NARROW) pool_coop<BF16, NARROW, HYB, IDS, R>
 
 // one wavefront's share of a launch's pooling: `wave` counts its wavefronts
 template <bool HYB, bool IDS, bool PAIRS, int R>
@@ -359,7 +363,7 @@ __device__ __forceinline__ void pool_wave(const PoolJob& job, int wave, int32_t*
         while (i + 1 < job.n_packs && wave >= job.pack[i + 1].item_begin) ++i;
         const PoolPack& k = job.pack[i];
         const int item = wave - k.item_begin;
-        PK_POOL_KINDS(pool_tile, , job, k, item, s_off)
+        PK_POOL_KINDS(PK_POOL_TILE, , job, k, item, s_off)
         return;
     }
     int idx = wave - job.n_items;
@@ -369,12 +373,13 @@ __device__ __forceinline__ void pool_wave(const PoolJob& job, int wave, int32_t*
     }
     for (int i = 0; i < job.n_packs; ++i) {
         const PoolPack& k = job.pack[i];
-        PK_POOL_KINDS(pool_coop, idx =, job, k, idx)
+        PK_POOL_KINDS(PK_POOL_COOP, idx =, job, k, idx)
     }
 }
 
-// PAIRS: for launches where two bags of a group hold eight IDs or more on average (without that code the others' loop is
-// 1 % faster: 26 one-hot fields of 65536 74.2 us, 75.2 with it)
+// PAIRS: for launches where two bags of a group hold eight IDs or more on average over all fields: some of them can then have
+// kPairAvg a bag (80 one-hot fields and 20 of 25 IDs, 5.8 on average: 43.6 us, 39.6 with pairs).  Without that code the walk of
+// one-hot fields is 1 % faster (26 of 65536 74.2 us, 75.2 with it); of 5.5 IDs a bag 181.5, 182.3, of sequences 128.7, 126.9.
 template <bool HYB, bool PAIRS>
 __global__ void __launch_bounds__(NT, 6)
 pk_pool_kernel(PoolJob job)
