@@ -92,7 +92,8 @@ static Layout layout_with(const pk_plan* plan, int32_t B, int64_t nnz, size_t ro
     while (bt > 32 && (int64_t)F * ((B + bt - 1) / bt) < kTilesMin) bt /= 2;
     L.bags_per_tile  = bt;
     L.packed_offsets = take((F * (size_t)B + P) * 4);
-    L.keys           = take(n * 4 + 32);                 // keys are read eight at a time: room for the last reading past the end
+    // keys are read eight at a time, and from the end itself on where the last bag is empty (pool_tile_pairs): room for eight
+    L.keys           = take((n + 8) * 4);
     L.inverse        = take(n * 4);
     // entries are read four at a time: room for the last reading past the end
     L.seg_ent        = take(n * (plan->any_mean ? 8 : 4) + 32);

@@ -30,3 +30,29 @@ def test_every_output_is_written(place, value, dim, debug):
         assert torch.isfinite(out).all()
     finally:
         layer.close()
+
+
+# the pooling with two bags to a lane group (fields of eight IDs a bag and more, batches that have 4096 tiles of such bags):
+# (field, bag) of the offset; inside a field, at both ends of one and of all
+@pytest.mark.parametrize("place,value", [((10, 300), 3), ((10, 301), 10**9), ((11, 664), -7), ((12, 0), 10**9), ((99, 664), 5),
+                                         ((100, 0), 0), ((0, 0), 2), ((0, 1), -2**31)])
+def test_every_output_of_pairs_is_written(place, value):
+    from paper_2204_04903_amd.layer import PackedEmbedding
+    dim, F, B = 20, 100, 665
+    tables, fields = [(5000, dim, 0)], [(0, f % 2) for f in range(F)]
+    pr = small_problem(97, B=B, tables=tables, fields=fields, max_len=22)
+    assert pr["offsets"][-1] >= 8 * F * B
+    layer = PackedEmbedding(tables, fields, debug=2)
+    try:
+        layer.load_table(0, pr["Wt"][0])
+        ids, offsets = torch.from_numpy(pr["ids"]).cuda(), torch.from_numpy(pr["offsets"]).cuda()
+        layer.forward(ids, offsets, B)                   # (the workspace then holds a batch's offsets and keys)
+        assert layer.error_word() == 0
+        offsets[place[0] * B + place[1]] = value
+        out = torch.full((B, layer.out_dim), float("nan"), dtype=torch.float32, device="cuda")
+        layer.forward(ids, offsets, B, out=out)
+        torch.cuda.synchronize()
+        assert layer.error_word() & 1
+        assert torch.isfinite(out).all()
+    finally:
+        layer.close()
