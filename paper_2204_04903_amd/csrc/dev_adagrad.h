@@ -77,10 +77,10 @@ __device__ __forceinline__ void grad_places(const GradView& g, uint32_t (&at)[N]
 
 // Bag lengths whose reciprocals a block of a large batch keeps in LDS (mean pooling; TABLE below): one read where the two
 // Newton steps and their conversions are nine instructions, in every lane, for every entry.  The other launches form
-// them: filling the table and the barrier after it would stand before the first load of a block that has little to do.
+// them: the table gains those nothing (eight one-hot fields of 512, mean: 6.4 us with and without), and with the entries that
+// accum_piece asks for ahead the Hot-storage's kernels spilled one and four registers (none and two without).
 constexpr uint32_t kRecips = 512;
-template <bool TABLE>
-__device__ __forceinline__ double recip_of(const GradView& g, uint32_t L) { return TABLE && L < kRecips ? g.recip[L] : recip_len(L); }
+__device__ __forceinline__ double recip_of(const GradView& g, uint32_t L) { return L < kRecips ? g.recip[L] : recip_len(L); }
 
 // a round's entries: the chunks' offsets and their bags' lengths (read past the range's end up to 3 entries far)
 template <bool MEAN> struct Entries { uint32_t v[MEAN ? 8 : 4]; };
@@ -397,9 +397,9 @@ __device__ __forceinline__ int ada_keys(const AdaJob& job, const AdaPack& k, int
 // occurrence: their entries are there, so row and gradient chunk are asked for at once.  Against handfuls of
 // consecutive keys, each taking rounds of four entries: 150 M vector instructions for 200 fields of 21 M IDs, 86 M now.  What is
 // left is the rate of line requests (26 M reads, of them 7 M for rows, and 11 M writes): with more wavefronts or
-// fewer, or more rows in flight in each, the times are the same.  200 fields 650 us a launch, 590; 1000 fields of 8 and 16
-// columns 418, 399; bf16 sequences 253, 212; the mixed layer of 1 M IDs 83, 70; 26 one-hot fields of 65536 126, 128.  A small batch
-// (26 one-hot fields of 8192) is a chain of loads, one longer here: 20 us, 23.
+// fewer, or more rows in flight in each, the times are the same.  200 fields 654 us a launch, 594; 1000 fields of 8 and 16
+// columns 423, 408; bf16 sequences 254, 212; the mixed layer of 1 M IDs 87, 69; 26 one-hot fields of 65536 126, 128.  A small batch
+// (26 one-hot fields of 8192) is a chain of loads, one longer here: 20 us, 23.  (keys_in_batches has the line between them.)
 // ---------------------------------------------------------------------------
 // batches of the XCD's eighth of U keys (a division here stands in every wavefront's way once per pack: the mixed layer of
 // eight packs 72.0 us, 70.1 with the product)
@@ -476,7 +476,7 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
                 load_f32x4<NARROW>(r.a, k.D, a);
                 if (i < n1 && act) {
                     double acc[4];
-                    const double c = MEAN ? recip_of<true>(gv, L) : 1.0;
+                    const double c = MEAN ? recip_of(gv, L) : 1.0;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) acc[v] = MEAN ? fma(c, (double)xg[v], 0.0) : 0.0 + (double)xg[v];
                     row_step<BF16, NARROW>(r, k.D, acc, w, a, job.lr, job.eps);
@@ -541,7 +541,6 @@ __device__ __forceinline__ void ada_recips(const AdaJob& job, double* s_recip)
     }
 }
 
-// (kBatches: for launches that keys_in_batches chooses)
 template <bool HYB, int KEYS>
 __global__ void __launch_bounds__(NT, 6)
 pk_adagrad_kernel(AdaJob job)
