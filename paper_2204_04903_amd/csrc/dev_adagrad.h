@@ -9,7 +9,8 @@
 // The ID distribution is heavily skewed (Sec. II-B), so keys are handled by how many occurrences they have:
 //   up to kColdMax:   one lane group per key (a group is as many lanes as the row has 16-byte chunks);
 //   up to kLongMin:   the wavefront that met the key among its own, its groups stride over the occurrences; of
-//                     narrow rows, several such keys side by side;
+//                     narrow rows, several such keys side by side; in large batches, where such keys are neighbours, the
+//                     blocks of the longer ones (ada_dense);
 //   longer:           a block of its own, which the launch starts first, in pieces of kPiece occurrences; the
 //                     pieces of a key with several add into a row of partial sums, the last one to arrive
 //                     takes the step.
@@ -187,6 +188,62 @@ __device__ __forceinline__ void wave_group_sum(double (&acc)[4], int lpr, int la
 constexpr int kMarksPerBlock = 4;      // (16: the mixed layer 16 % slower, a block then has several pieces one after the other)
 constexpr int kLongBlocks = 768;
 
+constexpr int kTeam = 4;               // lane groups that share a key of more than kColdMax occurrences at least
+
+// Keys of more than kColdMax and up to kLongMin occurrences, lanes first to first + n - 1 holding their segments and rows (batches):
+// dealt to teams of `team` lane groups: all groups for a key alone, several keys side by side.
+template <bool BF16, bool MEAN, bool NARROW, bool HYB>
+__device__ __forceinline__ void ada_team_keys(const AdaJob& job, const AdaPack& k, const GradView& gv, int d0, bool act, int first, int n,
+                                              int p_a, int p_b, uint32_t p_row)
+{
+    const int lane = threadIdx.x & 63, lpr = 1 << k.sh, gpw = 64 >> k.sh, g = lane >> k.sh;
+    int team = gpw;
+    while (team > kTeam && gpw < team * n) team >>= 1;
+    const int in_team = g & (team - 1);
+#pragma nounroll
+    for (int k0 = 0; k0 < n; k0 += gpw / team) {
+        const int kk = k0 + g / team, src = first + min(kk, n - 1);
+        const int wa = __shfl(p_a, src, 64), sb = __shfl(p_b, src, 64), wb = kk < n ? sb : wa;
+        const uint32_t row = (uint32_t)__shfl((int)p_row, src, 64);
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        if (act) accum_range<MEAN, NARROW, true>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
+        wave_group_sum(acc, lpr, lpr * team);
+        if (in_team == 0 && act && kk < n) {               // (asked for earlier, the row would not fit the registers)
+            const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, row, k.D, d0);
+            float w[4], ac[4];
+            load_w4<BF16, NARROW>(r.w, k.D, w);
+            load_f32x4<NARROW>(r.a, k.D, ac);
+            row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
+        }
+    }
+}
+
+// Stretches of kMarksPerBlock marks' positions that have few keys: in batches, where frequent IDs are neighbours, a wavefront
+// would have 16 to 64 keys of up to kLongMin occurrences one after the other.  Those that begin in such a stretch are
+// left to the block that looks for long keys there.  us with low IDs frequent, batches without this, this way, and handfuls:
+// 100 fields of 16 columns, 8.2 M IDs 249 162 172; 60 of 64, 2.5 M 260 134 132; 20 of 200, 0.8 M 345 178 175; 100 of 32, 4.5 M 299
+// 147 157.  Where they are scattered, the look at two marks costs the mixed layer of 1 M IDs 70.6 72.6, 200 fields of 21 M 592 597.
+constexpr int kDenseKeys = 64, kRange = kMarksPerBlock * kMarkStep;
+__device__ __forceinline__ bool ada_dense(const int32_t* marks, int n_marks, int range)
+{
+    const int m = range * kMarksPerBlock;
+    return m + kMarksPerBlock < n_marks && marks[m + kMarksPerBlock] - marks[m] <= kDenseKeys;
+}
+
+// stretches of the XCD's eighth
+__device__ __forceinline__ int ada_ranges(int n_marks, int x, int* per)
+{
+    const int n = (n_marks + kMarksPerBlock - 1) / kMarksPerBlock;
+    *per = (n + 7) >> 3;
+    return max(0, min(*per, n - x * *per));
+}
+
+// the lane's place among those of `mask`, after `before` others, as a byte address for a permute
+__device__ __forceinline__ int lane_rank(uint64_t mask, int before)
+{
+    return (before + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))) * 4;
+}
+
 // How a launch takes the keys of up to kLongMin occurrences: handfuls, a key of more than kColdMax at a time, or several in
 // teams of lane groups (ada_keys); batches by the number of occurrences (ada_batch_keys).
 constexpr int kHandfuls = 0, kTeams = 1, kBatches = 2;
@@ -202,9 +259,8 @@ __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k
     const int32_t* seg = as_global(job.seg) + start + k.p;
     const int32_t* marks = as_global(job.marks) + start / kMarkStep + k.p;
     const int n_marks = (n + kMarkStep - 1) / kMarkStep;
-    const int n_ranges = (n_marks + kMarksPerBlock - 1) / kMarksPerBlock;
-    const int per = (n_ranges + 7) >> 3;
-    const int n_mine = max(0, min(per, n_ranges - x * per));
+    int per;
+    const int n_mine = ada_ranges(n_marks, x, &per);
     const int lpr = 1 << k.sh, gpw = 64 >> k.sh, li = lane & (lpr - 1), g = lane >> k.sh;
     const int d0 = NARROW ? 0 : lane_col(li, k.D);
     const bool act = 4 * li < k.D;
@@ -287,7 +343,39 @@ __device__ __forceinline__ int ada_long_keys(const AdaJob& job, const AdaPack& k
     return idx - n_mine;
 }
 
-constexpr int kTeam = 4;               // lane groups that share a key of more than kColdMax occurrences at least
+// The keys of more than kColdMax and up to kLongMin occurrences that begin in a dense stretch (launches in batches), every fourth
+// of a stretch to a wavefront, after the long keys of the same blocks.  (The kernel spills a register, four with this inside
+// ada_long_keys' loop, none in blocks of their own, but those cost the mixed layer of 1 M IDs 2 us of 72.6.)
+template <bool BF16, bool MEAN, bool NARROW, bool HYB, int KEYS>
+__device__ __forceinline__ int ada_stretch_keys(const AdaJob& job, const AdaPack& k, int idx, int x, int stride, const double* recip)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const PackState* st = as_global(job.st) + k.p;
+    const int n = st->error ? 0 : st->nnz, start = st->start;
+    const int32_t* seg = as_global(job.seg) + start + k.p;
+    const int32_t* marks = as_global(job.marks) + start / kMarkStep + k.p;
+    const int n_marks = (n + kMarkStep - 1) / kMarkStep;
+    int per;
+    const int n_mine = ada_ranges(n_marks, x, &per);
+    const int li = lane & ((1 << k.sh) - 1), d0 = NARROW ? 0 : lane_col(li, k.D);
+    const GradView gv{as_global(job.grad) + d0, as_global(job.ent) + (size_t)start * job.ent_mult, recip, (uint32_t)job.gstride,
+                      (uint32_t)job.out_dim, k.addr_max, k.D};
+#pragma nounroll
+    for (; idx < n_mine; idx += stride) {
+        const int range = x * per + idx;
+        if (!ada_dense(marks, n_marks, range)) continue;
+        // (the first and the last may begin outside the stretch)
+        const int u0 = marks[range * kMarksPerBlock], u1 = marks[(range + 1) * kMarksPerBlock];
+        const int u = u0 + wv + lane * (NT / 64), v = min(u, u1), a = seg[v], b = seg[v + 1];
+        const bool on = u <= u1 && a / kRange == range && b - a > kColdMax && b - a <= kLongMin;
+        const uint64_t mine = __ballot(on);
+        if (mine == 0) continue;
+        const int to = lane_rank(on ? mine : ~mine, on ? 0 : __popcll(mine));
+        ada_team_keys<BF16, MEAN, NARROW, HYB>(job, k, gv, d0, 4 * li < k.D, 0, __popcll(mine), __builtin_amdgcn_ds_permute(to, a),
+                                               __builtin_amdgcn_ds_permute(to, b), (uint32_t)__builtin_amdgcn_ds_permute(to, (int)as_global(job.unique)[start + v]));
+    }
+    return idx - n_mine;
+}
 
 // The other keys of a pack.  XCD x takes the x-th eighth of the keys (neighbouring keys share gradient
 // columns: one L2 then holds them), its wavefronts take consecutive handfuls.
@@ -422,6 +510,8 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
     const int lpr = 1 << k.sh, gpw = 64 >> k.sh, li = lane & (lpr - 1), g = lane >> k.sh;
     const int32_t* seg = as_global(job.seg) + start + k.p + u0;
     const uint32_t* uq = as_global(job.unique) + start + u0;
+    const int32_t* marks = as_global(job.marks) + start / kMarkStep + k.p;
+    const int n_marks = (st->nnz + kMarkStep - 1) / kMarkStep;
     const int u_end = U - u0;
     const int d0 = NARROW ? 0 : lane_col(li, k.D);
     const bool act = 4 * li < k.D;
@@ -452,13 +542,15 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
         next = fetch(min(idx + 2 * stride, n_mine - 1));
         // the batch in the order of the keys' occurrences: one | up to 4 | up to kColdMax | up to kLongMin | others
         const int len = q.b - q.a;
+        bool team = len > kColdMax && len <= kLongMin;
+        if (team) team = !ada_dense(marks, n_marks, q.a / kRange);
         const uint64_t m1 = __ballot(len == 1), m4 = __ballot(len >= 2 && len <= 4), m8 = __ballot(len > 4 && len <= kColdMax);
-        const uint64_t mt = __ballot(len > kColdMax && len <= kLongMin), mo = ~(m1 | m4 | m8 | mt);
+        const uint64_t mt = __ballot(team), mo = ~(m1 | m4 | m8 | mt);
         const int n1 = __popcll(m1), n4 = n1 + __popcll(m4), n8 = n4 + __popcll(m8), nt = n8 + __popcll(mt);
-        const bool none = len < 1 || len > kLongMin;
+        const bool none = len < 1 || (len > kColdMax && !team);
         const uint64_t mm = none ? mo : len == 1 ? m1 : len <= 4 ? m4 : len <= kColdMax ? m8 : mt;
         const int base = none ? nt : len == 1 ? 0 : len <= 4 ? n1 : len <= kColdMax ? n4 : n8;
-        const int to = (base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u))) * 4;
+        const int to = lane_rank(mm, base);
         const uint32_t p_row = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)q.row);
         if (n1) {
             const uint32_t p_at = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)f.at);
@@ -500,27 +592,7 @@ __device__ __forceinline__ int ada_batch_keys(const AdaJob& job, const AdaPack& 
                 row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
             }
         }
-        // the keys of more occurrences, dealt to teams of `team` lane groups: all groups for a key alone, several keys side by side
-        const int n = nt - n8;
-        int team = gpw;
-        while (team > kTeam && gpw < team * n) team >>= 1;
-        const int in_team = g & (team - 1);
-#pragma nounroll
-        for (int k0 = 0; k0 < n; k0 += gpw / team) {
-            const int kk = k0 + g / team, src = n8 + min(kk, n - 1);
-            const int wa = __shfl(p_a, src, 64), sb = __shfl(p_b, src, 64), wb = kk < n ? sb : wa;
-            const uint32_t row = (uint32_t)__shfl((int)p_row, src, 64);
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            if (act) accum_range<MEAN, NARROW, true>(acc, gv, (uint32_t)(wa + 4 * in_team), (uint32_t)wb, (uint32_t)(4 * team));
-            wave_group_sum(acc, lpr, lpr * team);
-            if (in_team == 0 && act && kk < n) {           // (asked for earlier, the row would not fit the registers)
-                const RowPtr r = row_ptr<BF16, HYB>(k.W, k.A, k.hv, row, k.D, d0);
-                float w[4], ac[4];
-                load_w4<BF16, NARROW>(r.w, k.D, w);
-                load_f32x4<NARROW>(r.a, k.D, ac);
-                row_step<BF16, NARROW>(r, k.D, acc, w, ac, job.lr, job.eps);
-            }
-        }
+        ada_team_keys<BF16, MEAN, NARROW, HYB>(job, k, gv, d0, act, n8, nt - n8, p_a, p_b, p_row);
     }
     return idx - n_mine;
 }
@@ -553,6 +625,13 @@ pk_adagrad_kernel(AdaJob job)
         for (int i = 0; i < job.n_packs; ++i) {
             const AdaPack& k = job.pack[i];
             PK_ADA_KINDS(ada_long_keys, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip, s_red)
+        }
+        if constexpr (KEYS == kBatches) {
+            idx = blockIdx.x >> 3;
+            for (int i = 0; i < job.n_packs; ++i) {
+                const AdaPack& k = job.pack[i];
+                PK_ADA_KINDS(ada_stretch_keys, job, k, idx, blockIdx.x & 7, job.hot_blocks >> 3, s_recip)
+            }
         }
         return;
     }

@@ -135,7 +135,7 @@ inline int small_cut(int64_t nnz, int64_t n_tables)
 //     fields of 8 and 16 columns, 5.5 M 229, 226, 11 M 423, 408
 //   of 8: 3.4 M 98, 106; 8.6 M 198, 203; 21 M 421, 427; of 4: 83, 90 and 373, 386: a handful is 32 or 64 keys there anyway
 // Where tables have few rows for their IDs, keys have many occurrences each and there is little to sort (37 ragged fields of
-// 3.0 M IDs, 46 % of them distinct at most: 201, 193; of 3.5 M, 43 %: 221, 237).
+// 3.0 M IDs, 46 % of them distinct at most: 202, 183; before dense stretches had their own wavefronts 193, and of 3.5 M, 43 %, 221 and 237).
 struct KeyShare {
     int64_t fields = 0, wide16 = 0, wide32 = 0, wide48 = 0;    // fields; those with rows of 16, 32, 48 columns and more
     int64_t ids = 0, distinct = 0;                             // IDs; rows that they can be, at most

@@ -1,6 +1,6 @@
 """The large-batch backward pass takes keys in batches by their number of occurrences: batches of one class or of all, of one to
-eight handfuls, whole and ragged ones, bag lengths on both sides of the reciprocals that are kept.  Against one Adagrad
-step in double."""
+eight handfuls, whole and ragged ones, frequent keys that are neighbours, bag lengths on both sides of the reciprocals that are
+kept.  Against one Adagrad step in double."""
 import os
 import re
 
@@ -31,6 +31,8 @@ def counts_of(kind, n, rng):
         return rng.integers(2, 9, n)
     if kind == "teams":
         return rng.integers(9, 60, n)
+    if kind == "runs":                                     # frequent keys side by side, with others between
+        return np.where(np.arange(n) % 250 < 200, 1, rng.integers(9, 257, n))
     c = np.where(rng.random(n) < 0.6, 1, rng.integers(1, 12, n))
     c[rng.permutation(n)[:len(LENGTHS)]] = LENGTHS[:n]
     return c
@@ -39,7 +41,7 @@ def counts_of(kind, n, rng):
 # handfuls: how many keys a batch holds, in lane groups of a wavefront
 @pytest.mark.parametrize("dim,dtype,handfuls", [(2, 0, 1), (3, 1, 1), (6, 0, 1), (10, 1, 1), (32, 0, 2), (64, 0, 4), (100, 0, 8), (200, 1, 8)])
 @pytest.mark.parametrize("kind,n", [("ones", 1), ("ones", 513), ("few", 65), ("teams", 63), ("all", 16), ("all", 1100),
-                                    ("ones", LEAST + 3), ("few", 75_001), ("teams", 11_111), ("all", 115_000)])
+                                    ("ones", LEAST + 3), ("few", 75_001), ("teams", 11_111), ("runs", 20_011), ("all", 115_000)])
 def test_batches_of_keys(kind, n, dim, dtype, handfuls):
     check(kind, n, dim, dtype, handfuls)
 
@@ -59,7 +61,7 @@ def check(kind, n, dim, dtype, handfuls):
     nnz = max(LEAST, int(counts.sum()))
     counts[rng.integers(n)] += nnz - counts.sum()          # (where they are few, one key has what a launch in batches needs)
     rows = 3 * max(n, nnz // 3) + 1
-    keys = rng.permutation(rows)[:n]
+    keys = np.sort(rng.permutation(rows)[:n])
     # sum and mean pooling of one table: its entries carry bag lengths; a wide table that has no occurrence, so that the launch is
     # one in batches whatever the other's dimension
     wide_dim = 48
