@@ -179,7 +179,7 @@ __device__ __forceinline__ void pool_tile_by(const PoolJob& job, const PoolPack&
 // are not full than is gained.  us a launch, walk and pairs, of 6, 7, 8, 10, 12 IDs a bag: 100 fields of 16 columns, batch 8192,
 // 82.5 81.6, 90.9 87.4, 101 95.0, 116 110, 127 117; 600 of 8 and 16, 2048, 127 129, 146 145, 152 152, 186 184, 217 214; 60 of 64,
 // 4096, 57.2 57.9, 63.5 63.0, 69.9 68.2, 82.7 81.2, 94.6 89.8; 1000 of 8 and 16 with 5.5 IDs 242 254, the ragged layer's 9.5 34.2 32.8.
-constexpr int kPairAvg = 8;
+constexpr int kPairAvg = 8, kPairShift = 4;
 template <bool BF16, int R>
 __device__ __forceinline__ void pool_tile_pairs(const PoolJob& job, const PoolPack& k, int item, int j, const FieldMeta& m, const int32_t* offs,
                                                 int32_t* s_off)
@@ -256,8 +256,11 @@ __device__ __forceinline__ void pool_tile(const PoolJob& job, const PoolPack& k,
     if constexpr (R == 8) {
         const int64_t per_run = ((int64_t)offs[job.B] - offs[0]) * k.run;      // times B
         if (2 * per_run <= (int64_t)3 * job.B) return pool_tile_by<BF16, NARROW, HYB, IDS, 1>(job, k, item, j, m, offs, s_off);
-        if constexpr (PAIRS && !NARROW) {           // (rows of four columns and fewer have more bags to a tile than lanes)
-            if (k.run == 2 && k.sh >= 1 && per_run >= (int64_t)2 * kPairAvg * job.B) return pool_tile_pairs<BF16, R>(job, k, item, j, m, offs, s_off);
+        // (Rows of four columns and fewer have more bags to a tile than lanes.  Of rows of more than 64 a wavefront has one or two
+        // groups, little to even out, and an empty bag still takes a round: walk and pairs, 20 fields of 200 columns, 10 IDs a bag with half of
+        // the bags empty, 73 84 us; 30 of 128, 67 70, and with bags of 1 to 20, 67 70; 60 of 64, 78 76, 77 74.)
+        if constexpr (PAIRS && !NARROW) {
+            if (k.run == 2 && k.sh >= 1 && k.sh <= kPairShift && per_run >= (int64_t)2 * kPairAvg * job.B) return pool_tile_pairs<BF16, R>(job, k, item, j, m, offs, s_off);
         }
     }
     pool_tile_by<BF16, NARROW, HYB, IDS, R>(job, k, item, j, m, offs, s_off);
