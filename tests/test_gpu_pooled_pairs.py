@@ -1,5 +1,5 @@
-"""Pooling with two bags to a lane group (fields of eight IDs a bag and more and up to 64 columns, wider ones beside them, batches large enough for it) against the same
-bags in batches too small for it: both add a bag's rows up in order, in double, so the outputs are the same bits."""
+"""Pooling with two bags to a lane group (fields of eight IDs a bag and more, up to 64 columns, batches large enough for it), and wider
+rows beside it, against the same bags in batches too small for it: both add a bag's rows up in order, in double, so the outputs are the same bits."""
 import numpy as np
 import pytest
 
